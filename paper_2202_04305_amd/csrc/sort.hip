@@ -217,9 +217,10 @@ __global__ __launch_bounds__(256) void buckets_to_segments_kernel(const uint32_t
 // predecessor's start and not after its own.
 __global__ __launch_bounds__(256) void msd_chunks_kernel(const uint32_t *__restrict__ ctr2, const uint32_t *__restrict__ seg_start,
                                                          const uint32_t *__restrict__ seg_tile, uint32_t n, uint32_t nchunks,
-                                                         uint32_t *__restrict__ chunk_lo)
+                                                         uint32_t *__restrict__ chunk_lo, uint32_t *__restrict__ big, uint32_t *__restrict__ redo)
 {
     const uint32_t s = blockIdx.x * 256u + threadIdx.x;
+    if (s == 0) big[0] = redo[0] = 0;                             // lengths of the finishing kernel's two lists
     if (s > (uint32_t)kSub) return;
     auto start_of = [&](uint32_t sub) -> uint32_t {
         if (sub >= (uint32_t)kSub) return n;
@@ -274,137 +275,334 @@ __device__ __forceinline__ void rank_by_digit(const uint64_t (&k)[R], int rounds
     __syncthreads();
 }
 
-// The finishing pass.  Block k takes chunk k: a contiguous range of entries, sorted here by the whole key (stable, least
-// significant digit first, digits in which no two keys of the range differ skipped) and written to the same range of the
-// output.  kin/vin and kalt/valt are the same arrays: a range that does not fit the LDS is sorted through device memory,
-// tile by tile, hopping between its part of these and its part of the output.
+// The finishing pass: a chunk, which is a contiguous range of entries, is sorted by the whole key (stable) and written to the same
+// range of the output.  The range is cut by value into equal intervals between its smallest and its largest key, four intervals
+// per entry that fits.  An entry takes a number in its interval with one returning LDS add (any order), the counts are scanned,
+// the keys are dropped into their intervals, and an entry's final place is the interval's start plus the number of keys there
+// that are smaller (or equal and earlier in the input: this is what makes the order stable whatever order the adds took).  Keys,
+// then values, leave through one LDS buffer in sorted order.
+// What bounds it: the comparisons inside the intervals are a loop as long as the fullest interval of the wave, so intervals
+// have to be fine (rows of a matrix differ in length, so keys are not spread evenly over a chunk).
+// Measured on 16.9 M entries of the 1M x 1M lognormal matrix: 314 us with the ranking of whole 8-bit digits by ballots that this
+// replaces (now msd_redo_kernel's), 187 us with one interval per entry that fits, 168 us with four, 153 us with the comparisons on
+// 32-bit distances, entry by entry (3.5 TB/s moved); chunks of 2049 to 8192 entries, 6 % of that matrix, 28 us more.
+constexpr int kCrowd = 48;                                        // more keys than this in one interval: left to msd_redo_kernel
+
+template <typename P, int FT, int FE>
+struct finish_lds {
+    static constexpr int kCapacity = FT * FE, kIntervals = 4 * kCapacity;
+    uint64_t stage[kCapacity];
+    __align__(16) uint32_t bins[kIntervals / 2 + 4];              // 16-bit interval counts, then starts
+    uint16_t sidx[kCapacity];
+    uint32_t wsum[FT / 64], crowded[FT / 64];
+    unsigned long long lo[FT / 64], hi[FT / 64];
+};
+
+// at: (interval << 16) | number inside it  ->  place in the sorted order, for every entry of the block.  Ends with a barrier.
+template <typename D, typename P, int FT, int FE>
+__device__ __forceinline__ void place_in_intervals(const uint64_t (&k)[FE], uint64_t kmin, uint32_t (&at)[FE], uint32_t cnt, int rounds,
+                                                   finish_lds<P, FT, FE> &s)
+{
+    const uint16_t *starts = (const uint16_t *)s.bins;
+    D *dist = (D *)s.stage;
+    const int tid = threadIdx.x;
+    uint32_t end[FE];
+#pragma unroll
+    for (int r = 0; r < FE; ++r) {
+        end[r] = 0;
+        if (r < rounds && (uint32_t)(r * FT + tid) < cnt) {
+            const uint32_t b = at[r] >> 16, s0 = starts[b], slot = s0 + (at[r] & 0xffffu);
+            dist[slot] = (D)(k[r] - kmin);
+            s.sidx[slot] = (uint16_t)(r * FT + tid);
+            end[r] = starts[b + 1];
+            at[r] = s0;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < FE; ++r) {
+        if (r < rounds) {                                         // entries alone in their interval have nothing to compare with
+            const D mine = (D)(k[r] - kmin);
+            const uint32_t s0 = at[r], s1 = end[r] - s0 > 1 ? end[r] : 0u;
+            uint32_t same = 0;
+            for (uint32_t x = s0; x < s1; ++x) {
+                const D o = dist[x];
+                at[r] += o < mine ? 1u : 0u;
+                same += o == mine ? 1u : 0u;
+            }
+            if (same > 1)                                         // equal keys besides the entry itself
+                for (uint32_t x = s0; x < s1; ++x) at[r] += dist[x] == mine && (uint32_t)s.sidx[x] < (uint32_t)(r * FT + tid) ? 1u : 0u;
+        }
+    }
+    __syncthreads();
+}
+
+// false (for the whole block): some interval was too crowded, nothing has been written
+template <typename P, int FT, int FE>
+__device__ __forceinline__ bool finish_chunk(const uint64_t *__restrict__ kin, const P *__restrict__ vin, uint64_t *__restrict__ kout,
+                                             P *__restrict__ vout, uint32_t cnt, finish_lds<P, FT, FE> &s)
+{
+    typedef finish_lds<P, FT, FE> lds_t;
+    constexpr int W = FT / 64, WPT = lds_t::kIntervals / 2 / FT;  // 32-bit words of the interval table per thread
+    constexpr int kLogIntervals = __builtin_ctz(lds_t::kIntervals);
+    uint16_t *bins16 = (uint16_t *)s.bins;
+    P *sval = (P *)s.stage;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint64_t k[FE];
+    P v[FE];
+    uint32_t at[FE] = {};
+    const int rounds = (int)((cnt + FT - 1) / FT);                // <= FE
+    unsigned long long kmin = ~0ull, kmax = 0;
+#pragma unroll
+    for (int r = 0; r < FE; ++r) {
+        if (r < rounds) {
+            const uint32_t i = (uint32_t)(r * FT + tid);
+            k[r] = kin[i < cnt ? i : cnt - 1];
+            v[r] = vin[i < cnt ? i : cnt - 1];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < WPT / 4; ++j) ((uint4 *)s.bins)[j * FT + tid] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < FE; ++r) {
+        if (r < rounds) {
+            kmin = k[r] < kmin ? k[r] : kmin;
+            kmax = k[r] > kmax ? k[r] : kmax;
+        }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const unsigned long long a = __shfl_xor(kmin, d, 64), b = __shfl_xor(kmax, d, 64);
+        kmin = a < kmin ? a : kmin;
+        kmax = b > kmax ? b : kmax;
+    }
+    if (lane == 0) { s.lo[wave] = kmin; s.hi[wave] = kmax; }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        kmin = s.lo[w] < kmin ? s.lo[w] : kmin;
+        kmax = s.hi[w] > kmax ? s.hi[w] : kmax;
+    }
+    const int width = kmax > kmin ? 64 - __clzll((long long)(kmax - kmin)) : 0;
+    const int shift = width > kLogIntervals ? width - kLogIntervals : 0;
+#pragma unroll
+    for (int r = 0; r < FE; ++r) {                                // at: interval in the upper half, number inside it in the lower
+        if (r < rounds && (uint32_t)(r * FT + tid) < cnt) {
+            const uint32_t b = (uint32_t)((k[r] - kmin) >> shift), half = (b & 1u) * 16u;
+            at[r] = (b << 16) | ((atomicAdd(&s.bins[b >> 1], 1u << half) >> half) & 0xffffu);
+        }
+    }
+    __syncthreads();
+    uint32_t c[WPT], most = 0, tot = 0;
+#pragma unroll
+    for (int j = 0; j < WPT; ++j) {
+        c[j] = s.bins[tid * WPT + j];
+        const uint32_t a = c[j] & 0xffffu, b = c[j] >> 16;
+        tot += a + b;
+        most = a > most ? a : most;
+        most = b > most ? b : most;
+    }
+    const uint32_t incl = wave_inclusive_scan(tot, lane);
+    const unsigned long long many = __ballot(most > (uint32_t)kCrowd);
+    if (lane == 63) { s.wsum[wave] = incl; s.crowded[wave] = many != 0; }
+    __syncthreads();
+    uint32_t any_crowd = 0, start = incl - tot;
+#pragma unroll
+    for (int w = 0; w < W; ++w) { any_crowd |= s.crowded[w]; start += w < wave ? s.wsum[w] : 0u; }
+    if (any_crowd) return false;
+#pragma unroll
+    for (int j = 0; j < WPT; ++j) {
+        const uint32_t a = c[j] & 0xffffu, b = c[j] >> 16;
+        s.bins[tid * WPT + j] = start | ((start + a) << 16);
+        start += a + b;
+    }
+    if (tid == FT - 1) s.bins[lds_t::kIntervals / 2] = start;     // the end of the last interval
+    __syncthreads();
+    // distances from the smallest key: 32 bits of them when that is enough (half the LDS traffic and a third of the compare)
+    if (width <= 32) place_in_intervals<uint32_t, P, FT, FE>(k, kmin, at, cnt, rounds, s);
+    else place_in_intervals<uint64_t, P, FT, FE>(k, kmin, at, cnt, rounds, s);
+#pragma unroll
+    for (int r = 0; r < FE; ++r)
+        if (r < rounds && (uint32_t)(r * FT + tid) < cnt) s.stage[at[r]] = k[r];
+    __syncthreads();
+    for (uint32_t i = tid; i < cnt; i += FT) kout[i] = s.stage[i];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < FE; ++r)
+        if (r < rounds && (uint32_t)(r * FT + tid) < cnt) sval[at[r]] = v[r];
+    __syncthreads();
+    for (uint32_t i = tid; i < cnt; i += FT) vout[i] = sval[i];
+    return true;
+}
+
+// Block k takes chunk k.  A chunk that is too large goes to the list `big` (its length in big[0]) if msd_finish_big_kernel can
+// hold it, a still larger or a crowded one to the list `redo`.
+constexpr int kBigT = 1024, kBigCap = kBigT * kFE;
 template <typename P>
-__global__ __launch_bounds__(kFT) void msd_finish_kernel(const uint64_t *kin, const P *vin, uint64_t *kout, P *vout, uint64_t *kalt, P *valt,
-                                                         const uint32_t *__restrict__ chunk_lo)
+__global__ __launch_bounds__(kFT) void msd_finish_kernel(const uint64_t *__restrict__ kin, const P *__restrict__ vin, uint64_t *__restrict__ kout,
+                                                         P *__restrict__ vout, const uint32_t *__restrict__ chunk_lo, uint32_t *__restrict__ big,
+                                                         uint32_t *__restrict__ redo)
+{
+    __shared__ finish_lds<P, kFT, kFE> s;
+    const uint32_t lo = chunk_lo[blockIdx.x], hi = chunk_lo[blockIdx.x + 1];
+    if (lo >= hi) return;
+    const uint32_t cnt = hi - lo;
+    if (cnt <= (uint32_t)kCap && finish_chunk<P, kFT, kFE>(kin + lo, vin + lo, kout + lo, vout + lo, cnt, s)) return;
+    if (threadIdx.x == 0) {
+        uint32_t *list = cnt > (uint32_t)kCap && cnt <= (uint32_t)kBigCap ? big : redo;
+        list[1 + atomicAdd(&list[0], 1u)] = blockIdx.x;
+    }
+}
+
+template <typename P>
+__global__ __launch_bounds__(kBigT) void msd_finish_big_kernel(const uint64_t *__restrict__ kin, const P *__restrict__ vin, uint64_t *__restrict__ kout,
+                                                               P *__restrict__ vout, const uint32_t *__restrict__ chunk_lo,
+                                                               const uint32_t *__restrict__ big, uint32_t *__restrict__ redo)
+{
+    __shared__ finish_lds<P, kBigT, kFE> s;
+    const uint32_t nbig = big[0];
+    for (uint32_t i = blockIdx.x; i < nbig; i += gridDim.x) {
+        const uint32_t chunk = big[1 + i], lo = chunk_lo[chunk];
+        if (!finish_chunk<P, kBigT, kFE>(kin + lo, vin + lo, kout + lo, vout + lo, chunk_lo[chunk + 1] - lo, s) && threadIdx.x == 0)
+            redo[1 + atomicAdd(&redo[0], 1u)] = chunk;
+        __syncthreads();                                          // the buffers are used again
+    }
+}
+
+// The chunks the finishing kernels left: sorted digit by digit (rank_by_digit: stable, least significant digit first, digits in
+// which no two keys of the range differ skipped), in the LDS when they fit, else through device memory, tile by tile, hopping
+// between the chunk's part of kin / vin and its part of the output.  Slow; meant for a few chunks.
+template <typename P>
+__global__ __launch_bounds__(kFT) void msd_redo_kernel(uint64_t *kin, P *vin, uint64_t *kout, P *vout, const uint32_t *__restrict__ chunk_lo,
+                                                       const uint32_t *__restrict__ redo)
 {
     constexpr int W = kFT / 64;
-    __shared__ uint64_t skey[kCap];
-    __shared__ P sval[kCap];
+    __shared__ uint64_t stage[kCap];
     __shared__ uint32_t wrun[W * 256];
     __shared__ uint32_t wrel[W * 256];
     __shared__ uint32_t dig[256];
     __shared__ uint32_t dstart[256];
     __shared__ uint32_t wsum[W];
     __shared__ unsigned long long s_or[W];
+    P *sval = (P *)stage;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t lo = chunk_lo[blockIdx.x], hi = chunk_lo[blockIdx.x + 1];
-    if (lo >= hi) return;
-    const uint32_t cnt = hi - lo;
-    const uint64_t k0 = kin[lo];
-    uint64_t k[kFE];
-    P v[kFE];
-    uint32_t lpos[kFE];
-    uint32_t tot;
-    if (cnt <= (uint32_t)kCap) {
-        const uint32_t perw = ((cnt + W * 64 - 1) / (W * 64)) * 64;
-        const int rounds = (int)(perw / 64);                      // <= kFE
+    const uint32_t nredo = redo[0];
+    for (uint32_t which = blockIdx.x; which < nredo; which += gridDim.x) {
+        const uint32_t lo = chunk_lo[redo[1 + which]], hi = chunk_lo[redo[1 + which] + 1];
+        const uint32_t cnt = hi - lo;
+        const uint64_t k0 = kin[lo];
+        uint64_t k[kFE];
+        P v[kFE];
+        uint32_t lpos[kFE];
+        uint32_t tot;
         unsigned long long diff = 0;
-#pragma unroll
-        for (int r = 0; r < kFE; ++r) {
-            const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
-            const bool valid = r < rounds && i < cnt;
-            k[r] = valid ? kin[lo + i] : k0;
-            v[r] = valid ? vin[lo + i] : (P)0;
-            diff |= k[r] ^ k0;
-        }
+        for (uint32_t i = lo + tid; i < hi; i += kFT) diff |= kin[i] ^ k0;
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) diff |= __shfl_xor(diff, d, 64);
         if (lane == 0) s_or[wave] = diff;
         __syncthreads();
         diff = 0;
         for (int w = 0; w < W; ++w) diff |= s_or[w];
+        if (cnt <= (uint32_t)kCap) {
+            const uint32_t perw = ((cnt + W * 64 - 1) / (W * 64)) * 64;
+            const int rounds = (int)(perw / 64);                      // <= kFE
+#pragma unroll
+            for (int r = 0; r < kFE; ++r) {
+                const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
+                const bool valid = r < rounds && i < cnt;
+                k[r] = valid ? kin[lo + i] : k0;
+                v[r] = valid ? vin[lo + i] : (P)0;
+            }
+            for (int sh = 0; sh < 64; sh += 8) {
+                if (((diff >> sh) & 255ull) == 0) continue;            // block-uniform
+                rank_by_digit<kFE>(k, rounds, perw, cnt, sh, wrun, wrel, dig, wsum, lpos, tot);
+#pragma unroll
+                for (int r = 0; r < kFE; ++r) {
+                    if (r < rounds && (uint32_t)wave * perw + (uint32_t)(r * 64 + lane) < cnt) {
+                        const uint32_t d = (uint32_t)(k[r] >> sh) & 255u;
+                        lpos[r] += dig[d] + wrel[wave * 256 + d];
+                        stage[lpos[r]] = k[r];
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < kFE; ++r) {
+                    const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
+                    if (r < rounds && i < cnt) k[r] = stage[i];
+                }
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < kFE; ++r)
+                    if (r < rounds && (uint32_t)wave * perw + (uint32_t)(r * 64 + lane) < cnt) sval[lpos[r]] = v[r];
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < kFE; ++r) {
+                    const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
+                    if (r < rounds && i < cnt) v[r] = sval[i];
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int r = 0; r < kFE; ++r) {
+                const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
+                if (r < rounds && i < cnt) { kout[lo + i] = k[r]; vout[lo + i] = v[r]; }
+            }
+            __syncthreads();                                          // s_or is written for the next chunk
+            continue;
+        }
+        // more entries than the LDS holds: one block for the whole range
+        const uint64_t *src_k = kin;
+        const P *src_v = vin;
+        int hop = 0;
         for (int shift = 0; shift < 64; shift += 8) {
-            if (((diff >> shift) & 255ull) == 0) continue;         // block-uniform
-            rank_by_digit<kFE>(k, rounds, perw, cnt, shift, wrun, wrel, dig, wsum, lpos, tot);
+            if (((diff >> shift) & 255ull) == 0) continue;
+            uint64_t *dst_k = (hop & 1) ? kin : kout;
+            P *dst_v = (hop & 1) ? vin : vout;
+            ++hop;
+            dstart[tid] = 0;
+            __syncthreads();
+            for (uint32_t i = lo + tid; i < hi; i += kFT) atomicAdd(&dstart[(uint32_t)(src_k[i] >> shift) & 255u], 1u);
+            __syncthreads();
+            {
+                const uint32_t c = dstart[tid];
+                const uint32_t incl = wave_inclusive_scan(c, lane);
+                if (lane == 63) wsum[wave] = incl;
+                __syncthreads();
+                uint32_t start = incl - c;
+                for (int w = 0; w < wave; ++w) start += wsum[w];
+                dstart[tid] = lo + start;
+            }
+            for (uint32_t base = lo; base < hi; base += kCap) {      // tiles in order: the pass is stable
+                const uint32_t tcnt = hi - base < (uint32_t)kCap ? hi - base : (uint32_t)kCap;
+                const uint32_t perw = ((tcnt + W * 64 - 1) / (W * 64)) * 64;
+                const int rounds = (int)(perw / 64);
 #pragma unroll
-            for (int r = 0; r < kFE; ++r) {
-                if (r < rounds && (uint32_t)wave * perw + (uint32_t)(r * 64 + lane) < cnt) {
-                    const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
-                    const uint32_t slot = dig[d] + wrel[wave * 256 + d] + lpos[r];
-                    skey[slot] = k[r];
-                    sval[slot] = v[r];
+                for (int r = 0; r < kFE; ++r) {
+                    const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
+                    const bool valid = r < rounds && i < tcnt;
+                    k[r] = valid ? src_k[base + i] : 0;
+                    v[r] = valid ? src_v[base + i] : (P)0;
                 }
-            }
-            __syncthreads();
+                rank_by_digit<kFE>(k, rounds, perw, tcnt, shift, wrun, wrel, dig, wsum, lpos, tot);   // its first barrier also orders dstart
 #pragma unroll
-            for (int r = 0; r < kFE; ++r) {
-                const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
-                if (r < rounds && i < cnt) { k[r] = skey[i]; v[r] = sval[i]; }
-            }
-            // the next writes to skey / sval come after the barriers of the next ranking
-        }
-#pragma unroll
-        for (int r = 0; r < kFE; ++r) {
-            const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
-            if (r < rounds && i < cnt) { kout[lo + i] = k[r]; vout[lo + i] = v[r]; }
-        }
-        return;
-    }
-    // More entries than the LDS holds.  Slow (one block for the whole range); meant to be rare.
-    unsigned long long diff = 0;
-    for (uint32_t i = lo + tid; i < hi; i += kFT) diff |= kin[i] ^ k0;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) diff |= __shfl_xor(diff, d, 64);
-    if (lane == 0) s_or[wave] = diff;
-    __syncthreads();
-    diff = 0;
-    for (int w = 0; w < W; ++w) diff |= s_or[w];
-    const uint64_t *src_k = kin;
-    const P *src_v = vin;
-    int hop = 0;
-    for (int shift = 0; shift < 64; shift += 8) {
-        if (((diff >> shift) & 255ull) == 0) continue;
-        uint64_t *dst_k = (hop & 1) ? kalt : kout;
-        P *dst_v = (hop & 1) ? valt : vout;
-        ++hop;
-        dstart[tid] = 0;
-        __syncthreads();
-        for (uint32_t i = lo + tid; i < hi; i += kFT) atomicAdd(&dstart[(uint32_t)(src_k[i] >> shift) & 255u], 1u);
-        __syncthreads();
-        {
-            const uint32_t c = dstart[tid];
-            const uint32_t incl = wave_inclusive_scan(c, lane);
-            if (lane == 63) wsum[wave] = incl;
-            __syncthreads();
-            uint32_t start = incl - c;
-            for (int w = 0; w < wave; ++w) start += wsum[w];
-            dstart[tid] = lo + start;
-        }
-        for (uint32_t base = lo; base < hi; base += kCap) {      // tiles in order: the pass is stable
-            const uint32_t tcnt = hi - base < (uint32_t)kCap ? hi - base : (uint32_t)kCap;
-            const uint32_t perw = ((tcnt + W * 64 - 1) / (W * 64)) * 64;
-            const int rounds = (int)(perw / 64);
-#pragma unroll
-            for (int r = 0; r < kFE; ++r) {
-                const uint32_t i = (uint32_t)wave * perw + (uint32_t)(r * 64 + lane);
-                const bool valid = r < rounds && i < tcnt;
-                k[r] = valid ? src_k[base + i] : 0;
-                v[r] = valid ? src_v[base + i] : (P)0;
-            }
-            rank_by_digit<kFE>(k, rounds, perw, tcnt, shift, wrun, wrel, dig, wsum, lpos, tot);   // its first barrier also orders dstart
-#pragma unroll
-            for (int r = 0; r < kFE; ++r) {
-                if (r < rounds && (uint32_t)wave * perw + (uint32_t)(r * 64 + lane) < tcnt) {
-                    const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
-                    const uint32_t q = dstart[d] + wrel[wave * 256 + d] + lpos[r];
-                    dst_k[q] = k[r];
-                    dst_v[q] = v[r];
+                for (int r = 0; r < kFE; ++r) {
+                    if (r < rounds && (uint32_t)wave * perw + (uint32_t)(r * 64 + lane) < tcnt) {
+                        const uint32_t d = (uint32_t)(k[r] >> shift) & 255u;
+                        const uint32_t q = dstart[d] + wrel[wave * 256 + d] + lpos[r];
+                        dst_k[q] = k[r];
+                        dst_v[q] = v[r];
+                    }
                 }
+                __syncthreads();
+                dstart[tid] += tot;
             }
-            __syncthreads();
-            dstart[tid] += tot;
+            src_k = dst_k;
+            src_v = dst_v;
+            __syncthreads();                                          // the next pass reads what this one wrote (same workgroup)
         }
-        src_k = dst_k;
-        src_v = dst_v;
-        __syncthreads();                                          // the next pass reads what this one wrote (same workgroup)
-    }
-    if (src_k != kout) {                                          // no hop at all (every key equal), or an even number of them
-        for (uint32_t i = lo + tid; i < hi; i += kFT) { kout[i] = src_k[i]; vout[i] = src_v[i]; }
+        if (src_k != kout) {                                          // no hop at all (every key equal), or an even number of them
+            for (uint32_t i = lo + tid; i < hi; i += kFT) { kout[i] = src_k[i]; vout[i] = src_v[i]; }
+        }    __syncthreads();                                              // the tables are reused for the next chunk
     }
 }
 
@@ -491,9 +689,9 @@ sp_status msd_sort_t(uint64_t *keys, const P *vals_in, int64_t n, int key_bits, 
     const size_t ctr_words = (size_t)256 * tiles2_max;
     uint32_t *ctr = ctr_ready ? ctr_ready : (uint32_t *)tmp.get(ctr_words * 4);      // ctr_ready: the first pass's counts are in it already
     const uint32_t nchunks = n32 / (uint32_t)kTarget + 1;
-    uint32_t *seg = (uint32_t *)tmp.get((size_t)(2 * 257 + 2 * 2 + nchunks + 1 + 8) * 4);
+    uint32_t *seg = (uint32_t *)tmp.get((size_t)(2 * 257 + 2 * 2 + nchunks + 1 + 2 * (nchunks + 1) + 8) * 4);
     if (!kb || !va || !vb || !ctr || !seg) return SP_ERR_ALLOC;
-    uint32_t *seg_start1 = seg, *seg_tile1 = seg + 2, *seg_start2 = seg + 4, *seg_tile2 = seg + 4 + 257, *chunk_lo = seg + 4 + 2 * 257;
+    uint32_t *seg_start1 = seg, *seg_tile1 = seg + 2, *seg_start2 = seg + 4, *seg_tile2 = seg + 4 + 257, *chunk_lo = seg + 4 + 2 * 257, *big = chunk_lo + nchunks + 1, *redo = big + nchunks + 1;
     const int shift1 = key_bits > 8 ? key_bits - 8 : 0, shift2 = key_bits > 16 ? key_bits - 16 : 0;
     // first pass: keys / vals_in -> kb / va
     hipLaunchKernelGGL(one_segment_kernel, dim3(1), dim3(1), 0, st, seg_start1, seg_tile1, n32);
@@ -515,11 +713,14 @@ sp_status msd_sort_t(uint64_t *keys, const P *vals_in, int64_t n, int key_bits, 
     hipLaunchKernelGGL(partition_scatter_kernel<P>, dim3(round8(tiles2_max)), dim3(kT), 0, st, (const uint64_t *)kb, (const P *)va, keys, vb,
                        (const uint32_t *)seg_start2, (const uint32_t *)seg_tile2, 256, shift2, (const uint32_t *)ctr);
     hipLaunchKernelGGL(msd_chunks_kernel, dim3(kSub / 256 + 1), dim3(256), 0, st, (const uint32_t *)ctr, (const uint32_t *)seg_start2,
-                       (const uint32_t *)seg_tile2, n32, nchunks, chunk_lo);
+                       (const uint32_t *)seg_tile2, n32, nchunks, chunk_lo, big, redo);
     SP_HIP(hipGetLastError());
     // finishing pass: keys / vb -> kb / va (a range that does not fit the LDS also hops through its own part of keys / vb)
-    hipLaunchKernelGGL(msd_finish_kernel<P>, dim3(nchunks), dim3(kFT), 0, st, (const uint64_t *)keys, (const P *)vb, kb, va, keys, vb,
-                       (const uint32_t *)chunk_lo);
+    hipLaunchKernelGGL(msd_finish_kernel<P>, dim3(nchunks), dim3(kFT), 0, st, (const uint64_t *)keys, (const P *)vb, kb, va,
+                       (const uint32_t *)chunk_lo, big, redo);
+    hipLaunchKernelGGL(msd_finish_big_kernel<P>, dim3(nchunks < 256u ? nchunks : 256u), dim3(kBigT), 0, st, (const uint64_t *)keys, (const P *)vb, kb, va,
+                       (const uint32_t *)chunk_lo, (const uint32_t *)big, redo);
+    hipLaunchKernelGGL(msd_redo_kernel<P>, dim3(nchunks < 512u ? nchunks : 512u), dim3(kFT), 0, st, keys, vb, kb, va, (const uint32_t *)chunk_lo, (const uint32_t *)redo);
     SP_HIP(hipGetLastError());
     *keys_out = kb;
     *vals_out = va;
