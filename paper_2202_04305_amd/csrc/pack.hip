@@ -158,120 +158,54 @@ __global__ __launch_bounds__(kThreads) void check_duplicates_kernel(const uint64
     if (e >= 1 && e < nnz && keys[e] == keys[e - 1]) atomicOr(&flags[1], 1);
 }
 
-// Division of a key by a level's stride or size, which the host knows when it launches: a shift when the divisor is a
-// power of two, a multiplication by the reciprocal in double plus a one-step correction while the dividend is below
-// 2^52 (the estimate is then within one of the quotient), the hardware's 64-bit division otherwise.
-struct divisor {
-    uint64_t d;
-    double inv;
-    int shift;          // >= 0: d == 1 << shift
-};
-
-static divisor make_divisor(uint64_t d)
-{
-    divisor v;
-    v.d = d;
-    v.inv = 1.0 / (double)d;
-    v.shift = -1;
-    if ((d & (d - 1)) == 0) { v.shift = 0; while (((uint64_t)1 << v.shift) != d) ++v.shift; }
-    return v;
-}
-
-__device__ inline uint64_t div_by(uint64_t x, const divisor &v)
-{
-    if (v.shift >= 0) return x >> v.shift;
-    if (x < ((uint64_t)1 << 52)) {
-        uint64_t q = (uint64_t)((double)x * v.inv);
-        const int64_t r = (int64_t)(x - q * v.d);
-        if (r < 0) --q;
-        else if ((uint64_t)r >= v.d) ++q;
-        return q;
-    }
-    return x / v.d;
-}
-
-// dense level: position = parent * size + coordinate
-__global__ __launch_bounds__(kThreads) void dense_level_kernel(const uint64_t *__restrict__ keys, int64_t nnz, divisor stride,
-                                                               divisor size, const uint64_t *__restrict__ parent_in,
-                                                               uint64_t *__restrict__ parent_out)
-{
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= nnz) return;
-    const uint64_t pre = div_by(keys[e], stride);
-    const uint64_t c = pre - div_by(pre, size) * size.d;
-    parent_out[e] = (parent_in ? parent_in[e] : 0ull) * size.d + c;
-}
-
-// compressed level, step 1: mark[e] = 1 where the key prefix down to this level changes
-__global__ __launch_bounds__(kThreads) void mark_children_kernel(const uint64_t *__restrict__ keys, int64_t nnz, divisor stride,
-                                                                 uint32_t *__restrict__ mark)
-{
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= nnz) return;
-    mark[e] = (e == 0 || div_by(keys[e], stride) != div_by(keys[e - 1], stride)) ? 1u : 0u;
-}
-
-// compressed level, step 2: write crd, count children per parent (one add per run end, one
-// subtract per run start: integer atomics, so the result does not depend on their order),
-// and hand each entry its child position.  child_excl = exclusive scan of the marks, or
-// nullptr on the innermost level, where every entry is its own child.  dup_flags (may be null): the duplicate check of the
-// sorted keys, done here on the way when the builder has not run it yet.
-template <typename PT, typename CT>
-__global__ __launch_bounds__(kThreads) void emit_level_kernel(const uint64_t *__restrict__ keys, int64_t nnz, divisor stride,
-                                                              divisor size, const uint32_t *__restrict__ child_excl,
-                                                              const uint64_t *__restrict__ parent_in, uint64_t *__restrict__ parent_out,
-                                                              PT *__restrict__ cnt, CT *__restrict__ crd, int *__restrict__ dup_flags)
-{
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= nnz) return;
-    const uint64_t key = keys[e], key_before = e > 0 ? keys[e - 1] : 0;
-    if (dup_flags && e > 0 && key == key_before) atomicOr(&dup_flags[1], 1);      // an entry given twice (see check_duplicates_kernel)
-    const uint64_t pre = div_by(key, stride);
-    const uint64_t pre_before = e > 0 ? div_by(key_before, stride) : 0;
-    const bool first = (e == 0) || (pre_before != pre);
-    const uint64_t child = child_excl ? (uint64_t)child_excl[e] + (first ? 1u : 0u) - 1u : (uint64_t)e;
-    const uint64_t up = div_by(pre, size);
-    if (first) crd[child] = (CT)(pre - up * size.d);
-    // position of the entry at the level above: carried in parent_in, or, while every level above is dense, simply
-    // the key prefix down to that level (pre / size), which needs no array
-    const uint64_t par = parent_in ? parent_in[e] : up;
-    const bool head = (e == 0) || (parent_in ? parent_in[e - 1] : div_by(pre_before, size)) != par;
-    const bool tail = (e == nnz - 1) || (parent_in ? parent_in[e + 1] : div_by(div_by(keys[e + 1], stride), size)) != par;
-    typedef typename std::conditional<sizeof(PT) == 8, unsigned long long, unsigned int>::type UT;
-    if (tail) atomicAdd((UT *)&cnt[par], (UT)(child + 1));
-    if (head) atomicAdd((UT *)&cnt[par], (UT)(0) - (UT)child);
-    if (parent_out) parent_out[e] = child;
-}
-
-template <typename P>
-__global__ __launch_bounds__(kThreads) void place_values_kernel(const P *__restrict__ sorted, const uint64_t *__restrict__ position,
-                                                                int64_t nnz, P *__restrict__ vout)
-{
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= nnz) return;
-    vout[position ? position[e] : (uint64_t)e] = sorted[e];
-}
-
-// longest pos segment: grid-stride maximum per thread, wave and block reduction, one atomic per block
+// Longest pos segment and, where asked for (nonempty not null, zero before), the number of segments that hold something: four
+// consecutive segments per thread and step (16-byte loads), wave and block reduction, and then at most one atomic per block and
+// answer.  They all go to one address, so the grid is small where the array is (1 M segments: 16 us with 1024 blocks, 8 us with
+// 128) and wide where reading it is what takes the time (57 M segments: 240 us with 256 blocks of one 4-byte load per thread and
+// step, 52 us with 1024 blocks), and a block keeps its maximum to itself when a longer one is there already.
+constexpr int kSegBlocks = 1024;
 template <typename PT>
-__global__ __launch_bounds__(kThreads) void max_segment_kernel(const PT *__restrict__ pos, int64_t nseg, unsigned long long *__restrict__ out)
+__global__ __launch_bounds__(kThreads) void pos_stats_kernel(const PT *__restrict__ pos, int64_t nseg, unsigned long long *__restrict__ out,
+                                                             unsigned long long *__restrict__ nonempty)
 {
-    __shared__ unsigned long long wmax[kThreads / 64];
-    unsigned long long len = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nseg; i += (int64_t)gridDim.x * kThreads) {
-        const unsigned long long l = (unsigned long long)(pos[i + 1] - pos[i]);
-        len = l > len ? l : len;
+    __shared__ unsigned long long wmax[kThreads / 64], wsum[kThreads / 64];
+    typedef PT vec_t __attribute__((ext_vector_type(16 / sizeof(PT))));
+    constexpr int V = 16 / sizeof(PT);
+    unsigned long long len = 0, filled = 0;
+    const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
+    for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4; i < nseg; i += stride) {
+        PT p[5];
+        if (i + 4 <= nseg) {
+#pragma unroll
+            for (int v = 0; v < 4 / V; ++v) {
+                const vec_t q = *(const vec_t *)(pos + i + v * V);
+#pragma unroll
+                for (int j = 0; j < V; ++j) p[v * V + j] = q[j];
+            }
+            p[4] = pos[i + 4];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 5; ++j) p[j] = pos[i + j <= nseg ? i + j : nseg];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const unsigned long long l = (unsigned long long)(p[j + 1] - p[j]);
+            len = l > len ? l : len;
+            filled += l ? 1u : 0u;
+        }
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         const unsigned long long o = __shfl_xor(len, d, 64);
         len = o > len ? o : len;
+        filled += __shfl_xor(filled, d, 64);
     }
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = len;
+    if ((threadIdx.x & 63) == 0) { wmax[threadIdx.x >> 6] = len; wsum[threadIdx.x >> 6] = filled; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) len = wmax[w] > len ? wmax[w] : len;
-        if (len) atomicMax(out, len);
+        for (int w = 1; w < kThreads / 64; ++w) { len = wmax[w] > len ? wmax[w] : len; filled += wsum[w]; }
+        if (nonempty && filled) atomicAdd(nonempty, filled);
+        if (len > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out, len);
     }
 }
 
@@ -368,6 +302,16 @@ sp_status spmi_exclusive_scan(void *data, int64_t n, int bits, sp_scratch &tmp, 
     return exclusive_scan_t<unsigned long long>((unsigned long long *)data, n, tmp, st);
 }
 
+static sp_status pos_stats(const void *pos, int pw, int64_t nseg, unsigned long long *longest, unsigned long long *nonempty, hipStream_t st)
+{
+    if (nseg <= 0) return SP_OK;
+    const unsigned nb = std::min(blocks_for((nseg + 3) / 4), (unsigned)(nseg < ((int64_t)1 << 23) ? 128 : kSegBlocks));
+    if (pw == 32) hipLaunchKernelGGL(pos_stats_kernel<int32_t>, dim3(nb), dim3(kThreads), 0, st, (const int32_t *)pos, nseg, longest, nonempty);
+    else hipLaunchKernelGGL(pos_stats_kernel<int64_t>, dim3(nb), dim3(kThreads), 0, st, (const int64_t *)pos, nseg, longest, nonempty);
+    SP_HIP(hipGetLastError());
+    return SP_OK;
+}
+
 static size_t pad16(size_t b) { return (b + 15) & ~(size_t)15; }
 
 static sp_status build_rowblocks_for(const void *pos, int pw, int64_t nrows, int64_t nnz, const sp_mem &mem, sp_rowblocks *out,
@@ -443,43 +387,24 @@ struct nonempty_probe {
     void take(const int *h) { memcpy(&nz, &h[8], 8); memcpy(&span, &h[10], 8); }
 };
 
-// *out += the number of rows that hold something: grid-stride count per thread, wave and block reduction, one atomic per block
-template <typename PT>
-__global__ __launch_bounds__(kThreads) void count_nonempty_kernel(const PT *__restrict__ pos, int64_t nrows, unsigned long long *__restrict__ out)
+static bool wants_nonempty(const sp_tensor *t)
 {
-    __shared__ unsigned long long wsum[kThreads / 64];
-    unsigned long long c = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nrows; i += (int64_t)gridDim.x * kThreads) c += pos[i + 1] > pos[i] ? 1u : 0u;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) c += wsum[w];
-        if (c) atomicAdd(out, c);
-    }
+    if (t->enc.rank != 2 || t->enc.lt[0] != SP_DENSE || t->enc.lt[1] != SP_COMPRESSED) return false;
+    const int64_t nrows = t->npos[1] - 1;
+    return nrows >= 4096 && nrows < ((int64_t)1 << 31) - 1 && t->ncrd[1] != 0;
 }
 
-// flags: the 64 zeroed device bytes of the build (see nonempty_probe for the slots used here)
+// flags: the 64 zeroed device bytes of the build (see nonempty_probe for the slots used here); the caller has enqueued
+// pos_stats() with wants_nonempty() true, which counts the non-empty rows into ints 8-9
 static sp_status nonempty_enqueue(const sp_tensor *t, hipStream_t st, int *flags, nonempty_probe &q)
 {
-    if (t->enc.rank != 2 || t->enc.lt[0] != SP_DENSE || t->enc.lt[1] != SP_COMPRESSED) return SP_OK;
-    const int64_t nrows = t->npos[1] - 1;
-    if (nrows < 4096 || nrows >= ((int64_t)1 << 31) - 1 || t->ncrd[1] == 0) return SP_OK;
-    const unsigned cnt_blocks = blocks_for(nrows) < 256u ? blocks_for(nrows) : 256u;
-    if (t->enc.pw == 32)
-        hipLaunchKernelGGL(count_nonempty_kernel<int32_t>, dim3(cnt_blocks), dim3(kThreads), 0, st, (const int32_t *)t->pos[1], nrows,
-                           (unsigned long long *)(flags + 8));
-    else
-        hipLaunchKernelGGL(count_nonempty_kernel<int64_t>, dim3(cnt_blocks), dim3(kThreads), 0, st, (const int64_t *)t->pos[1], nrows,
-                           (unsigned long long *)(flags + 8));
-    SP_HIP(hipGetLastError());
+    if (!wants_nonempty(t)) return SP_OK;
     if (t->rowblocks.start) {
         hipLaunchKernelGGL(max_span_kernel, dim3(blocks_for(t->rowblocks.nblocks)), dim3(kThreads), 0, st, (const int32_t *)t->rowblocks.start,
                            t->rowblocks.nblocks, (unsigned long long *)(flags + 10));
         SP_HIP(hipGetLastError());
     }
-    q.nrows = nrows; q.active = true;
+    q.nrows = t->npos[1] - 1; q.active = true;
     return SP_OK;
 }
 
@@ -528,8 +453,9 @@ static sp_status build_nonempty_rows(const sp_tensor *t, sp_scratch &tmp, hipStr
     if (!flags) return SP_ERR_ALLOC;
     SP_TRY(spmi_fill_zero(flags, 64, st));
     nonempty_probe q;
+    if (!wants_nonempty(t)) return SP_OK;
+    SP_TRY(pos_stats(t->pos[1], t->enc.pw, t->npos[1] - 1, (unsigned long long *)(flags + 4), (unsigned long long *)(flags + 8), st));
     SP_TRY(nonempty_enqueue(t, st, flags, q));
-    if (!q.active) return SP_OK;
     int h[16];
     SP_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st));
     SP_HIP(hipStreamSynchronize(st));
@@ -911,11 +837,12 @@ extern "C" void sp_tensor_free(sp_tensor *t)
     delete t;
 }
 
-// The same for the innermost level of a format whose levels above are all dense (CSR, CSC and their kin of any rank): every
+// The sweep for the innermost level of a format whose levels above are all dense (CSR, CSC and their kin of any rank): every
 // entry is its own child, its parent is the key divided by the level's size.  Four consecutive entries per thread, their keys
-// and the two neighbours loaded once, the four coordinates written with one store.
+// and the two neighbours loaded once, the four coordinates written with one store.  dup_flags (may be null): the duplicate check
+// of the sorted keys, done here on the way.
 template <typename PT, typename CT>
-__global__ __launch_bounds__(kThreads) void emit_inner_kernel(const uint64_t *__restrict__ keys, int64_t nnz, divisor size, PT *__restrict__ cnt,
+__global__ __launch_bounds__(kThreads) void emit_inner_kernel(const uint64_t *__restrict__ keys, int64_t nnz, spmi_divisor size, PT *__restrict__ cnt,
                                                               CT *__restrict__ crd, int *__restrict__ dup_flags)
 {
     typedef unsigned long long u2 __attribute__((ext_vector_type(2)));
@@ -934,7 +861,7 @@ __global__ __launch_bounds__(kThreads) void emit_inner_kernel(const uint64_t *__
     k[5] = e0 + 4 < nnz ? keys[e0 + 4] : 0;
     uint64_t up[6];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) up[i] = div_by(k[i], size);
+    for (int i = 0; i < 6; ++i) up[i] = spmi_div_by(k[i], size);
     CT c[4];
     bool dup = false;
 #pragma unroll
@@ -960,20 +887,6 @@ __global__ __launch_bounds__(kThreads) void emit_inner_kernel(const uint64_t *__
     }
 }
 
-template <typename PT, typename CT>
-static sp_status launch_emit(const uint64_t *keys, int64_t nnz, divisor stride, divisor size, const uint32_t *child_excl,
-                             const uint64_t *pin, uint64_t *pout, void *cnt, void *crd, int *dup_flags, hipStream_t st)
-{
-    if (!child_excl && !pin && !pout && stride.d == 1)
-        hipLaunchKernelGGL((emit_inner_kernel<PT, CT>), dim3(blocks_for((nnz + 3) / 4)), dim3(kThreads), 0, st, keys, nnz, size, (PT *)cnt, (CT *)crd,
-                           dup_flags);
-    else
-        hipLaunchKernelGGL((emit_level_kernel<PT, CT>), dim3(blocks_for(nnz)), dim3(kThreads), 0, st, keys, nnz, stride, size, child_excl,
-                           pin, pout, (PT *)cnt, (CT *)crd, dup_flags);
-    SP_HIP(hipGetLastError());
-    return SP_OK;
-}
-
 // The tables a finished storage carries for the product kernels: longest innermost segment (kernel choice), the row
 // blocks of the streaming kernels, the list of non-empty rows of a mostly empty CSR.  flags: 64 device bytes, the
 // second half zero.  Synchronises.  input_flags (HOST int[2], may be null) receives flags[0..1], the input checks of
@@ -983,16 +896,9 @@ sp_status spmi_finish_tensor(sp_tensor *t, int *flags, sp_scratch &tmp, hipStrea
     const sp_encoding *enc = &t->enc;
     const int rank = enc->rank;
     const bool want_max = enc->lt[rank - 1] == SP_COMPRESSED && t->npos[rank - 1] > 1;
-    if (want_max) {
-        unsigned long long *mx = (unsigned long long *)(flags + 4);
-        const int64_t nseg = t->npos[rank - 1] - 1;
-        const unsigned seg_blocks = blocks_for(nseg) < 256u ? blocks_for(nseg) : 256u;      // one atomic per block, all to one address: few blocks
-        if (enc->pw == 32)
-            hipLaunchKernelGGL(max_segment_kernel<int32_t>, dim3(seg_blocks), dim3(kThreads), 0, st, (const int32_t *)t->pos[rank - 1], nseg, mx);
-        else
-            hipLaunchKernelGGL(max_segment_kernel<int64_t>, dim3(seg_blocks), dim3(kThreads), 0, st, (const int64_t *)t->pos[rank - 1], nseg, mx);
-        SP_HIP(hipGetLastError());
-    }
+    if (want_max)
+        SP_TRY(pos_stats(t->pos[rank - 1], enc->pw, t->npos[rank - 1] - 1, (unsigned long long *)(flags + 4),
+                         wants_nonempty(t) ? (unsigned long long *)(flags + 8) : nullptr, st));
     // everything that can be enqueued before the host has to look at an answer: the row blocks and the questions of the
     // non-empty-rows list (all in bounds whatever the input checks say), then one synchronisation for all read-backs
     SP_TRY(spmi_build_rowblocks(t, st));
@@ -1019,12 +925,7 @@ sp_status spmi_finish_tensor(sp_tensor *t, int *flags, sp_scratch &tmp, hipStrea
 // *out (DEVICE, zero before the call) = the longest of the nseg segments of a pos array of width pw; enqueued only.
 sp_status spmi_max_segment_async(const void *pos, int pw, int64_t nseg, unsigned long long *out, hipStream_t st)
 {
-    if (nseg <= 0) return SP_OK;
-    const unsigned seg_blocks = blocks_for(nseg) < 256u ? blocks_for(nseg) : 256u;      // one atomic per block, all to one address: few blocks
-    if (pw == 32) hipLaunchKernelGGL(max_segment_kernel<int32_t>, dim3(seg_blocks), dim3(kThreads), 0, st, (const int32_t *)pos, nseg, out);
-    else hipLaunchKernelGGL(max_segment_kernel<int64_t>, dim3(seg_blocks), dim3(kThreads), 0, st, (const int64_t *)pos, nseg, out);
-    SP_HIP(hipGetLastError());
-    return SP_OK;
+    return pos_stats(pos, pw, nseg, out, nullptr, st);
 }
 
 sp_status spmi_ensure_tables(const sp_tensor *t, hipStream_t st)
@@ -1073,32 +974,24 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
     const int rank = enc->rank;
     const sp_dtype dt = (sp_dtype)t->dtype;
     const int vsz0 = dt == SP_F64 ? 8 : 4;
-    const size_t cnt = (size_t)(nnz > 0 ? nnz : 1);
-    uint64_t *parentA = nullptr, *parentB = nullptr;      // allocated when a level needs them
-    uint32_t *child = (uint32_t *)tmp.get(cnt * 4);
-    if (!child) return SP_ERR_ALLOC;
     if (nnz > 0) SP_TRY(spmi_sort_pairs(keys, payload, vsz0, nnz, key_bits, tmp, st, plan, &keys, &payload));
-    // The duplicate check rides along with the first compressed level's kernel (it reads the same neighbouring keys); it
-    // runs on its own only where no such kernel comes before its result is needed.
-    bool dup_pending = !sum_duplicates && nnz > 0;
-    auto run_dup_check = [&]() -> sp_status {
-        if (!dup_pending) return SP_OK;
-        dup_pending = false;
-        hipLaunchKernelGGL(check_duplicates_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, st, (const uint64_t *)keys, nnz, flags);
-        SP_HIP(hipGetLastError());
-        return SP_OK;
-    };
     // The input checks (a coordinate out of range, an entry given twice) come back to the host with the last read-back
     // of the build, not here: a host synchronisation in the middle costs a tenth of a small pack.  Every kernel below stays
     // in bounds on such input (bad coordinates were replaced by 0 when the keys were made; equal keys only make equal
     // writes).  input_error() reads them early where another error would otherwise be reported in their place.
+    int *dup_flags = sum_duplicates ? nullptr : flags;
     auto input_error = [&]() -> sp_status {
-        SP_TRY(run_dup_check());
+        if (dup_flags && nnz > 1) {
+            hipLaunchKernelGGL(check_duplicates_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, st, (const uint64_t *)keys, nnz, flags);
+            SP_HIP(hipGetLastError());
+        }
         int h[2] = {0, 0};
         if (hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) return SP_ERR_HIP;
         return h[0] ? SP_ERR_COORD_RANGE : h[1] ? SP_ERR_DUPLICATE : SP_OK;
     };
     if (sum_duplicates && nnz > 1) {
+        uint32_t *child = (uint32_t *)tmp.get((size_t)nnz * 4);
+        if (!child) return SP_ERR_ALLOC;
         hipLaunchKernelGGL(mark_heads_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, st, (const uint64_t *)keys, nnz, child);
         SP_HIP(hipGetLastError());
         SP_TRY(spmi_exclusive_scan(child, nnz, 32, tmp, st));
@@ -1128,76 +1021,74 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
     }
     t->nnz = nnz;
 
-    // level sweep
-    const uint64_t *pin = nullptr;      // nullptr = the position at the level above is the key prefix (dense levels so far)
-    bool dense_prefix = true;
-    int which = 0;
+    // level sweep: the sizes of the compressed levels above the innermost come back to the host, then everything is written
+    uint32_t *counts = nullptr;
+    unsigned long long totals[SP_MAX_RANK] = {0};
+    {
+        unsigned long long *d_totals = (unsigned long long *)tmp.get(sizeof(totals));
+        if (!d_totals) return SP_ERR_ALLOC;
+        SP_TRY(spmi_sweep_count(t, keys, nnz, tmp, st, d_totals, &counts));
+        if (counts) {
+            SP_HIP(hipMemcpyAsync(totals, d_totals, sizeof(totals), hipMemcpyDeviceToHost, st));
+            SP_HIP(hipStreamSynchronize(st));
+        }
+    }
     int64_t P = 1;
-    for (int l = 0; l < rank; ++l) {
-        uint64_t stride_u = 1;
-        for (int k = l + 1; k < rank; ++k) stride_u *= (uint64_t)(t->size[k] > 0 ? t->size[k] : 1);
-        const divisor stride = make_divisor(stride_u);
-        const divisor size = make_divisor((uint64_t)(t->size[l] > 0 ? t->size[l] : 1));
-        if (enc->lt[l] == SP_DENSE && dense_prefix) {
-            P *= t->size[l];                  // nothing to compute: the position at this level is the key prefix
-            continue;
+    for (int l = 0, slot = 0; l < rank; ++l) {
+        if (enc->lt[l] == SP_DENSE) { P *= t->size[l]; continue; }
+        const int64_t nchild = l == rank - 1 ? nnz : (int64_t)totals[slot++];
+        if (enc->pw_store < 64 && nchild > (((int64_t)1 << (enc->pw_store - 1)) - 1)) {
+            SP_TRY(input_error());
+            return SP_ERR_WIDTH;
         }
-        const bool last_compressed = enc->lt[l] == SP_COMPRESSED && l == rank - 1;
-        uint64_t *pout = nullptr;
-        if (!last_compressed && nnz > 0) {
-            uint64_t *&buf = which ? parentB : parentA;
-            if (!buf) { buf = (uint64_t *)tmp.get(cnt * 8); if (!buf) return SP_ERR_ALLOC; }
-            pout = buf;
-        }
-        if (enc->lt[l] == SP_DENSE) {
-            if (nnz > 0) {
-                hipLaunchKernelGGL(dense_level_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, st, (const uint64_t *)keys, nnz,
-                                   stride, size, pin, pout);
-                SP_HIP(hipGetLastError());
-            }
-            P *= t->size[l];
+        const size_t pbytes = pad16((size_t)(P + 1) * (enc->pw / 8));
+        const size_t cbytes = pad16((size_t)(nchild > 0 ? nchild : 1) * (enc->cw / 8));
+        t->pos[l] = mem.get(pbytes);
+        t->crd[l] = mem.get(cbytes);
+        t->npos[l] = P + 1;
+        t->ncrd[l] = nchild;
+        if (!t->pos[l] || !t->crd[l]) return SP_ERR_ALLOC;
+        // under a dense level the children of every position are counted first (some have none)
+        if (nnz == 0 || (l > 0 && enc->lt[l - 1] == SP_DENSE)) SP_TRY(spmi_fill_zero(t->pos[l], pbytes, st));
+        else if (l == 0) SP_TRY(spmi_fill_zero(t->pos[l], 16, st));
+        P = nchild;
+    }
+
+    // values: zero padding only where a dense level sits below a compressed one.  With a compressed innermost level the
+    // sorted payload already is the values array: the tensor takes that buffer over when the sort (or the summation)
+    // made it, and copies only when it still is the caller's own array.
+    const size_t vsz = dt == SP_F64 ? 8 : 4;
+    const size_t vbytes = pad16((size_t)(P > 0 ? P : 1) * vsz);
+    t->nvalues = P;
+    const bool inner_compressed = enc->lt[rank - 1] == SP_COMPRESSED;
+    if (nnz > 0 && inner_compressed && tmp.release((void *)payload)) {
+        t->values = (void *)payload;
+    } else {
+        t->values = mem.get(vbytes);
+        if (!t->values) return SP_ERR_ALLOC;
+        if (P != nnz) SP_TRY(spmi_fill_zero(t->values, vbytes, st));
+        if (nnz > 0 && inner_compressed) SP_HIP(hipMemcpyAsync(t->values, payload, (size_t)nnz * vsz, hipMemcpyDeviceToDevice, st));
+    }
+
+    if (nnz > 0) {
+        bool csr_like = inner_compressed && rank > 1;             // every level above the innermost dense
+        for (int l = 0; l + 1 < rank; ++l) csr_like &= enc->lt[l] == SP_DENSE;
+        if (csr_like) {
+            const spmi_divisor size = spmi_make_divisor((uint64_t)t->size[rank - 1]);
+#define SPMI_INNER(PT, CT)                                                                                                        \
+    hipLaunchKernelGGL((emit_inner_kernel<PT, CT>), dim3(blocks_for((nnz + 3) / 4)), dim3(kThreads), 0, st, (const uint64_t *)keys, nnz, size, \
+                       (PT *)t->pos[rank - 1], (CT *)t->crd[rank - 1], dup_flags)
+            if (enc->pw == 32 && enc->cw == 32) SPMI_INNER(int32_t, int32_t);
+            else if (enc->pw == 32) SPMI_INNER(int32_t, int64_t);
+            else if (enc->cw == 32) SPMI_INNER(int64_t, int32_t);
+            else SPMI_INNER(int64_t, int64_t);
+#undef SPMI_INNER
+            SP_HIP(hipGetLastError());
         } else {
-            int64_t nchild = nnz;
-            const uint32_t *child_excl = nullptr;
-            if (l != rank - 1 && nnz > 0) {
-                hipLaunchKernelGGL(mark_children_kernel, dim3(blocks_for(nnz)), dim3(kThreads), 0, st, (const uint64_t *)keys, nnz, stride, child);
-                SP_HIP(hipGetLastError());
-                SP_TRY(spmi_exclusive_scan(child, nnz, 32, tmp, st));
-                // children = exclusive[nnz-1] + mark[nnz-1]; the last mark is recomputed from the two last keys
-                uint32_t last_excl = 0;
-                uint64_t lastk[2] = {0, 0};
-                SP_HIP(hipMemcpyAsync(&last_excl, child + (nnz - 1), 4, hipMemcpyDeviceToHost, st));
-                const int64_t from = nnz >= 2 ? nnz - 2 : 0;
-                SP_HIP(hipMemcpyAsync(lastk, keys + from, (size_t)(nnz - from) * 8, hipMemcpyDeviceToHost, st));
-                SP_HIP(hipStreamSynchronize(st));
-                const bool last_mark = nnz == 1 || (lastk[0] / stride_u != lastk[1] / stride_u);
-                nchild = (int64_t)last_excl + (last_mark ? 1 : 0);
-                child_excl = child;
-            }
-            if (enc->pw_store < 64 && nchild > (((int64_t)1 << (enc->pw_store - 1)) - 1)) {
-                SP_TRY(input_error());
-                return SP_ERR_WIDTH;
-            }
-            const size_t pbytes = pad16((size_t)(P + 1) * (enc->pw / 8));
-            const size_t cbytes = pad16((size_t)(nchild > 0 ? nchild : 1) * (enc->cw / 8));
-            t->pos[l] = mem.get(pbytes);
-            t->crd[l] = mem.get(cbytes);
-            t->npos[l] = P + 1;
-            t->ncrd[l] = nchild;
-            if (!t->pos[l] || !t->crd[l]) return SP_ERR_ALLOC;
-            SP_TRY(spmi_fill_zero(t->pos[l], pbytes, st));
-            if (nnz > 0) {
-                if (enc->pw == 32 && enc->cw == 32) SP_TRY((launch_emit<int32_t, int32_t>(keys, nnz, stride, size, child_excl, pin, pout, t->pos[l], t->crd[l], dup_pending ? flags : nullptr, st)));
-                else if (enc->pw == 32) SP_TRY((launch_emit<int32_t, int64_t>(keys, nnz, stride, size, child_excl, pin, pout, t->pos[l], t->crd[l], dup_pending ? flags : nullptr, st)));
-                else if (enc->cw == 32) SP_TRY((launch_emit<int64_t, int32_t>(keys, nnz, stride, size, child_excl, pin, pout, t->pos[l], t->crd[l], dup_pending ? flags : nullptr, st)));
-                else SP_TRY((launch_emit<int64_t, int64_t>(keys, nnz, stride, size, child_excl, pin, pout, t->pos[l], t->crd[l], dup_pending ? flags : nullptr, st)));
-                dup_pending = false;
-            }
-            SP_TRY(spmi_exclusive_scan(t->pos[l], P + 1, enc->pw, tmp, st));
-            P = nchild;
+            SP_TRY(spmi_sweep_emit(t, keys, nnz, counts, payload, inner_compressed ? nullptr : t->values, dup_flags, st));
         }
-        if (enc->lt[l] == SP_COMPRESSED) dense_prefix = false;
-        if (nnz > 0 && !last_compressed) { pin = pout; which ^= 1; }
+        for (int l = 1; l < rank; ++l)
+            if (enc->lt[l] == SP_COMPRESSED && enc->lt[l - 1] == SP_DENSE) SP_TRY(spmi_exclusive_scan(t->pos[l], t->npos[l], enc->pw, tmp, st));
     }
 
     // 8- and 16-bit widths: the arrays handed out are narrowed copies of the 32-bit working arrays
@@ -1226,32 +1117,6 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
         SP_HIP(hipGetLastError());
     }
 
-    // values: zero padding only where a dense level sits below a compressed one.  With a compressed innermost level the
-    // sorted payload already is the values array: the tensor takes that buffer over when the sort (or the summation)
-    // made it, and copies only when it still is the caller's own array.
-    const size_t vsz = dt == SP_F64 ? 8 : 4;
-    const size_t vbytes = pad16((size_t)(P > 0 ? P : 1) * vsz);
-    t->nvalues = P;
-    if (nnz > 0 && enc->lt[rank - 1] == SP_COMPRESSED && tmp.release((void *)payload)) {
-        t->values = (void *)payload;
-    } else {
-        t->values = mem.get(vbytes);
-        if (!t->values) return SP_ERR_ALLOC;
-        if (P != nnz) SP_TRY(spmi_fill_zero(t->values, vbytes, st));
-        if (nnz > 0) {
-            // where each sorted entry's value goes: its own rank (innermost level compressed), the key itself (every
-            // level dense), or the position carried down from the last compressed level
-            const uint64_t *position = (enc->lt[rank - 1] == SP_COMPRESSED) ? nullptr : dense_prefix ? (const uint64_t *)keys : pin;
-            if (dt == SP_F64)
-                hipLaunchKernelGGL(place_values_kernel<unsigned long long>, dim3(blocks_for(nnz)), dim3(kThreads), 0, st,
-                                   (const unsigned long long *)payload, position, nnz, (unsigned long long *)t->values);
-            else
-                hipLaunchKernelGGL(place_values_kernel<uint32_t>, dim3(blocks_for(nnz)), dim3(kThreads), 0, st,
-                                   (const uint32_t *)payload, position, nnz, (uint32_t *)t->values);
-            SP_HIP(hipGetLastError());
-        }
-    }
-    SP_TRY(run_dup_check());
     int hf[2] = {0, 0};
     SP_TRY(spmi_finish_tensor(t, flags, tmp, st, sum_duplicates ? nullptr : hf));
     if (hf[0]) return SP_ERR_COORD_RANGE;

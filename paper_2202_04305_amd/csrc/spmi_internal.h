@@ -195,6 +195,49 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// Division of a key by a level's stride or size, which the host knows when it launches: a shift when the divisor is a
+// power of two, a multiplication by the reciprocal in double plus a one-step correction while the dividend is below
+// 2^52 (the estimate is then within one of the quotient), the hardware's 64-bit division otherwise.
+struct spmi_divisor {
+    uint64_t d;
+    double inv;
+    int shift;          // >= 0: d == 1 << shift
+};
+
+static inline spmi_divisor spmi_make_divisor(uint64_t d)
+{
+    spmi_divisor v;
+    v.d = d;
+    v.inv = 1.0 / (double)d;
+    v.shift = -1;
+    if ((d & (d - 1)) == 0) { v.shift = 0; while (((uint64_t)1 << v.shift) != d) ++v.shift; }
+    return v;
+}
+
+__device__ inline uint64_t spmi_div_by(uint64_t x, const spmi_divisor &v)
+{
+    if (v.shift >= 0) return x >> v.shift;
+    if (x < ((uint64_t)1 << 52)) {
+        uint64_t q = (uint64_t)((double)x * v.inv);
+        const int64_t r = (int64_t)(x - q * v.d);
+        if (r < 0) --q;
+        else if ((uint64_t)r >= v.d) ++q;
+        return q;
+    }
+    return x / v.d;
+}
+
+// ---- levels.hip ----
+// First half of the level sweep over n sorted keys: *counts = what the second half needs (a temporary of `tmp`; null when no
+// compressed level lies above the innermost one), totals[0..] (DEVICE, one per such level from the outermost on) = their sizes.
+sp_status spmi_sweep_count(const sp_tensor *t, const uint64_t *keys, int64_t n, sp_scratch &tmp, hipStream_t st, unsigned long long *totals,
+                           uint32_t **counts);
+// Second half: writes crd and pos of every compressed level of t (allocated by the caller; pos under a dense level is left as
+// counts to be scanned, and arrives zeroed), and, where the innermost level is dense (vout not null), every value to its position.
+// dup_flags (may be null): dup_flags[1] is set when a key occurs twice.
+sp_status spmi_sweep_emit(const sp_tensor *t, const uint64_t *keys, int64_t n, const uint32_t *counts, const void *vals, void *vout, int *dup_flags,
+                          hipStream_t st);
+
 // ---- pack.hip ----------------------------------------------------------------------------
 // In-place exclusive prefix sum of n elements of width `bits` (32 or 64); data[n-1] afterwards
 // holds the sum of the first n-1 inputs.
