@@ -593,7 +593,7 @@ def bench_matmul(args, torch, sp, dev, name, w, wbits, full):
             kernel_name = "dense_rows_kernel"
     else:
         kernel_name = "sddmm_rows_vec_kernel" if sddmm else "spmm_scatter_kernel" if (name == "cfg5" and args.csc_mode == 1) else (
-            "spmm_rows_kernel" if args.spmm_kernel == 1 else "spmm_rows_vec_kernel" if args.spmm_kernel == 2 else "spmm_windows_vec_kernel (+ fix-up)")
+            "spmm_rows_kernel" if args.spmm_kernel == 1 else "spmm_rows_vec_kernel" if args.spmm_kernel == 2 else "spmm_runs_kernel (+ fix-up)")
     achieved = abytes / (kernel_ms * 1e-3) / 1e9
     traffic, traffic_source = (None, None) if args.small else measured_traffic(name, wbits, kk if spmv else 0)
     # what the kernel's own design has to move (the binned SpMV streams 28 bytes per stored entry instead of CSR's 12), priced at

@@ -426,93 +426,136 @@ __global__ __launch_bounds__(kThreads) void spmm_rows_vec_kernel(const PT *__res
     }
 }
 
-// The same product cut by stored entries instead of rows (tune value 3; automatic when some row is long): block w
-// owns the entries [w*T, (w+1)*T) with T and `rowblk` as in the stream SpMV, its four waves take the rows that meet
-// the window in turn.  The part of a row that began in an earlier window goes to carry[w] (N values) and the fix-up
-// kernel below adds the carries to C in block order; everything else is written to C directly.  No atomics.
-// The window's values and, instead of its coordinates, the byte offsets of the rows of B that they select (OT: 32 bits
-// when B is below 4 GB) are first copied into LDS with coalesced loads: the loop over the entries then works on small
-// window-relative integers and every gather address is a wave-uniform base plus a lane offset.
-template <typename PT, typename CT, typename VT, int LR, typename OT>
-__global__ __launch_bounds__(kThreads) void spmm_windows_vec_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd,
-                                                                    const VT *__restrict__ val, const CT *__restrict__ rowid,
-                                                                    const int32_t *__restrict__ rowblk, int64_t nrows, int64_t nnz,
-                                                                    const VT *__restrict__ B, int64_t ldb, VT *__restrict__ C, int64_t ldc,
-                                                                    VT *__restrict__ carry, int accumulate, int lr_any)
+// The product cut by stored entries for any number of columns, leading dimension and element-aligned address.  Block = window
+// of 1024 stored entries as above (blockIdx.y: a tile of lr_tile * V columns).  A group of LR lanes covers a row of B, V
+// elements per lane, and takes a run of consecutive entries, whatever rows they belong to: it adds up while the row stays the
+// same and writes C when it changes, so rows of any length keep every lane busy.  The sum of a row that began in an earlier
+// run of the window waits in LDS for the group that began it, which adds such sums in order; the part of a row that began in
+// an earlier window goes to carry[w].  Fixed order, no atomics.
+// The last lane of a row moves back to the last V columns and stores only those that the lane before it does not have, so
+// every load is V elements wide (the memory path takes such loads at any element-aligned address).
+// Bound by the rows of B it gathers (16.9 M random 512-byte rows alone: 1.15 ms).  Measured before (a wave per row of the
+// window with shuffles at the end of every row; a wave per row and a column per lane for widths that are no multiple of 16
+// bytes) and now: 16.9 M entries, 64 f64 columns 1.329 -> 1.289 ms; 33.6 M entries with short rows, 32 f32 columns 561 -> 417 us;
+// 5.0 M entries, 64-bit pos / crd, 33 f64 columns 1.250 -> 0.282 ms; 4 M entries, 4 per row, 2 f64 columns 303 -> 75 us.
+template <typename PT, typename CT, typename VT, int V, typename OT>
+__global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd, const VT *__restrict__ val,
+                                                             const CT *__restrict__ rowid, const int32_t *__restrict__ rowblk, int64_t nrows,
+                                                             int64_t nnz, const VT *__restrict__ B, int64_t N, int64_t ldb, int lr_tile,
+                                                             VT *__restrict__ C, int64_t ldc, VT *__restrict__ carry, int accumulate)
 {
-    constexpr int V = 16 / sizeof(VT);
-    const int LRv = LR > 0 ? LR : lr_any;             // LR = 0: any number of lanes per row of B, known at run time
-    const int S = 64 / LRv;
-    constexpr int U = (LR > 0 && 64 / (LR > 0 ? LR : 1) >= 4) ? 2 : 4;
+    constexpr int T = (int)kStreamT, U = 4, kWaves = kThreads / 64;
     typedef VT vec_t __attribute__((ext_vector_type(V)));
-    __shared__ OT s_off[kStreamT];
-    __shared__ VT s_val[kStreamT];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int jl = lane % LRv, sl = lane / LRv;
-    const int64_t s = (int64_t)blockIdx.x * kStreamT;
-    const int64_t e = s + kStreamT < nnz ? s + kStreamT : nnz;
+    typedef VT mem_vec_t __attribute__((ext_vector_type(V), aligned(sizeof(VT))));
+    constexpr int kRoom = T + kThreads;                              // groups * run length, run length rounded up
+    __shared__ OT s_off[kRoom];
+    __shared__ VT s_val[kRoom];
+    __shared__ CT s_row[kRoom];
+    __shared__ vec_t s_part[kThreads];
+    __shared__ int s_wave[kWaves];
+    const int64_t j0 = (int64_t)blockIdx.y * lr_tile * V;
+    const int64_t width = N - j0 < (int64_t)lr_tile * V ? N - j0 : (int64_t)lr_tile * V;
+    const int LR = (int)((width + V - 1) / V);                       // 1..64
+    const int S = 64 / LR, G = kWaves * S;                           // groups per wave, per block
+    const int run = (T + G - 1) / G;                                 // entries per group
+    const uint32_t by_run = (uint32_t)(((uint64_t)1 << 22) / (uint32_t)run + 1);      // i / run for i < 1024: exact, run <= 256
+    // entry i of the window is kept at (i % run) * G + i / run: the groups of a wave read neighbouring words
+    auto at = [=](int i) { const int g = (int)(((uint32_t)i * by_run) >> 22); return (i - g * run) * G + g; };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t s = (int64_t)blockIdx.x * T;
+    const int64_t e = s + T < nnz ? s + T : nnz;
     const int ne = (int)(e - s);
     const OT brow = (OT)(ldb * (int64_t)sizeof(VT));
-    for (int i = threadIdx.x; i < ne; i += kThreads) {
-        s_off[i] = (OT)crd[s + i] * brow;
-        s_val[i] = val[s + i];
+#pragma unroll
+    for (int x = 0; x < T / kThreads; ++x) {
+        const int i = x * kThreads + threadIdx.x;
+        if (i < ne) {
+            const int w = at(i);
+            s_off[w] = (OT)crd[s + i] * brow;
+            s_val[w] = val[s + i];
+        }
     }
     const int64_t lo = rowblk[blockIdx.x], hi = rowblk[blockIdx.x + 1];
     const int64_t last = hi < nrows ? hi : nrows - 1;
-    __syncthreads();
+    const bool continued = (int64_t)pos[lo] < s;                     // the first row began in an earlier window
+    spmi_rows_of_entries<kThreads, T / kThreads>(pos, rowid, lo, last, s, e, s_row, s_wave, at);
+    if (!accumulate && !rowid)                                       // rows without entries: zero (with a row list C was cleared before)
+        for (int64_t r0 = lo + wave * 64; r0 <= last; r0 += kThreads) {
+            const int64_t r = r0 + lane;
+            uint64_t empty = __ballot(r <= last && r != hi && pos[r <= last ? r : last] == pos[(r <= last ? r : last) + 1]);
+            for (; empty; empty &= empty - 1) {
+                VT *dst = C + (r0 + __builtin_ctzll(empty)) * ldc + j0;
+                for (int64_t j = lane; j < width; j += 64) dst[j] = (VT)0;
+            }
+        }
+    const int sl = lane / LR, jl = lane - sl * LR;
+    const int group = sl < S ? wave * S + sl : G;                    // lanes beyond S * LR take nothing
+    const int first = group * run < ne ? group * run : ne, end = first + run < ne ? first + run : ne;
+    const int64_t want = j0 + (int64_t)jl * V;
+    const int64_t col = want <= N - V ? want : N - V;                // this lane's columns: [col, col + V), its own from skip on
+    const int skip = (int)(want - col);
+    const OT colb = (OT)(col * (int64_t)sizeof(VT));
     const char *Bb = (const char *)B;
-    const OT colb = (OT)(jl * V * (int)sizeof(VT));
-    int slot[U];
+    auto store = [&](VT *dst, vec_t v, bool add) {
+        if (skip == 0) {
+            mem_vec_t *d = (mem_vec_t *)dst;
+            if (add) *d = *d + v;
+            else *d = v;
+        } else {
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot[u] = sl < S ? sl + u * S : (1 << 24);      // lanes beyond LR * S never take an entry
-    for (int64_t r = lo + wave; r <= last; r += kThreads / 64) {
-        const int64_t pa = (int64_t)pos[r], pb = (int64_t)pos[r + 1];
-        const int a = (int)((pa > s ? pa : s) - s), b = (int)((pb < e ? pb : e) - s);
-        if (r == hi && b <= a) continue;              // row hi starts at the next window: not ours (wave-uniform)
-        vec_t accu[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) accu[u] = (vec_t)(0);
-        for (int p0 = a; p0 < b; p0 += U * S) {       // wave-uniform
-            VT v[U];
-            vec_t bv[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int pp = p0 + slot[u];
-                const bool in = pp < b;
-                const int idx = in ? pp : a;
-                v[u] = in ? s_val[idx] : (VT)0;
-                bv[u] = *(const vec_t *)(Bb + (s_off[idx] + colb));
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) accu[u] += v[u] * bv[u];
+            for (int c = 1; c < V; ++c)
+                if (c >= skip) dst[c] = add ? dst[c] + v[c] : v[c];
         }
-        vec_t acc0 = accu[0];
+    };
+    const int slot = group * LR + jl;                                // this lane's place in s_part
+    vec_t acc = (vec_t)(0);
+    CT row = 0;
+    bool head = false;                                               // the row being added up began before this run
+    if (first < end) {
+        row = s_row[group];
+        head = group == 0 ? continued : s_row[(run - 1) * G + group - 1] == row;
+    }
+    for (int k = 0; k < end - first; k += U) {
+        VT v[U];
+        vec_t bv[U];
+        CT rw[U];
 #pragma unroll
-        for (int u = 1; u < U; ++u) acc0 += accu[u];
-        if (LR > 0) {
-#pragma unroll
-            for (int ee = 0; ee < V; ++ee) {
-                VT x = acc0[ee];
-#pragma unroll
-                for (int d = 32; d >= (LR > 0 ? LR : 64); d >>= 1) x += __shfl_xor(x, d, 64);
-                acc0[ee] = x;
-            }
-        } else {                                      // the S groups' sums meet in group 0
-            const vec_t mine = acc0;
-            for (int g = 1; g < S; ++g) {
-#pragma unroll
-                for (int ee = 0; ee < V; ++ee) acc0[ee] += __shfl(mine[ee], jl + g * LRv, 64);
-            }
+        for (int u = 0; u < U; ++u) {
+            const int w = (first + k + u < end ? k + u : end - first - 1) * G + group;
+            rw[u] = s_row[w];
+            v[u] = s_val[w];
+            bv[u] = *(const mem_vec_t *)(Bb + (s_off[w] + colb));
         }
-        if (sl == 0) {
-            if (pa < s) *(vec_t *)(carry + (int64_t)blockIdx.x * LRv * V + jl * V) = acc0;
-            else {
-                const int64_t row = rowid ? (int64_t)rowid[r] : r;
-                vec_t *dst = (vec_t *)(C + row * ldc + jl * V);
-                *dst = accumulate ? *dst + acc0 : acc0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (first + k + u < end) {
+                if (rw[u] != row) {
+                    if (head) s_part[slot] = acc;
+                    else store(C + (int64_t)row * ldc + col, acc, accumulate);
+                    head = false;
+                    row = rw[u];
+                    acc = (vec_t)(0);
+                }
+                acc += v[u] * bv[u];
             }
         }
+    }
+    if (head) s_part[slot] = acc;                                    // the whole run belongs to a row that began before it
+    // The sums of a row that fills whole runs are added up towards the first of them, over twice as many groups each step.
+    const int full = (ne + run - 1) / run;                           // groups that took something
+    if (__syncthreads_or(head))
+        for (int d = 1; d < full; d <<= 1) {
+            const bool take = group + d < full && s_row[group + d] == s_row[group];      // rows ascend: everything between is that row's too
+            const vec_t other = take ? s_part[slot + d * LR] : (vec_t)(0);
+            __syncthreads();
+            if (take) s_part[slot] += other;
+            __syncthreads();
+        }
+    if (first >= end) return;
+    if (group == 0 && continued) store(carry + (int64_t)blockIdx.x * N + col, s_part[slot], false);
+    if (!head) {
+        if (group + 1 < full && s_row[group + 1] == row) acc += s_part[slot + LR];
+        store(C + (int64_t)row * ldc + col, acc, accumulate);
     }
 }
 
@@ -529,9 +572,21 @@ __global__ __launch_bounds__(kThreads) void spmm_windows_fixup_kernel(const PT *
     const int64_t start = (int64_t)pos[r];
     if (start >= b * kStreamT || start < (b - 1) * kStreamT) return;   // not crossed here, or crossed earlier already
     const int64_t row = rowid ? (int64_t)rowid[r] : r;
+    // the blocks whose window begins inside the row: 64 of them looked at a time
+    int64_t stop = b;
+    for (uint64_t same = ~(uint64_t)0; same == ~(uint64_t)0; ) {
+        const int64_t bb = stop + lane;
+        same = __ballot(bb < nblocks && rowblk[bb < nblocks ? bb : nblocks] == r);
+        stop += same == ~(uint64_t)0 ? 64 : __builtin_ctzll(~same);
+    }
     for (int64_t j = lane; j < N; j += 64) {
         VT sum = 0;
-        for (int64_t bb = b; bb < nblocks && rowblk[bb] == r; ++bb) sum += carry[bb * N + j];
+        int64_t bb = b;
+        for (; bb + 4 <= stop; bb += 4) {
+            const VT c0 = carry[bb * N + j], c1 = carry[(bb + 1) * N + j], c2 = carry[(bb + 2) * N + j], c3 = carry[(bb + 3) * N + j];
+            sum = (((sum + c0) + c1) + c2) + c3;
+        }
+        for (; bb < stop; ++bb) sum += carry[bb * N + j];
         C[row * ldc + j] += sum;
     }
 }
@@ -696,13 +751,12 @@ struct row_view {
 };
 
 // The SpMM cut by stored entries plus its fix-up, with the per-block carries in `carry` (room for N values per block).
-// N * sizeof(VT) is a multiple of 16 with at most 64 such pieces per row; B, C and their leading dimensions are 16-byte aligned.
+// N >= 2.
 template <typename PT, typename CT, typename VT>
 sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, const VT *B, int64_t N, int64_t ldb, VT *C, int64_t ldc,
                               int accumulate, VT *carry, hipStream_t st)
 {
-    constexpr int64_t V = 16 / sizeof(VT);
-    const int64_t lr = N / V;
+    constexpr int V = 16 / sizeof(VT);
     const PT *pos = rv.pos;
     const CT *crd = (const CT *)A->crd[1];
     const VT *val = (const VT *)A->values;
@@ -711,22 +765,24 @@ sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, co
     const sp_rowblocks *rowblocks = rv.rowblocks;
     const int64_t nb = rowblocks->nblocks;
     const bool small = sizeof(CT) == 4 && (uint64_t)A->shape[1] * (uint64_t)ldb * sizeof(VT) < ((uint64_t)1 << 32);     // 32-bit byte offsets into B (64-bit coordinates keep 64-bit offsets)
-#define SPMI_SPMM_WIN_O(LR, OT)                                                                                               \
-    hipLaunchKernelGGL((spmm_windows_vec_kernel<PT, CT, VT, LR, OT>), dim3((unsigned)nb), dim3(kThreads), 0, st, pos, crd, val, rowid,    \
-                       (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, carry, accumulate, (int)lr)
-#define SPMI_SPMM_WIN(LR)                           \
+#define SPMI_SPMM_RUNS_O(VV, OT)                                                                                              \
+    hipLaunchKernelGGL((spmm_runs_kernel<PT, CT, VT, VV, OT>), dim3((unsigned)nb, (unsigned)ceil_div(ceil_div(N, VV), lr_tile)), dim3(kThreads), 0, \
+                       st, pos, crd, val, rowid, (const int32_t *)rowblocks->start, nrows, nnz, B, N, ldb, lr_tile, C, ldc, carry, accumulate)
+#define SPMI_SPMM_RUNS(VV)                          \
     do {                                            \
-        if (small) SPMI_SPMM_WIN_O(LR, uint32_t);   \
-        else SPMI_SPMM_WIN_O(LR, uint64_t);         \
+        if (small) SPMI_SPMM_RUNS_O(VV, uint32_t);  \
+        else SPMI_SPMM_RUNS_O(VV, uint64_t);        \
     } while (0)
-    if (lr == 1) SPMI_SPMM_WIN(1);
-    else if (lr == 2) SPMI_SPMM_WIN(2);
-    else if (lr == 4) SPMI_SPMM_WIN(4);
-    else if (lr == 8) SPMI_SPMM_WIN(8);
-    else if (lr == 16) SPMI_SPMM_WIN(16);
-    else if (lr == 32) SPMI_SPMM_WIN(32);
-    else if (lr == 64) SPMI_SPMM_WIN(64);
-    else SPMI_SPMM_WIN(0);                    // any other number of 16-byte pieces per row, up to 64
+    const int VV = N >= V ? V : 2;                // two or three columns in f32: loads of two
+    const int64_t pieces = ceil_div(N, VV);
+    // at least 512 blocks where the columns allow: few windows share the columns out among more blocks
+    const int64_t split = nb < 512 ? ceil_div(512, nb) : 1;
+    const int64_t wanted = ceil_div(pieces, split) > 4 ? ceil_div(pieces, split) : 4;
+    const int lr_tile = (int)(wanted < 64 ? wanted : 64);
+    if (VV == V) SPMI_SPMM_RUNS(V);
+    else SPMI_SPMM_RUNS(2);
+#undef SPMI_SPMM_RUNS
+#undef SPMI_SPMM_RUNS_O
 #undef SPMI_SPMM_WIN
 #undef SPMI_SPMM_WIN_O
     SP_HIP(hipGetLastError());
@@ -910,16 +966,28 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
         const bool fits_any = aligned && lr >= 1 && lr <= 64;                                                           // cut by entries
         if (A->tune_spmm == 2 && !fits) return SP_ERR_UNSUPPORTED;
         if (A->tune_spmm == 3 && (!fits_any || !rowblocks->start)) return SP_ERR_UNSUPPORTED;
-        // measured faster than a wave per row on every workload tried (1.42 vs 1.57 ms, 0.68 vs 0.83 ms), and a very long
-        // row no longer sets the run time: the default
-        const bool by_entries = A->tune_spmm == 3 || (A->tune_spmm == 0 && rowblocks->start);
-        if (fits_any && by_entries) {
+        // Cut by entries is faster than a wave per row from some 10^5 entries on, whatever the width and the row lengths (300,000
+        // entries, 20,000 skewed rows, f64: 14 against 29 us with 5 columns, 30 against 413 us with 64).  A smaller product
+        // is its second launch (20,000 entries: 12 against 8 us), unless a wave walks a long row in many steps: widths that
+        // have no 16-byte kernel keep the single launch up to twelve steps.
+        const int64_t cg = N > 32 ? 64 * ceil_div(N, 64) * 2 : N > 16 ? 32 : N > 8 ? 16 : N > 4 ? 8 : 4;       // lanes of a wave per entry there
+        const bool tiny = !fits_any && nnz < ((int64_t)1 << 17) && A->max_segment * cg <= 256 * 12;
+        const bool by_entries = A->tune_spmm == 3 || (A->tune_spmm == 0 && rowblocks->start && !tiny);
+        if (by_entries) {
             const int64_t nb = rowblocks->nblocks;
-            if (A->spmm_carry_bytes < (size_t)nb * N * sizeof(VT)) {       // no sp_prepare for this many columns: the scratch is made now
-                ++A->lazy_prepares;
-                SP_TRY((prepare_spmm_t<PT, CT, VT>(A, N, st)));
+            bool scratch = A->spmm_carry_bytes >= (size_t)nb * N * sizeof(VT);
+            if (!scratch) {                      // no sp_prepare for this many columns: the scratch is made now
+                // a product that the wave-per-row kernel can also do goes there when there is no scratch to be had
+                hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+                if (!fits_any) SP_HIP(hipStreamIsCapturing(st, &capturing));
+                if (capturing == hipStreamCaptureStatusNone) {
+                    ++A->lazy_prepares;
+                    const sp_status made = prepare_spmm_t<PT, CT, VT>(A, N, st);
+                    if (made != SP_OK && (fits_any || made != SP_ERR_ALLOC)) return made;
+                    scratch = made == SP_OK;
+                }
             }
-            return spmm_windows_launch<PT, CT, VT>(A, rv, B, N, ldb, C, ldc, accumulate, (VT *)A->spmm_carry, st);
+            if (scratch) return spmm_windows_launch<PT, CT, VT>(A, rv, B, N, ldb, C, ldc, accumulate, (VT *)A->spmm_carry, st);
         }
         if (fits && A->tune_spmm != 1) {
 #define SPMI_SPMM_VEC(LR)                                                                                                     \

@@ -195,6 +195,47 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// The row of every stored entry of a stretch [s, e) of a compressed innermost level (at most kThreads * PER entries), made by a
+// whole block in LDS: row[at(i)] = the row of entry s + i, mapped through rowid where there is one.  lo..last are the rows that
+// can meet the stretch, lo among those that begin at or before it.  Each row marks its first entry, the marks' running maximum
+// is every entry's row.  waves: LDS, one int per wave.  The block meets at a barrier on the way in and out.
+template <int kThreads, int PER, typename PT, typename CT, typename AT>
+__device__ __forceinline__ void spmi_rows_of_entries(const PT *__restrict__ pos, const CT *__restrict__ rowid, int64_t lo, int64_t last, int64_t s,
+                                                     int64_t e, CT *row, int *waves, AT at)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = (int)(e - s);
+    for (int i = tid; i < n; i += kThreads) row[at(i)] = 0;
+    __syncthreads();
+    for (int64_t r = lo + tid; r <= last; r += kThreads) {
+        const int64_t pa = (int64_t)pos[r], pb = (int64_t)pos[r + 1];
+        const int64_t a = pa > s ? pa : s, b = pb < e ? pb : e;
+        if (a < b) row[at((int)(a - s))] = (CT)(r - lo);
+    }
+    __syncthreads();
+    int run = 0, mark[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int x = tid * PER + i;
+        mark[i] = x < n ? (int)row[at(x)] : 0;
+        run = mark[i] > run ? mark[i] : run;
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) { const int v = __shfl_up(run, d, 64); if (lane >= d && v > run) run = v; }
+    if (lane == 63) waves[wave] = run;
+    int before = __shfl_up(run, 1, 64);
+    if (lane == 0) before = 0;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) before = waves[w] > before ? waves[w] : before;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int x = tid * PER + i;
+        before = mark[i] > before ? mark[i] : before;
+        if (x < n) row[at(x)] = rowid ? rowid[lo + before] : (CT)(lo + before);
+    }
+    __syncthreads();
+}
+
 // Division of a key by a level's stride or size, which the host knows when it launches: a shift when the divisor is a
 // power of two, a multiplication by the reciprocal in double plus a one-step correction while the dividend is below
 // 2^52 (the estimate is then within one of the quotient), the hardware's 64-bit division otherwise.

@@ -1,0 +1,107 @@
+"""Dense operands of any width, leading dimension and element-aligned address, against the CPU checker.
+
+The kernels load 16 bytes wherever a row begins and move the last load of a row back to the row's end, so the sizes are
+the edges of that rule: fewer columns than a load holds, one more and one less than a whole number of loads, one more
+than a wave covers; rows longer than a window of 1024 stored entries; an infinity in the columns that two loads share.
+Tolerance: the products' own, 1e-12 (f64) / 1e-5 (f32) times sum|a*b| per element.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2202_04305_amd as sp
+from gen import workloads as W, prng
+from gpu_util import say, dev, gpu_pack, assert_product_close, DEV
+
+pytestmark = pytest.mark.gpu
+
+
+def embedded(a, ld, offset):
+    """The array as a window of a wider one that begins `offset` elements past a 256-byte boundary, NaN around it."""
+    rows, cols = a.shape
+    flat = torch.full((offset + rows * ld + 64,), float("nan"), dtype=torch.from_numpy(a[:1]).dtype, device=DEV)
+    view = flat[offset:offset + rows * ld].view(rows, ld)[:, :cols]
+    view.copy_(dev(a))
+    return flat, view
+
+
+@pytest.mark.parametrize("lt", [(0, 1), (1, 1)])
+@pytest.mark.parametrize("dtype,N", [(np.float64, n) for n in (2, 3, 5, 33, 64, 127, 129, 131)] +
+                         [(np.float32, n) for n in (2, 3, 4, 5, 7, 33, 64, 255, 257)])
+def test_spmm_any_width_and_address(lt, dtype, N):
+    w = W.cfg2_powerlaw_csr(700, 3000, mean=40.0, sigma=1.5, cap=2900)
+    w.rows = w.rows * 2                                    # an empty row after every row
+    w.shape = (1400, 3000)
+    vals = w.vals.astype(dtype)
+    A = gpu_pack(lt, (0, 1), w.shape, [w.rows, w.cols], vals)
+    B = prng.uniform_pm1(7, 1, w.shape[1] * N, dtype=dtype).reshape(-1, N)
+    C0 = prng.uniform_pm1(7, 2, w.shape[0] * N, dtype=dtype).reshape(-1, N)
+    ref, mag = oracle.matmul_coo(w.shape, w.rows, w.cols, vals, B)
+    for extra, offset in [(0, 0), (1, 1), (3, 2)]:
+        for accumulate in (False, True):
+            say("case spmm any width", lt, dtype.__name__, N, extra, offset, accumulate)
+            _, Bd = embedded(B, N + extra, offset)
+            flat, Cd = embedded(C0, N + extra, offset)
+            before = flat.clone()
+            sp.sp_matmul(A, Bd, Cd, accumulate=accumulate)
+            base = C0 if accumulate else np.zeros_like(C0)
+            assert_product_close(Cd, ref + base, mag + np.abs(base), dtype, "spmm")
+            written = torch.zeros_like(flat, dtype=torch.bool)
+            written[offset:offset + w.shape[0] * (N + extra)].view(w.shape[0], N + extra)[:, :N] = True
+            assert torch.equal(torch.isnan(flat[~written]), torch.isnan(before[~written]))
+
+
+@pytest.mark.parametrize("N", [3, 33])
+def test_spmm_any_width_recorded_before_any_scratch_exists(N):
+    """Under capture, on a tensor that was never prepared, the product takes the kernel that needs no scratch."""
+    w = W.cfg2_powerlaw_csr(3000, 2500, cap=900)
+    enc = sp.sp_encode((0, 1), (0, 1), 32, 32)
+    A = sp.sp_pack(enc, w.shape, [dev(w.rows), dev(w.cols)], dev(w.vals))
+    B = prng.uniform_pm1(7, 3, w.shape[1] * N).reshape(-1, N)
+    ref, mag = oracle.matmul_coo(w.shape, w.rows, w.cols, w.vals, B)
+    Bd, Cd = dev(B), torch.empty((w.shape[0], N), dtype=torch.float64, device=DEV)
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):                 # never prepared: nothing may be allocated here
+        sp.sp_matmul(A, Bd, Cd)
+    for _ in range(3):
+        Cd.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert_product_close(Cd, ref, mag, np.float64, "replay")
+
+
+@pytest.mark.parametrize("dtype,K", [(np.float64, k) for k in (2, 3, 15, 17, 33, 64, 127, 129)] +
+                         [(np.float32, k) for k in (3, 4, 5, 31, 33, 64, 255, 257)])
+def test_sddmm_any_width_and_address(dtype, K):
+    """Rows longer than a window, empty rows, operands inside wider ones; CSR and DCSR."""
+    w = W.cfg2_powerlaw_csr(700, 3000, mean=40.0, sigma=1.5, cap=2900)
+    w.rows = w.rows * 2
+    w.shape = (1400, 3000)
+    vals = w.vals.astype(dtype)
+    A = prng.uniform_pm1(8, 1, w.shape[0] * K, dtype=dtype).reshape(-1, K)
+    B = prng.uniform_pm1(8, 2, w.shape[1] * K, dtype=dtype).reshape(-1, K)
+    x, mag = oracle.sddmm_coo(w.shape, w.rows, w.cols, vals, A, np.ascontiguousarray(B.T))
+    for lt in [(0, 1), (1, 1)]:
+        S = gpu_pack(lt, (0, 1), w.shape, [w.rows, w.cols], vals)
+        xs = oracle.pack(lt, (0, 1), w.shape, [w.rows, w.cols], x, 32, 32).values
+        ms = oracle.pack(lt, (0, 1), w.shape, [w.rows, w.cols], mag, 32, 32).values
+        for extra, offset in [(0, 0), (1, 1), (3, 2)]:
+            say("case sddmm any width", lt, dtype.__name__, K, extra, offset)
+            Ad, Bd = embedded(A, K + extra, offset)[1], embedded(B, K + extra, offset)[1]
+            X = torch.full((w.nnz,), float("nan"), dtype=S.dtype, device=DEV)
+            sp.sp_sddmm(S, Ad, Bd, X, b_is_transposed=True)
+            assert_product_close(X, xs, ms, dtype, "sddmm")
+
+
+@pytest.mark.parametrize("K", [5, 33])
+def test_sddmm_keeps_infinities_where_two_loads_meet(K):
+    """inf * 0 in a column that two loads cover must not turn a row's infinite sum into NaN, nor spread to other rows."""
+    w = W.uniform_random(60, 50, 900)
+    A, B = np.ones((60, K)), np.ones((50, K))
+    B[7, K - 2] = B[9, K - 1] = np.inf
+    S = gpu_pack((0, 1), (0, 1), w.shape, [w.rows, w.cols], np.ones(w.nnz))
+    X = sp.sp_sddmm(S, dev(A), dev(B), b_is_transposed=True).cpu().numpy()
+    hit = np.isin(sp.sp_crd(S, 1).cpu().numpy(), (7, 9))
+    assert hit.any() and np.all(np.isposinf(X[hit])) and np.all(X[~hit] == K)
