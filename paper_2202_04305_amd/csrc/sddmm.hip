@@ -5,9 +5,8 @@
 // Per stored entry (i, j) the kernel needs row i of A and column j of B.  B is K x n row-major in the paper's
 // formula, so a column is a stride-n walk; it is transposed once per call into an n x K scratch (unless the caller
 // already holds it that way), after which every entry reads one contiguous row of K values, exactly as the SpMM
-// kernel reads rows of its dense operand.  A wave takes one stored row of S: the row of A sits in registers, LR
-// lanes cover one row of the transposed B with 16-byte loads, 64 / LR entries go side by side, and a short
-// shuffle reduction over the LR lanes finishes each dot product.
+// kernel reads rows of its dense operand.  Groups of lanes take runs of stored entries: the row of A sits in registers,
+// the row of the transposed B comes in 16-byte loads, and a short shuffle reduction finishes each dot product.
 #include "spmi_internal.h"
 
 namespace {
@@ -30,108 +29,138 @@ __global__ __launch_bounds__(256) void transpose_kernel(const VT *__restrict__ B
         if (j0 + r < n && k0 + tx < K) Bt[(j0 + r) * ldt + k0 + tx] = tile[tx][r];
 }
 
-// 16-byte loads: K = LR * (16 / sizeof(VT)), rows of A and of the transposed B 16-byte aligned.
-// Work is cut by stored entries, not by rows: block w owns the entries [w*T, (w+1)*T) (T and the table `rowblk` of
-// the row holding every T-th entry are the stream SpMV's), its waves take the rows that meet that window in turn
-// and each handles the part of its row inside the window.  A row of 20,000 entries is thus spread over 20 blocks
-// instead of being walked by one wave; no results need combining because every entry has its own output.
-// The window's values of S and, instead of its coordinates, the byte offsets of the rows of the transposed B that they
-// select are first copied into LDS with coalesced loads, so
-// that the loop over the entries does its index arithmetic on small window-relative integers and every gather address
-// is a wave-uniform base plus a lane offset (OT: 32 bits when the matrix is below 4 GB).
-template <typename PT, typename CT, typename VT, int LR, typename OT>
-__global__ __launch_bounds__(kThreads) void sddmm_windows_vec_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd,
-                                                                     const VT *__restrict__ sval, const CT *__restrict__ rowid,
-                                                                     const int32_t *__restrict__ rowblk, int64_t nrows, int64_t nnz,
-                                                                     const VT *__restrict__ A, int64_t lda,
-                                                                     const VT *__restrict__ Bt, int64_t ldt, VT *__restrict__ X)
+// Work is cut by stored entries: block w owns the entries [w*T, (w+1)*T) (T and the table `rowblk` of the row holding
+// every T-th entry are the stream SpMV's), or, where there are too few such windows to fill the chip, the block's share
+// of `parts` equal shares of one.  A group of LR lanes takes a run of consecutive entries, one dot product at a time:
+// lane jl holds vectors jl, jl + LR, ... (NV of them, 16 bytes each) of the row of A, which it loads again only when the
+// run reaches another row, and loads the same pieces of the row of the transposed B.  No row of S is too short to fill a
+// wave and none is walked by one wave alone.  The window's values of S, the byte offsets of the rows of the transposed
+// B (OT: 32 bits when the matrix is below 4 GB) and the row of every entry are made in LDS first; the results replace
+// the values there and leave with coalesced stores.
+//
+// Any K >= V and any leading dimension: the lane that holds the end of a row moves back to its last V columns and clears
+// those that another lane has, so every load is 16 bytes wide (the memory path takes them at any element-aligned address).
+//
+// The rows of the transposed B set the pace (16.9 M random rows of 512 bytes: 1.15 ms).  Measured before (a wave per row of
+// the window; any K that is not a power of two of 16-byte pieces: a lane per column and a wave per row) and now, whole product:
+// 16.9 M entries, K = 64 f64 1.564 -> 1.497 ms; 5.0 M entries, K = 33 f64 3.51 -> 0.33 ms, K = 100 5.08 -> 0.78 ms; 20,000 entries,
+// K = 64 65 -> 12 us.
+template <typename VT>
+struct sddmm_vec {
+    static constexpr int V = 16 / sizeof(VT);
+    typedef VT type __attribute__((ext_vector_type(V)));
+    typedef VT in_memory __attribute__((ext_vector_type(V), aligned(sizeof(VT))));
+};
+
+template <typename PT, typename CT, typename VT, int LR, int NV, typename OT>
+__global__ __launch_bounds__(kThreads) void sddmm_entries_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd,
+                                                                 const VT *__restrict__ sval, const CT *__restrict__ rowid,
+                                                                 const int32_t *__restrict__ rowblk, int64_t nrows, int64_t nnz, int parts,
+                                                                 const VT *__restrict__ A, int64_t lda, const VT *__restrict__ Bt,
+                                                                 int64_t ldt, int64_t K, VT *__restrict__ X)
 {
-    constexpr int V = 16 / sizeof(VT);
-    constexpr int S = 64 / LR;
-    constexpr int U = S >= 4 ? 2 : 4;
+    constexpr int V = sddmm_vec<VT>::V;
     constexpr int T = (int)kSpmiStreamT;
-    typedef VT vec_t __attribute__((ext_vector_type(V)));
-    __shared__ OT s_off[T];
-    __shared__ VT s_val[T];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int jl = lane % LR, sl = lane / LR;
-    const int64_t s = (int64_t)blockIdx.x * T;
-    const int64_t e = s + T < nnz ? s + T : nnz;
+    constexpr int U = NV <= 2 ? 4 : NV <= 4 ? 2 : 1;                 // entries of a group in flight
+    typedef typename sddmm_vec<VT>::type vec_t;
+    typedef typename sddmm_vec<VT>::in_memory mem_vec_t;
+    constexpr int kPad = T + T / 32;                                 // groups read 32 entries apart: kept off each other's bank
+    __shared__ OT s_off[kPad];
+    __shared__ VT s_val[kPad];
+    __shared__ CT s_row[kPad];
+    __shared__ int s_wave[kThreads / 64];
+    auto at = [](int i) { return i + (i >> 5); };
+    const int64_t win = blockIdx.x / parts;
+    const int share = T / parts;
+    const int64_t s = win * T + (int64_t)(blockIdx.x % parts) * share;
+    if (s >= nnz) return;                                            // the whole block
+    const int64_t e = s + share < nnz ? s + share : nnz;
     const int ne = (int)(e - s);
     const OT brow = (OT)(ldt * (int64_t)sizeof(VT));
     for (int i = threadIdx.x; i < ne; i += kThreads) {
-        s_off[i] = (OT)crd[s + i] * brow;
-        s_val[i] = sval[s + i];
+        s_off[at(i)] = (OT)crd[s + i] * brow;
+        s_val[at(i)] = sval[s + i];
     }
-    const int64_t lo = rowblk[blockIdx.x], hi = rowblk[blockIdx.x + 1];
+    const int64_t lo = rowblk[win], hi = rowblk[win + 1];
     const int64_t last = hi < nrows ? hi : nrows - 1;
-    __syncthreads();
+    spmi_rows_of_entries<kThreads, T / kThreads>(pos, rowid, lo, last, s, e, s_row, s_wave, at);
+    const int jl = threadIdx.x % LR, group = threadIdx.x / LR;
+    const int run_len = share * LR / kThreads;                       // entries of a group: 4 * LR, or LR
+    const int64_t want = (int64_t)(jl + (NV - 1) * LR) * V;          // only the last piece of a row can reach past its end
+    const int64_t tail = want <= K - V ? want : K - V;
+    const int skip = want - tail < V ? (int)(want - tail) : V;       // columns of the last piece that another lane has
+    const OT colb = (OT)(jl * V * (int)sizeof(VT)), tailb = (OT)(tail * (int64_t)sizeof(VT));
     const char *Bb = (const char *)Bt;
-    const OT colb = (OT)(jl * V * (int)sizeof(VT));
-    VT *Xw = X + s;                                   // this window's part of the result
-    int slot[U];
+    vec_t av[NV];
 #pragma unroll
-    for (int u = 0; u < U; ++u) slot[u] = sl + u * S;
-    for (int64_t r = lo + wave; r <= last; r += kThreads / 64) {
-        const int64_t pa = (int64_t)pos[r], pb = (int64_t)pos[r + 1];
-        const int a = (int)((pa > s ? pa : s) - s), b = (int)((pb < e ? pb : e) - s);
-        if (b <= a) continue;                         // wave-uniform
-        const int64_t i = rowid ? (int64_t)rowid[r] : r;
-        const vec_t av = *(const vec_t *)(A + i * lda + jl * V);
-        // the step count is the same for every lane of the wave, so the shuffles run with all lanes active;
-        // entries past the end are clamped and their result dropped
-        for (int p0 = a; p0 < b; p0 += U * S) {
-            vec_t bv[U];
-            int pp[U];
+    for (int v = 0; v < NV; ++v) av[v] = (vec_t)(0);
+    CT row = (CT)-1;
+    for (int k = 0; k < run_len; k += U) {
+        int idx[U];
+        vec_t bv[U][NV];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = group * run_len + k + u;
+            idx[u] = i < ne ? i : ne - 1;                            // past the end: loaded, not stored
+            const OT off = s_off[at(idx[u])];
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                bv[u][v] = *(const mem_vec_t *)(Bb + (off + (v < NV - 1 ? colb + (OT)(v * LR * 16) : tailb)));
+        }
+        VT dot[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const CT mine = s_row[at(idx[u])];
+            if (mine != row) {
+                row = mine;
+                const char *Ab = (const char *)(A + (int64_t)row * lda);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) av[v] = *(const mem_vec_t *)(Ab + (v < NV - 1 ? colb + (OT)(v * LR * 16) : tailb));
+#pragma unroll
+                for (int c = 0; c < V; ++c) if (c < skip) av[NV - 1][c] = (VT)0;
+            }
+#pragma unroll
+            for (int c = 0; c < V; ++c) if (c < skip) bv[u][NV - 1][c] = (VT)0;      // not 0 * infinity
+            dot[u] = 0;
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int c = 0; c < V; ++c) dot[u] += av[v][c] * bv[u][v][c];
+        }
+        if (LR >= U && U > 1) {
+            // The U sums are reduced together: each of the first log2(U) exchange steps halves the number of sums a lane
+            // carries (a lane keeps the half its bit selects and hands the other half over), the remaining steps finish the
+            // one sum left: sum u ends complete in the lanes whose top bits of jl are u.
+            int m = LR / 2;
+#pragma unroll
+            for (int n = U; n > 1; n >>= 1) {
+                const bool upper = (jl & m) != 0;
+#pragma unroll
+                for (int q = 0; q < n / 2; ++q) {
+                    const VT send = upper ? dot[q] : dot[q + n / 2];
+                    const VT keep = upper ? dot[q + n / 2] : dot[q];
+                    dot[q] = keep + __shfl_xor(send, m, 64);
+                }
+                m >>= 1;
+            }
+#pragma unroll
+            for (; m >= 1; m >>= 1) dot[0] += __shfl_xor(dot[0], m, 64);
+            constexpr int D = LR / U > 0 ? LR / U : 1;               // lanes that end with the same sum
+            const int u = jl / D;
+            const int i = group * run_len + k + u;
+            if (jl % D == 0 && k + u < run_len && i < ne) s_val[at(i)] *= dot[0];
+        } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                pp[u] = p0 + slot[u];
-                const int pc = pp[u] < b ? pp[u] : b - 1;
-                bv[u] = *(const vec_t *)(Bb + (s_off[pc] + colb));
-            }
-            VT dot[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                dot[u] = 0;
-#pragma unroll
-                for (int ee = 0; ee < V; ++ee) dot[u] += av[ee] * bv[u][ee];
-            }
-            if (LR >= U) {
-                // The U sums are reduced together: each of the first log2(U) exchange steps halves the number of sums
-                // a lane carries (a lane keeps the half its bit selects and hands the other half over), the remaining
-                // steps finish the one sum left.  U - 1 + log2(LR / U) shuffles instead of U * log2(LR); sum u ends
-                // complete in the lanes whose top bits of jl are u.
-                int m = LR / 2;
-#pragma unroll
-                for (int n = U; n > 1; n >>= 1) {
-                    const bool upper = (jl & m) != 0;
-#pragma unroll
-                    for (int k = 0; k < n / 2; ++k) {
-                        const VT send = upper ? dot[k] : dot[k + n / 2];
-                        const VT keep = upper ? dot[k + n / 2] : dot[k];
-                        dot[k] = keep + __shfl_xor(send, m, 64);
-                    }
-                    m >>= 1;
-                }
-#pragma unroll
-                for (; m >= 1; m >>= 1) dot[0] += __shfl_xor(dot[0], m, 64);
-                constexpr int G = LR / U > 0 ? LR / U : 1;      // lanes that end with the same sum
-                const int u = jl / G;
-                int mine = pp[0];
-#pragma unroll
-                for (int k = 1; k < U; ++k) mine = u == k ? pp[k] : mine;
-                if (jl % G == 0 && mine < b) Xw[mine] = s_val[mine] * dot[0];
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-#pragma unroll
-                    for (int d = LR / 2; d >= 1; d >>= 1) dot[u] += __shfl_xor(dot[u], d, 64);
-                    if (jl == 0 && pp[u] < b) Xw[pp[u]] = s_val[pp[u]] * dot[u];
-                }
+                for (int d = LR / 2; d >= 1; d >>= 1) dot[u] += __shfl_xor(dot[u], d, 64);
+                const int i = group * run_len + k + u;
+                if (jl == 0 && k + u < run_len && i < ne) s_val[at(i)] *= dot[u];
             }
         }
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < ne; i += kThreads) X[s + i] = s_val[at(i)];
 }
 
 // any K: CG lanes per entry, each striding over k
@@ -201,27 +230,33 @@ sp_status sddmm_t(const sp_tensor *S, const VT *A, int64_t lda, const VT *B, int
     }
     {
         sp_prof_scope prof(S, st);
-        const int64_t lr = K / V;
-        const bool vec = rowblocks->start && K % V == 0 && (lr == 1 || lr == 2 || lr == 4 || lr == 8 || lr == 16 || lr == 32 || lr == 64) && lda % V == 0 &&
-                         ldt % V == 0 && (uintptr_t)A % 16 == 0 && (uintptr_t)Bt % 16 == 0;
+        const int64_t nvec = ceil_div(K, V);                        // 16-byte pieces of a row
+        const bool vec = rowblocks->start && K >= V && nvec <= 64;
         const bool small = sizeof(CT) == 4 && (uint64_t)n * (uint64_t)ldt * sizeof(VT) < ((uint64_t)1 << 32);      // 32-bit byte offsets into the transposed B (64-bit coordinates keep 64-bit offsets)
         const dim3 grid(grid_for(nrows, kThreads / 64));
         if (vec) {
-#define SPMI_SDDMM_VEC_O(LR, OT)                                                                                              \
-    hipLaunchKernelGGL((sddmm_windows_vec_kernel<PT, CT, VT, LR, OT>), dim3((unsigned)rowblocks->nblocks), dim3(kThreads), 0, st, pos, crd, \
-                       sval, rowid, (const int32_t *)rowblocks->start, nrows, S->ncrd[1], A, lda, Bt, ldt, X)
-#define SPMI_SDDMM_VEC(LR)                              \
-    do {                                                \
-        if (small) SPMI_SDDMM_VEC_O(LR, uint32_t);      \
-        else SPMI_SDDMM_VEC_O(LR, uint64_t);            \
+            // fewer windows than four per CU: a block takes a quarter of one
+            const int parts = rowblocks->nblocks < 1024 ? 4 : 1;
+            const dim3 blocks((unsigned)(rowblocks->nblocks * parts));
+#define SPMI_SDDMM_VEC_O(LR, NV, OT)                                                                                          \
+    hipLaunchKernelGGL((sddmm_entries_kernel<PT, CT, VT, LR, NV, OT>), blocks, dim3(kThreads), 0, st, pos, crd, sval, rowid,  \
+                       (const int32_t *)rowblocks->start, nrows, S->ncrd[1], parts, A, lda, Bt, ldt, K, X)
+#define SPMI_SDDMM_VEC(LR, NV)                              \
+    do {                                                    \
+        if (sizeof(CT) == 4 && small) SPMI_SDDMM_VEC_O(LR, NV, uint32_t);      \
+        else SPMI_SDDMM_VEC_O(LR, NV, uint64_t);            \
     } while (0)
-            if (lr == 1) SPMI_SDDMM_VEC(1);
-            else if (lr == 2) SPMI_SDDMM_VEC(2);
-            else if (lr == 4) SPMI_SDDMM_VEC(4);
-            else if (lr == 8) SPMI_SDDMM_VEC(8);
-            else if (lr == 16) SPMI_SDDMM_VEC(16);
-            else if (lr == 32) SPMI_SDDMM_VEC(32);
-            else SPMI_SDDMM_VEC(64);
+            if (nvec == 1) SPMI_SDDMM_VEC(1, 1);
+            else if (nvec == 2) SPMI_SDDMM_VEC(2, 1);
+            else if (nvec <= 4) SPMI_SDDMM_VEC(4, 1);
+            else if (nvec <= 8) SPMI_SDDMM_VEC(8, 1);
+            else if (nvec <= 16) SPMI_SDDMM_VEC(8, 2);
+            else if (nvec <= 24) SPMI_SDDMM_VEC(8, 3);
+            else if (nvec <= 32) SPMI_SDDMM_VEC(8, 4);
+            else if (nvec <= 40) SPMI_SDDMM_VEC(8, 5);
+            else if (nvec <= 48) SPMI_SDDMM_VEC(8, 6);
+            else if (nvec <= 56) SPMI_SDDMM_VEC(8, 7);
+            else SPMI_SDDMM_VEC(8, 8);
 #undef SPMI_SDDMM_VEC
 #undef SPMI_SDDMM_VEC_O
         } else {
