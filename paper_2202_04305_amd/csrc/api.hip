@@ -188,30 +188,15 @@ extern "C" sp_status sp_profile_read(sp_tensor *t, double *ms_total, int64_t *la
     return s;
 }
 
-// Row-major copy of a column-major tensor, through the coordinate scheme (the paper's route for
-// conversions, Section 4.2).  Built on first use and kept by the handle.
+// Row-major copy of a column-major tensor.  Built on first use and kept by the handle.
 sp_status spmi_build_transposed(const sp_tensor *A, hipStream_t st)
 {
     if (A->transposed) return SP_OK;
-    sp_mem mem{A->alloc, A->free_, A->ctx};
-    sp_status s = SP_OK;
+    sp_encoding enc = A->enc;
+    enc.perm[0] = 0; enc.perm[1] = 1;
+    enc.pw_store = enc.pw; enc.cw_store = enc.cw;         // an internal copy: working widths only
     sp_tensor *T = nullptr;
-    {
-        sp_scratch tmp(mem);
-        const size_t cnt = (size_t)(A->nvalues > 0 ? A->nvalues : 1);
-        int64_t *rows = (int64_t *)tmp.get(cnt * 8);
-        int64_t *cols = (int64_t *)tmp.get(cnt * 8);
-        void *vals = tmp.get(cnt * 8);
-        if (!rows || !cols || !vals) return SP_ERR_ALLOC;
-        int64_t *coords[2] = {rows, cols};
-        SP_TRY(sp_unpack(A, coords, vals, st));
-        sp_encoding enc = A->enc;
-        enc.perm[0] = 0; enc.perm[1] = 1;
-        enc.pw_store = enc.pw; enc.cw_store = enc.cw;     // an internal copy: working widths only
-        const int64_t *ccoords[2] = {rows, cols};
-        s = sp_pack(&enc, A->shape, A->nvalues, ccoords, vals, (sp_dtype)A->dtype, A->alloc, A->free_, A->ctx, st, &T);
-    }
-    if (s != SP_OK) return s;
+    SP_TRY(spmi_repack(A, &enc, st, &T));
     T->tune_spmv = A->tune_spmv;
     T->tune_spmm = A->tune_spmm;
     T->lazy_prepares = 0;
@@ -225,21 +210,7 @@ extern "C" sp_status sp_convert(const sp_tensor *from, const sp_encoding *to, vo
     if (!from || !to || !out) return SP_ERR_NULL;
     *out = nullptr;
     if (to->rank != from->enc.rank) return SP_ERR_RANK;
-    hipStream_t st = (hipStream_t)stream;
-    sp_mem mem{from->alloc, from->free_, from->ctx};
-    sp_scratch tmp(mem);
-    const int rank = from->enc.rank;
-    const size_t cnt = (size_t)(from->nvalues > 0 ? from->nvalues : 1);
-    int64_t *coords[SP_MAX_RANK] = {nullptr};
-    for (int d = 0; d < rank; ++d) {
-        coords[d] = (int64_t *)tmp.get(cnt * 8);
-        if (!coords[d]) return SP_ERR_ALLOC;
-    }
-    void *vals = tmp.get(cnt * 8);
-    if (!vals) return SP_ERR_ALLOC;
-    SP_TRY(sp_unpack(from, coords, vals, st));
-    return sp_pack(to, from->shape, from->nvalues, (const int64_t *const *)coords, vals, (sp_dtype)from->dtype, from->alloc,
-                   from->free_, from->ctx, st, out);
+    return spmi_repack(from, to, (hipStream_t)stream, out);
 }
 
 // C = A + B element by element: the stored positions of both go through the storage builder as one list of

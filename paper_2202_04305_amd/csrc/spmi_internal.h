@@ -319,6 +319,8 @@ extern std::atomic<int> g_pack_sort_mode;
 // with the value bits as payload, both temporaries of `tmp`; entries with equal keys are added up in the order given.
 sp_status spmi_pack_keys(const sp_encoding *enc, const int64_t *shape, sp_dtype dt, sp_alloc_fn alloc, sp_free_fn free_, void *ctx,
                          int64_t n, uint64_t *keys, void *payload, sp_scratch &tmp, hipStream_t st, sp_tensor **out);
+// Every stored position of `from` packed under another encoding of the same rank; synchronises.
+sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t st, sp_tensor **out);
 sp_status spmi_build_rowblocks(const sp_tensor *t, hipStream_t st);
 sp_status spmi_build_segments(const sp_tensor *A, int64_t row_bytes, int64_t slice_bytes, hipStream_t st);
 #ifndef SPMI_BIN_PSHIFT
