@@ -436,8 +436,9 @@ __global__ __launch_bounds__(kThreads) void spmm_rows_vec_kernel(const PT *__res
 // every load is V elements wide (the memory path takes such loads at any element-aligned address).
 // Bound by the rows of B it gathers (16.9 M random 512-byte rows alone: 1.15 ms).  Measured before (a wave per row of the
 // window with shuffles at the end of every row; a wave per row and a column per lane for widths that are no multiple of 16
-// bytes) and now: 16.9 M entries, 64 f64 columns 1.329 -> 1.289 ms; 33.6 M entries with short rows, 32 f32 columns 561 -> 417 us;
-// 5.0 M entries, 64-bit pos / crd, 33 f64 columns 1.250 -> 0.282 ms; 4 M entries, 4 per row, 2 f64 columns 303 -> 75 us.
+// bytes) and now: 16.9 M entries, 64 f64 columns 1.329 -> 1.280 ms; 33.6 M entries with short rows, 32 f32 columns 561 -> 363 us
+// (417 with the groups' entries kept at an even stride);
+// 5.0 M entries, 64-bit pos / crd, 33 f64 columns 1.250 -> 0.276 ms; 4 M entries, 4 per row, 2 f64 columns 303 -> 75 us.
 template <typename PT, typename CT, typename VT, int V, typename OT>
 __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd, const VT *__restrict__ val,
                                                              const CT *__restrict__ rowid, const int32_t *__restrict__ rowblk, int64_t nrows,
@@ -447,7 +448,7 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
     constexpr int T = (int)kStreamT, U = 4, kWaves = kThreads / 64;
     typedef VT vec_t __attribute__((ext_vector_type(V)));
     typedef VT mem_vec_t __attribute__((ext_vector_type(V), aligned(sizeof(VT))));
-    constexpr int kRoom = T + kThreads;                              // groups * run length, run length rounded up
+    constexpr int kRoom = T + kThreads;                              // run length (rounded up) * odd stride: 256 * 5 at most
     __shared__ OT s_off[kRoom];
     __shared__ VT s_val[kRoom];
     __shared__ CT s_row[kRoom];
@@ -459,8 +460,10 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
     const int S = 64 / LR, G = kWaves * S;                           // groups per wave, per block
     const int run = (T + G - 1) / G;                                 // entries per group
     const uint32_t by_run = (uint32_t)(((uint64_t)1 << 22) / (uint32_t)run + 1);      // i / run for i < 1024: exact, run <= 256
-    // entry i of the window is kept at (i % run) * G + i / run: the groups of a wave read neighbouring words
-    auto at = [=](int i) { const int g = (int)(((uint32_t)i * by_run) >> 22); return (i - g * run) * G + g; };
+    // entry i of the window is kept at (i % run) * P + i / run: the groups of a wave read neighbouring words, and with an odd P
+    // neighbouring entries lie on different banks when they are put there
+    const int P = G | 1;
+    auto at = [=](int i) { const int g = (int)(((uint32_t)i * by_run) >> 22); return (i - g * run) * P + g; };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t s = (int64_t)blockIdx.x * T;
     const int64_t e = s + T < nnz ? s + T : nnz;
@@ -478,7 +481,7 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
     const int64_t lo = rowblk[blockIdx.x], hi = rowblk[blockIdx.x + 1];
     const int64_t last = hi < nrows ? hi : nrows - 1;
     const bool continued = (int64_t)pos[lo] < s;                     // the first row began in an earlier window
-    spmi_rows_of_entries<kThreads, T / kThreads>(pos, rowid, lo, last, s, e, s_row, s_wave, at);
+    spmi_rows_of_entries<kThreads, T / kThreads>([=](int64_t r) { return (int64_t)pos[r]; }, rowid, lo, last, s, e, s_row, s_wave, at);
     if (!accumulate && !rowid)                                       // rows without entries: zero (with a row list C was cleared before)
         for (int64_t r0 = lo + wave * 64; r0 <= last; r0 += kThreads) {
             const int64_t r = r0 + lane;
@@ -513,7 +516,7 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
     bool head = false;                                               // the row being added up began before this run
     if (first < end) {
         row = s_row[group];
-        head = group == 0 ? continued : s_row[(run - 1) * G + group - 1] == row;
+        head = group == 0 ? continued : s_row[(run - 1) * P + group - 1] == row;
     }
     for (int k = 0; k < end - first; k += U) {
         VT v[U];
@@ -521,7 +524,7 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
         CT rw[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int w = (first + k + u < end ? k + u : end - first - 1) * G + group;
+            const int w = (first + k + u < end ? k + u : end - first - 1) * P + group;
             rw[u] = s_row[w];
             v[u] = s_val[w];
             bv[u] = *(const mem_vec_t *)(Bb + (s_off[w] + colb));

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kThreads) void sddmm_entries_kernel(const PT *__res
     }
     const int64_t lo = rowblk[win], hi = rowblk[win + 1];
     const int64_t last = hi < nrows ? hi : nrows - 1;
-    spmi_rows_of_entries<kThreads, T / kThreads>(pos, rowid, lo, last, s, e, s_row, s_wave, at);
+    spmi_rows_of_entries<kThreads, T / kThreads>([=](int64_t r) { return (int64_t)pos[r]; }, rowid, lo, last, s, e, s_row, s_wave, at);
     const int jl = threadIdx.x % LR, group = threadIdx.x / LR;
     const int run_len = share * LR / kThreads;                       // entries of a group: 4 * LR, or LR
     const int64_t want = (int64_t)(jl + (NV - 1) * LR) * V;          // only the last piece of a row can reach past its end

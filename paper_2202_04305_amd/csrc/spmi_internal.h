@@ -196,11 +196,12 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid)
 }
 
 // The row of every stored entry of a stretch [s, e) of a compressed innermost level (at most kThreads * PER entries), made by a
-// whole block in LDS: row[at(i)] = the row of entry s + i, mapped through rowid where there is one.  lo..last are the rows that
-// can meet the stretch, lo among those that begin at or before it.  Each row marks its first entry, the marks' running maximum
-// is every entry's row.  waves: LDS, one int per wave.  The block meets at a barrier on the way in and out.
-template <int kThreads, int PER, typename PT, typename CT, typename AT>
-__device__ __forceinline__ void spmi_rows_of_entries(const PT *__restrict__ pos, const CT *__restrict__ rowid, int64_t lo, int64_t last, int64_t s,
+// whole block in LDS: row[at(i)] = the row of entry s + i, mapped through rowid where there is one.  pos(r) is where row r
+// begins; lo..last are the rows that can meet the stretch, lo among those that begin at or before it.  Each row marks its first
+// entry, the marks' running maximum is every entry's row.  waves: LDS, one int per wave.  The block meets at a barrier on the
+// way in and out.
+template <int kThreads, int PER, typename POS, typename CT, typename AT>
+__device__ __forceinline__ void spmi_rows_of_entries(POS pos, const CT *__restrict__ rowid, int64_t lo, int64_t last, int64_t s,
                                                      int64_t e, CT *row, int *waves, AT at)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -208,7 +209,7 @@ __device__ __forceinline__ void spmi_rows_of_entries(const PT *__restrict__ pos,
     for (int i = tid; i < n; i += kThreads) row[at(i)] = 0;
     __syncthreads();
     for (int64_t r = lo + tid; r <= last; r += kThreads) {
-        const int64_t pa = (int64_t)pos[r], pb = (int64_t)pos[r + 1];
+        const int64_t pa = pos(r), pb = pos(r + 1);
         const int64_t a = pa > s ? pa : s, b = pb < e ? pb : e;
         if (a < b) row[at((int)(a - s))] = (CT)(r - lo);
     }
