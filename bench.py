@@ -214,7 +214,7 @@ def bench_mttkrp(args, torch, sp, dev):
                "sample": "the whole workload (%d stored entries x %d columns, one product), one run, %.3f s" % (nnz, J, cpu_s),
                "gflops": flops / cpu_s / 1e9}
     achieved = abytes / (kernel_ms * 1e-3) / 1e9
-    kernel_name = "mttkrp_windows_kernel (+ fix-up)"
+    kernel_name = "mttkrp_runs_kernel (+ fix-up)"
     out = {
         "metric": "effective HBM GB/s (algorithmic bytes / time per product)",
         "value": abytes / (ms_cold * 1e-3) / 1e9, "unit": "GB/s", "n_gpus": 1, "steps": steps, "warmup": warmup,

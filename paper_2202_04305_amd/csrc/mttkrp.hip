@@ -9,20 +9,20 @@
 // per fibre, and a running sum per slice i.  Both factor matrices are small next to B (megabytes) and live in cache;
 // B's crd2 / values stream from HBM once.
 //
-// Work is cut by stored entries: wave w owns the entries [w*TW, (w+1)*TW) and walks the fibres that meet that window,
-// each clipped to it.  LR lanes cover the J columns (16-byte loads when J allows) and S = 64 / LR entries go side by
-// side; the S partial sums meet only when a slice ends.  The part of a slice that began in an earlier window goes to
-// carry[w] (J values); a second kernel adds a slice's carries to A in a fixed pattern; everything else is written to A
-// directly.  No atomics: results are bit-reproducible.
+// Work is cut by stored entries: a block owns the entries [w*TW, (w+1)*TW), a group of LR lanes covers the J columns (16-byte
+// loads) and takes a run of consecutive entries, whatever fibres and slices they belong to: it adds up a fibre, takes the
+// fibre's row of `mid` in when the fibre ends, and writes A when the slice does.  Parts of a slice that began in an earlier run
+// meet in LDS, the part that began in an earlier window goes to carry[w] (J values); a second kernel adds a slice's carries to
+// A in a fixed pattern; everything else is written to A directly.  No atomics: results are bit-reproducible.
 #include "spmi_internal.h"
 
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-// stored entries per wave.  Measured on the 76.9 M-entry tensor with 42 columns: 512 -> 3.18 ms, 256 -> 2.21, 128 -> 1.97,
-// 64 -> 2.15: with small windows fewer slices are in flight at a time and more of their factor rows are found in the L2.
-constexpr int64_t kTW = 128;
+// Stored entries per block.  20 M entries, 42 f64 columns: 256 -> 682 us, 512 -> 523, 1024 -> 461 (every block makes its tables once;
+// larger ones leave too few blocks on a CU for the LDS).
+constexpr int64_t kTW = 1024;
 
 __global__ __launch_bounds__(kThreads) void zero_rows_kernel(char *__restrict__ A, int64_t rows, int64_t row_bytes, int64_t ld_bytes)
 {
@@ -32,15 +32,16 @@ __global__ __launch_bounds__(kThreads) void zero_rows_kernel(char *__restrict__ 
         *(uint32_t *)(A + (t / words) * ld_bytes + (t % words) * 4) = 0u;
 }
 
-// dst[r, 0..cols) = src[r, 0..cols) for a row-major matrix with other leading dimensions (16-byte pieces)
+// dst[r, 0..cols) = src[r, 0..cols) for a row-major matrix with other leading dimensions, in pieces of type W
+template <typename W>
 __global__ __launch_bounds__(kThreads) void repitch_rows_kernel(const char *__restrict__ src, int64_t src_ld_bytes, int64_t rows,
                                                                 int64_t row_bytes, char *__restrict__ dst, int64_t dst_ld_bytes)
 {
-    const int64_t pieces = row_bytes / 16;
+    const int64_t pieces = row_bytes / (int64_t)sizeof(W);
     const int64_t total = rows * pieces;
     for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total; t += (int64_t)gridDim.x * kThreads) {
         const int64_t r = t / pieces, c = t % pieces;
-        *(uint4 *)(dst + r * dst_ld_bytes + c * 16) = *(const uint4 *)(src + r * src_ld_bytes + c * 16);
+        *(W *)(dst + r * dst_ld_bytes + c * (int64_t)sizeof(W)) = *(const W *)(src + r * src_ld_bytes + c * (int64_t)sizeof(W));
     }
 }
 
@@ -84,132 +85,154 @@ __global__ __launch_bounds__(kThreads) void mttkrp_windows_table_kernel(const PT
 }
 
 template <typename VT, int V>
-struct vec_of { typedef VT type __attribute__((ext_vector_type(V))); };
+struct vec_of {
+    typedef VT type __attribute__((ext_vector_type(V)));
+    typedef VT in_memory __attribute__((ext_vector_type(V), aligned(sizeof(VT))));
+};
 
-// grid = (windows / waves per block rounded up to a multiple of 8, column tiles of 64 * V columns).  Each wave first
-// copies its window into LDS with coalesced loads that are all in flight together: the values, and instead of the
-// coordinates the byte offsets of the rows they select (crd2 -> row of the inner factor, crd1 -> row of the mid
-// factor, of type OT: 32 bits when both matrices are below 4 GB), plus the fibres' bounds relative to the window.
-// The walk over the fibres afterwards does no index arithmetic beyond one add per gather.
-template <typename PT, typename CT, typename VT, int V, int U, typename OT>
-__global__ __launch_bounds__(kThreads) void mttkrp_windows_kernel(const PT *__restrict__ pos1, const CT *__restrict__ crd0,
-                                                                  const CT *__restrict__ crd1, const PT *__restrict__ pos2,
-                                                                  const CT *__restrict__ crd2, const VT *__restrict__ val,
-                                                                  const int32_t *__restrict__ wfib, const int32_t *__restrict__ wslc,
-                                                                  int64_t nwin, int64_t nfib, int64_t nnz,
-                                                                  const VT *__restrict__ M, int64_t ldm, const VT *__restrict__ X,
-                                                                  int64_t ldx, VT *__restrict__ A, int64_t lda,
-                                                                  VT *__restrict__ carry, int64_t J, int accumulate)
+// grid = (windows rounded up to a multiple of 8, column tiles of lr_tile * V columns).  The block first makes in LDS, for every
+// entry of its window, the value, the byte offset of the row of the inner factor (OT: 32 bits when both factor matrices are
+// below 4 GB), the row of the mid factor and the slice.  Any J >= V, leading dimension and element-aligned address: the last
+// lane of a row moves back to the last V columns and stores only those that the lane before it does not have.
+// Bound by the rows of the inner factor that it gathers.  Measured before (a wave per 128 entries that walked their fibres one
+// after the other; a column per lane for widths that are no multiple of 16 bytes) and now: 76.9 M entries, 42 f64 columns
+// 1.893 -> 1.865 ms; 20 M entries, 33 columns 737 -> 439 us, 16 columns 337 -> 256 us; 30,000 entries in fibres of one or two,
+// 42 columns 54 -> 18 us.
+template <typename PT, typename CT, typename VT, int V, typename OT>
+__global__ __launch_bounds__(kThreads) void mttkrp_runs_kernel(const PT *__restrict__ pos1, const CT *__restrict__ crd0, const CT *__restrict__ crd1,
+                                                               const PT *__restrict__ pos2, const CT *__restrict__ crd2, const VT *__restrict__ val,
+                                                               const int32_t *__restrict__ wfib, const int32_t *__restrict__ wslc, int64_t nwin,
+                                                               int64_t nfib, int64_t nslc, int64_t nnz, const VT *__restrict__ M, int64_t ldm,
+                                                               const VT *__restrict__ X, int64_t ldx, VT *__restrict__ A, int64_t lda,
+                                                               VT *__restrict__ carry, int64_t J, int lr_tile, int accumulate)
 {
+    constexpr int T = (int)kTW, U = 4, PER = T / kThreads;
+    static_assert(T % kThreads == 0, "a whole number of entries per thread");
     typedef typename vec_of<VT, V>::type vec_t;
-    __shared__ VT s_val[kWaves][kTW];
-    __shared__ OT s_xoff[kWaves][kTW];
-    __shared__ OT s_moff[kWaves][kTW + 1];      // at most TW + 1 fibres meet a window (the last may only touch its end)
-    __shared__ int32_t s_off[kWaves][kTW + 2];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // Workgroups go to the 8 XCDs in turn, each with an L2 of its own.  Block b therefore takes the (b / 8)-th block of
+    typedef typename vec_of<VT, V>::in_memory mem_vec_t;
+    constexpr int kRoom = T + kThreads;                            // run length (rounded up) * odd stride: 256 * 5 at most
+    __shared__ OT s_xoff[kRoom];
+    __shared__ VT s_val[kRoom];
+    __shared__ CT s_mid[kRoom], s_slc[kRoom];
+    __shared__ vec_t s_part[kThreads];
+    __shared__ int s_wave[kWaves];
+    // Workgroups go to the 8 XCDs in turn, each with an L2 of its own.  Block b therefore takes the (b / 8)-th window of
     // the (b % 8)-th eighth of the windows: an XCD walks a contiguous range of entries, so the rows of the factor
     // matrices that a slice keeps coming back to are found in that XCD's L2.  (Only the mapping depends on this.)
-    const int64_t per = gridDim.x / 8;
-    const int64_t w = ((int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8) * kWaves + wave;
-    const bool active = w < nwin;
-    const int64_t s = w * kTW;
-    const int64_t e = s + kTW < nnz ? s + kTW : nnz;
-    int64_t f0 = 0, q = 0, qend = 0;
-    int nf = 0;
-    bool cont = false;
-    if (active) {
-        f0 = wfib[w];
-        q = wslc[w];
-        nf = (int)((w + 1 < nwin ? (int64_t)wfib[w + 1] : nfib - 1) - f0) + 1;
-        const OT xrow = (OT)(ldx * (int64_t)sizeof(VT)), mrow = (OT)(ldm * (int64_t)sizeof(VT));
-        for (int64_t p = s + lane; p < e; p += 64) {
-            s_xoff[wave][p - s] = (OT)crd2[p] * xrow;
-            s_val[wave][p - s] = val[p];
+    const int64_t w = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (w >= nwin) return;                                         // the whole block
+    const int64_t j0 = (int64_t)blockIdx.y * lr_tile * V;
+    const int64_t width = J - j0 < (int64_t)lr_tile * V ? J - j0 : (int64_t)lr_tile * V;
+    const int LR = (int)((width + V - 1) / V);                     // 1..64
+    const int S = 64 / LR, G = kWaves * S;                         // groups per wave, per block
+    const int run = (T + G - 1) / G;                               // entries per group
+    const uint32_t by_run = (uint32_t)(((uint64_t)1 << 21) / (uint32_t)run + 1);      // i / run for i < 1024: exact, run <= 256
+    // entry i of the window is kept at (i % run) * P + i / run: the groups of a wave read neighbouring words, and with an odd P
+    // neighbouring entries lie on different banks when they are put there
+    const int P = G | 1;
+    auto at = [=](int i) { const int g = (int)(((uint32_t)i * by_run) >> 21); return (i - g * run) * P + g; };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t s = w * T;
+    const int64_t e = s + T < nnz ? s + T : nnz;
+    const int ne = (int)(e - s);
+    const OT xrow = (OT)(ldx * (int64_t)sizeof(VT)), mrow = (OT)(ldm * (int64_t)sizeof(VT));
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+        const int i = x * kThreads + threadIdx.x;
+        if (i < ne) {
+            s_xoff[at(i)] = (OT)crd2[s + i] * xrow;
+            s_val[at(i)] = val[s + i];
         }
-        for (int fi = lane; fi <= nf; fi += 64) {
-            int64_t o = (int64_t)pos2[f0 + fi] - s;
-            o = o < 0 ? 0 : o > e - s ? e - s : o;
-            s_off[wave][fi] = (int32_t)o;
-            if (fi < nf) s_moff[wave][fi] = (OT)crd1[f0 + fi] * mrow;
-        }
-        qend = (int64_t)pos1[q + 1];
-        cont = (int64_t)pos2[(int64_t)pos1[q]] < s;                // the first slice began in an earlier window
     }
-    __syncthreads();
-    if (!active) return;
-    const int64_t j0 = (int64_t)blockIdx.y * 64 * V;
-    const int64_t jw = J - j0 < 64 * V ? J - j0 : 64 * V;          // columns of this tile (a multiple of V)
-    const int LR = (int)(jw / V);                                  // lanes per row, 1..64
-    const int S = 64 / LR;                                         // entries side by side
-    const int jl = lane % LR, sl = lane / LR;
-    const int64_t col = j0 + (int64_t)jl * V;
+    const int64_t f0 = wfib[w], f1 = w + 1 < nwin ? (int64_t)wfib[w + 1] : nfib - 1;
+    const int64_t q0 = wslc[w], q1 = w + 1 < nwin ? (int64_t)wslc[w + 1] : nslc - 1;
+    spmi_rows_of_entries<kThreads, PER>([=](int64_t f) { return (int64_t)pos2[f]; }, crd1, f0, f1, s, e, s_mid, s_wave, at);
+    spmi_rows_of_entries<kThreads, PER>([=](int64_t q) { return (int64_t)pos2[(int64_t)pos1[q]]; }, crd0, q0, q1, s, e, s_slc, s_wave, at);
+    const bool continued = (int64_t)pos2[(int64_t)pos1[q0]] < s;   // the first slice began in an earlier window
+    const int sl = lane / LR, jl = lane - sl * LR;
+    const int group = sl < S ? wave * S + sl : G;                  // lanes beyond S * LR take nothing
+    const int first = group * run < ne ? group * run : ne, end = first + run < ne ? first + run : ne;
+    const int64_t want = j0 + (int64_t)jl * V;
+    const int64_t col = want <= J - V ? want : J - V;              // this lane's columns: [col, col + V), its own from skip on
+    const int skip = (int)(want - col);
     const OT colb = (OT)(col * (int64_t)sizeof(VT));
-    int slot[U];                                                   // this lane's place in a group of S * U entries
-#pragma unroll
-    for (int u = 0; u < U; ++u) slot[u] = sl < S ? sl + u * S : (1 << 24);   // lanes beyond LR * S never take an entry
     const char *Xb = (const char *)X, *Mb = (const char *)M;
-    vec_t acc = (vec_t)(0);
-
-    auto flush = [&](int64_t slice) {
-        vec_t r = acc;
-        for (int g = 1; g < S; ++g) {
+    auto store = [&](VT *dst, vec_t v, bool add) {
+        if (skip == 0) {
+            mem_vec_t *d = (mem_vec_t *)dst;
+            if (add) *d = *d + v;
+            else *d = v;
+        } else {
 #pragma unroll
-            for (int c = 0; c < V; ++c) r[c] += __shfl(acc[c], jl + g * LR, 64);
+            for (int c = 1; c < V; ++c)
+                if (c >= skip) dst[c] = add ? dst[c] + v[c] : v[c];
         }
-        if (sl == 0) {
-            if (cont) *(vec_t *)(carry + w * J + col) = r;
-            else {
-                const int64_t i = crd0 ? (int64_t)crd0[slice] : slice;
-                vec_t *dst = (vec_t *)(A + i * lda + col);
-                *dst = accumulate ? *dst + r : r;
-            }
-        }
-        cont = false;
-        acc = (vec_t)(0);
     };
-
-    vec_t c_next = *(const vec_t *)(Mb + (s_moff[wave][0] + colb));
-    int b = s_off[wave][0];
-    for (int fi = 0; fi < nf; ++fi) {                              // wave-uniform throughout
-        const vec_t c = c_next;
-        const int a = b;
-        b = s_off[wave][fi + 1];
-        if (fi + 1 < nf) c_next = *(const vec_t *)(Mb + (s_moff[wave][fi + 1] + colb));
-        if (b <= a) continue;                                      // only the last fibre, when it begins where the window ends
-        const int64_t f = f0 + fi;
-        if (f >= qend) {
-            flush(q);
-            do { ++q; qend = (int64_t)pos1[q + 1]; } while (f >= qend);
-        }
-        vec_t t[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) t[u] = (vec_t)(0);
-        for (int p0 = a; p0 < b; p0 += S * U) {
-            VT v[U];
-            vec_t xv[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (p0 + u * S < b) {                              // wave-uniform: no gather for a slot group past the fibre's end
-                    const int pp = p0 + slot[u];
-                    const int idx = pp < b ? pp : b - 1;
-                    v[u] = s_val[wave][idx];
-                    xv[u] = *(const vec_t *)(Xb + (s_xoff[wave][idx] + colb));
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (p0 + u * S < b) {
-                    if (p0 + slot[u] < b) t[u] += v[u] * xv[u];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 1; u < U; ++u) t[0] += t[u];
-        acc += c * t[0];
+    const int slot = group * LR + jl;                              // this lane's place in s_part
+    vec_t acc = (vec_t)(0), t = (vec_t)(0), c = (vec_t)(0);        // of the slice, of the fibre, the fibre's row of the mid factor
+    CT slice = 0, mid = 0;
+    bool head = false;                                             // the slice being added up began before this run
+    if (first < end) {
+        slice = s_slc[group];
+        mid = s_mid[group];
+        head = group == 0 ? continued : s_slc[(run - 1) * P + group - 1] == slice;
+        c = *(const mem_vec_t *)(Mb + ((OT)mid * mrow + colb));
     }
-    flush(q);
+    CT mid_ahead = mid, slice_ahead = slice;                       // of the last entry requested
+    for (int k = 0; k < end - first; k += U) {
+        VT v[U];
+        vec_t bv[U], mv[U];
+        CT qs[U];
+        bool fresh[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int x = (first + k + u < end ? k + u : end - first - 1) * P + group;
+            const CT m = s_mid[x];
+            qs[u] = s_slc[x];
+            v[u] = s_val[x];
+            bv[u] = *(const mem_vec_t *)(Xb + (s_xoff[x] + colb));
+            fresh[u] = m != mid_ahead || qs[u] != slice_ahead;     // a new fibre
+            mid_ahead = m;
+            slice_ahead = qs[u];
+            if (fresh[u]) mv[u] = *(const mem_vec_t *)(Mb + ((OT)m * mrow + colb));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (first + k + u < end) {
+                if (fresh[u]) {
+                    acc += c * t;
+                    t = (vec_t)(0);
+                    c = mv[u];
+                    if (qs[u] != slice) {
+                        if (head) s_part[slot] = acc;
+                        else store(A + (int64_t)slice * lda + col, acc, accumulate);
+                        head = false;
+                        slice = qs[u];
+                        acc = (vec_t)(0);
+                    }
+                }
+                t += v[u] * bv[u];
+            }
+        }
+    }
+    acc += c * t;
+    if (head) s_part[slot] = acc;                                  // the whole run belongs to a slice that began before it
+    // The sums of a slice that fills whole runs are added up towards the first of them, over twice as many groups each step.
+    const int full = (ne + run - 1) / run;                         // groups that took something
+    if (__syncthreads_or(head))
+        for (int d = 1; d < full; d <<= 1) {
+            const bool take = group + d < full && s_slc[group + d] == s_slc[group];      // slices ascend: everything between is that slice's too
+            const vec_t other = take ? s_part[slot + d * LR] : (vec_t)(0);
+            __syncthreads();
+            if (take) s_part[slot] += other;
+            __syncthreads();
+        }
+    if (first >= end) return;
+    if (group == 0 && continued) store(carry + w * J + col, s_part[slot], false);
+    if (!head) {
+        if (group + 1 < full && s_slc[group + 1] == slice) acc += s_part[slot + LR];
+        store(A + (int64_t)slice * lda + col, acc, accumulate);
+    }
 }
 
 // A block per listed window boundary (the first one a slice crosses): adds all of that slice's carries to A.  The
@@ -296,28 +319,29 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
     }
     const int32_t *wfib = (const int32_t *)B->mttkrp_windows, *wslc = wfib + nwin, *cross = wslc + nwin + 4;
     constexpr int VV = 16 / sizeof(VT);
-    const bool vec = J % VV == 0 && ldm % VV == 0 && ldx % VV == 0 && lda % VV == 0 && (uintptr_t)M % 16 == 0 && (uintptr_t)X % 16 == 0 &&
-                     (uintptr_t)A % 16 == 0 && (uintptr_t)B->mttkrp_carry % 16 == 0;
-    // f32 with an even J that is no multiple of four (the 42 columns of the paper's experiment): 8-byte loads
-    const bool half_vec = !vec && sizeof(VT) == 4 && J % 2 == 0 && ldm % 2 == 0 && ldx % 2 == 0 && lda % 2 == 0 && (uintptr_t)M % 8 == 0 &&
-                          (uintptr_t)X % 8 == 0 && (uintptr_t)A % 8 == 0;
+    // rows that can be copied 16 bytes at a time
+    const bool pieces16 = J % VV == 0 && ldm % VV == 0 && ldx % VV == 0 && lda % VV == 0 && (uintptr_t)M % 16 == 0 && (uintptr_t)X % 16 == 0 &&
+                          (uintptr_t)A % 16 == 0;
     const int64_t K = B->shape[1], L = B->shape[2];
     const int64_t rows_m = B->enc.perm[1] == 1 ? K : L, rows_x = B->enc.perm[1] == 1 ? L : K;
     // The inner factor is gathered a row per stored entry, the mid factor a row per fibre.  When such a matrix is
     // larger than an XCD's L2 and its rows do not start on 128-byte lines, a copy with rows padded to whole lines is
     // gathered from instead (a 336-byte row then touches 3 lines, not 3.6 on average); the copy is made on every call
-    // into a buffer the tensor keeps.
+    // into a buffer the tensor keeps.  Rows of an odd size go without the copy where that buffer cannot be had.
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (!pieces16) SP_HIP(hipStreamIsCapturing(st, &capturing));
     const int64_t row_bytes = J * (int64_t)sizeof(VT);
     for (int which = 0; which < 2; ++which) {
         const VT *&F = which == 0 ? X : M;
         int64_t &ldf = which == 0 ? ldx : ldm;
         const int64_t rows_f = which == 0 ? rows_x : rows_m;
-        if (!(vec && rows_f * row_bytes > ((int64_t)4 << 20) && row_bytes % 128 != 0 &&
+        if (!(J >= VV && rows_f * row_bytes > ((int64_t)4 << 20) && row_bytes % 128 != 0 &&
               (ldf * (int64_t)sizeof(VT) % 128 != 0 || (uintptr_t)F % 128 != 0)))
             continue;
         const int64_t ldp_bytes = (row_bytes + 127) / 128 * 128;
         const size_t want = (size_t)rows_f * (size_t)ldp_bytes;
         if (Bt->mttkrp_pad_bytes[which] < want) {
+            if (capturing != hipStreamCaptureStatusNone) continue;
             if (Bt->mttkrp_pad[which]) {
                 SP_HIP(hipStreamSynchronize(st));
                 mem.put(Bt->mttkrp_pad[which]);
@@ -325,12 +349,20 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
                 Bt->mttkrp_pad_bytes[which] = 0;
             }
             Bt->mttkrp_pad[which] = mem.get(want);
-            if (!Bt->mttkrp_pad[which]) return SP_ERR_ALLOC;
+            if (!Bt->mttkrp_pad[which]) {
+                if (pieces16) return SP_ERR_ALLOC;
+                continue;
+            }
             Bt->mttkrp_pad_bytes[which] = want;
         }
-        const int64_t pieces = rows_f * (row_bytes / 16);
-        hipLaunchKernelGGL(repitch_rows_kernel, dim3((unsigned)(ceil_div(pieces, kThreads) < 4096 ? ceil_div(pieces, kThreads) : 4096)), dim3(kThreads),
-                           0, st, (const char *)F, ldf * (int64_t)sizeof(VT), rows_f, row_bytes, (char *)Bt->mttkrp_pad[which], ldp_bytes);
+        const int64_t pieces = rows_f * (pieces16 ? row_bytes / 16 : J);
+        const dim3 copy_grid((unsigned)(ceil_div(pieces, kThreads) < 4096 ? ceil_div(pieces, kThreads) : 4096));
+        if (pieces16)
+            hipLaunchKernelGGL(repitch_rows_kernel<uint4>, copy_grid, dim3(kThreads), 0, st, (const char *)F, ldf * (int64_t)sizeof(VT), rows_f,
+                               row_bytes, (char *)Bt->mttkrp_pad[which], ldp_bytes);
+        else
+            hipLaunchKernelGGL(repitch_rows_kernel<VT>, copy_grid, dim3(kThreads), 0, st, (const char *)F, ldf * (int64_t)sizeof(VT), rows_f,
+                               row_bytes, (char *)Bt->mttkrp_pad[which], ldp_bytes);
         SP_HIP(hipGetLastError());
         F = (const VT *)Bt->mttkrp_pad[which];
         ldf = ldp_bytes / (int64_t)sizeof(VT);
@@ -340,19 +372,24 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
                        (uint64_t)rows_x * (uint64_t)ldx * sizeof(VT) < ((uint64_t)1 << 32);      // 64-bit coordinates keep 64-bit offsets
     {
         sp_prof_scope prof(B, st);
-        const unsigned gx = (unsigned)(ceil_div(ceil_div(nwin, kWaves), 8) * 8);   // a multiple of 8: see the block mapping in the kernel
-#define SPMI_MTTKRP(V, U, OT)                                                                                                          \
-    hipLaunchKernelGGL((mttkrp_windows_kernel<PT, CT, VT, V, U, OT>), dim3(gx, (unsigned)ceil_div(J, 64 * V)), dim3(kThreads), 0, st, pos1, crd0, \
-                       crd1, pos2, crd2, (const VT *)B->values, wfib, wslc, nwin, nfib, nnz, M, ldm, X, ldx, A, lda,                    \
-                       (VT *)B->mttkrp_carry, J, accumulate)
-#define SPMI_MTTKRP_V(V)                                                        \
-    do {                                                                        \
-        const int64_t lanes = J / V < 64 ? J / V : 64;                          \
-        if (64 / lanes < 4) { if (small) SPMI_MTTKRP(V, 4, uint32_t); else SPMI_MTTKRP(V, 4, uint64_t); } \
-        else { if (small) SPMI_MTTKRP(V, 2, uint32_t); else SPMI_MTTKRP(V, 2, uint64_t); }               \
+        const unsigned gx = (unsigned)(ceil_div(nwin, 8) * 8);                     // a multiple of 8: see the block mapping in the kernel
+        const int V = J >= VV ? VV : J >= 2 ? 2 : 1;                              // fewer columns than a load holds: shorter loads
+        const int64_t pieces = ceil_div(J, V);
+        // at least 512 blocks where the columns allow: few windows share the columns out among more blocks
+        const int64_t split = nwin < 512 ? ceil_div(512, nwin) : 1;
+        const int64_t wanted = ceil_div(pieces, split) > 4 ? ceil_div(pieces, split) : 4;
+        const int lr_tile = (int)(wanted < 64 ? wanted : 64);
+#define SPMI_MTTKRP(V, OT)                                                                                                             \
+    hipLaunchKernelGGL((mttkrp_runs_kernel<PT, CT, VT, V, OT>), dim3(gx, (unsigned)ceil_div(pieces, lr_tile)), dim3(kThreads), 0, st, pos1, crd0, \
+                       crd1, pos2, crd2, (const VT *)B->values, wfib, wslc, nwin, nfib, nslc, nnz, M, ldm, X, ldx, A, lda,              \
+                       (VT *)B->mttkrp_carry, J, lr_tile, accumulate)
+#define SPMI_MTTKRP_V(V)                            \
+    do {                                            \
+        if (small) SPMI_MTTKRP(V, uint32_t);        \
+        else SPMI_MTTKRP(V, uint64_t);              \
     } while (0)
-        if (vec) SPMI_MTTKRP_V(VV);
-        else if (half_vec) SPMI_MTTKRP_V(2);
+        if (V == VV) SPMI_MTTKRP_V(VV);
+        else if (V == 2) SPMI_MTTKRP_V(2);
         else SPMI_MTTKRP_V(1);
 #undef SPMI_MTTKRP_V
 #undef SPMI_MTTKRP

@@ -105,3 +105,24 @@ def test_sddmm_keeps_infinities_where_two_loads_meet(K):
     X = sp.sp_sddmm(S, dev(A), dev(B), b_is_transposed=True).cpu().numpy()
     hit = np.isin(sp.sp_crd(S, 1).cpu().numpy(), (7, 9))
     assert hit.any() and np.all(np.isposinf(X[hit])) and np.all(X[~hit] == K)
+
+
+@pytest.mark.parametrize("order", [(0, 1, 2), (0, 2, 1)])
+@pytest.mark.parametrize("dtype,J", [(np.float64, j) for j in (2, 3, 33, 127, 129)] + [(np.float32, j) for j in (2, 3, 5, 42, 255, 257)])
+def test_mttkrp_any_width_and_address(order, dtype, J):
+    w = W.tensor3_slices(I=40, K=90, L=200, nnz=9000, k_mean=25, l_mean=60, sigma=1.2, J=J, dtype=dtype)
+    C, D = w.factors()
+    ref, mag = oracle.mttkrp_coo(w.shape, w.ci, w.ck, w.cl, w.vals, C, D)
+    T = gpu_pack((0, 1, 1), order, w.shape, [w.ci, w.ck, w.cl], w.vals)
+    A0 = prng.uniform_pm1(9, 1, w.shape[0] * J, dtype=dtype).reshape(-1, J)
+    for extra, offset, accumulate in [(0, 0, False), (1, 1, False), (3, 2, True)]:
+        say("case mttkrp any width", order, dtype.__name__, J, extra, offset)
+        Cd, Dd = embedded(C, J + extra, offset)[1], embedded(D, J + extra, offset)[1]
+        flat, Ad = embedded(A0, J + extra, offset)
+        before = flat.clone()
+        sp.sp_mttkrp(T, Cd, Dd, A=Ad, accumulate=accumulate)
+        base = A0 if accumulate else np.zeros_like(A0)
+        assert_product_close(Ad, ref + base, mag + np.abs(base), dtype, "mttkrp")
+        written = torch.zeros_like(flat, dtype=torch.bool)
+        written[offset:offset + w.shape[0] * (J + extra)].view(w.shape[0], J + extra)[:, :J] = True
+        assert torch.equal(torch.isnan(flat[~written]), torch.isnan(before[~written]))
