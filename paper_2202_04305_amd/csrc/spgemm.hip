@@ -123,12 +123,14 @@ template <typename PT>
 __global__ void spgemm_last_pos_kernel(const PT *__restrict__ last, long long *__restrict__ out) { *out = (long long)*last; }
 
 // block = one stored row r of A, four waves that take the selected rows of B in turn (marking a column is an OR: the order
-// does not matter).  count[i] = number of distinct columns the row reaches.
+// does not matter).  count[i] = number of distinct columns the row reaches; kept (may be null): the row's marks, `stride`
+// 32-bit words per stored row.
 constexpr int kCountWaves = 4;
 template <typename PT, typename CT>
 __global__ __launch_bounds__(64 * kCountWaves) void spgemm_ws_count_kernel(const PT *__restrict__ apos, const CT *__restrict__ acrd,
                                                                            const CT *__restrict__ arowid, const PT *__restrict__ bpos,
-                                                                           const CT *__restrict__ bcrd, int64_t n, PT *__restrict__ count)
+                                                                           const CT *__restrict__ bcrd, int64_t n, PT *__restrict__ count,
+                                                                           uint32_t *__restrict__ kept, int64_t stride)
 {
     extern __shared__ uint32_t ws_bits[];
     __shared__ int partial[kCountWaves];
@@ -160,6 +162,8 @@ __global__ __launch_bounds__(64 * kCountWaves) void spgemm_ws_count_kernel(const
     __syncthreads();
     int c = 0;
     for (int64_t w = threadIdx.x; w < words; w += 64 * kCountWaves) c += __popc(ws_bits[w]);
+    if (kept)
+        for (int64_t w = threadIdx.x; w < stride; w += 64 * kCountWaves) kept[r * stride + w] = w < words ? ws_bits[w] : 0u;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
     if (lane == 0) partial[wave] = c;
@@ -426,151 +430,157 @@ __global__ __launch_bounds__(64 * kPanelWaves) void spgemm_ws_numeric_panels_ker
     }
 }
 
+// One entry of B as the kernel below reads it: column and value side by side, so that a short stretch of a row is one load per
+// entry and one or two cache lines instead of two loads and three lines.
+template <typename VT>
+struct alignas(2 * sizeof(VT)) b_record { VT val; uint32_t col; };
+
 // bounds[k * (panels + 1) + p] = position of the first entry of row k of B whose column is >= p << shift (p = panels: the
-// end of the row): where each column panel's share of the row starts, the row staying where it is.
-template <typename PT, typename CT>
-__global__ __launch_bounds__(256) void spgemm_panel_bounds_kernel(const PT *__restrict__ bpos, const CT *__restrict__ bcrd, int64_t kdim,
-                                                                  int shift, int panels, uint32_t *__restrict__ bounds)
+// end of the row): where each column panel's share of the row starts, the row staying where it is.  records: B's entries.
+template <typename PT, typename CT, typename VT>
+__global__ __launch_bounds__(256) void spgemm_panel_bounds_kernel(const PT *__restrict__ bpos, const CT *__restrict__ bcrd,
+                                                                  const VT *__restrict__ bval, int64_t nb, int64_t kdim, int shift, int panels,
+                                                                  uint32_t *__restrict__ bounds, b_record<VT> *__restrict__ records)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= kdim * (panels + 1)) return;
-    const int64_t k = i / (panels + 1);
-    const int p = (int)(i - k * (panels + 1));
-    int64_t lo = (int64_t)bpos[k], hi = (int64_t)bpos[k + 1];
-    const int64_t first = (int64_t)p << shift;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if ((int64_t)bcrd[mid] < first) lo = mid + 1;
-        else hi = mid;
+    const int64_t stride = (int64_t)gridDim.x * 256, i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t i = i0; i < nb; i += stride) {
+        b_record<VT> e;
+        e.val = bval[i];
+        e.col = (uint32_t)bcrd[i];
+        records[i] = e;
     }
-    bounds[i] = (uint32_t)lo;
+    for (int64_t i = i0; i < kdim * (panels + 1); i += stride) {
+        const int64_t k = i / (panels + 1);
+        const int p = (int)(i - k * (panels + 1));
+        int64_t lo = (int64_t)bpos[k], hi = (int64_t)bpos[k + 1];
+        const int64_t first = (int64_t)p << shift;
+        while (lo < hi) {
+            const int64_t mid = lo + (hi - lo) / 2;
+            if ((int64_t)bcrd[mid] < first) lo = mid + 1;
+            else hi = mid;
+        }
+        bounds[i] = (uint32_t)lo;
+    }
 }
 
-// Sixteen waves per row of A, for wide rows of C: the same ownership of columns (wave w works on the columns of panel
-// w and on its own part of the workspace, so the additions to an element keep a fixed order) with four times the waves
-// in flight per CU.  B is read where it is, through the table of panel bounds inside each row (above): the sixteen
-// shares of a row of B are neighbours in memory and the block's waves ask for them at about the same time, so a line
-// is fetched once (with the regrouped copy that the four-wave kernel reads, every 40-byte share cost its own lines:
-// 1.83 GB past the L2 per product).  A wave loads 64 entries of the row of A at once (one per lane, with the bounds
-// of the selected row of B inside the wave's panel) and hands them out, 32 at a time through a small LDS table, to its
-// eight groups of eight lanes, four entries per group in flight: a group walks its segment of the row of B eight
-// entries at a time.  Measured on the 8192 x 8192 product of density 0.01 (348 us; 478 us with four waves): leaving the
-// adds out changes nothing, the kernel waits for its many short loads (a panel's share of a row of B is five entries);
-// 75 us of it are clearing the workspace, 50 us writing the row out.
-constexpr int kWideWaves = 16, kWideGroup = 8, kWideStage = 32;
-constexpr int64_t kWideMinColumns = 8192;               // from this many columns of C on the sixteen-wave kernel is the default
+// A wave per (row of A, panel of 2^kPanelShift columns of C), every wave for itself: the panel's part of the workspace is
+// 8 KB of LDS, so a CU holds sixteen of them and nothing waits at a barrier.  The marks that the
+// counting kernel made say which columns the panel has, how many the row has before it and whether there is anything to do at
+// all, so this pass marks nothing.  B is read from its records through the table of panel bounds inside each row (above).
+// A wave loads 64 entries of the row of A at once (one per lane, with the bounds of the selected row of B inside the panel) and
+// hands them out, 32 at a time through a small LDS table, to groups of G lanes, U entries per group in flight: a group walks
+// its segment of the row of B, G entries at a time (G by the average length of a segment).  The order of the additions to an
+// element is fixed by the structure.
+// Bound by the cache lines that short stretches of B's rows cost on their way from the L2 (8192 x 8192 of density 0.01: 55 M
+// pairs in stretches of ten).  That product, whole call: sixteen waves per row that shared one workspace, marked the columns
+// again and met at two barriers 439 us; a wave per panel of 512 columns over crd and values 424; over records 390; panels of
+// 1024 columns 385 (64 entries handed out at a time: 414).  The same in f32: 596 -> 498 us.
+template <typename VT>
+constexpr int kPanelShift = sizeof(VT) == 8 ? 10 : 11;   // 8 KB of values
+constexpr int kTaskWaves = 4, kTaskStage = 32;
+constexpr int kWideWaves = 16, kWideStage = 32;         // the kernel below
 template <typename VT>
 struct wide_entry {
-    uint32_t b0, b1;      // the segment of the selected row of B inside the wave's panel (offsets into the panel copy)
+    uint32_t b0, b1;      // the segment of the selected row of B inside the wave's panel
     VT a;                 // the value of the entry of A
 };
 
-template <typename PT, typename CT, typename VT>
-__global__ __launch_bounds__(64 * kWideWaves) void spgemm_ws_numeric_wide_kernel(
+template <typename PT, typename CT, typename VT, int G>
+__global__ __launch_bounds__(64 * kTaskWaves) void spgemm_panel_tasks_kernel(
     const PT *__restrict__ apos, const CT *__restrict__ acrd, const VT *__restrict__ aval, const CT *__restrict__ arowid, int64_t arows,
-    const uint32_t *__restrict__ bounds, const CT *__restrict__ scrd, const VT *__restrict__ sval, int shift, int64_t n,
-    const PT *__restrict__ cpos, CT *__restrict__ ccrd, VT *__restrict__ cval)
+    const uint32_t *__restrict__ bounds, const b_record<VT> *__restrict__ brec, int panels,
+    const uint64_t *__restrict__ marks, int64_t words, const PT *__restrict__ cpos, CT *__restrict__ ccrd, VT *__restrict__ cval)
 {
-    constexpr int G = kWideGroup, NG = 64 / G, U = 4;
-    static_assert(NG * U == kWideStage, "one pass over the table hands out all of it");
-    extern __shared__ unsigned char ws_raw[];
-    __shared__ wide_entry<VT> table[kWideWaves][kWideStage];
-    VT *acc = (VT *)ws_raw;
-    uint32_t *bits = (uint32_t *)(ws_raw + (size_t)n * sizeof(VT));
+    constexpr int W = 1 << kPanelShift<VT>, NG = 64 / G, U = kTaskStage / NG;
+    __shared__ VT workspace[kTaskWaves][W];
+    __shared__ wide_entry<VT> table[kTaskWaves][kTaskStage];
     const int lane = threadIdx.x & 63, g = lane / G, gl = lane % G;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t words = (n + 31) >> 5;
-    // The block keeps its workspace over all the rows it takes (r = blockIdx.x, + gridDim.x, ...): cleared once here, and
-    // after every row each wave clears exactly what the row has touched in its columns while it writes them out.
-    for (int64_t j = threadIdx.x; j < n; j += 64 * kWideWaves) acc[j] = (VT)0;
-    for (int64_t w = threadIdx.x; w < words; w += 64 * kWideWaves) bits[w] = 0u;
-    __syncthreads();
-    const int64_t col_lo = (int64_t)wave << shift;                 // this wave's columns: [col_lo, col_hi), a multiple of 64 wide
-    const int64_t col_hi = col_lo + ((int64_t)1 << shift) < n ? col_lo + ((int64_t)1 << shift) : n;
-    const uint32_t *wbounds = bounds + wave;                       // this wave's panel in every row's kWideWaves + 1 bounds
-    wide_entry<VT> *mine = table[wave];
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (int64_t r = blockIdx.x; r < arows; r += gridDim.x) {
-        const int64_t a0 = (int64_t)apos[r], a1 = (int64_t)apos[r + 1];
-        if (a1 == a0) continue;                                    // the whole block
-        if (col_lo < n) {
-            for (int64_t g0 = a0; g0 < a1; g0 += 64) {
-                const int64_t e = g0 + lane;
-                wide_entry<VT> w;
-                w.b0 = 0; w.b1 = 0; w.a = (VT)0;                   // lanes past the row hold empty segments
-                if (e < a1) {
-                    const int64_t k = (int64_t)acrd[e];
-                    w.a = aval[e];
-                    w.b0 = wbounds[k * (kWideWaves + 1)];
-                    w.b1 = wbounds[k * (kWideWaves + 1) + 1];
-                }
-                const int cnt = (int)(a1 - g0 < 64 ? a1 - g0 : 64);   // wave-uniform
-                for (int s0 = 0; s0 < cnt; s0 += kWideStage) {
-                    if (lane >= s0 && lane < s0 + kWideStage) mine[lane - s0] = w;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    wide_entry<VT> seg[U];
+    const int64_t task = (int64_t)blockIdx.x * kTaskWaves + wave;
+    const int64_t r = task / panels;
+    const int panel = (int)(task - r * panels);
+    if (r >= arows) return;                                        // the whole wave, here and below
+    const int64_t a0 = (int64_t)apos[r], a1 = (int64_t)apos[r + 1];
+    if (a1 == a0) return;
+    const uint64_t *rowmarks = marks + r * words;
+    const int64_t w0 = (int64_t)panel * (W / 64);
+    static_assert(W / 64 <= 64, "one word of marks per lane");
+    const uint64_t mine = lane < W / 64 && w0 + lane < words ? rowmarks[w0 + lane] : 0;
+    if (!__any(mine != 0)) return;                                 // the row reaches no column of this panel
+    int before = 0;                                                // columns the row reaches before the panel
+    for (int64_t w = lane; w < w0; w += 64) before += __popcll(rowmarks[w]);
+    const int64_t row_at = (int64_t)cpos[arowid ? (int64_t)arowid[r] : r];
+    VT *acc = workspace[wave];
+    wide_entry<VT> *stage = table[wave];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) seg[u] = mine[u * NG + g];
-                    uint32_t j[U];
-                    VT p[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {                  // the first eight entries of each segment: all loads first
-                        const uint32_t t = seg[u].b0 + (uint32_t)gl;
-                        j[u] = 0xffffffffu;
-                        p[u] = (VT)0;
-                        if (t < seg[u].b1) { j[u] = (uint32_t)scrd[t]; p[u] = seg[u].a * sval[t]; }
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if (j[u] != 0xffffffffu) {
-                            atomicOr(&bits[j[u] >> 5], 1u << (j[u] & 31));
-                            atomicAdd(&acc[j[u]], p[u]);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u)                    // what is left of longer segments
-                        for (uint32_t t = seg[u].b0 + (uint32_t)(G + gl); __any(t < seg[u].b1); t += G)
-                            if (t < seg[u].b1) {
-                                const uint32_t jj = (uint32_t)scrd[t];
-                                atomicOr(&bits[jj >> 5], 1u << (jj & 31));
-                                atomicAdd(&acc[jj], seg[u].a * sval[t]);
-                            }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the table is rewritten in the next pass
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                }
-            }
+    for (int i = 0; i < W / 64; ++i) acc[i * 64 + lane] = (VT)0;
+    const uint32_t col_lo = (uint32_t)panel << kPanelShift<VT>;
+    const uint32_t *pbounds = bounds + panel;
+    auto load = [&](int64_t e) {
+        wide_entry<VT> w;
+        w.b0 = 0; w.b1 = 0; w.a = (VT)0;                           // lanes past the row hold empty segments
+        if (e < a1) {
+            const int64_t k = (int64_t)acrd[e];
+            w.a = aval[e];
+            w.b0 = pbounds[k * (panels + 1)];
+            w.b1 = pbounds[k * (panels + 1) + 1];
         }
-        __syncthreads();
-        // the compress step for this wave's columns; its first output follows the set bits of the columns before
-        if (col_lo < n) {
-            int before_cols = 0;
-            for (int64_t w = lane; w < (col_lo >> 5); w += 64) before_cols += __popc(bits[w]);
+        return w;
+    };
+    wide_entry<VT> next = load(a0 + lane);
+    for (int64_t g0 = a0; g0 < a1; g0 += 64) {
+        const wide_entry<VT> w = next;
+        if (g0 + 64 < a1) next = load(g0 + 64 + lane);             // on its way while this one's segments are walked
+        const int cnt = (int)(a1 - g0 < 64 ? a1 - g0 : 64);        // wave-uniform
+        for (int s0 = 0; s0 < cnt; s0 += kTaskStage) {
+            if (lane >= s0 && lane < s0 + kTaskStage) stage[lane - s0] = w;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            uint32_t b0[U], b1[U];
+            VT a[U];
+            b_record<VT> rec[U];
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) before_cols += __shfl_xor(before_cols, d, 64);
-            const int64_t row_at = (int64_t)cpos[arowid ? (int64_t)arowid[r] : r] + before_cols;
-            CT *crow = ccrd + row_at;
-            VT *vrow = cval + row_at;
-            uint32_t base = 0;
-            for (uint32_t j0 = (uint32_t)col_lo; j0 < (uint32_t)col_hi; j0 += 64) {
-                const uint32_t j = j0 + lane;
-                const bool set = j < (uint32_t)col_hi && ((bits[j >> 5] >> (j & 31)) & 1u);
-                const unsigned long long mask = __ballot(set);
-                if (set) {
-                    const uint32_t o = base + (uint32_t)__popcll(mask & below);
-                    crow[o] = (CT)j;
-                    vrow[o] = acc[j];
-                    acc[j] = (VT)0;                                // clean for the block's next row
-                }
-                base += (uint32_t)__popcll(mask);
+            for (int u = 0; u < U; ++u) {                          // the first G entries of each segment: all loads first
+                const wide_entry<VT> seg = stage[u * NG + g];
+                b0[u] = seg.b0 + (uint32_t)gl;
+                b1[u] = seg.b1;
+                a[u] = seg.a;
+                rec[u].val = (VT)0;
+                rec[u].col = col_lo;
+                if (b0[u] < b1[u]) rec[u] = brec[b0[u]];
             }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (b0[u] < b1[u]) atomicAdd(&acc[rec[u].col - col_lo], a[u] * rec[u].val);
+#pragma unroll
+            for (int u = 0; u < U; ++u)                            // what is left of longer segments
+                for (uint32_t t = b0[u] + (uint32_t)G; __any(t < b1[u]); t += G)
+                    if (t < b1[u]) {
+                        const b_record<VT> more = brec[t];
+                        atomicAdd(&acc[more.col - col_lo], a[u] * more.val);
+                    }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront"); // the table is rewritten in the next pass
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        __syncthreads();                                           // every wave has counted the bits before its columns
-        if (col_lo < n)
-            for (int64_t w = (col_lo >> 5) + lane; w < ((col_hi + 31) >> 5); w += 64) bits[w] = 0u;
-        // no barrier needed here: until the next row's barrier only this wave touches these words again
+    }
+    // the compress step: the marked columns in order
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) before += __shfl_xor(before, d, 64);
+    CT *crow = ccrd + row_at + before;
+    VT *vrow = cval + row_at + before;
+    uint32_t base = 0;
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int i = 0; i < W / 64; ++i) {
+        const uint64_t mask = (uint64_t)uniform_i64((int64_t)mine, i);
+        if ((mask >> lane) & 1u) {
+            const uint32_t o = base + (uint32_t)__popcll(mask & below);
+            crow[o] = (CT)(col_lo + (uint32_t)(i * 64 + lane));
+            vrow[o] = acc[i * 64 + lane];
+        }
+        base += (uint32_t)__popcll(mask);
     }
 }
 
@@ -701,7 +711,34 @@ sp_status spgemm_workspace_t(const sp_tensor *A, const sp_tensor *Br, const sp_e
     {
         sp_scratch tmp(mem);
         do {
-            int *flags = (int *)tmp.get(64);
+            // A wave per row and column panel where that pays, unless another kernel is asked for (tune values 2, 3, 5) or its
+            // tables cannot be had; they and the flags are one block of scratch.
+            const bool a_outer_compressed = A->enc.lt[0] == SP_COMPRESSED;
+            const int64_t arows = a_outer_compressed ? A->ncrd[0] : m;
+            const CT *arowid = a_outer_compressed ? (const CT *)A->crd[0] : nullptr;
+            const bool work = arows > 0 && A->nvalues > 0 && Br->nvalues > 0 && n > 0;
+            const int panels = (int)ceil_div(n, (int64_t)1 << kPanelShift<VT>);
+            const int64_t words = ceil_div(n, 64);                     // 64-bit words of marks per stored row
+            const int64_t nbounds = Br->shape[0] * (panels + 1);
+            char *block = nullptr;
+            uint64_t *marks = nullptr;
+            uint32_t *bounds = nullptr;
+            b_record<VT> *records = nullptr;
+            const size_t record_bytes = (size_t)Br->nvalues * sizeof(b_record<VT>), mark_bytes = (size_t)(arows * words) * 8;
+            // below two million pairs the extra launch and the tables outweigh what they save (2000 columns, 0.8 M pairs, whole call:
+            // 92 us without, 114 with; 4000 columns, 2.5 M pairs: 146 and 135), but rows of 8192 columns and more would leave
+            // the kernel without tables two waves per CU
+            const double pairs = (double)A->nvalues * (double)Br->nvalues / (double)(Br->shape[0] > 0 ? Br->shape[0] : 1);
+            const bool by_panels = A->tune_spgemm == 4 || (A->tune_spgemm == 0 && (n >= 8192 || pairs >= 2097152.0));
+            if (work && by_panels) {
+                block = (char *)tmp.get(64 + record_bytes + mark_bytes + (size_t)nbounds * 4);
+                if (block) {
+                    records = (b_record<VT> *)(block + 64);
+                    marks = (uint64_t *)(block + 64 + record_bytes);
+                    bounds = (uint32_t *)(block + 64 + record_bytes + mark_bytes);
+                }
+            }
+            int *flags = block ? (int *)block : (int *)tmp.get(64);
             if (!flags) { status = SP_ERR_ALLOC; break; }
             if ((status = spmi_fill_zero(flags, 64, st)) != SP_OK) break;
             const size_t pbytes = ((size_t)(m + 1) * sizeof(PT) + 15) & ~(size_t)15;
@@ -709,32 +746,22 @@ sp_status spgemm_workspace_t(const sp_tensor *A, const sp_tensor *Br, const sp_e
             t->npos[1] = m + 1;
             if (!t->pos[1]) { status = SP_ERR_ALLOC; break; }
             if ((status = spmi_fill_zero(t->pos[1], pbytes, st)) != SP_OK) break;
-            const bool a_outer_compressed = A->enc.lt[0] == SP_COMPRESSED;
-            const int64_t arows = a_outer_compressed ? A->ncrd[0] : m;
-            const CT *arowid = a_outer_compressed ? (const CT *)A->crd[0] : nullptr;
             const size_t bits_bytes = (size_t)((n + 31) / 32) * 4;
             const size_t ws_bytes = (size_t)n * sizeof(VT) + bits_bytes;
-            const bool work = arows > 0 && A->nvalues > 0 && Br->nvalues > 0 && n > 0;
-            // sixteen waves per row for wide results (tune value 4 asks for them from 1024 columns on), else four
-            const bool wide = A->tune_spgemm == 4 ? n >= kWideWaves * 64 : (A->tune_spgemm == 0 && n >= kWideMinColumns);
+            if (bounds) {
+                const int64_t most = nbounds > Br->nvalues ? nbounds : Br->nvalues, nblk = ceil_div(most, 256);
+                hipLaunchKernelGGL((spgemm_panel_bounds_kernel<PT, CT, VT>), dim3((unsigned)(nblk < 8192 ? nblk : 8192)), dim3(256), 0, st,
+                                   (const PT *)Br->pos[1], (const CT *)Br->crd[1], (const VT *)Br->values, Br->nvalues, Br->shape[0],
+                                   kPanelShift<VT>, panels, bounds, records);
+                if (hipGetLastError() != hipSuccess) { status = SP_ERR_HIP; break; }
+            }
             if (work) {
                 hipLaunchKernelGGL((spgemm_ws_count_kernel<PT, CT>), dim3((unsigned)arows), dim3(64 * kCountWaves), bits_bytes, st, (const PT *)A->pos[1],
-                                   (const CT *)A->crd[1], arowid, (const PT *)Br->pos[1], (const CT *)Br->crd[1], n, (PT *)t->pos[1]);
+                                   (const CT *)A->crd[1], arowid, (const PT *)Br->pos[1], (const CT *)Br->crd[1], n, (PT *)t->pos[1],
+                                   bounds ? (uint32_t *)marks : nullptr, 2 * words);
                 if (hipGetLastError() != hipSuccess) { status = SP_ERR_HIP; break; }
             }
-            // the sixteen-wave kernel's table of panel bounds does not depend on the counts: enqueued here, ahead of the
-            // synchronisation below, so that nothing but the allocation of C stands between that and the numeric kernel
             int pshift = 0;
-            uint32_t *bounds = nullptr;
-            if (work && wide) {
-                while (((int64_t)kWideWaves << pshift) < n) ++pshift;       // the narrowest power of two with at most sixteen panels
-                const int64_t kdim = Br->shape[0], nb = kdim * (kWideWaves + 1);
-                bounds = (uint32_t *)tmp.get((size_t)nb * 4);
-                if (!bounds) { status = SP_ERR_ALLOC; break; }
-                hipLaunchKernelGGL((spgemm_panel_bounds_kernel<PT, CT>), dim3((unsigned)ceil_div(nb, 256)), dim3(256), 0, st, (const PT *)Br->pos[1],
-                                   (const CT *)Br->crd[1], kdim, pshift, kWideWaves, bounds);
-                if (hipGetLastError() != hipSuccess) { status = SP_ERR_HIP; break; }
-            }
             if ((status = spmi_exclusive_scan(t->pos[1], m + 1, (int)sizeof(PT) * 8, tmp, st)) != SP_OK) break;
             // the longest row of C (the products choose kernels by it) comes back with the total, in one synchronisation
             if ((status = spmi_max_segment_async(t->pos[1], (int)sizeof(PT) * 8, m, (unsigned long long *)(flags + 4), st)) != SP_OK) break;
@@ -775,16 +802,17 @@ sp_status spgemm_workspace_t(const sp_tensor *A, const sp_tensor *Br, const sp_e
                                    n, (const PT *)t->pos[1], (CT *)t->crd[1], (VT *)t->values);
                 if (hipGetLastError() != hipSuccess) { status = SP_ERR_HIP; break; }
             } else if (bounds) {
-                auto kernel = spgemm_ws_numeric_wide_kernel<PT, CT, VT>;
-                if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ws_bytes) != hipSuccess) {
-                    status = SP_ERR_HIP;
-                    break;
-                }
-                // two blocks fit a CU's LDS: that many blocks, each taking every 512th row
-                const unsigned wide_blocks = (unsigned)(arows < 512 ? arows : 512);
-                hipLaunchKernelGGL(kernel, dim3(wide_blocks), dim3(64 * kWideWaves), ws_bytes, st, (const PT *)A->pos[1], (const CT *)A->crd[1],
-                                   (const VT *)A->values, arowid, arows, (const uint32_t *)bounds, (const CT *)Br->crd[1], (const VT *)Br->values,
-                                   pshift, n, (const PT *)t->pos[1], (CT *)t->crd[1], (VT *)t->values);
+                // lanes per segment of a row of B inside a panel, by their average length
+                const double segment = (double)Br->nvalues / ((double)Br->shape[0] * (double)panels);
+                const dim3 grid((unsigned)ceil_div(arows * panels, kTaskWaves));
+#define SPMI_TASKS(G)                                                                                                          \
+    hipLaunchKernelGGL((spgemm_panel_tasks_kernel<PT, CT, VT, G>), grid, dim3(64 * kTaskWaves), 0, st, (const PT *)A->pos[1], (const CT *)A->crd[1], \
+                       (const VT *)A->values, arowid, arows, (const uint32_t *)bounds, (const b_record<VT> *)records, panels,                                \
+                       (const uint64_t *)marks, words, (const PT *)t->pos[1], (CT *)t->crd[1], (VT *)t->values)
+                if (segment <= 3) SPMI_TASKS(4);
+                else if (segment <= 7) SPMI_TASKS(8);
+                else SPMI_TASKS(16);
+#undef SPMI_TASKS
                 if (hipGetLastError() != hipSuccess) { status = SP_ERR_HIP; break; }
             } else if (Bseg) {
                 auto kernel = spgemm_ws_numeric_panels_kernel<PT, CT, VT, 8>;

@@ -232,3 +232,22 @@ def test_spgemm_density_of_the_papers_table_rows():
                 assert np.all(np.abs(val[seg] - cv[at:at + k]) <= 1e-12 * mag[at:at + k])
                 at += k
             assert at == len(ci)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 2048, 2049, 4100, 9000])
+def test_spgemm_wave_per_panel_edges(n, dtype):
+    """Kernel 4 at the edges of its panels (1024 columns in f64, 2048 in f32) and of the words of marks; rows of A beyond one and
+    two batches of 64 entries, rows of B from empty to longer than a group, panels a row does not reach; small integers: bit
+    for bit."""
+    a, b = pair(150, 140, n, 9000, min(140 * n // 2, 20000), seed=n + 5)
+    keep = b.rows % 3 != 1                                         # rows of B without entries
+    br, bc = b.rows[keep], b.cols[keep]
+    va, vb = prng.small_ints(9, 3, a.nnz).astype(dtype), prng.small_ints(9, 4, b.nnz).astype(dtype)[keep]
+    ref = oracle.spgemm_coo(a.shape, a.rows, a.cols, va, b.shape, br, bc, vb)
+    for fa in ("csr", "dcsr"):
+        say("case spgemm wave per panel", n, dtype.__name__, fa)
+        A = gpu_pack(*ENC[fa], a.shape, [a.rows, a.cols], va)
+        B = gpu_pack(*ENC["csr"], b.shape, [br, bc], vb)
+        sp.sp_tensor_tune(A, sp.SP_TUNE_SPGEMM_KERNEL, 4)
+        check(sp.sp_spgemm(A, B, sp.sp_encode(*ENC["csr"], 32, 32)), "csr", (150, n), ref, dtype, exact=True)
