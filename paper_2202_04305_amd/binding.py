@@ -110,7 +110,11 @@ def _check(code, what=""):
 
 
 def _stream_ptr():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device, as torch.cuda.current_stream() has it, without building a Stream object for it
+    (0.2 against 2.8 us; a small product's whole call 7.5 -> 4.4 us)."""
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class _TorchAllocator:
