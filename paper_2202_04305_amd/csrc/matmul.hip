@@ -975,7 +975,7 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
         // have no 16-byte kernel keep the single launch up to twelve steps.
         const int64_t cg = N > 32 ? 64 * ceil_div(N, 64) * 2 : N > 16 ? 32 : N > 8 ? 16 : N > 4 ? 8 : 4;       // lanes of a wave per entry there
         const bool tiny = !fits_any && nnz < ((int64_t)1 << 17) && A->max_segment * cg <= 256 * 12;
-        const bool by_entries = A->tune_spmm == 3 || (A->tune_spmm == 0 && rowblocks->start && !tiny);
+        const bool by_entries = A->tune_spmm == 3 || (A->tune_spmm == 0 && rowblocks->start && !tiny && N / (64 * V) < 65535);      // a grid's y
         if (by_entries) {
             const int64_t nb = rowblocks->nblocks;
             bool scratch = A->spmm_carry_bytes >= (size_t)nb * N * sizeof(VT);
