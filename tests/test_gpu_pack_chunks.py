@@ -57,3 +57,14 @@ def test_distances_around_32_bits_and_runs_of_neighbours(msd_first, bits):
     c = np.repeat(base_c, runs) + (np.arange(r.size) - np.repeat(np.cumsum(runs) - runs, runs))
     lin = np.unique(r.astype(np.int64) * n + c)
     check((m, n), [lin // n, lin % n], np.float64, "key of %d bits" % bits)
+
+
+@pytest.mark.parametrize("per_row,col_bits", [(1500, 24), (3000, 24), (3000, 26), (5200, 26)])
+def test_every_sub_bucket_larger_than_a_chunk(per_row, col_bits):
+    """The sort as the builder chooses it, a million entries and more in few of the 65536 sub-buckets: each alone in its chunk, in
+    the finishing kernel, the larger one, or left to the other sort."""
+    rows = (1 << 20) // per_row + 20
+    r = np.repeat(np.arange(rows, dtype=np.int64) * 3, per_row)
+    c = prng.below(SEED, 30, r.size, 1 << col_bits).astype(np.int64)
+    lin = np.unique((r << col_bits) + c)
+    check((1 << 16, 1 << col_bits), [lin >> col_bits, lin & ((1 << col_bits) - 1)], np.float64, "rows of %d, %d bits" % (per_row, 16 + col_bits))
