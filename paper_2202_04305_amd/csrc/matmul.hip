@@ -9,7 +9,9 @@
 //                    staged in LDS, rows reduced from LDS (a thread per short row, a wave per
 //                    long one); rows that cross a block boundary are completed by a small
 //                    fix-up kernel from per-block carries (deterministic, no atomics).
-//   spmm kernel      one wave per stored row, lanes across the columns of B.
+//   runs kernel      SpMM: groups of lanes across the columns of B take runs of consecutive stored entries (windows, carries
+//                    and fix-up as above).
+//   spmm kernels     one wave per stored row, lanes across the columns of B: small products, and where no scratch can be had.
 //   scatter kernel   column-major storage (CSC / DCSC): a wave per stored column, atomic
 //                    adds into the rows of C.
 //

@@ -96,7 +96,7 @@ struct vec_of {
 // lane of a row moves back to the last V columns and stores only those that the lane before it does not have.
 // Bound by the rows of the inner factor that it gathers.  Measured before (a wave per 128 entries that walked their fibres one
 // after the other; a column per lane for widths that are no multiple of 16 bytes) and now: 76.9 M entries, 42 f64 columns
-// 1.893 -> 1.865 ms; 20 M entries, 33 columns 737 -> 439 us, 16 columns 337 -> 256 us; 30,000 entries in fibres of one or two,
+// 1.893 -> 1.828 ms; 20 M entries, 33 columns 737 -> 439 us, 16 columns 337 -> 256 us; 30,000 entries in fibres of one or two,
 // 42 columns 54 -> 18 us.
 template <typename PT, typename CT, typename VT, int V, typename OT>
 __global__ __launch_bounds__(kThreads) void mttkrp_runs_kernel(const PT *__restrict__ pos1, const CT *__restrict__ crd0, const CT *__restrict__ crd1,
@@ -238,12 +238,12 @@ __global__ __launch_bounds__(kThreads) void mttkrp_runs_kernel(const PT *__restr
 // A block per listed window boundary (the first one a slice crosses): adds all of that slice's carries to A.  The
 // carries are summed in a fixed pattern (four strided partial sums per column, combined in order), so the result is
 // the same on every call.
-constexpr int kFixThreads = 1024, kFixGroups = kFixThreads / 64;
-template <typename CT, typename VT>
+template <typename CT, typename VT, int kFixThreads>
 __global__ __launch_bounds__(kFixThreads) void mttkrp_fixup_kernel(const CT *__restrict__ crd0, const int32_t *__restrict__ wslc,
                                                                    const int32_t *__restrict__ cross, int64_t nwin, int64_t J,
                                                                    const VT *__restrict__ carry, VT *__restrict__ A, int64_t lda)
 {
+    constexpr int kFixGroups = kFixThreads / 64;
     __shared__ VT part[kFixGroups][64];
     if ((int)blockIdx.x >= cross[-1]) return;                      // block-uniform
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
@@ -396,8 +396,14 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
         SP_HIP(hipGetLastError());
     }
     if (ncross > 0) {
-        hipLaunchKernelGGL((mttkrp_fixup_kernel<CT, VT>), dim3((unsigned)ncross), dim3(kFixThreads), 0, st, crd0, wslc, cross, nwin, J,
-                           (const VT *)B->mttkrp_carry, A, lda);
+        // sixteen waves where slices fill many windows, four where a few carries per slice leave most of them idle (12,092 slices of
+        // six windows: 46 us with sixteen, 20 with four)
+        if (nwin > 32 * ncross)
+            hipLaunchKernelGGL((mttkrp_fixup_kernel<CT, VT, 1024>), dim3((unsigned)ncross), dim3(1024), 0, st, crd0, wslc, cross, nwin, J,
+                               (const VT *)B->mttkrp_carry, A, lda);
+        else
+            hipLaunchKernelGGL((mttkrp_fixup_kernel<CT, VT, 256>), dim3((unsigned)ncross), dim3(256), 0, st, crd0, wslc, cross, nwin, J,
+                               (const VT *)B->mttkrp_carry, A, lda);
         SP_HIP(hipGetLastError());
     }
     return SP_OK;

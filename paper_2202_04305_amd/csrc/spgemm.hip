@@ -14,7 +14,8 @@
 // marks the columns a row reaches in an n-bit map and counts them, the counts are scanned into C's pos, and a second
 // kernel adds the products into a dense row of n values (32 chunks of 64 entries of B requested at a time), then walks the bit map in column order and writes crd and
 // values: the paper's expand / compress, with the sort of the added indices replaced by the ordered walk.  One wave
-// owns a row and takes the pairs in a fixed order, so there are no atomics on values and the bits repeat.
+// owns a row and takes the pairs in a fixed order, so there are no atomics on values and the bits repeat.  Large products take a
+// wave per row and panel of columns instead, each with its own small workspace (spgemm_panel_tasks_kernel).
 #include "spmi_internal.h"
 
 namespace {
