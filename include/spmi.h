@@ -108,7 +108,10 @@ sp_status sp_prepare(sp_tensor *A, int64_t N, void *stream);
  * a caller can assert that its loop ran without any.  The handle's derived state is a cache that a product may fill
  * in although it takes the handle as const: a handle must not be used by two host threads at the same time, and the
  * scratch it holds is shared by all products on it, so products of one tensor that run concurrently on different
- * streams race.  B and C must not overlap.  Summation order inside a row is unspecified (floating-point reassociation,
+ * streams race.  (Exception: products of N >= 2 columns where N * element size, ldb, ldc, B or C are no multiples of 16
+ * bytes may overlap on different streams: one stream at a time has the scratch, the others take a kernel without any.)
+ * A product recorded into a graph may be replayed until sp_tensor_free, whatever other products run in between: scratch
+ * it was recorded with stays.  B and C must not overlap.  Summation order inside a row is unspecified (floating-point reassociation,
  * Section 5.2); whether it is the same from call to call depends on the kernel (see SP_TUNE_SPMV_KERNEL). */
 sp_status sp_matmul(const sp_tensor *A, const void *B, int64_t N, int64_t ldb,
                     void *C, int64_t ldc, int accumulate, void *stream);

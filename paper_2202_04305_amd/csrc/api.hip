@@ -116,8 +116,9 @@ extern "C" sp_status sp_tensor_info(const sp_tensor *t, sp_info *info)
     info->storageBytes = bytes;
     // what the handle keeps beyond the paper's storage: tables, regrouped copies, scratch
     const int64_t v = t->dtype == SP_F64 ? 8 : 4;
-    int64_t extra = (t->rowblocks.nblocks + t->nz_rowblocks.nblocks) * (4 + v) + (int64_t)t->dense_partial_bytes + (int64_t)t->spmm_carry_bytes +
-                    (int64_t)t->sddmm_bt_bytes + (int64_t)t->mttkrp_carry_bytes + (int64_t)t->mttkrp_pad_bytes[0] + (int64_t)t->mttkrp_pad_bytes[1];
+    int64_t extra = (t->rowblocks.nblocks + t->nz_rowblocks.nblocks) * (4 + v) + (int64_t)t->dense_partial_bytes + (int64_t)t->spmm_carry.mem.bytes +
+                    (int64_t)t->sddmm_bt.bytes + (int64_t)t->mttkrp_carry.bytes + (int64_t)t->mttkrp_pad[0].bytes + (int64_t)t->mttkrp_pad[1].bytes +
+                    (int64_t)t->outgrown_bytes;
     if (t->nz_pos) extra += t->nz_rows * (t->enc.cw / 8) + (t->nz_rows + 1) * (t->enc.pw / 8);
     if (t->bins) extra += t->bins->np * (2 * v + 4) + t->bins->np / 8 * 4 + ((int64_t)t->bins->panels + t->bins->rowblocks + 2) * 8;
     const sp_tensor *copies[2] = {t->segments ? t->segments->seg : nullptr, t->transposed};

@@ -843,20 +843,34 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
     return SP_OK;
 }
 
-// Scratch of the SpMM cut by stored entries: one row of N values per block, kept by the tensor and grown on demand.
+// Scratch of the SpMM cut by stored entries: one row of N values per block for every part of sp_spmm_carry, kept by the tensor
+// and made larger on demand.
 template <typename PT, typename CT, typename VT>
 sp_status prepare_spmm_t(const sp_tensor *A, int64_t N, hipStream_t st)
 {
     const row_view<PT, CT> rv(A);
     if (!rv.rowblocks->start || A->tune_spmm == 1 || A->tune_spmm == 2) return SP_OK;
-    const size_t need = (size_t)rv.rowblocks->nblocks * N * sizeof(VT);
-    if (A->spmm_carry_bytes >= need) return SP_OK;
-    sp_mem mem{A->alloc, A->free_, A->ctx};
-    if (A->spmm_carry) { SP_HIP(hipStreamSynchronize(st)); mem.put(A->spmm_carry); A->spmm_carry = nullptr; A->spmm_carry_bytes = 0; }
-    A->spmm_carry = mem.get((need + 255) & ~(size_t)255);
-    if (!A->spmm_carry) return SP_ERR_ALLOC;
-    A->spmm_carry_bytes = need;
+    sp_spmm_carry &c = A->spmm_carry;
+    if (c.columns >= N) return SP_OK;
+    constexpr int64_t V = 16 / sizeof(VT);
+    const size_t column = (size_t)rv.rowblocks->nblocks * sizeof(VT);
+    const size_t whole = (column * (size_t)(N < 64 * V ? N : 64 * V) + 255) & ~(size_t)255, any = (column * (size_t)N + 255) & ~(size_t)255;
+    c.mem.shared |= c.used[0] && c.user[0] != st;
+    c.columns = 0;
+    c.used[0] = c.used[1] = false;
+    SP_TRY(spmi_reserve(A, c.mem, whole + 2 * any, st));
+    c.offset[0] = 0; c.offset[1] = whole; c.offset[2] = whole + any;
+    c.columns = N;
     return SP_OK;
+}
+
+// May a product on this stream, or in this recording, use part 1 or 2 of the scratch?  Part 1 goes to another stream once its
+// user has nothing left to do; a graph keeps part 2.
+bool spmm_part_is_ours(const sp_spmm_carry &c, int part, hipStream_t st, unsigned long long graph)
+{
+    const bool same = c.used[part - 1] && c.user[part - 1] == st;
+    if (part == 1) return !c.used[0] || same || spmi_idle(c.user[0]);
+    return graph != 0 && (!c.used[1] || (same && c.graph == graph));
 }
 
 template <typename PT, typename CT, typename VT>
@@ -979,20 +993,27 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
         const bool tiny = !fits_any && nnz < ((int64_t)1 << 17) && A->max_segment * cg <= 256 * 12;
         const bool by_entries = A->tune_spmm == 3 || (A->tune_spmm == 0 && rowblocks->start && !tiny && N / (64 * V) < 65535);      // a grid's y
         if (by_entries) {
-            const int64_t nb = rowblocks->nblocks;
-            bool scratch = A->spmm_carry_bytes >= (size_t)nb * N * sizeof(VT);
-            if (!scratch) {                      // no sp_prepare for this many columns: the scratch is made now
-                // a product that the wave-per-row kernel can also do goes there when there is no scratch to be had
-                hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-                if (!fits_any) SP_HIP(hipStreamIsCapturing(st, &capturing));
-                if (capturing == hipStreamCaptureStatusNone) {
+            // a product that the wave-per-row kernel can also do goes there when there is no scratch to be had
+            sp_spmm_carry &c = A->spmm_carry;
+            unsigned long long graph = 0;
+            const bool recording = spmi_recording(st, &graph);
+            const int part = fits_any ? 0 : recording ? 2 : 1;
+            bool scratch = part == 0 || spmm_part_is_ours(c, part, st, graph);
+            if (scratch && c.columns < N) {      // no sp_prepare for this many columns: the scratch is made now
+                scratch = false;
+                if (part != 2) {
                     ++A->lazy_prepares;
                     const sp_status made = prepare_spmm_t<PT, CT, VT>(A, N, st);
-                    if (made != SP_OK && (fits_any || made != SP_ERR_ALLOC)) return made;
+                    if (made != SP_OK && (part == 0 || made != SP_ERR_ALLOC)) return made;
                     scratch = made == SP_OK;
                 }
             }
-            if (scratch) return spmm_windows_launch<PT, CT, VT>(A, rv, B, N, ldb, C, ldc, accumulate, (VT *)A->spmm_carry, st);
+            if (scratch) {
+                if (part > 0) { c.user[part - 1] = st; c.used[part - 1] = true; }
+                if (part == 2) c.graph = graph;
+                c.mem.shared |= recording;
+                return spmm_windows_launch<PT, CT, VT>(A, rv, B, N, ldb, C, ldc, accumulate, (VT *)((char *)c.mem.ptr + c.offset[part]), st);
+            }
         }
         if (fits && A->tune_spmm != 1) {
 #define SPMI_SPMM_VEC(LR)                                                                                                     \

@@ -310,13 +310,10 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
         if (built != SP_OK) { (void)hipStreamSynchronize(st); mem.put(table); return built; }
         Bt->mttkrp_windows = table;
     }
-    const size_t need = (size_t)nwin * J * sizeof(VT);
-    if (Bt->mttkrp_carry_bytes < need) {
-        if (Bt->mttkrp_carry) { SP_HIP(hipStreamSynchronize(st)); mem.put(Bt->mttkrp_carry); Bt->mttkrp_carry = nullptr; Bt->mttkrp_carry_bytes = 0; }
-        Bt->mttkrp_carry = mem.get((need + 255) & ~(size_t)255);
-        if (!Bt->mttkrp_carry) return SP_ERR_ALLOC;
-        Bt->mttkrp_carry_bytes = need;
-    }
+    const bool recording = spmi_recording(st);
+    SP_TRY(spmi_reserve(B, Bt->mttkrp_carry, (size_t)nwin * J * sizeof(VT), st));
+    Bt->mttkrp_carry.shared |= recording;
+    VT *carry = (VT *)Bt->mttkrp_carry.ptr;
     const int32_t *wfib = (const int32_t *)B->mttkrp_windows, *wslc = wfib + nwin, *cross = wslc + nwin + 4;
     constexpr int VV = 16 / sizeof(VT);
     // rows that can be copied 16 bytes at a time
@@ -328,8 +325,6 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
     // larger than an XCD's L2 and its rows do not start on 128-byte lines, a copy with rows padded to whole lines is
     // gathered from instead (a 336-byte row then touches 3 lines, not 3.6 on average); the copy is made on every call
     // into a buffer the tensor keeps.  Rows of an odd size go without the copy where that buffer cannot be had.
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (!pieces16) SP_HIP(hipStreamIsCapturing(st, &capturing));
     const int64_t row_bytes = J * (int64_t)sizeof(VT);
     for (int which = 0; which < 2; ++which) {
         const VT *&F = which == 0 ? X : M;
@@ -340,31 +335,22 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
             continue;
         const int64_t ldp_bytes = (row_bytes + 127) / 128 * 128;
         const size_t want = (size_t)rows_f * (size_t)ldp_bytes;
-        if (Bt->mttkrp_pad_bytes[which] < want) {
-            if (capturing != hipStreamCaptureStatusNone) continue;
-            if (Bt->mttkrp_pad[which]) {
-                SP_HIP(hipStreamSynchronize(st));
-                mem.put(Bt->mttkrp_pad[which]);
-                Bt->mttkrp_pad[which] = nullptr;
-                Bt->mttkrp_pad_bytes[which] = 0;
-            }
-            Bt->mttkrp_pad[which] = mem.get(want);
-            if (!Bt->mttkrp_pad[which]) {
-                if (pieces16) return SP_ERR_ALLOC;
-                continue;
-            }
-            Bt->mttkrp_pad_bytes[which] = want;
-        }
+        sp_kept &pad = Bt->mttkrp_pad[which];
+        if (!pieces16 && recording && pad.bytes < want) continue;
+        const sp_status room = spmi_reserve(B, pad, want, st);
+        if (room == SP_ERR_ALLOC && !pieces16) continue;
+        SP_TRY(room);
+        pad.shared |= recording;
         const int64_t pieces = rows_f * (pieces16 ? row_bytes / 16 : J);
         const dim3 copy_grid((unsigned)(ceil_div(pieces, kThreads) < 4096 ? ceil_div(pieces, kThreads) : 4096));
         if (pieces16)
             hipLaunchKernelGGL(repitch_rows_kernel<uint4>, copy_grid, dim3(kThreads), 0, st, (const char *)F, ldf * (int64_t)sizeof(VT), rows_f,
-                               row_bytes, (char *)Bt->mttkrp_pad[which], ldp_bytes);
+                               row_bytes, (char *)pad.ptr, ldp_bytes);
         else
             hipLaunchKernelGGL(repitch_rows_kernel<VT>, copy_grid, dim3(kThreads), 0, st, (const char *)F, ldf * (int64_t)sizeof(VT), rows_f,
-                               row_bytes, (char *)Bt->mttkrp_pad[which], ldp_bytes);
+                               row_bytes, (char *)pad.ptr, ldp_bytes);
         SP_HIP(hipGetLastError());
-        F = (const VT *)Bt->mttkrp_pad[which];
+        F = (const VT *)pad.ptr;
         ldf = ldp_bytes / (int64_t)sizeof(VT);
     }
     // byte offsets into the factor matrices fit 32 bits when both are below 4 GB
@@ -382,7 +368,7 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
 #define SPMI_MTTKRP(V, OT)                                                                                                             \
     hipLaunchKernelGGL((mttkrp_runs_kernel<PT, CT, VT, V, OT>), dim3(gx, (unsigned)ceil_div(pieces, lr_tile)), dim3(kThreads), 0, st, pos1, crd0, \
                        crd1, pos2, crd2, (const VT *)B->values, wfib, wslc, nwin, nfib, nslc, nnz, M, ldm, X, ldx, A, lda,              \
-                       (VT *)B->mttkrp_carry, J, lr_tile, accumulate)
+                       carry, J, lr_tile, accumulate)
 #define SPMI_MTTKRP_V(V)                            \
     do {                                            \
         if (small) SPMI_MTTKRP(V, uint32_t);        \
@@ -400,10 +386,10 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
         // six windows: 46 us with sixteen, 20 with four)
         if (nwin > 32 * ncross)
             hipLaunchKernelGGL((mttkrp_fixup_kernel<CT, VT, 1024>), dim3((unsigned)ncross), dim3(1024), 0, st, crd0, wslc, cross, nwin, J,
-                               (const VT *)B->mttkrp_carry, A, lda);
+                               (const VT *)carry, A, lda);
         else
             hipLaunchKernelGGL((mttkrp_fixup_kernel<CT, VT, 256>), dim3((unsigned)ncross), dim3(256), 0, st, crd0, wslc, cross, nwin, J,
-                               (const VT *)B->mttkrp_carry, A, lda);
+                               (const VT *)carry, A, lda);
         SP_HIP(hipGetLastError());
     }
     return SP_OK;

@@ -901,6 +901,50 @@ sp_status spmi_build_bins(const sp_tensor *A, hipStream_t st)
     return status;
 }
 
+bool spmi_recording(hipStream_t st, unsigned long long *graph)
+{
+    if (graph) *graph = 0;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) {
+        if (status == hipStreamCaptureStatusNone) return false;
+        if (graph && hipStreamGetCaptureInfo(st, &status, graph) == hipSuccess) return true;
+    }
+    (void)hipGetLastError();
+    if (graph) *graph = 0;
+    return true;
+}
+
+bool spmi_idle(hipStream_t st)
+{
+    if (spmi_recording(st)) return false;
+    // relaxed: the question must not end a recording that another stream has running
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return false; }
+    const bool done = hipStreamQuery(st) == hipSuccess;
+    if (!done) (void)hipGetLastError();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return done;
+}
+
+sp_status spmi_reserve(const sp_tensor *t, sp_kept &k, size_t need, hipStream_t st)
+{
+    if (k.bytes >= need) return SP_OK;
+    sp_mem mem{t->alloc, t->free_, t->ctx};
+    if (k.ptr && k.shared) {
+        if (!t->outgrown) t->outgrown = new std::vector<void *>();
+        t->outgrown->push_back(k.ptr);
+        t->outgrown_bytes += k.bytes;
+    } else if (k.ptr) {
+        SP_HIP(hipStreamSynchronize(st));
+        mem.put(k.ptr);
+    }
+    k = sp_kept{};
+    k.ptr = mem.get((need + 255) & ~(size_t)255);
+    if (!k.ptr) return SP_ERR_ALLOC;
+    k.bytes = need;
+    return SP_OK;
+}
+
 static void release_tensor_arrays(sp_tensor *t)
 {
     sp_mem mem{t->alloc, t->free_, t->ctx};
@@ -912,11 +956,16 @@ static void release_tensor_arrays(sp_tensor *t)
     mem.put(t->rowblocks.start); t->rowblocks.start = nullptr;
     mem.put(t->rowblocks.carry); t->rowblocks.carry = nullptr;
     mem.put(t->dense_partial); t->dense_partial = nullptr; t->dense_partial_bytes = 0;
-    mem.put(t->spmm_carry); t->spmm_carry = nullptr; t->spmm_carry_bytes = 0;
-    mem.put(t->sddmm_bt); t->sddmm_bt = nullptr; t->sddmm_bt_bytes = 0;
+    for (sp_kept *k : {&t->spmm_carry.mem, &t->sddmm_bt, &t->mttkrp_carry, &t->mttkrp_pad[0], &t->mttkrp_pad[1]}) {
+        mem.put(k->ptr);
+        *k = sp_kept{};
+    }
+    if (t->outgrown) {
+        for (void *p : *t->outgrown) mem.put(p);
+        delete t->outgrown;
+        t->outgrown = nullptr;
+    }
     mem.put(t->mttkrp_windows); t->mttkrp_windows = nullptr;
-    mem.put(t->mttkrp_carry); t->mttkrp_carry = nullptr; t->mttkrp_carry_bytes = 0;
-    for (int w = 0; w < 2; ++w) { mem.put(t->mttkrp_pad[w]); t->mttkrp_pad[w] = nullptr; t->mttkrp_pad_bytes[w] = 0; }
     mem.put(t->nz_rowid); mem.put(t->nz_pos); mem.put(t->nz_rowblocks.start); mem.put(t->nz_rowblocks.carry);
     t->nz_rowid = t->nz_pos = t->nz_rowblocks.start = t->nz_rowblocks.carry = nullptr;
 }

@@ -57,6 +57,29 @@ struct sp_bins {
 };
 
 
+// Scratch that a handle keeps between products and makes larger on demand (spmi_reserve).
+struct sp_kept {
+    void *ptr;                        // DEVICE
+    size_t bytes;
+    bool shared;                      // something besides the calling stream may still use it: see spmi_reserve
+};
+
+// The per-block carries of the SpMM cut by stored entries: one block of scratch in three parts, each with room for `columns`
+// values (part 0: for as many of them as its products have) per block.
+//   0  products that have no other kernel of their speed (rows of 16-byte pieces): shared by all streams, the caller keeps
+//      products of one tensor on different streams apart
+//   1  products of any other width, which a kernel without scratch can do as well: used by one stream at a time, so that
+//      such products may overlap on different streams
+//   2  the same, recorded into one graph from one stream: its replays may overlap with anything else
+struct sp_spmm_carry {
+    sp_kept mem;
+    int64_t columns;
+    size_t offset[3];
+    hipStream_t user[2];              // the stream that uses part 1 / part 2
+    bool used[2];
+    unsigned long long graph;         // the recording that uses part 2
+};
+
 struct sp_tensor {
     sp_encoding enc;
     int dtype;
@@ -87,17 +110,15 @@ struct sp_tensor {
     mutable sp_segments *segments;           // owned, built on first use
     mutable sp_bins *bins;                   // owned, built on first use
     mutable double scatter;                  // share of stored entries whose successor lies in another 128-byte line of x; < 0: not measured yet
-    mutable void *dense_partial;             // DEVICE scratch of the dense-row SpMV (per-chunk partial sums), grown on demand
+    mutable void *dense_partial;             // DEVICE scratch of the dense-row SpMV (per-chunk partial sums)
     mutable size_t dense_partial_bytes;
-    mutable void *spmm_carry;                // DEVICE scratch of the SpMM cut by entries (N values per block), grown on demand
-    mutable size_t spmm_carry_bytes;
-    mutable void *sddmm_bt;                  // DEVICE scratch of the SDDMM: the transposed dense operand (n x K), grown on demand
-    mutable size_t sddmm_bt_bytes;
+    mutable sp_spmm_carry spmm_carry;
+    mutable sp_kept sddmm_bt;                // scratch of the SDDMM: the transposed dense operand (n x K)
     mutable void *mttkrp_windows;            // DEVICE int32[2 * windows]: fibre and slice holding the first entry of each window (rank 3)
-    mutable void *mttkrp_carry;              // DEVICE scratch of the MTTKRP (J values per window), grown on demand
-    mutable size_t mttkrp_carry_bytes;
-    mutable void *mttkrp_pad[2];             // DEVICE scratch of the MTTKRP: inner / mid factor matrix with rows padded to whole cache lines
-    mutable size_t mttkrp_pad_bytes[2];
+    mutable sp_kept mttkrp_carry;            // scratch of the MTTKRP (J values per window)
+    mutable sp_kept mttkrp_pad[2];           // scratch of the MTTKRP: inner / mid factor matrix with rows padded to whole cache lines
+    mutable std::vector<void *> *outgrown;   // scratch that was outgrown while it was shared, owned
+    mutable size_t outgrown_bytes;
     mutable int tables_pending;              // rowblocks / non-empty rows not built yet (a result of sp_spgemm): built on first use by a product
     mutable int plan_spmv;                   // SpMV kernel a product with one column runs (1..4); 0 = not decided yet (sp_prepare or the first product decides)
     mutable int lazy_prepares;               // how many products had to build, allocate or decide something first (none after sp_prepare)
@@ -146,6 +167,16 @@ struct sp_mem {
     void *get(size_t bytes) const;
     void put(void *p) const;
 };
+
+// Is work on this stream being recorded instead of run?  (An error counts as yes: what may not be asked now may not allocate
+// either.)  graph (may be null): the number of the recording, 0 when it is not known.
+bool spmi_recording(hipStream_t st, unsigned long long *graph = nullptr);
+// Has everything enqueued on this stream been done?  (No while it is being recorded.)
+bool spmi_idle(hipStream_t st);
+// Room for `need` bytes in scratch the handle keeps; the contents do not survive.  A block that becomes too small is given back
+// once `st` has done its work, unless it is shared: a graph recorded with it, or another stream, may use it at any time, so it
+// stays with the handle (t->outgrown) until sp_tensor_free.
+sp_status spmi_reserve(const sp_tensor *t, sp_kept &k, size_t need, hipStream_t st);
 
 // A scope that frees its temporaries on exit.
 struct sp_scratch {
