@@ -432,29 +432,37 @@ __global__ __launch_bounds__(kThreads) void spmm_rows_vec_kernel(const PT *__res
 // of 1024 stored entries as above (blockIdx.y: a tile of lr_tile * V columns).  A group of LR lanes covers a row of B, V
 // elements per lane, and takes a run of consecutive entries, whatever rows they belong to: it adds up while the row stays the
 // same and writes C when it changes, so rows of any length keep every lane busy.  The sum of a row that began in an earlier
-// run of the window waits in LDS for the group that began it, which adds such sums in order; the part of a row that began in
+// run of the window waits in LDS for the group that began it; the part of a row that began in
 // an earlier window goes to carry[w].  Fixed order, no atomics.
+// Runs are long (up to 256 entries), so a group adds up four entries at a time and these sums in spmi_long_sum: against a plain
+// chain the error falls from 1.07e-7 to 5.5e-8 (rows of 64 entries, 32 f32 columns; 6.8e-8 with the wave per row) and from 2.4e-16 to
+// 9.7e-17 (lognormal rows, 64 f64 columns; 1.6e-16), relative 2-norm; it costs 1 % (33.6 M entries, 32 f32 columns).
 // The last lane of a row moves back to the last V columns and stores only those that the lane before it does not have, so
 // every load is V elements wide (the memory path takes such loads at any element-aligned address).
 // Bound by the rows of B it gathers (16.9 M random 512-byte rows alone: 1.15 ms).  Measured before (a wave per row of the
 // window with shuffles at the end of every row; a wave per row and a column per lane for widths that are no multiple of 16
 // bytes) and now: 16.9 M entries, 64 f64 columns 1.329 -> 1.280 ms; 33.6 M entries with short rows, 32 f32 columns 561 -> 363 us
 // (417 with the groups' entries kept at an even stride);
-// 5.0 M entries, 64-bit pos / crd, 33 f64 columns 1.250 -> 0.276 ms; 4 M entries, 4 per row, 2 f64 columns 303 -> 75 us.
-template <typename PT, typename CT, typename VT, int V, typename OT>
-__global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd, const VT *__restrict__ val,
+// 5.0 M entries, 64-bit pos / crd, 33 f64 columns 1.250 -> 0.276 ms; 4 M entries, 4 per row, 2 f64 columns 303 -> 74 us.
+// kNarrow: runs of a few entries (one or two lanes per row of B).  Most of a sum's additions are then those of the groups' parts,
+// which keep what they round off as well.
+template <typename PT, typename CT, typename VT, int V, typename OT, bool kNarrow>
+__global__ __launch_bounds__(kThreads, !kNarrow && sizeof(VT) + sizeof(OT) + sizeof(CT) <= 12 ? 8 : 4) void spmm_runs_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd, const VT *__restrict__ val,
                                                              const CT *__restrict__ rowid, const int32_t *__restrict__ rowblk, int64_t nrows,
                                                              int64_t nnz, const VT *__restrict__ B, int64_t N, int64_t ldb, int lr_tile,
                                                              VT *__restrict__ C, int64_t ldc, VT *__restrict__ carry, int accumulate)
 {
     constexpr int T = (int)kStreamT, U = 4, kWaves = kThreads / 64;
+    static_assert(T == 1024, "by_run, kRoom and the 16-byte vectors in s_val and s_row");
     typedef VT vec_t __attribute__((ext_vector_type(V)));
     typedef VT mem_vec_t __attribute__((ext_vector_type(V), aligned(sizeof(VT))));
     constexpr int kRoom = T + kThreads;                              // run length (rounded up) * odd stride: 256 * 5 at most
     __shared__ OT s_off[kRoom];
-    __shared__ VT s_val[kRoom];
-    __shared__ CT s_row[kRoom];
-    __shared__ vec_t s_part[kThreads];
+    __shared__ __align__(16) VT s_val[kRoom];
+    __shared__ __align__(16) CT s_row[kRoom];
+    __shared__ vec_t s_part[kThreads];                               // sums of rows that began before a group's run ...
+    vec_t *s_lo = (vec_t *)s_val;                                    // ... and what they round off, once the values are used up
+    static_assert(sizeof(vec_t) * kThreads <= sizeof(s_val) && sizeof(vec_t) * kThreads <= sizeof(s_row), "room for a vector per thread");
     __shared__ int s_wave[kWaves];
     const int64_t j0 = (int64_t)blockIdx.y * lr_tile * V;
     const int64_t width = N - j0 < (int64_t)lr_tile * V ? N - j0 : (int64_t)lr_tile * V;
@@ -465,7 +473,10 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
     // entry i of the window is kept at (i % run) * P + i / run: the groups of a wave read neighbouring words, and with an odd P
     // neighbouring entries lie on different banks when they are put there
     const int P = G | 1;
-    auto at = [=](int i) { const int g = (int)(((uint32_t)i * by_run) >> 22); return (i - g * run) * P + g; };
+    auto at = [=](int i) {
+        const int g = (int)(__umul24((uint32_t)i, by_run) >> 22);
+        return (int)__umul24((uint32_t)(i - (int)__umul24((uint32_t)g, (uint32_t)run)), (uint32_t)P) + g;
+    };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t s = (int64_t)blockIdx.x * T;
     const int64_t e = s + T < nnz ? s + T : nnz;
@@ -483,8 +494,7 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
     const int64_t lo = rowblk[blockIdx.x], hi = rowblk[blockIdx.x + 1];
     const int64_t last = hi < nrows ? hi : nrows - 1;
     const bool continued = (int64_t)pos[lo] < s;                     // the first row began in an earlier window
-    spmi_rows_of_entries<kThreads, T / kThreads>([=](int64_t r) { return (int64_t)pos[r]; }, rowid, lo, last, s, e, s_row, s_wave, at);
-    if (!accumulate && !rowid)                                       // rows without entries: zero (with a row list C was cleared before)
+    if (!accumulate && !rowid && last > lo)                          // rows without entries: zero (with a row list C was cleared before)
         for (int64_t r0 = lo + wave * 64; r0 <= last; r0 += kThreads) {
             const int64_t r = r0 + lane;
             uint64_t empty = __ballot(r <= last && r != hi && pos[r <= last ? r : last] == pos[(r <= last ? r : last) + 1]);
@@ -513,53 +523,87 @@ __global__ __launch_bounds__(kThreads) void spmm_runs_kernel(const PT *__restric
         }
     };
     const int slot = group * LR + jl;                                // this lane's place in s_part
-    vec_t acc = (vec_t)(0);
+    spmi_long_sum<VT, V> sum;                                        // of the row so far
+    vec_t acc = (vec_t)(0), head_lo = (vec_t)(0);                    // acc: up to U entries more of it
+    sum.clear();
+    spmi_rows_of_entries<kThreads, T / kThreads>([=](int64_t r) { return (int64_t)pos[r]; }, rowid, lo, last, s, e, s_row, s_wave, at);
+    auto keep_head = [&]() {
+        if (!kNarrow) { s_part[slot] = sum.value(acc); return; }
+        const spmi_pair<VT, V> done = sum.pair(acc);
+        s_part[slot] = done.half(0);
+        head_lo = done.half(1);
+    };
     CT row = 0;
     bool head = false;                                               // the row being added up began before this run
     if (first < end) {
         row = s_row[group];
         head = group == 0 ? continued : s_row[(run - 1) * P + group - 1] == row;
     }
-    for (int k = 0; k < end - first; k += U) {
+    const int mine = end - first, last_w = (mine - 1) * P + group;   // entries of this run, where the last one is kept
+    for (int k = 0; k < mine; k += U) {
         VT v[U];
         vec_t bv[U];
         CT rw[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int w = (first + k + u < end ? k + u : end - first - 1) * P + group;
+            const int next = (k + u) * P + group, w = next < last_w ? next : last_w;
             rw[u] = s_row[w];
             v[u] = s_val[w];
             bv[u] = *(const mem_vec_t *)(Bb + (s_off[w] + colb));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (first + k + u < end) {
+            if (k + u < mine) {
                 if (rw[u] != row) {
-                    if (head) s_part[slot] = acc;
-                    else store(C + (int64_t)row * ldc + col, acc, accumulate);
+                    if (head) keep_head();
+                    else store(C + (int64_t)row * ldc + col, sum.value(acc), accumulate);
                     head = false;
                     row = rw[u];
                     acc = (vec_t)(0);
+                    sum.clear();
                 }
                 acc += v[u] * bv[u];
             }
         }
+        if (k + U < mine) {
+            sum.add(acc);
+            acc = (vec_t)(0);
+        }
     }
-    if (head) s_part[slot] = acc;                                    // the whole run belongs to a row that began before it
+    if (head) keep_head();                                           // the whole run belongs to a row that began before it
     // The sums of a row that fills whole runs are added up towards the first of them, over twice as many groups each step.
     const int full = (ne + run - 1) / run;                           // groups that took something
-    if (__syncthreads_or(head))
+    const bool whole_runs = __syncthreads_or(head);
+    if (kNarrow) {                                                   // the values of the window have been read
+        if (group < G) s_lo[slot] = head_lo;
+        __syncthreads();
+    }
+    auto part_of = [&](int at_slot) { return spmi_pair<VT, V>::from(s_part[at_slot], s_lo[at_slot]); };      // kNarrow
+    if (whole_runs)
         for (int d = 1; d < full; d <<= 1) {
             const bool take = group + d < full && s_row[group + d] == s_row[group];      // rows ascend: everything between is that row's too
-            const vec_t other = take ? s_part[slot + d * LR] : (vec_t)(0);
+            const vec_t other = take ? s_part[slot + d * LR] : (vec_t)(0), other_lo = take && kNarrow ? s_lo[slot + d * LR] : (vec_t)(0);
             __syncthreads();
-            if (take) s_part[slot] += other;
+            if (take && kNarrow) {
+                spmi_pair<VT, V> part = part_of(slot);
+                part.add(spmi_pair<VT, V>::from(other, other_lo));
+                s_part[slot] = part.half(0);
+                s_lo[slot] = part.half(1);
+            } else if (take) s_part[slot] += other;
             __syncthreads();
         }
     if (first >= end) return;
-    if (group == 0 && continued) store(carry + (int64_t)blockIdx.x * N + col, s_part[slot], false);
+    if (group == 0 && continued) store(carry + (int64_t)blockIdx.x * N + col, kNarrow ? part_of(slot).value() : s_part[slot], false);
     if (!head) {
-        if (group + 1 < full && s_row[group + 1] == row) acc += s_part[slot + LR];
+        const bool more = group + 1 < full && s_row[group + 1] == row;
+        if (kNarrow) {
+            spmi_pair<VT, V> all = sum.pair(acc);
+            if (more) all.add(part_of(slot + LR));
+            acc = all.value();
+        } else {
+            acc = sum.value(acc);
+            if (more) acc += s_part[slot + LR];
+        }
         store(C + (int64_t)row * ldc + col, acc, accumulate);
     }
 }
@@ -770,13 +814,13 @@ sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, co
     const sp_rowblocks *rowblocks = rv.rowblocks;
     const int64_t nb = rowblocks->nblocks;
     const bool small = sizeof(CT) == 4 && (uint64_t)A->shape[1] * (uint64_t)ldb * sizeof(VT) < ((uint64_t)1 << 32);     // 32-bit byte offsets into B (64-bit coordinates keep 64-bit offsets)
-#define SPMI_SPMM_RUNS_O(VV, OT)                                                                                              \
-    hipLaunchKernelGGL((spmm_runs_kernel<PT, CT, VT, VV, OT>), dim3((unsigned)nb, (unsigned)ceil_div(ceil_div(N, VV), lr_tile)), dim3(kThreads), 0, \
+#define SPMI_SPMM_RUNS_O(VV, OT, NARROW)                                                                                      \
+    hipLaunchKernelGGL((spmm_runs_kernel<PT, CT, VT, VV, OT, NARROW>), dim3((unsigned)nb, (unsigned)ceil_div(ceil_div(N, VV), lr_tile)), dim3(kThreads), 0, \
                        st, pos, crd, val, rowid, (const int32_t *)rowblocks->start, nrows, nnz, B, N, ldb, lr_tile, C, ldc, carry, accumulate)
-#define SPMI_SPMM_RUNS(VV)                          \
-    do {                                            \
-        if (small) SPMI_SPMM_RUNS_O(VV, uint32_t);  \
-        else SPMI_SPMM_RUNS_O(VV, uint64_t);        \
+#define SPMI_SPMM_RUNS(VV, NARROW)                          \
+    do {                                                    \
+        if (small) SPMI_SPMM_RUNS_O(VV, uint32_t, NARROW);  \
+        else SPMI_SPMM_RUNS_O(VV, uint64_t, NARROW);        \
     } while (0)
     const int VV = N >= V ? V : 2;                // two or three columns in f32: loads of two
     const int64_t pieces = ceil_div(N, VV);
@@ -784,12 +828,11 @@ sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, co
     const int64_t split = nb < 512 ? ceil_div(512, nb) : 1;
     const int64_t wanted = ceil_div(pieces, split) > 4 ? ceil_div(pieces, split) : 4;
     const int lr_tile = (int)(wanted < 64 ? wanted : 64);
-    if (VV == V) SPMI_SPMM_RUNS(V);
-    else SPMI_SPMM_RUNS(2);
+    if (VV == V && pieces <= 2) SPMI_SPMM_RUNS(V, true);
+    else if (VV == V) SPMI_SPMM_RUNS(V, false);
+    else SPMI_SPMM_RUNS(2, true);                 // f32 only
 #undef SPMI_SPMM_RUNS
 #undef SPMI_SPMM_RUNS_O
-#undef SPMI_SPMM_WIN
-#undef SPMI_SPMM_WIN_O
     SP_HIP(hipGetLastError());
     if (nb > 1) {
         hipLaunchKernelGGL((spmm_windows_fixup_kernel<PT, CT, VT>), dim3(grid_for(nb - 1, kThreads / 64)), dim3(kThreads), 0, st, pos,

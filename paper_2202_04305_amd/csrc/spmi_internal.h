@@ -268,6 +268,107 @@ __device__ __forceinline__ void spmi_rows_of_entries(POS pos, const CT *__restri
     __syncthreads();
 }
 
+// Sums whose rounding error hardly grows with the number of terms.  f64: held as hi + lo, hi rounded and lo collecting what the
+// additions to hi round off (Knuth's two-sum, exact for any two numbers); an infinity stays one, although lo is not a number
+// then.  f32: held in f64.  half(i) / from(): the two vectors that a sum takes in memory.
+template <typename VT, int V>
+struct spmi_pair {
+    typedef VT vec_t __attribute__((ext_vector_type(V)));
+    vec_t hi, lo;
+    __device__ __forceinline__ vec_t half(int i) const { return i ? lo : hi; }
+    static __device__ __forceinline__ spmi_pair from(vec_t a, vec_t b) { spmi_pair p; p.hi = a; p.lo = b; return p; }
+    __device__ __forceinline__ void add(const spmi_pair &o)
+    {
+        const vec_t s = hi + o.hi, b = s - hi;
+        lo += o.lo + ((hi - (s - b)) + (o.hi - b));
+        hi = s;
+    }
+    __device__ __forceinline__ vec_t value() const
+    {
+        vec_t r = hi + lo;
+#pragma unroll
+        for (int c = 0; c < V; ++c) r[c] = r[c] == r[c] ? r[c] : hi[c];
+        return r;
+    }
+};
+template <int V>
+struct spmi_pair<float, V> {
+    typedef float vec_t __attribute__((ext_vector_type(V)));
+    typedef double sum_t __attribute__((ext_vector_type(V)));
+    sum_t sum;
+    __device__ __forceinline__ vec_t half(int i) const
+    {
+        vec_t h[2];
+        __builtin_memcpy(h, &sum, sizeof(sum));
+        return h[i];
+    }
+    static __device__ __forceinline__ spmi_pair from(vec_t a, vec_t b)
+    {
+        const vec_t h[2] = {a, b};
+        spmi_pair p;
+        __builtin_memcpy(&p.sum, h, sizeof(p.sum));
+        return p;
+    }
+    __device__ __forceinline__ void add(const spmi_pair &o) { sum += o.sum; }
+    __device__ __forceinline__ vec_t value() const
+    {
+        vec_t r;
+#pragma unroll
+        for (int c = 0; c < V; ++c) r[c] = (float)sum[c];
+        return r;
+    }
+};
+// One lane's long sum, which gets a few terms at a time, added up in VT before.  value(t), pair(t): with the last of them.
+// f64: with a cheaper addition that is exact where hi is the larger one (Dekker's; only the first few terms are not smaller).
+template <typename VT, int V>
+struct spmi_long_sum {
+    typedef typename spmi_pair<VT, V>::vec_t vec_t;
+    spmi_pair<VT, V> p;
+    __device__ __forceinline__ void clear() { p.hi = (vec_t)(0); p.lo = (vec_t)(0); }
+    __device__ __forceinline__ void add(vec_t t)
+    {
+        const vec_t s = p.hi + t;
+        p.lo += t - (s - p.hi);
+        p.hi = s;
+    }
+    __device__ __forceinline__ vec_t value(vec_t t) const
+    {
+        vec_t r = p.hi + (p.lo + t);
+#pragma unroll
+        for (int c = 0; c < V; ++c) r[c] = r[c] == r[c] ? r[c] : p.hi[c] + t[c];
+        return r;
+    }
+    __device__ __forceinline__ spmi_pair<VT, V> pair(vec_t t) const
+    {
+        spmi_pair<VT, V> q = p;
+        q.add(spmi_pair<VT, V>::from(t, (vec_t)(0)));
+        return q;
+    }
+};
+template <int V>
+struct spmi_long_sum<float, V> {
+    typedef typename spmi_pair<float, V>::vec_t vec_t;
+    spmi_pair<float, V> p;
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int c = 0; c < V; ++c) p.sum[c] = 0;
+    }
+    __device__ __forceinline__ void add(vec_t t)
+    {
+#pragma unroll
+        for (int c = 0; c < V; ++c) p.sum[c] += (double)t[c];
+    }
+    __device__ __forceinline__ spmi_pair<float, V> pair(vec_t t) const
+    {
+        spmi_pair<float, V> q = p;
+#pragma unroll
+        for (int c = 0; c < V; ++c) q.sum[c] += (double)t[c];
+        return q;
+    }
+    __device__ __forceinline__ vec_t value(vec_t t) const { return pair(t).value(); }
+};
+
 // Division of a key by a level's stride or size, which the host knows when it launches: a shift when the divisor is a
 // power of two, a multiplication by the reciprocal in double plus a one-step correction while the dividend is below
 // 2^52 (the estimate is then within one of the quotient), the hardware's 64-bit division otherwise.

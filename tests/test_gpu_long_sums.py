@@ -1,0 +1,63 @@
+"""Long sums lose no more than their first few terms: one large term and many that a sum as large as it rounds away.
+
+The large term is 1, the others 0.45 of the last place of 1, so a plain chain of n terms is off by 0.9 n u (u: half of that last
+place, the unit roundoff).  Bounds count the roundings a term can pass through: each is at most u times the sum so far."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2202_04305_amd as sp
+from gen import prng
+from gpu_util import say, dev, gpu_pack, DEV
+
+pytestmark = pytest.mark.gpu
+
+
+def unit(dtype):
+    return float(np.finfo(dtype).eps) / 2
+
+
+def rows_with_one_large_entry(dtype, long_rows, length, short_rows):
+    """rows, cols, values, and every row's exact sum (in long double): long rows among short ones, so that neither is even."""
+    lens = np.full(long_rows + short_rows, 3, dtype=np.int64)
+    lens[prng.permutation(3, 1, lens.size)[:long_rows]] = length
+    rows = np.repeat(np.arange(lens.size, dtype=np.int64), lens)
+    first = np.cumsum(lens) - lens
+    cols = np.arange(rows.size, dtype=np.int64) - np.repeat(first, lens)
+    vals = np.full(rows.size, 0.9 * unit(dtype), dtype=dtype)
+    vals[first] = 1
+    exact = 1 + (lens - 1).astype(np.longdouble) * np.longdouble(vals[1])
+    return rows, cols, vals, lens, exact
+
+
+def worst(got, exact, dtype):
+    """largest error of any element, in units of u times the row's sum of magnitudes"""
+    err = np.abs(got.cpu().numpy().astype(np.longdouble) - exact.reshape(-1, 1))
+    return float((err / exact.reshape(-1, 1)).max() / unit(dtype))
+
+
+@pytest.mark.parametrize("lt", [(0, 1), (1, 1)])
+@pytest.mark.parametrize("dtype,N", [(np.float64, n) for n in (2, 8, 33, 64, 128)] + [(np.float32, n) for n in (3, 8, 32, 65, 256)])
+def test_spmm(lt, dtype, N):
+    """More than 512 windows, so that a row of B gets all the lanes it needs and a group up to 256 entries.
+    Four entries in a chain, the long sum's rounding, up to eight levels among the groups of a window, one more for a window that
+    the row crosses: 14."""
+    rows, cols, vals, lens, exact = rows_with_one_large_entry(dtype, 450, 1000, 40000)
+    A = gpu_pack(lt, (0, 1), (lens.size, 1000), [rows, cols], vals)
+    B = torch.ones((1000, N), dtype=A.dtype, device=DEV)
+    C = torch.full((lens.size, N), float("nan"), dtype=A.dtype, device=DEV)
+    sp.sp_matmul(A, B, C)
+    say("case spmm long sums", lt, dtype.__name__, N, "worst", worst(C, exact, dtype))
+    assert worst(C, exact, dtype) <= 14
+
+
+@pytest.mark.parametrize("dtype,N", [(np.float64, 8), (np.float64, 33), (np.float32, 32), (np.float32, 3)])
+def test_spmm_keeps_infinities_and_nan(dtype, N):
+    """An infinite product gives an infinite sum whatever is added after it; a NaN gives NaN; neither reaches another row or column."""
+    rows, cols, vals, lens, _ = rows_with_one_large_entry(dtype, 20, 700, 2000)
+    A = gpu_pack((0, 1), (0, 1), (lens.size, 700), [rows, cols], vals)
+    B = np.ones((700, N), dtype=dtype)
+    B[5, 0], B[9, N - 1] = np.inf, np.nan
+    C = sp.sp_matmul(A, dev(B), torch.empty((lens.size, N), dtype=A.dtype, device=DEV)).cpu().numpy()
+    assert np.all(np.isposinf(C[lens > 5, 0])) and np.all(np.isnan(C[lens > 9, N - 1]))
+    assert np.all(np.isfinite(C[:, 1:N - 1])) and np.all(np.isfinite(C[lens <= 5]))
