@@ -11,6 +11,7 @@
 //                    fix-up kernel from per-block carries (deterministic, no atomics).
 //   runs kernel      SpMM: groups of lanes across the columns of B take runs of consecutive stored entries (windows, carries
 //                    and fix-up as above).
+//   windows kernel   SpMM: the same windows, a wave per row inside them: even rows of medium length.
 //   spmm kernels     one wave per stored row, lanes across the columns of B: small products, and where no scratch can be had.
 //   scatter kernel   column-major storage (CSC / DCSC): a wave per stored column, atomic
 //                    adds into the rows of C.
@@ -433,9 +434,9 @@ __global__ __launch_bounds__(kThreads) void spmm_rows_vec_kernel(const PT *__res
 // elements per lane, and takes a run of consecutive entries, whatever rows they belong to: it adds up while the row stays the
 // same and writes C when it changes, so rows of any length keep every lane busy.  The sum of a row that began in an earlier
 // run of the window waits in LDS for the group that began it; the part of a row that began in
-// an earlier window goes to carry[w].  Fixed order, no atomics.
+// an earlier window goes to carry[w].  Fixed order, no atomics.  A window that lies inside one row is dealt out entry by entry.
 // Runs are long (up to 256 entries), so a group adds up four entries at a time and these sums in spmi_long_sum: against a plain
-// chain the error falls from 1.07e-7 to 5.5e-8 (rows of 64 entries, 32 f32 columns; 6.8e-8 with the wave per row) and from 2.4e-16 to
+// chain the error falls from 1.07e-7 to 5.5e-8 (rows of 64 entries, 32 f32 columns; 6.8e-8 with a wave per row) and from 2.4e-16 to
 // 9.7e-17 (lognormal rows, 64 f64 columns; 1.6e-16), relative 2-norm; it costs 1 % (33.6 M entries, 32 f32 columns).
 // The last lane of a row moves back to the last V columns and stores only those that the lane before it does not have, so
 // every load is V elements wide (the memory path takes such loads at any element-aligned address).
@@ -443,7 +444,8 @@ __global__ __launch_bounds__(kThreads) void spmm_rows_vec_kernel(const PT *__res
 // window with shuffles at the end of every row; a wave per row and a column per lane for widths that are no multiple of 16
 // bytes) and now: 16.9 M entries, 64 f64 columns 1.329 -> 1.280 ms; 33.6 M entries with short rows, 32 f32 columns 561 -> 363 us
 // (417 with the groups' entries kept at an even stride);
-// 5.0 M entries, 64-bit pos / crd, 33 f64 columns 1.250 -> 0.276 ms; 4 M entries, 4 per row, 2 f64 columns 303 -> 74 us.
+// 5.0 M entries, 64-bit pos / crd, 33 f64 columns 1.250 -> 0.276 ms; 4 M entries, 4 per row, 2 f64 columns 303 -> 74 us;
+// 6 M entries in rows of 20,000, 12 f32 columns 39 us (48 without the windows inside one row).
 // kNarrow: runs of a few entries (one or two lanes per row of B).  Most of a sum's additions are then those of the groups' parts,
 // which keep what they round off as well.
 template <typename PT, typename CT, typename VT, int V, typename OT, bool kNarrow>
@@ -494,6 +496,7 @@ __global__ __launch_bounds__(kThreads, !kNarrow && sizeof(VT) + sizeof(OT) + siz
     const int64_t lo = rowblk[blockIdx.x], hi = rowblk[blockIdx.x + 1];
     const int64_t last = hi < nrows ? hi : nrows - 1;
     const bool continued = (int64_t)pos[lo] < s;                     // the first row began in an earlier window
+    const bool one_row = (int64_t)pos[lo + 1] >= e;                  // and holds the whole window
     if (!accumulate && !rowid && last > lo)                          // rows without entries: zero (with a row list C was cleared before)
         for (int64_t r0 = lo + wave * 64; r0 <= last; r0 += kThreads) {
             const int64_t r = r0 + lane;
@@ -526,6 +529,40 @@ __global__ __launch_bounds__(kThreads, !kNarrow && sizeof(VT) + sizeof(OT) + siz
     spmi_long_sum<VT, V> sum;                                        // of the row so far
     vec_t acc = (vec_t)(0), head_lo = (vec_t)(0);                    // acc: up to U entries more of it
     sum.clear();
+    if (one_row) {
+        // No rows to tell apart: the groups take the entries in turn, so that neighbouring columns are asked for together.
+        __syncthreads();
+        for (int k = group < G ? group : ne; k < ne; k += U * G) {
+            VT v[U];
+            vec_t bv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int w = at(k + u * G < ne ? k + u * G : k);
+                v[u] = s_val[w];
+                bv[u] = *(const mem_vec_t *)(Bb + (s_off[w] + colb));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k + u * G < ne) acc += v[u] * bv[u];
+            sum.add(acc);
+            acc = (vec_t)(0);
+        }
+        vec_t part = sum.value(acc);
+        for (int d = 1; d < S; d <<= 1) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                const VT other = __shfl(part[c], lane + d * LR < 64 ? lane + d * LR : lane, 64);
+                part[c] += sl + d < S ? other : (VT)0;
+            }
+        }
+        if (sl == 0) s_part[slot] = part;
+        __syncthreads();
+        if (group != 0) return;
+        for (int g = S; g < G; g += S) part += s_part[g * LR + jl];
+        if (continued) store(carry + (int64_t)blockIdx.x * N + col, part, false);
+        else store(C + (rowid ? (int64_t)rowid[lo] : lo) * ldc + col, part, accumulate);
+        return;
+    }
     spmi_rows_of_entries<kThreads, T / kThreads>([=](int64_t r) { return (int64_t)pos[r]; }, rowid, lo, last, s, e, s_row, s_wave, at);
     auto keep_head = [&]() {
         if (!kNarrow) { s_part[slot] = sum.value(acc); return; }
@@ -605,6 +642,82 @@ __global__ __launch_bounds__(kThreads, !kNarrow && sizeof(VT) + sizeof(OT) + siz
             if (more) acc += s_part[slot + LR];
         }
         store(C + (int64_t)row * ldc + col, acc, accumulate);
+    }
+}
+
+// The same product with a wave per row of the window, for even rows of medium length (see spmm_windows_launch): block w owns
+// the entries [w*T, (w+1)*T), its four waves take the rows that meet the window in turn, LR lanes (a power of two) across a row of
+// B and 64 / LR entries side by side, their sums meet in a shuffle tree.  No rows to tell apart inside a run and neighbouring
+// entries asked for together; but a wave with a long row keeps the block.
+// The window's values and, instead of its coordinates, the byte offsets of the rows of B that they select (OT: 32 bits
+// when B is below 4 GB) are first copied into LDS with coalesced loads: the loop over the entries then works on small
+// window-relative integers and every gather address is a wave-uniform base plus a lane offset.
+template <typename PT, typename CT, typename VT, int LR, typename OT>
+__global__ __launch_bounds__(kThreads) void spmm_windows_vec_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd,
+                                                                    const VT *__restrict__ val, const CT *__restrict__ rowid,
+                                                                    const int32_t *__restrict__ rowblk, int64_t nrows, int64_t nnz,
+                                                                    const VT *__restrict__ B, int64_t ldb, VT *__restrict__ C, int64_t ldc,
+                                                                    VT *__restrict__ carry, int accumulate)
+{
+    constexpr int V = 16 / sizeof(VT), S = 64 / LR, U = S >= 4 ? 2 : 4;
+    typedef VT vec_t __attribute__((ext_vector_type(V)));
+    __shared__ OT s_off[kStreamT];
+    __shared__ VT s_val[kStreamT];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int jl = lane % LR, sl = lane / LR;
+    const int64_t s = (int64_t)blockIdx.x * kStreamT;
+    const int64_t e = s + kStreamT < nnz ? s + kStreamT : nnz;
+    const int ne = (int)(e - s);
+    const OT brow = (OT)(ldb * (int64_t)sizeof(VT));
+    for (int i = threadIdx.x; i < ne; i += kThreads) {
+        s_off[i] = (OT)crd[s + i] * brow;
+        s_val[i] = val[s + i];
+    }
+    const int64_t lo = rowblk[blockIdx.x], hi = rowblk[blockIdx.x + 1];
+    const int64_t last = hi < nrows ? hi : nrows - 1;
+    __syncthreads();
+    const char *Bb = (const char *)B;
+    const OT colb = (OT)(jl * V * (int)sizeof(VT));
+    for (int64_t r = lo + wave; r <= last; r += kThreads / 64) {
+        const int64_t pa = (int64_t)pos[r], pb = (int64_t)pos[r + 1];
+        const int a = (int)((pa > s ? pa : s) - s), b = (int)((pb < e ? pb : e) - s);
+        if (r == hi && b <= a) continue;              // row hi starts at the next window: not ours (wave-uniform)
+        vec_t accu[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) accu[u] = (vec_t)(0);
+        for (int p0 = a; p0 < b; p0 += U * S) {       // wave-uniform
+            VT v[U];
+            vec_t bv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int pp = p0 + sl + u * S;
+                const bool in = pp < b;
+                const int idx = in ? pp : a;
+                v[u] = in ? s_val[idx] : (VT)0;
+                bv[u] = *(const vec_t *)(Bb + (s_off[idx] + colb));
+                if (!in) bv[u] = (vec_t)(0);          // not 0 * infinity
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) accu[u] += v[u] * bv[u];
+        }
+        vec_t acc = accu[0];
+#pragma unroll
+        for (int u = 1; u < U; ++u) acc += accu[u];
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+            VT x = acc[c];
+#pragma unroll
+            for (int d = 32; d >= LR; d >>= 1) x += __shfl_xor(x, d, 64);
+            acc[c] = x;
+        }
+        if (sl == 0) {
+            if (pa < s) *(vec_t *)(carry + (int64_t)blockIdx.x * LR * V + jl * V) = acc;
+            else {
+                vec_t *dst = (vec_t *)(C + (rowid ? (int64_t)rowid[r] : r) * ldc + jl * V);
+                *dst = accumulate ? *dst + acc : acc;
+            }
+        }
     }
 }
 
@@ -822,17 +935,43 @@ sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, co
         if (small) SPMI_SPMM_RUNS_O(VV, uint32_t, NARROW);  \
         else SPMI_SPMM_RUNS_O(VV, uint64_t, NARROW);        \
     } while (0)
+    // A wave per row where rows are even and of medium length, and for one or two 16-byte pieces where they are long: there the
+    // runs kernel's tables of rows cost more than its balance gives.  4.2 M entries, rows of even length, a wave per row against
+    // runs: 64 entries, 4 f32 columns 33 / 38 us, 64 f32 columns 128 / 135; 256 entries, 4 f32 29 / 38, 32 f64 60 / 78; 48 entries,
+    // 16 f32 63 / 62; 512 entries, 32 f64 88 / 62.  Lognormal rows of mean 64, 64 f32: 193 / 144.  6 M entries in rows of 20,000, 4 f32: 28 / 34.
+    const double mean = (double)nnz / (double)nrows;
+    const int64_t lr = N / V;
+    const bool one_load = N % V == 0 && ldb % V == 0 && ldc % V == 0 && (uintptr_t)B % 16 == 0 && (uintptr_t)C % 16 == 0 && lr >= 1 && lr <= 64 && (lr & (lr - 1)) == 0;
+    const bool wave_per_row = one_load && ((mean >= 96 && lr <= 2) || (mean >= (lr <= 8 ? 56 : 96) && mean < 448 && (double)A->max_segment <= 4 * mean));
+#define SPMI_SPMM_WIN_O(LR, OT)                                                                                               \
+    hipLaunchKernelGGL((spmm_windows_vec_kernel<PT, CT, VT, LR, OT>), dim3((unsigned)nb), dim3(kThreads), 0, st, pos, crd, val, rowid,    \
+                       (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, carry, accumulate)
+#define SPMI_SPMM_WIN(LR)                           \
+    do {                                            \
+        if (small) SPMI_SPMM_WIN_O(LR, uint32_t);   \
+        else SPMI_SPMM_WIN_O(LR, uint64_t);         \
+    } while (0)
     const int VV = N >= V ? V : 2;                // two or three columns in f32: loads of two
     const int64_t pieces = ceil_div(N, VV);
     // at least 512 blocks where the columns allow: few windows share the columns out among more blocks
     const int64_t split = nb < 512 ? ceil_div(512, nb) : 1;
     const int64_t wanted = ceil_div(pieces, split) > 4 ? ceil_div(pieces, split) : 4;
     const int lr_tile = (int)(wanted < 64 ? wanted : 64);
-    if (VV == V && pieces <= 2) SPMI_SPMM_RUNS(V, true);
+    if (wave_per_row) {
+        if (lr == 1) SPMI_SPMM_WIN(1);
+        else if (lr == 2) SPMI_SPMM_WIN(2);
+        else if (lr == 4) SPMI_SPMM_WIN(4);
+        else if (lr == 8) SPMI_SPMM_WIN(8);
+        else if (lr == 16) SPMI_SPMM_WIN(16);
+        else if (lr == 32) SPMI_SPMM_WIN(32);
+        else SPMI_SPMM_WIN(64);
+    } else if (VV == V && pieces <= 2) SPMI_SPMM_RUNS(V, true);
     else if (VV == V) SPMI_SPMM_RUNS(V, false);
     else SPMI_SPMM_RUNS(2, true);                 // f32 only
 #undef SPMI_SPMM_RUNS
 #undef SPMI_SPMM_RUNS_O
+#undef SPMI_SPMM_WIN
+#undef SPMI_SPMM_WIN_O
     SP_HIP(hipGetLastError());
     if (nb > 1) {
         hipLaunchKernelGGL((spmm_windows_fixup_kernel<PT, CT, VT>), dim3(grid_for(nb - 1, kThreads / 64)), dim3(kThreads), 0, st, pos,

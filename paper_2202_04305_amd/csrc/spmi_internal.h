@@ -237,6 +237,12 @@ __device__ __forceinline__ void spmi_rows_of_entries(POS pos, const CT *__restri
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)(e - s);
+    if (pos(lo + 1) >= e) {                                        // one row holds them all (block-uniform)
+        const CT only = rowid ? rowid[lo] : (CT)lo;
+        for (int i = tid; i < n; i += kThreads) row[at(i)] = only;
+        __syncthreads();
+        return;
+    }
     for (int i = tid; i < n; i += kThreads) row[at(i)] = 0;
     __syncthreads();
     for (int64_t r = lo + tid; r <= last; r += kThreads) {
