@@ -61,3 +61,17 @@ def test_spmm_keeps_infinities_and_nan(dtype, N):
     C = sp.sp_matmul(A, dev(B), torch.empty((lens.size, N), dtype=A.dtype, device=DEV)).cpu().numpy()
     assert np.all(np.isposinf(C[lens > 5, 0])) and np.all(np.isnan(C[lens > 9, N - 1]))
     assert np.all(np.isfinite(C[:, 1:N - 1])) and np.all(np.isfinite(C[lens <= 5]))
+
+
+@pytest.mark.parametrize("dtype,K", [(np.float64, k) for k in (16, 33, 64, 128)] + [(np.float32, k) for k in (16, 33, 100, 128, 256)])
+def test_sddmm(dtype, K):
+    """A dot product is a tree: a chain of the products of one 16-byte load, three levels among a lane's loads, three among its
+    eight lanes, one multiplication: 4 + 3 + 3 + 1 = 11."""
+    rows, cols, vals, lens, _ = rows_with_one_large_entry(dtype, 5, 300, 100)
+    S = gpu_pack((0, 1), (0, 1), (lens.size, 300), [rows, cols], np.ones_like(vals))
+    A, B = np.full((lens.size, K), 0.9 * unit(dtype), dtype=dtype), np.ones((300, K), dtype=dtype)
+    A[:, 0] = 1
+    exact = np.full(rows.size, 1 + (K - 1) * np.longdouble(A[0, 1]))
+    X = sp.sp_sddmm(S, dev(A), dev(B), b_is_transposed=True)
+    say("case sddmm long sums", dtype.__name__, K, "worst", worst(X.reshape(-1, 1), exact, dtype))
+    assert worst(X.reshape(-1, 1), exact, dtype) <= 11
