@@ -75,3 +75,40 @@ def test_sddmm(dtype, K):
     X = sp.sp_sddmm(S, dev(A), dev(B), b_is_transposed=True)
     say("case sddmm long sums", dtype.__name__, K, "worst", worst(X.reshape(-1, 1), exact, dtype))
     assert worst(X.reshape(-1, 1), exact, dtype) <= 11
+
+
+@pytest.mark.parametrize("fibres", ["one", "many"])
+@pytest.mark.parametrize("dtype,J", [(np.float64, j) for j in (8, 42, 64, 127)] + [(np.float32, j) for j in (16, 42, 256)])
+def test_mttkrp(fibres, dtype, J):
+    """Slices of 900 entries, in one fibre or in as many, in more than 512 windows.
+    Four entries in a chain, one multiplication by the fibre's row, eight such fours, eight of these in a run, one more where the two
+    meet, up to eight levels among the groups of a window, three for the windows a slice crosses: 33."""
+    slices, length = 640, 900
+    i = np.repeat(np.arange(slices, dtype=np.int64), length)
+    at = np.tile(np.arange(length, dtype=np.int64), slices)
+    k, l = (np.zeros_like(at), at) if fibres == "one" else (at, at % 3)
+    vals = np.full(i.size, 0.9 * unit(dtype), dtype=dtype)
+    vals[at == 0] = 1
+    T = gpu_pack((0, 1, 1), (0, 1, 2), (slices, length, length), [i, k, l], vals)
+    ones = torch.ones((length, J), dtype=T.dtype, device=DEV)
+    A = sp.sp_mttkrp(T, ones, ones)
+    exact = np.full(slices, 1 + (length - 1) * np.longdouble(vals[1]))
+    say("case mttkrp long sums", fibres, dtype.__name__, J, "worst", worst(A, exact, dtype))
+    assert worst(A, exact, dtype) <= 33
+
+
+def test_mttkrp_keeps_infinities():
+    """A row of either factor that is infinite in one column: the slices that reach it are infinite there and nowhere else.  All
+    other terms are positive, so nothing may turn into NaN, wherever a run of entries is cut."""
+    slices, K, L, J = 300, 50, 40, 9
+    p = prng.permutation(5, 1, slices * K * L)[:60000].astype(np.int64)
+    p.sort()
+    i, k, l = p // (K * L), p // L % K, p % L
+    T = gpu_pack((0, 1, 1), (0, 1, 2), (slices, K, L), [i, k, l], np.ones(p.size))
+    for which in (0, 1):
+        C, D = np.ones((K, J)), np.ones((L, J))
+        (C if which == 0 else D)[7, 4] = np.inf
+        A = sp.sp_mttkrp(T, dev(C), dev(D)).cpu().numpy()
+        hit = np.zeros(slices, dtype=bool)
+        hit[i[(k if which == 0 else l) == 7]] = True
+        assert hit.any() and np.all(np.isposinf(A[hit, 4])) and np.all(np.isfinite(np.delete(A, 4, axis=1))) and np.all(np.isfinite(A[~hit]))
