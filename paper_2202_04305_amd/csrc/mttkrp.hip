@@ -95,11 +95,13 @@ struct vec_of {
 // below 4 GB), the row of the mid factor and the slice.  Any J >= V, leading dimension and element-aligned address: the last
 // lane of a row moves back to the last V columns and stores only those that the lane before it does not have.
 // The entries are added up four at a time, these sums eight at a time: one chain for all of a run's had up to 1.3 times the error
-// on wide rows (2,000 slices of 750 entries, 100 f64 columns 4.5e-16 -> 1.8e-16 relative 2-norm).
+// on wide rows (2,000 slices of 750 entries, 100 f64 columns 4.5e-16 -> 1.8e-16 relative 2-norm).  A window that one
+// slice fills ends in shuffles instead of the search for equal slices.
 // Bound by the rows of the inner factor that it gathers.  Measured before (a wave per 128 entries that walked their fibres one
 // after the other; a column per lane for widths that are no multiple of 16 bytes) and now: 76.9 M entries, 42 f64 columns
 // 1.870 -> 1.825 ms; 20 M entries in fibres of one to four, 16 columns 577 -> 290 us; 20 M entries in 40 slices, 16 f64 columns
-// 203 -> 199 us, 64 f64 columns 450 -> 457, 32 f32 columns 180 -> 198, 64 f32 columns 245 -> 279; 30,000 entries in fibres of one or two, 42 columns 56 -> 20 us.
+// 203 -> 199 us, 64 f64 columns 450 -> 457, 32 f32 columns 180 -> 198, 64 f32 columns 245 -> 279 (without the windows of one slice 219,
+// 458, 218, 299); 30,000 entries in fibres of one or two, 42 columns 56 -> 20 us.
 template <typename PT, typename CT, typename VT, int V, typename OT>
 __global__ __launch_bounds__(kThreads) void mttkrp_runs_kernel(const PT *__restrict__ pos1, const CT *__restrict__ crd0, const CT *__restrict__ crd1,
                                                                const PT *__restrict__ pos2, const CT *__restrict__ crd2, const VT *__restrict__ val,
@@ -154,6 +156,7 @@ __global__ __launch_bounds__(kThreads) void mttkrp_runs_kernel(const PT *__restr
     spmi_rows_of_entries<kThreads, PER>([=](int64_t f) { return (int64_t)pos2[f]; }, crd1, f0, f1, s, e, s_mid, s_wave, at);
     spmi_rows_of_entries<kThreads, PER>([=](int64_t q) { return (int64_t)pos2[(int64_t)pos1[q]]; }, crd0, q0, q1, s, e, s_slc, s_wave, at);
     const bool continued = (int64_t)pos2[(int64_t)pos1[q0]] < s;   // the first slice began in an earlier window
+    const bool one_slice = (int64_t)pos2[(int64_t)pos1[q0 + 1]] >= e;   // and holds the whole window
     const int sl = lane / LR, jl = lane - sl * LR;
     const int group = sl < S ? wave * S + sl : G;                  // lanes beyond S * LR take nothing
     const int first = group * run < ne ? group * run : ne, end = first + run < ne ? first + run : ne;
@@ -227,6 +230,23 @@ __global__ __launch_bounds__(kThreads) void mttkrp_runs_kernel(const PT *__restr
         if (k % (8 * U) == 7 * U) { sum += mid_sum; mid_sum = (vec_t)(0); }
     }
     acc = sum + mid_sum;
+    if (one_slice) {
+        // every group has a part of one sum: towards the first group of each wave, then over the waves
+        for (int d = 1; d < S; d <<= 1) {
+#pragma unroll
+            for (int x = 0; x < V; ++x) {
+                const VT other = __shfl(acc[x], lane + d * LR < 64 ? lane + d * LR : lane, 64);
+                acc[x] += sl + d < S ? other : (VT)0;
+            }
+        }
+        if (sl == 0) s_part[slot] = acc;
+        __syncthreads();
+        if (group != 0) return;
+        for (int g = S; g < G; g += S) acc += s_part[g * LR + jl];
+        if (continued) store(carry + w * J + col, acc, false);
+        else store(A + (int64_t)slice * lda + col, acc, accumulate);
+        return;
+    }
     if (head) s_part[slot] = acc;                                  // the whole run belongs to a slice that began before it
     // The sums of a slice that fills whole runs are added up towards the first of them, over twice as many groups each step.
     const int full = (ne + run - 1) / run;                         // groups that took something
