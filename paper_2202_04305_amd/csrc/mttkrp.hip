@@ -306,6 +306,22 @@ __global__ __launch_bounds__(kFixThreads) void mttkrp_fixup_kernel(const CT *__r
     }
 }
 
+// Is a copy of a factor matrix with rows padded to whole lines made up for by the lines that the gathers then leave out?  The copy
+// costs its bytes, read and written; a gather saves the lines its row touches beyond the padded ones, over all the places
+// in a line where rows begin.  The line is where measured times cross (42 and 60 f64 columns, 60,000 to 1 M rows: 24 to 36
+// gathers per row; 60 f32 columns 10 to 16; 33 f64 columns, which save nothing: never), at 3.5 times the bytes saved.  1 M rows,
+// 42 f64 columns: 8 gathers per row 619 us with the copy, 510 without; 64 per row, 200,000 rows 696 and 758; 20,000 rows (6.7 MB),
+// 2000 per row 1119 and 1055; 28,818 rows (9.7 MB), 2668 per row 1826 and 1943.
+bool padding_pays(uintptr_t first, int64_t rows, int64_t row_bytes, int64_t ld_bytes, int64_t gathers)
+{
+    const int64_t padded = (row_bytes + 127) / 128;
+    if (rows * row_bytes <= ((int64_t)8 << 20)) return false;
+    int64_t touched = 0;                                             // by rows 0..127: their places in a line repeat after that
+    for (int64_t r = 0; r < 128; ++r) touched += ((int64_t)((first + (uint64_t)r * (uint64_t)ld_bytes) % 128) + row_bytes + 127) / 128;
+    const double saved = (double)touched / 128 - (double)padded;     // lines per gather
+    return (double)gathers * saved * 128 >= 3.5 * (double)rows * (double)(row_bytes + padded * 128);
+}
+
 template <typename PT, typename CT, typename VT>
 sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, int64_t ldx, int64_t J, VT *A, int64_t lda,
                    int accumulate, hipStream_t st)
@@ -352,18 +368,16 @@ sp_status mttkrp_t(const sp_tensor *B, const VT *M, int64_t ldm, const VT *X, in
                           (uintptr_t)A % 16 == 0;
     const int64_t K = B->shape[1], L = B->shape[2];
     const int64_t rows_m = B->enc.perm[1] == 1 ? K : L, rows_x = B->enc.perm[1] == 1 ? L : K;
-    // The inner factor is gathered a row per stored entry, the mid factor a row per fibre.  When such a matrix is
-    // larger than an XCD's L2 and its rows do not start on 128-byte lines, a copy with rows padded to whole lines is
-    // gathered from instead (a 336-byte row then touches 3 lines, not 3.6 on average); the copy is made on every call
+    // The inner factor is gathered a row per stored entry, the mid factor a row per fibre.  Where such a matrix is larger
+    // than two L2 caches and enough gathers save a line each, a copy with rows padded to whole 128-byte lines is
+    // gathered from instead (a 336-byte row then touches 3 lines, not 3.5 on average); the copy is made on every call
     // into a buffer the tensor keeps.  Rows of an odd size go without the copy where that buffer cannot be had.
     const int64_t row_bytes = J * (int64_t)sizeof(VT);
     for (int which = 0; which < 2; ++which) {
         const VT *&F = which == 0 ? X : M;
         int64_t &ldf = which == 0 ? ldx : ldm;
         const int64_t rows_f = which == 0 ? rows_x : rows_m;
-        if (!(J >= VV && rows_f * row_bytes > ((int64_t)4 << 20) && row_bytes % 128 != 0 &&
-              (ldf * (int64_t)sizeof(VT) % 128 != 0 || (uintptr_t)F % 128 != 0)))
-            continue;
+        if (!(J >= VV && padding_pays((uintptr_t)F, rows_f, row_bytes, ldf * (int64_t)sizeof(VT), which == 0 ? nnz : nfib))) continue;
         const int64_t ldp_bytes = (row_bytes + 127) / 128 * 128;
         const size_t want = (size_t)rows_f * (size_t)ldp_bytes;
         sp_kept &pad = Bt->mttkrp_pad[which];
