@@ -217,10 +217,10 @@ __global__ __launch_bounds__(256) void buckets_to_segments_kernel(const uint32_t
 // predecessor's start and not after its own.
 __global__ __launch_bounds__(256) void msd_chunks_kernel(const uint32_t *__restrict__ ctr2, const uint32_t *__restrict__ seg_start,
                                                          const uint32_t *__restrict__ seg_tile, uint32_t n, uint32_t nchunks,
-                                                         uint32_t *__restrict__ chunk_lo, uint32_t *__restrict__ big, uint32_t *__restrict__ redo)
+                                                         uint32_t *__restrict__ chunk_lo, uint32_t *__restrict__ big)
 {
     const uint32_t s = blockIdx.x * 256u + threadIdx.x;
-    if (s == 0) big[0] = redo[0] = 0;                             // lengths of the finishing kernel's two lists
+    if (s == 0) big[0] = 0;                                       // the finishing kernel counts in it
     if (s > (uint32_t)kSub) return;
     auto start_of = [&](uint32_t sub) -> uint32_t {
         if (sub >= (uint32_t)kSub) return n;
@@ -436,45 +436,50 @@ __device__ __forceinline__ bool finish_chunk(const uint64_t *__restrict__ kin, c
 }
 
 // Block k takes chunk k.  A chunk that is too large goes to the list `big` (its length in big[0]) if msd_finish_big_kernel can
-// hold it, a still larger or a crowded one to the list `redo`.
+// hold it; a still larger or a crowded one is left to msd_redo_kernel: left[k] says so for every chunk (a list of them costs an
+// atomic add each to one address, and in a banded or blocked matrix, where a row's columns lie in one interval of a chunk
+// that spans several rows, nearly every chunk is crowded).
 constexpr int kBigT = 1024, kBigCap = kBigT * kFE;
 template <typename P>
 __global__ __launch_bounds__(kFT) void msd_finish_kernel(const uint64_t *__restrict__ kin, const P *__restrict__ vin, uint64_t *__restrict__ kout,
                                                          P *__restrict__ vout, const uint32_t *__restrict__ chunk_lo, uint32_t *__restrict__ big,
-                                                         uint32_t *__restrict__ redo)
+                                                         uint32_t *__restrict__ left)
 {
     __shared__ finish_lds<P, kFT, kFE> s;
     const uint32_t lo = chunk_lo[blockIdx.x], hi = chunk_lo[blockIdx.x + 1];
-    if (lo >= hi) return;
-    const uint32_t cnt = hi - lo;
-    if (cnt <= (uint32_t)kCap && finish_chunk<P, kFT, kFE>(kin + lo, vin + lo, kout + lo, vout + lo, cnt, s)) return;
+    const uint32_t cnt = lo < hi ? hi - lo : 0;
+    const bool large = cnt > (uint32_t)kCap && cnt <= (uint32_t)kBigCap;
+    bool leave = cnt > (uint32_t)kBigCap;
+    if (cnt > 0 && cnt <= (uint32_t)kCap) leave = !finish_chunk<P, kFT, kFE>(kin + lo, vin + lo, kout + lo, vout + lo, cnt, s);
     if (threadIdx.x == 0) {
-        uint32_t *list = cnt > (uint32_t)kCap && cnt <= (uint32_t)kBigCap ? big : redo;
-        list[1 + atomicAdd(&list[0], 1u)] = blockIdx.x;
+        left[blockIdx.x] = leave ? 1u : 0u;
+        if (large) big[1 + atomicAdd(&big[0], 1u)] = blockIdx.x;
     }
 }
 
 template <typename P>
 __global__ __launch_bounds__(kBigT) void msd_finish_big_kernel(const uint64_t *__restrict__ kin, const P *__restrict__ vin, uint64_t *__restrict__ kout,
                                                                P *__restrict__ vout, const uint32_t *__restrict__ chunk_lo,
-                                                               const uint32_t *__restrict__ big, uint32_t *__restrict__ redo)
+                                                               const uint32_t *__restrict__ big, uint32_t *__restrict__ left)
 {
     __shared__ finish_lds<P, kBigT, kFE> s;
     const uint32_t nbig = big[0];
     for (uint32_t i = blockIdx.x; i < nbig; i += gridDim.x) {
         const uint32_t chunk = big[1 + i], lo = chunk_lo[chunk];
         if (!finish_chunk<P, kBigT, kFE>(kin + lo, vin + lo, kout + lo, vout + lo, chunk_lo[chunk + 1] - lo, s) && threadIdx.x == 0)
-            redo[1 + atomicAdd(&redo[0], 1u)] = chunk;
+            left[chunk] = 1u;
         __syncthreads();                                          // the buffers are used again
     }
 }
 
 // The chunks the finishing kernels left: sorted digit by digit (rank_by_digit: stable, least significant digit first, digits in
 // which no two keys of the range differ skipped), in the LDS when they fit, else through device memory, tile by tile, hopping
-// between the chunk's part of kin / vin and its part of the output.  Slow; meant for a few chunks.
+// between the chunk's part of kin / vin and its part of the output (slow; meant for a few chunks).  As many blocks as the chip holds
+// (four on a CU).  16.8 M entries in bands of 64, whole pack: 1183 us with the chunks listed and 512 blocks here, 945 now, 918 with
+// the ranking of digits alone; in blocks of 64 x 64 1107, 880, 900.
 template <typename P>
 __global__ __launch_bounds__(kFT) void msd_redo_kernel(uint64_t *kin, P *vin, uint64_t *kout, P *vout, const uint32_t *__restrict__ chunk_lo,
-                                                       const uint32_t *__restrict__ redo)
+                                                       const uint32_t *__restrict__ left, uint32_t nchunks)
 {
     constexpr int W = kFT / 64;
     __shared__ uint64_t stage[kCap];
@@ -486,9 +491,11 @@ __global__ __launch_bounds__(kFT) void msd_redo_kernel(uint64_t *kin, P *vin, ui
     __shared__ unsigned long long s_or[W];
     P *sval = (P *)stage;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t nredo = redo[0];
-    for (uint32_t which = blockIdx.x; which < nredo; which += gridDim.x) {
-        const uint32_t lo = chunk_lo[redo[1 + which]], hi = chunk_lo[redo[1 + which] + 1];
+    // this block's chunks: blockIdx.x, + gridDim.x, ...; 64 of them looked at a time, by every wave alike
+    for (uint32_t first = blockIdx.x; first < nchunks; first += 64u * gridDim.x) {
+      const uint64_t at = (uint64_t)first + (uint64_t)lane * gridDim.x;
+      for (uint64_t todo = __ballot(at < nchunks && left[at < nchunks ? at : 0] != 0); todo; todo &= todo - 1) {
+        const uint32_t chunk = first + (uint32_t)__builtin_ctzll(todo) * gridDim.x, lo = chunk_lo[chunk], hi = chunk_lo[chunk + 1];
         const uint32_t cnt = hi - lo;
         const uint64_t k0 = kin[lo];
         uint64_t k[kFE];
@@ -602,7 +609,9 @@ __global__ __launch_bounds__(kFT) void msd_redo_kernel(uint64_t *kin, P *vin, ui
         }
         if (src_k != kout) {                                          // no hop at all (every key equal), or an even number of them
             for (uint32_t i = lo + tid; i < hi; i += kFT) { kout[i] = src_k[i]; vout[i] = src_v[i]; }
-        }    __syncthreads();                                              // the tables are reused for the next chunk
+        }
+        __syncthreads();                                              // the tables are reused for the next chunk
+      }
     }
 }
 
@@ -694,7 +703,7 @@ sp_status msd_sort_t(uint64_t *keys, const P *vals_in, int64_t n, int key_bits, 
     const uint32_t nchunks = n32 / (uint32_t)kTarget + 1;
     uint32_t *seg = (uint32_t *)tmp.get((size_t)(2 * 257 + 2 * 2 + nchunks + 1 + 2 * (nchunks + 1) + 8) * 4);
     if (!kb || !va || !vb || !ctr || !seg) return SP_ERR_ALLOC;
-    uint32_t *seg_start1 = seg, *seg_tile1 = seg + 2, *seg_start2 = seg + 4, *seg_tile2 = seg + 4 + 257, *chunk_lo = seg + 4 + 2 * 257, *big = chunk_lo + nchunks + 1, *redo = big + nchunks + 1;
+    uint32_t *seg_start1 = seg, *seg_tile1 = seg + 2, *seg_start2 = seg + 4, *seg_tile2 = seg + 4 + 257, *chunk_lo = seg + 4 + 2 * 257, *big = chunk_lo + nchunks + 1, *left = big + nchunks + 1;
     const int shift1 = key_bits > 8 ? key_bits - 8 : 0, shift2 = key_bits > 16 ? key_bits - 16 : 0;
     // first pass: keys / vals_in -> kb / va
     hipLaunchKernelGGL(one_segment_kernel, dim3(1), dim3(1), 0, st, seg_start1, seg_tile1, n32);
@@ -716,14 +725,15 @@ sp_status msd_sort_t(uint64_t *keys, const P *vals_in, int64_t n, int key_bits, 
     hipLaunchKernelGGL(partition_scatter_kernel<P>, dim3(round8(tiles2_max)), dim3(kT), 0, st, (const uint64_t *)kb, (const P *)va, keys, vb,
                        (const uint32_t *)seg_start2, (const uint32_t *)seg_tile2, 256, shift2, (const uint32_t *)ctr);
     hipLaunchKernelGGL(msd_chunks_kernel, dim3(kSub / 256 + 1), dim3(256), 0, st, (const uint32_t *)ctr, (const uint32_t *)seg_start2,
-                       (const uint32_t *)seg_tile2, n32, nchunks, chunk_lo, big, redo);
+                       (const uint32_t *)seg_tile2, n32, nchunks, chunk_lo, big);
     SP_HIP(hipGetLastError());
     // finishing pass: keys / vb -> kb / va (a range that does not fit the LDS also hops through its own part of keys / vb)
     hipLaunchKernelGGL(msd_finish_kernel<P>, dim3(nchunks), dim3(kFT), 0, st, (const uint64_t *)keys, (const P *)vb, kb, va,
-                       (const uint32_t *)chunk_lo, big, redo);
+                       (const uint32_t *)chunk_lo, big, left);
     hipLaunchKernelGGL(msd_finish_big_kernel<P>, dim3(nchunks < 256u ? nchunks : 256u), dim3(kBigT), 0, st, (const uint64_t *)keys, (const P *)vb, kb, va,
-                       (const uint32_t *)chunk_lo, (const uint32_t *)big, redo);
-    hipLaunchKernelGGL(msd_redo_kernel<P>, dim3(nchunks < 512u ? nchunks : 512u), dim3(kFT), 0, st, keys, vb, kb, va, (const uint32_t *)chunk_lo, (const uint32_t *)redo);
+                       (const uint32_t *)chunk_lo, (const uint32_t *)big, left);
+    hipLaunchKernelGGL(msd_redo_kernel<P>, dim3(nchunks < 1024u ? nchunks : 1024u), dim3(kFT), 0, st, keys, vb, kb, va, (const uint32_t *)chunk_lo, (const uint32_t *)left,
+                       nchunks);
     SP_HIP(hipGetLastError());
     *keys_out = kb;
     *vals_out = va;

@@ -68,3 +68,16 @@ def test_every_sub_bucket_larger_than_a_chunk(per_row, col_bits):
     c = prng.below(SEED, 30, r.size, 1 << col_bits).astype(np.int64)
     lin = np.unique((r << col_bits) + c)
     check((1 << 16, 1 << col_bits), [lin >> col_bits, lin & ((1 << col_bits) - 1)], np.float64, "rows of %d, %d bits" % (per_row, 16 + col_bits))
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_every_chunk_crowded(msd_first, dtype):
+    """A band of 64 columns: nearly every chunk spans several rows and has each row's columns in one interval; more such chunks than
+    the kernel that sorts them digit by digit has blocks, some rows long enough for the large block."""
+    m, n, per = 22000, 1 << 20, 64
+    r = np.repeat(np.arange(m, dtype=np.int64), per)
+    c = np.repeat((np.arange(m, dtype=np.int64) * 47) % (n - 4096), per) + np.tile(np.arange(per, dtype=np.int64), m)
+    extra = np.arange(3000, dtype=np.int64)
+    rows = np.concatenate([r, np.full(3000, 5000), np.full(3000, 15000)])
+    cols = np.concatenate([c, n - 3100 + extra, n - 3100 + extra])
+    check((m, n), [rows, cols], dtype, "band of 64 columns")
