@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kThreads) void make_keys_counting_kernel(level_args
             any_bad |= bad;
             keys[e] = key;
             atomicAdd(&h[(uint32_t)(key >> plan.digit_shift) & 255u], 1u);
-            if ((e & 63) == 0) atomicAdd(&plan.samp[(uint32_t)(key >> plan.samp_shift) & 0xffffu], 1u);
+            if ((uint32_t)(e & 63) == spmi_sampled_place((uint32_t)(e >> 6))) atomicAdd(&plan.samp[(uint32_t)(key >> plan.samp_shift) & 0xffffu], 1u);
         }
     }
     if (any_bad) atomicOr(&flags[0], 1);
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kThreads) void convert_keys_kernel(convert_args a, 
         keys[e] = key;
         if (plan.ctr) {
             atomicAdd(&h[(uint32_t)(key >> plan.digit_shift) & 255u], 1u);
-            if ((e & 63) == 0) atomicAdd(&plan.samp[(uint32_t)(key >> plan.samp_shift) & 0xffffu], 1u);
+            if ((uint32_t)(e & 63) == spmi_sampled_place((uint32_t)(e >> 6))) atomicAdd(&plan.samp[(uint32_t)(key >> plan.samp_shift) & 0xffffu], 1u);
         }
     }
     if (!plan.ctr) return;                               // the whole grid

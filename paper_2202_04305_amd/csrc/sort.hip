@@ -618,7 +618,7 @@ __global__ __launch_bounds__(kFT) void msd_redo_kernel(uint64_t *kin, P *vin, ui
 // Sampled histogram of the top 16 bits of the keys (one key in 64), and what it says about the finishing pass.
 __global__ __launch_bounds__(256) void msd_sample_kernel(const uint64_t *__restrict__ keys, int64_t n, int shift, uint32_t *__restrict__ samp)
 {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 64;
+    const int64_t group = (int64_t)blockIdx.x * 256 + threadIdx.x, i = group * 64 + spmi_sampled_place((uint32_t)group);
     if (i < n) atomicAdd(&samp[(uint32_t)(keys[i] >> shift) & 0xffffu], 1u);
 }
 

@@ -375,6 +375,10 @@ struct spmi_long_sum<float, V> {
     __device__ __forceinline__ vec_t value(vec_t t) const { return pair(t).value(); }
 };
 
+// Of 64 entries the sort's sampled histogram takes one, at a place that changes from group to group: entries often come in
+// order, and with rows of 64 a fixed place would be the same one of every row (a full last column would never be seen).
+__device__ __forceinline__ uint32_t spmi_sampled_place(uint32_t group) { return (group * 2654435761u) >> 26; }
+
 // Division of a key by a level's stride or size, which the host knows when it launches: a shift when the divisor is a
 // power of two, a multiplication by the reciprocal in double plus a one-step correction while the dividend is below
 // 2^52 (the estimate is then within one of the quotient), the hardware's 64-bit division otherwise.

@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 import paper_2202_04305_amd as sp
-from gen import workloads as W
+from gen import workloads as W, prng
 from gpu_util import say, dev, gpu_pack, assert_storage_equal
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +63,21 @@ def test_convert_rank_three(lt, order):
     vals = rng.standard_normal(4500)
     check(shape, coords, vals, ((1, 1, 1), (0, 1, 2)), (lt, order))
     check(shape, coords, vals, (lt, order), ((1, 1, 1), (0, 1, 2)))
+
+
+@pytest.mark.parametrize("per_row", [64, 128])
+@pytest.mark.parametrize("full", ["first", "last"])
+def test_a_full_column_at_the_same_place_of_every_row(per_row, full):
+    """Rows of 64 or 128 entries, one column in all of them: whatever places of a row the sort's sample looks at, the columns come out
+    in order (the sample decides between the two sorts; a column of 20,000 entries is no chunk for the finishing kernels)."""
+    m, n = 20000, 1 << 16
+    r = np.repeat(np.arange(m, dtype=np.int64), per_row)
+    c = np.tile(np.arange(per_row, dtype=np.int64), m) * (n // per_row - 3) + r % 700
+    c[(per_row - 1 if full == "last" else 0)::per_row] = n - 1 if full == "last" else 0
+    if full == "first":
+        c[1::per_row] = np.maximum(c[1::per_row], 1)
+    v = prng.uniform_pm1(W.BASE_SEED, 77, r.size)
+    A = gpu_pack((0, 1), (0, 1), (m, n), [r, c], v)
+    say("case full column", full, "rows of", per_row)
+    B = sp.sp_convert(A, sp.sp_encode((0, 1), (1, 0), 32, 32))
+    assert_storage_equal(B, oracle.pack((0, 1), (1, 0), (m, n), [r, c], v, 32, 32))
