@@ -109,12 +109,19 @@ def _check(code, what=""):
         raise SpError(code, what)
 
 
+# torch's own names for the current device and the handle of its current stream; not part of its documented interface
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr():
     """The current stream of the current device, as torch.cuda.current_stream() has it, without building a Stream object for it
-    (0.2 against 2.8 us; a small product's whole call 7.5 -> 4.4 us)."""
+    where torch lets one (0.2 against 2.8 us; a small product's whole call 7.5 -> 4.4 us)."""
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_raw_device())
 
 
 class _TorchAllocator:
