@@ -1,8 +1,10 @@
 """Dense operands of any width, leading dimension and element-aligned address, against the CPU checker.
 
 The kernels load 16 bytes wherever a row begins and move the last load of a row back to the row's end, so the sizes are
-the edges of that rule: fewer columns than a load holds, one more and one less than a whole number of loads, one more
-than a wave covers; rows longer than a window of 1024 stored entries; an infinity in the columns that two loads share.
+the edges of that rule: fewer columns than a load holds, one more and one less than a whole number of loads; rows longer
+than a window of 1024 stored entries; an infinity in the columns that two loads share.  Most inputs are of a few windows, and
+few windows share the columns out four loads to a block; the tests "of many windows" have more than 512, so that a row of
+the operand takes 33 to 64 lanes, one more than a wave covers, and a second tile of columns.
 Tolerance: the products' own, 1e-12 (f64) / 1e-5 (f32) times sum|a*b| per element.
 """
 import numpy as np
@@ -126,3 +128,55 @@ def test_mttkrp_any_width_and_address(order, dtype, J):
         written = torch.zeros_like(flat, dtype=torch.bool)
         written[offset:offset + w.shape[0] * (J + extra)].view(w.shape[0], J + extra)[:, :J] = True
         assert torch.equal(torch.isnan(flat[~written]), torch.isnan(before[~written]))
+
+
+@pytest.fixture(scope="module")
+def many_windows():
+    w = W.cfg2_powerlaw_csr(20000, 4000, mean=30.0, sigma=1.3, cap=3500)
+    assert w.nnz > 512 * 1024
+    return w
+
+
+@pytest.mark.parametrize("dtype,N", [(np.float64, n) for n in (67, 127, 129, 131)] + [(np.float32, n) for n in (255, 257)])
+def test_spmm_of_many_windows(many_windows, dtype, N):
+    w = many_windows
+    vals = w.vals.astype(dtype)
+    A = gpu_pack((0, 1), (0, 1), w.shape, [w.rows, w.cols], vals)
+    B = prng.uniform_pm1(7, 1, w.shape[1] * N, dtype=dtype).reshape(-1, N)
+    ref, mag = oracle.matmul_coo(w.shape, w.rows, w.cols, vals, B)
+    for extra, offset in [(0, 0), (1, 1)]:
+        say("case spmm many windows", dtype.__name__, N, extra, offset)
+        _, Bd = embedded(B, N + extra, offset)
+        _, Cd = embedded(np.zeros((w.shape[0], N), dtype=dtype), N + extra, offset)
+        sp.sp_matmul(A, Bd, Cd)
+        assert_product_close(Cd, ref, mag, dtype, "spmm")
+
+
+@pytest.mark.parametrize("dtype,J", [(np.float64, j) for j in (67, 127, 129)] + [(np.float32, j) for j in (255, 257)])
+def test_mttkrp_of_many_windows(dtype, J):
+    w = W.tensor3_slices(I=300, K=200, L=500, nnz=600000, k_mean=80, l_mean=120, sigma=0.8, J=J, dtype=dtype)
+    C, D = w.factors()
+    ref, mag = oracle.mttkrp_coo(w.shape, w.ci, w.ck, w.cl, w.vals, C, D)
+    T = gpu_pack((0, 1, 1), (0, 1, 2), w.shape, [w.ci, w.ck, w.cl], w.vals)
+    assert len(w.vals) > 512 * 1024
+    for extra, offset in [(0, 0), (1, 1)]:
+        say("case mttkrp many windows", dtype.__name__, J, extra, offset)
+        Cd, Dd = embedded(C, J + extra, offset)[1], embedded(D, J + extra, offset)[1]
+        assert_product_close(sp.sp_mttkrp(T, Cd, Dd), ref, mag, dtype, "mttkrp")
+
+
+@pytest.mark.parametrize("dtype,K", [(np.float64, k) for k in (5, 33, 64, 100)] + [(np.float32, k) for k in (5, 33, 64, 100, 200)])
+def test_sddmm_of_many_windows(dtype, K):
+    """More than 1024 windows: a block takes a whole one.  Small whole numbers, so that every sum is exact: bit for bit."""
+    w = W.cfg2_powerlaw_csr(40000, 5000, mean=36.0, sigma=1.2, cap=3000)
+    assert w.nnz > 1024 * 1024
+    vals = (1 + prng.below(8, 3, w.nnz, 3)).astype(dtype)
+    A = (prng.below(8, 1, w.shape[0] * K, 7).astype(dtype) - 3).reshape(-1, K)
+    B = (prng.below(8, 2, w.shape[1] * K, 7).astype(dtype) - 3).reshape(-1, K)
+    S = gpu_pack((0, 1), (0, 1), w.shape, [w.rows, w.cols], vals)
+    say("case sddmm many windows", dtype.__name__, K)
+    X = sp.sp_sddmm(S, dev(A), dev(B), b_is_transposed=True)
+    co, v = sp.sp_unpack(S)
+    exact = torch.cat([v[e:e + (1 << 17)] * (dev(A)[co[0][e:e + (1 << 17)]] * dev(B)[co[1][e:e + (1 << 17)]]).sum(1)
+                       for e in range(0, w.nnz, 1 << 17)])
+    assert torch.equal(X, exact)
