@@ -380,7 +380,7 @@ def bench_spmspm(args, torch, sp, dev):
                               2: "spgemm_ws_count_kernel + scan + spgemm_ws_numeric_panels_kernel (4 waves per row)",
                               3: "spgemm_ws_count_kernel + scan + spgemm_ws_numeric_kernel (1 wave per row)",
                               5: "spgemm_ws_count_kernel + scan + spgemm_ws_numeric_entries_kernel (16 waves per row, order of the additions not fixed)",
-                              }.get(args.spgemm_kernel, "spgemm_ws_count_kernel + scan + spgemm_ws_numeric_wide_kernel (16 waves per row; 4 below 8192 columns)"),
+                              }.get(args.spgemm_kernel, "spgemm_ws_count_kernel + scan + spgemm_panel_tasks_kernel (a wave per row and column panel; from 8192 columns or 2 M pairs on, below that 4 waves per row)"),
                    "small": bool(args.small)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": None, "kernel": "whole sp_spgemm call (allocation and host synchronisations included)",
@@ -592,7 +592,7 @@ def bench_matmul(args, torch, sp, dev, name, w, wbits, full):
         if lt[1] == 0:
             kernel_name = "dense_rows_kernel"
     else:
-        kernel_name = "sddmm_rows_vec_kernel" if sddmm else "spmm_scatter_kernel" if (name == "cfg5" and args.csc_mode == 1) else (
+        kernel_name = "sddmm_entries_kernel" if sddmm else "spmm_scatter_kernel" if (name == "cfg5" and args.csc_mode == 1) else (
             "spmm_rows_kernel" if args.spmm_kernel == 1 else "spmm_rows_vec_kernel" if args.spmm_kernel == 2 else "spmm_runs_kernel (+ fix-up)")
     achieved = abytes / (kernel_ms * 1e-3) / 1e9
     traffic, traffic_source = (None, None) if args.small else measured_traffic(name, wbits, kk if spmv else 0)

@@ -137,7 +137,7 @@ sp_status sp_pos(const sp_tensor *t, int level, const void **ptr, int64_t *len);
 sp_status sp_crd(const sp_tensor *t, int level, const void **ptr, int64_t *len);
 sp_status sp_values(const sp_tensor *t, const void **ptr, int64_t *len);
 
-/* Back to the coordinate scheme (Section 4.2: the intermediate form every conversion passes through; it is the first
+/* Back to the coordinate scheme (Section 4.2: the intermediate form every conversion of the paper passes through, the first
  * half of the paper's convert operation, whose second half is sp_pack): every stored position in storage order
  * (padding zeros of a dense level under a compressed one included), coordinates in the original dimension order.
  * coords: HOST array of `rank` DEVICE int64 arrays, each with room for sp_values' length (sp_tensor_info: nvalues) entries;
@@ -191,7 +191,8 @@ sp_status sp_spgemm(const sp_tensor *A, const sp_tensor *B, const sp_encoding *e
 sp_status sp_add(const sp_tensor *A, const sp_tensor *B, const sp_encoding *encC, void *stream, sp_tensor **C);
 
 /* The paper's convert operation between two sparse encodings (Section 4.2: conversions go through an intermediate
- * coordinate scheme, which avoids one converter per pair of formats).  Every stored position of `from` (explicit and
+ * coordinate scheme, which avoids one converter per pair of formats; here through the sort keys that sp_pack would make of
+ * those coordinates, made straight from the storage).  Every stored position of `from` (explicit and
  * padding zeros included) becomes a stored entry of the new tensor, which has `from`'s shape, dtype and allocator and
  * the encoding `to` (same rank).  Synchronises like sp_pack; `from` is left untouched. */
 sp_status sp_convert(const sp_tensor *from, const sp_encoding *to, void *stream, sp_tensor **out);

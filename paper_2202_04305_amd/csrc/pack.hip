@@ -1,11 +1,11 @@
 // Storage builder: coordinate scheme -> pos / crd / values per level (arXiv 2202.04305, Section 4.1).
 //
-// Steps, all on the GPU: linearise the level coordinates into one 64-bit key per entry,
-// stable LSD radix sort of (key, entry id), adjacent-equal check for duplicates, then one
-// sweep per level: a compressed level marks where a new (parent, coordinate) pair starts,
-// prefix-sums the marks into child positions, counts children per parent and prefix-sums
-// the counts into pos; a dense level only folds the coordinate into the position.  The
-// values travel through the sort as the payload and are put in place last.  Only level sizes and the error flags travel to the host.
+// Steps, all on the GPU: linearise the level coordinates into one 64-bit key per entry (or make the key straight from the
+// storage of another encoding, for conversions), a stable radix sort of (key, value) with the digits in the order that suits
+// the keys (sort.hip), and the sweep that writes pos and crd of all levels at once from the sorted keys and finds entries given
+// twice on the way (levels.hip; formats with every level but the innermost dense have a kernel of their own here).  The
+// sorted values are the values array, or go to their positions in that sweep where the innermost level is dense.  Only level
+// sizes and the error flags travel to the host.
 #include <algorithm>
 #include "spmi_internal.h"
 

@@ -436,13 +436,14 @@ sp_status spmi_radix_sort_pairs(uint64_t *keys, const void *vals, int payload_by
                                 hipStream_t st, uint64_t **keys_out, const void **vals_out);
 // The same sort (same arguments, same stability) with the most significant digits first: two passes over device memory, the
 // rest inside the LDS.  Only for inputs that spmi_msd_sort_suits() accepted: enough entries, keys wide enough, and (from a
-// sampled histogram of the top 16 key bits, samp_ready when the caller has it already; synchronises the stream) few entries
-// in groups of equal top 16 key bits too large for the LDS, none of them huge.
+// sampled histogram of the top 16 key bits, samp_ready when the caller has it already; synchronises the stream) either few
+// entries in groups of equal top 16 key bits too large for the LDS, none of them huge, or all groups of about a size that
+// the larger finishing kernel holds.
 //
 // Whoever makes the keys can fill in, on the way, what the first pass would otherwise read them for (sp_msd_plan, empty when
 // this sort is out of the question): for the tile e / kSpmiMsdTile of entry e, ctr[digit * tiles + tile] counts the entries
 // whose digit is (key >> digit_shift) & 255 (every word written, zero included), and samp[(key >> samp_shift) & 0xffff]
-// counts every 64th entry (e % 64 == 0; samp arrives zeroed).
+// counts one entry of 64 (entry e with e % 64 == spmi_sampled_place(e / 64); samp arrives zeroed).
 #ifndef SPMI_SORT_T
 #define SPMI_SORT_T 256
 #endif
