@@ -1,6 +1,6 @@
 """SpMM where rows are long: windows that one row fills, and even rows of medium length, which have a kernel of their own; at
 the lengths where the choice changes, with a row that is longer than the others by just as much as still counts as even, rows
-without entries, widths with and without 16-byte pieces, and a row that crosses more than 64 windows.  Against the CPU checker."""
+without entries, widths with and without 16-byte pieces, and a row that crosses more than 64 windows.  Against the oracle."""
 import numpy as np
 import pytest
 import torch

@@ -1,5 +1,5 @@
 """MTTKRP's padded copies of a factor matrix: made where gathers outnumber the rows, in 16-byte pieces or element by element, and
-not where a long mode has few entries (the copy would be most of the work, and stay with the tensor).  Against the CPU checker."""
+not where a long mode has few entries (the copy would be most of the work, and stay with the tensor).  Against the oracle."""
 import numpy as np
 import pytest
 import torch
