@@ -1,0 +1,1124 @@
+// The storage builder's sort by buckets (arXiv 2202.04305, Section 4.2: the entries of the coordinate scheme are brought into the
+// level order of the target format before its arrays are built).  For entries with distinct keys: the order of equal keys is not
+// kept, they are only reported (sort.hip has the stable sorts).
+//
+// The key range is cut into buckets by splitters taken from a sorted sample, so that buckets hold about the same number of
+// entries whatever the pattern is; entries are moved straight from where the caller has them (coordinates, or keys made from
+// another encoding) into their buckets; a block then sorts one bucket in the LDS and writes the finished arrays.
+//
+//   sample      up to 32768 keys, sorted in runs of 1024, ranked against each other: the splitters
+//   partition   a block takes a tile of entries, finds every entry's bucket, reserves room in each bucket with one atomic add, orders
+//               the tile by bucket in the LDS and writes runs.  No counting pass: a bucket's room is what the sample says
+//               plus six standard deviations.  Keys shrink to 32 bits where no bucket spans more (multiples of 2^32 are
+//               splitters too): 12 bytes per entry from here on.
+//   second partition, above 4 M entries: the same inside each bucket, splitters from a fresh sample of it
+//   finish      a block per bucket: sorted by value intervals in the LDS, then crd, pos and values leave (levels above the innermost
+//               all dense), or the sorted keys and values (the level sweep does the rest)
+//
+// Should a bucket get more entries than its room (a sample that misleads, or many equal keys), nothing is written out of
+// bounds, the build is marked and the caller builds again with the stable sorts.
+//
+// What bounds it: memory.  Per entry of a CSR matrix in f64: 24 bytes read and 12 written, 12 and 12, 12 and 12.
+// Reserving instead of counting first, 16.9 M entries: 128 us for the first partition into 256 buckets (4.7 TB/s), against
+// 70 for a counting pass, 25 to scan its table and 90 to move.
+#include <algorithm>
+#include <cmath>
+#include "spmi_internal.h"
+
+namespace {
+
+constexpr int kMaxBuckets = 3072;             // of the first partition
+constexpr int kCells = 2048;                  // equal parts of the key range, each knowing which buckets it meets
+constexpr int kRun = 1024;                    // sampled keys a block sorts
+constexpr int kMaxSample = 32 * kRun;
+constexpr int kSubSample = 8192;              // most keys sampled inside one bucket
+constexpr int kShare = 48;                    // sampled keys per final bucket
+constexpr int kShareFirst = 32;               // sampled keys per bucket that is partitioned again
+constexpr int kPR = 12;                       // partition: entries per thread
+constexpr int kPT = 512, kWideT = 1024;       // its threads; a larger tile where there are more than kPT buckets
+constexpr int kSmallR = 2;                    // entries per thread where larger tiles would leave most of the chip idle
+constexpr int kFT = 256, kFE = 16;            // finishing kernel: threads, entries per thread
+constexpr int kCap = kFT * kFE;               // entries a block sorts in the LDS
+constexpr int kTarget = 2048;                 // entries per final bucket where a sample cuts them
+constexpr int kExact = 3456;                  // the same where they are counted first
+constexpr int kPartCells = 16384;             // equal intervals of a bucket whose entries are counted
+constexpr int kHeavy = 512;                   // more entries than this in one of them: a sample cuts the bucket (kExact + kHeavy < kCap)
+constexpr int kFirst = 65536;                 // entries per bucket of the first of two partitions
+constexpr int kCells1 = 2 * kFT;              // equal intervals of a final bucket, each then cut by what it holds
+constexpr int kCrowd = 64;                    // more keys than this in one interval: left to finish_crowded_kernel
+
+struct source {
+    const int64_t *coord[SP_MAX_RANK];   // by level, or
+    const uint64_t *keys;                // the keys themselves (coord unused)
+    int64_t size[SP_MAX_RANK];
+    int rank;
+};
+
+// key of entry e; a coordinate out of range sets bad and makes the key 0
+__device__ __forceinline__ uint64_t key_of(const source &s, int64_t e, bool &bad)
+{
+    if (s.keys) return s.keys[e];
+    uint64_t key = 0;
+    bool b = false;
+    for (int l = 0; l < s.rank; ++l) {
+        const int64_t c = s.coord[l][e];
+        b |= (c < 0) | (c >= s.size[l]);
+        key = key * (uint64_t)s.size[l] + (uint64_t)c;
+    }
+    bad |= b;
+    return b ? 0 : key;
+}
+
+__device__ __forceinline__ uint32_t scramble(uint32_t x)
+{
+    x ^= x >> 16; x *= 0x7feb352du;
+    x ^= x >> 15; x *= 0x846ca68bu;
+    return x ^ (x >> 16);
+}
+
+// position of sample i of S among n entries: one per stretch of n / S, at a scrambled place in it (entries often come in an order
+// with a period)
+__device__ __forceinline__ int64_t sampled_position(uint32_t i, uint32_t S, int64_t n)
+{
+    const int64_t at = (int64_t)(((double)i + (double)scramble(i) * 0x1p-32) * ((double)n / (double)S));
+    return at < n ? at : n - 1;
+}
+
+// Bitonic sort of S numbers (a power of two, 1024 * E at most) by a block of 1024 threads: thread t holds numbers t, t + 1024, ...  Steps
+// between lanes of a wave are shuffles, steps of 1024 and more stay in the thread, the others go through the LDS.  Sorted numbers
+// are left in key.
+template <int E>
+__device__ __forceinline__ void block_sort(uint32_t (&x)[E], uint32_t S, uint32_t *key)
+{
+    const uint32_t tid = threadIdx.x;
+#pragma unroll 1
+    for (uint32_t size = 2; size <= S; size *= 2) {
+#pragma unroll 1
+        for (uint32_t half = size / 2; half > 0; half /= 2) {
+            if (half >= 1024) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+#pragma unroll
+                    for (int h = 1; h < E; h *= 2) {
+                        if ((e & h) == 0 && half == (uint32_t)h * 1024u && (uint32_t)(e | h) * 1024u < S) {
+                            const bool up = ((tid + (uint32_t)e * 1024u) & size) == 0;
+                            const uint32_t a = x[e], c = x[e | h];
+                            x[e] = (a < c) == up ? a : c;
+                            x[e | h] = (a < c) == up ? c : a;
+                        }
+                    }
+                }
+                continue;
+            }
+            if (half >= 64) {
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if (tid + (uint32_t)e * 1024u < S) key[tid + e * 1024] = x[e];
+                __syncthreads();
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const uint32_t i = tid + (uint32_t)e * 1024u;
+                if ((uint32_t)e * 1024u < S) {
+                    const uint32_t o = half >= 64 ? key[(i ^ half) < S ? i ^ half : 0u] : (uint32_t)__shfl_xor((int)x[e], (int)half, 64);
+                    const bool keep_less = ((i & half) == 0) == ((i & size) == 0);
+                    x[e] = (x[e] < o) == keep_less ? x[e] : o;
+                }
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (tid + (uint32_t)e * 1024u < S) key[tid + e * 1024] = x[e];
+    __syncthreads();
+}
+
+// A block sorts kRun sampled keys (their upper 32 bits).
+__global__ __launch_bounds__(kRun) void sample_runs_kernel(source s, int64_t n, uint32_t S, int shift, uint32_t *__restrict__ runs)
+{
+    __shared__ uint32_t key[kRun];
+    const uint32_t i = blockIdx.x * kRun + threadIdx.x;
+    bool bad = false;
+    uint32_t x[1] = {(uint32_t)(key_of(s, sampled_position(i, S, n), bad) >> shift)};
+    block_sort<1>(x, kRun, key);
+    runs[i] = key[threadIdx.x];
+}
+
+// Every sampled key's place among all of them, from a binary search in each of the other runs (all runs in the LDS); those whose
+// place begins a share of S / Q become splitters.  The multiples of 2^32 get their places the same way.
+constexpr int kRankT = 256;
+__global__ __launch_bounds__(kRankT) void sample_ranks_kernel(const uint32_t *__restrict__ runs, uint32_t S, int shift, uint32_t Q, uint32_t F,
+                                                              uint32_t *__restrict__ splitter, uint32_t *__restrict__ forced_rank)
+{
+    extern __shared__ __align__(16) uint32_t key[];
+    for (uint32_t i = threadIdx.x; i < S / 4; i += kRankT) ((uint4 *)key)[i] = ((const uint4 *)runs)[i];
+    __syncthreads();
+    const uint32_t i = blockIdx.x * kRankT + threadIdx.x, nruns = S / kRun;
+    if (i >= S + F) return;
+    const uint32_t mine = i < S ? key[i] : (uint32_t)(((uint64_t)(i - S + 1) << 32) >> shift);
+    const uint32_t own = i < S ? i / kRun : nruns;
+    uint32_t rank = i < S ? i % kRun : 0;
+    for (uint32_t r0 = 0; r0 < nruns; r0 += 4) {
+        uint32_t at[4] = {0, 0, 0, 0};                       // keys of the run that come before mine: equal ones of an earlier run do
+#pragma unroll
+        for (uint32_t w = kRun / 2; w > 0; w >>= 1) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t r = r0 + j < nruns ? r0 + j : r0;
+                const uint32_t o = key[r * kRun + at[j] + w - 1];
+                if (o < mine || (o == mine && r < own && i < S)) at[j] += w;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t r = r0 + j;
+            if (r < nruns && r != own) {
+                const uint32_t o = key[r * kRun + at[j]];    // at <= kRun - 1 so far: one more step
+                rank += at[j] + ((o < mine || (o == mine && r < own && i < S)) ? 1u : 0u);
+            }
+        }
+    }
+    if (i >= S) { forced_rank[i - S] = rank; return; }
+    const uint32_t j = (uint32_t)(((uint64_t)rank * Q + S - 1) / S);
+    if (j >= 1 && j < Q && (uint32_t)(((uint64_t)j * S) / Q) == rank) splitter[j - 1] = mine;
+}
+
+// Room for a bucket that d of S sampled keys fell into: its share of n plus six standard deviations and a little.
+__host__ __device__ inline uint64_t room_for(double d, double S, double n)
+{
+    const double r = n / S * (d + 6.0 * sqrt(d + 4.0) + 10.0);
+    return ((uint64_t)(r < n ? r : n) + 31u) & ~(uint64_t)15u;
+}
+
+struct level1 {
+    uint64_t *lo;             // [B + 1] smallest key of each bucket; lo[B] = the end of the key range
+    uint32_t *start, *end;    // [B] room of each bucket
+    uint32_t *cur;            // [B] where the next entry goes (beyond end: overflow)
+    uint16_t *lut;            // [kCells + 1] bucket of the first key of each cell
+    uint32_t *out;            // [B + 1] where the bucket's entries end up in the sorted order
+    uint32_t *sub0;           // [B + 1] first part of each bucket (two partitions)
+    uint32_t *tile0;          // [B + 1] first tile of each bucket
+    uint32_t *room2;          // [B] where the room of its parts begins
+    uint32_t *used;           // [B] how many parts it has (those after them stay empty)
+    int B;
+};
+
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *wsum, uint32_t &total)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const uint32_t incl = wave_inclusive_scan(v, lane);
+    __syncthreads();
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - v;
+    total = 0;
+    for (int w = 0; w < waves; ++w) { before += w < wave ? wsum[w] : 0u; total += wsum[w]; }
+    return before;
+}
+
+// One block: the splitters and the multiples of 2^32 merged into the buckets' lower ends, room for each of them, the cells' table.
+__global__ __launch_bounds__(1024) void buckets_kernel(const uint32_t *__restrict__ splitter, const uint32_t *__restrict__ forced_rank, uint32_t S,
+                                                       int shift, uint32_t Q, uint32_t F, uint64_t total, int cell_shift, int64_t n, level1 t)
+{
+    __shared__ uint64_t lo[kMaxBuckets + 1];
+    __shared__ uint32_t rank[kMaxBuckets + 1];
+    __shared__ uint32_t wsum[16];
+    const int tid = threadIdx.x;
+    const uint32_t B = Q + F;
+    if (tid == 0) { lo[0] = 0; rank[0] = 0; lo[B] = total; rank[B] = S; }
+    for (uint32_t i = tid; i + 1 < Q; i += 1024) {
+        const uint64_t v = (uint64_t)splitter[i] << shift;
+        const uint32_t f = (uint32_t)((v >> 32) < F ? (v >> 32) : F);
+        lo[1 + i + f] = v;
+        rank[1 + i + f] = (uint32_t)(((uint64_t)(i + 1) * S) / Q);
+    }
+    for (uint32_t j = tid; j < F; j += 1024) {
+        const uint64_t v = (uint64_t)(j + 1) << 32;
+        uint32_t a = 0, z = Q - 1;                               // splitters below v
+        while (a < z) {
+            const uint32_t mid = (a + z) / 2;
+            if (((uint64_t)splitter[mid] << shift) < v) a = mid + 1;
+            else z = mid;
+        }
+        lo[1 + j + a] = v;
+        rank[1 + j + a] = forced_rank[j];
+    }
+    __syncthreads();
+    uint32_t run = 0;
+    for (uint32_t b0 = 0; b0 < B; b0 += 1024) {
+        const uint32_t b = b0 + tid;
+        uint32_t room = 0;
+        if (b < B) {
+            const uint32_t d = rank[b + 1] > rank[b] ? rank[b + 1] - rank[b] : 0u;
+            room = S ? (uint32_t)room_for((double)d, (double)S, (double)n) : (uint32_t)((n + 31) & ~(int64_t)15);
+        }
+        uint32_t all;
+        const uint32_t at = run + block_exclusive_scan(room, wsum, all);
+        run += all;
+        if (b < B) { t.lo[b] = lo[b]; t.start[b] = at; t.end[b] = at + room; t.cur[b] = at; }
+    }
+    if (tid == 0) t.lo[B] = total;
+    for (int c = tid; c <= kCells; c += 1024) {
+        const uint64_t first = (uint64_t)c << cell_shift;
+        uint32_t a = 0, z = B - 1;                               // last bucket that begins at or before the cell
+        while (a < z) {
+            const uint32_t mid = (a + z + 1) / 2;
+            if (lo[mid] <= first) a = mid;
+            else z = mid - 1;
+        }
+        t.lut[c] = (uint16_t)a;
+    }
+}
+
+// The workgroups of a launch go to the eight XCDs in turn: block b takes tile (b / 8) of the (b % 8)-th eighth, so that an XCD
+// runs neighbouring tiles together and the lines that two runs share are completed in one L2.
+inline unsigned round8(uint32_t n) { return (n + 7u) & ~7u; }
+__device__ __forceinline__ uint32_t tile_of_block() { return (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3); }
+
+// The tile in registers (key k, bucket b, payload v; cnt entries, entry r * PT + tid in round r) to its buckets.  cur: LDS counters [B],
+// all zero; stage: LDS, room for the tile's keys and buckets, then for its payloads; next / end: the buckets' places in memory.
+// Entries of a bucket that is full go to the tile-sized stretch at `dump`, which nobody reads.
+template <typename K, typename P, int PT, int R, int PER>
+__device__ __forceinline__ void move_tile(const K (&k)[R], const uint32_t (&b)[R], const P (&v)[R], int cnt, int B, uint32_t *cur, uint32_t *wsum,
+                                          void *stage, uint32_t *__restrict__ next, const uint32_t *__restrict__ end, uint32_t dump,
+                                          K *__restrict__ kout, P *__restrict__ vout)
+{
+    constexpr int T = PT * R;
+    K *sk = (K *)stage;
+    uint16_t *sb = (uint16_t *)(sk + T);
+    P *sv = (P *)stage;
+    const int tid = threadIdx.x;
+    uint32_t slot[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * PT + tid < cnt) slot[r] = atomicAdd(&cur[b[r]], 1u);
+    __syncthreads();
+    const int per = (B + PT - 1) / PT;                             // <= PER consecutive buckets per thread
+    uint32_t g[PER], tot = 0, all;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int x = tid * per + j;
+        g[j] = 0;
+        if (j < per && x < B) {
+            const uint32_t c = cur[x];
+            tot += c;
+            if (c) {
+                g[j] = atomicAdd(&next[x], c);
+                if (g[j] + c > end[x] || g[j] + c < g[j]) g[j] = dump;
+            }
+        }
+    }
+    uint32_t start = block_exclusive_scan(tot, wsum, all);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int x = tid * per + j;
+        if (j < per && x < B) {
+            const uint32_t c = cur[x];
+            cur[x] = start;
+            g[j] -= start;
+            start += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r * PT + tid < cnt) {
+            slot[r] += cur[b[r]];
+            sk[slot[r]] = k[r];
+            sb[slot[r]] = (uint16_t)b[r];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int x = tid * per + j;
+        if (j < per && x < B) cur[x] = g[j];
+    }
+    __syncthreads();
+    uint32_t q[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int s = r * PT + tid;
+        if (s < cnt) {
+            q[r] = cur[sb[s]] + (uint32_t)s;
+            kout[q[r]] = sk[s];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * PT + tid < cnt) sv[slot[r]] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int s = r * PT + tid;
+        if (s < cnt) vout[q[r]] = sv[s];
+    }
+}
+
+template <typename K, typename P>
+constexpr size_t stage_bytes(int tile) { return (size_t)tile * (sizeof(K) + 2 > sizeof(P) ? sizeof(K) + 2 : sizeof(P)); }
+
+// First partition.  Loads are marked as read once, so that the L2 keeps the lines that are being written (101 -> 91 us for the move
+// alone, 16.9 M entries in 512 buckets).
+template <typename K, typename P, int PT, int R, int PER>
+__global__ __launch_bounds__(PT) void partition_kernel(source s, const P *__restrict__ vin, int64_t n, level1 t, int cell_shift, uint32_t dump,
+                                                        K *__restrict__ kout, P *__restrict__ vout, int *__restrict__ flags)
+{
+    constexpr int T = PT * R;
+    extern __shared__ __align__(16) unsigned char lds[];
+    uint32_t *cur = (uint32_t *)lds;                                 // [B], padded to 16 bytes
+    __shared__ uint32_t wsum[PT / 64];
+    void *stage = lds + (((size_t)t.B * 4 + 15) & ~(size_t)15);
+    uint64_t *lo = (uint64_t *)stage;                                // the buckets' table lies where the tile is staged later
+    uint16_t *lut = (uint16_t *)(lo + t.B);
+    const uint32_t tile = tile_of_block();
+    const int64_t e0 = (int64_t)tile * T;
+    if (e0 >= n) return;
+    const int cnt = n - e0 < T ? (int)(n - e0) : T, tid = threadIdx.x;
+    uint64_t key[R];
+    P v[R];
+    uint32_t b[R];
+    bool any_bad = false;
+    uint32_t bad = 0;
+    if (s.keys) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = r * PT + tid;
+            key[r] = __builtin_nontemporal_load(s.keys + e0 + (i < cnt ? i : cnt - 1));
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) key[r] = 0;
+        for (int l = 0; l < s.rank; ++l) {
+            const int64_t *__restrict__ c = s.coord[l] + e0;
+            int64_t x[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int i = r * PT + tid;
+                x[r] = __builtin_nontemporal_load(c + (i < cnt ? i : cnt - 1));
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (x[r] < 0 || x[r] >= s.size[l]) bad |= 1u << r;
+                key[r] = key[r] * (uint64_t)s.size[l] + (uint64_t)x[r];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * PT + tid;
+        v[r] = __builtin_nontemporal_load(vin + e0 + (i < cnt ? i : cnt - 1));
+    }
+    for (int i = tid; i < t.B; i += PT) { cur[i] = 0; lo[i] = t.lo[i]; }
+    for (int i = tid; i <= kCells; i += PT) lut[i] = t.lut[i];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if ((bad >> r) & 1u) { key[r] = 0; any_bad = true; }
+        const uint32_t c = (uint32_t)(key[r] >> cell_shift);
+        uint32_t a = lut[c], z = lut[c + 1];
+        while (a < z) {
+            const uint32_t mid = (a + z + 1) / 2;
+            if (lo[mid] <= key[r]) a = mid;
+            else z = mid - 1;
+        }
+        b[r] = a;
+    }
+    if (any_bad) atomicOr(&flags[0], 1);
+    __syncthreads();
+    K k[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) k[r] = (K)key[r];
+    move_tile<K, P, PT, R, PER>(k, b, v, cnt, t.B, cur, wsum, stage, t.cur, t.end, dump, kout, vout);
+}
+
+struct level2 {
+    uint64_t *lo;             // [parts + 1]
+    uint32_t *start, *end, *cur;
+    uint16_t *tile_bucket;    // [tiles] bucket a tile of the second partition belongs to
+};
+
+__device__ __forceinline__ uint32_t sub_samples(uint32_t parts)
+{
+    uint32_t s = 64;
+    while (s < parts * (uint32_t)kShare && s < (uint32_t)kSubSample) s *= 2;
+    return s;
+}
+
+// One block, after the first partition: the sizes of the buckets are known.  Where each begins in the sorted order, and, for a second
+// partition, its parts, tiles and their room.
+__global__ __launch_bounds__(1024) void bucket_sizes_kernel(level1 t, int two, uint32_t tile, uint32_t room2_end, int *__restrict__ flags)
+{
+    __shared__ uint32_t wsum[16];
+    uint32_t out = 0, sub = 0, tiles = 0, room = 0;
+    for (int b0 = 0; b0 < t.B; b0 += 1024) {
+        const int b = b0 + (int)threadIdx.x;
+        uint32_t cnt = 0, parts = 0, nt = 0, need = 0;
+        if (b < t.B) {
+            cnt = t.cur[b] - t.start[b];
+            const uint32_t cap = t.end[b] - t.start[b];
+            if (cnt > cap) flags[2] = 1;
+            if (two) {
+                const uint32_t held = cnt < cap ? cnt : cap;
+                parts = held > (uint32_t)kTarget ? (held + kTarget - 1) / kTarget : 1u;
+                nt = (held + tile - 1) / tile;
+                if (parts == 1) need = (held + 15u) & ~15u;
+                else {
+                    const uint32_t S = sub_samples(parts);
+                    need = parts * (uint32_t)room_for((double)S / (double)parts, (double)S, (double)held);
+                }
+            }
+        }
+        uint32_t all;
+        const uint32_t o = out + block_exclusive_scan(cnt, wsum, all);
+        out += all;
+        if (b < t.B) t.out[b] = o;
+        if (!two) continue;                                          // uniform
+        const uint32_t s = sub + block_exclusive_scan(parts, wsum, all);
+        sub += all;
+        const uint32_t ti = tiles + block_exclusive_scan(nt, wsum, all);
+        tiles += all;
+        uint32_t r = room + block_exclusive_scan(need, wsum, all);
+        room += all;
+        if (b < t.B) {
+            if (r > room2_end || need > room2_end - r) { flags[2] = 1; r = 0; }
+            t.sub0[b] = s; t.tile0[b] = ti; t.room2[b] = r;
+        }
+    }
+    if (threadIdx.x == 0) {
+        t.out[t.B] = out;
+        if (two) { t.sub0[t.B] = sub; t.tile0[t.B] = tiles; }
+    }
+}
+
+// Block = bucket: splitters of its parts.  Its keys are counted by kPartCells equal intervals of its range; parts end where the count
+// passes their share.  Where an interval holds too much for that, a sorted sample of the bucket gives the splitters instead.
+// Both read little: 4 bytes per entry, 20 us for 16.9 M.
+template <typename K>
+__global__ __launch_bounds__(1024) void parts_kernel(level1 t, level2 u, const K *__restrict__ keys, uint64_t total, const int *__restrict__ flags)
+{
+    __shared__ uint32_t key[kSubSample];                             // counts, then what comes before; or the sample
+    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t heavy;
+    const int b = blockIdx.x, tid = threadIdx.x;
+    if (flags[2]) return;
+    const uint32_t s0 = t.sub0[b], room = t.sub0[b + 1] - s0, cnt = t.cur[b] - t.start[b];
+    const uint64_t lo = t.lo[b], range = t.lo[b + 1] - lo;
+    const K *__restrict__ kp = keys + t.start[b];
+    for (uint32_t i = t.tile0[b] + tid; i < t.tile0[b + 1]; i += 1024) u.tile_bucket[i] = (uint16_t)b;
+    if (b == t.B - 1 && tid == 0) u.lo[s0 + room] = total;
+    const uint32_t base = t.room2[b], exact = (cnt + (uint32_t)kExact - 1) / (uint32_t)kExact;
+    if (exact <= 1) {
+        if (tid == 0) t.used[b] = 1;
+        for (uint32_t j = tid; j < room; j += 1024) {
+            const uint32_t at = base + (j ? cnt : 0u);
+            u.lo[s0 + j] = j ? t.lo[b + 1] : lo;
+            u.start[s0 + j] = u.cur[s0 + j] = at;
+            u.end[s0 + j] = base + cnt;
+        }
+        return;
+    }
+    const int bits = range > 1 ? 64 - __clzll((long long)(range - 1)) : 0, cshift = bits > 14 ? bits - 14 : 0;
+    static_assert(kPartCells == 1 << 14 && kPartCells == 2 * kSubSample, "intervals of a bucket, two to a word");
+    if (tid == 0) heavy = 0;
+#pragma unroll
+    for (int i = 0; i < kSubSample / 1024; ++i) key[i * 1024 + tid] = 0;
+    __syncthreads();
+    for (uint32_t i = tid; i < cnt; i += 16 * 1024) {
+        K x[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = kp[i + e * 1024 < cnt ? i + e * 1024 : cnt - 1];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            // 16-bit counts; more than 65535 keys in one interval would spoil its neighbour's: the parts overflow then
+            const uint32_t cell = (uint32_t)((uint64_t)(K)(x[e] - (K)lo) >> cshift);
+            if (i + e * 1024 < cnt) atomicAdd(&key[cell >> 1], 1u << ((cell & 1u) * 16u));
+        }
+    }
+    __syncthreads();
+    // eight words per thread, from the LDS in an order without bank conflicts
+    uint32_t tot = 0, most = 0, all;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const uint32_t word = tid * 8 + ((e + tid) & 7);
+        const uint32_t x = key[word], a = x & 0xffffu, z = x >> 16;
+        tot += a + z;
+        most = a > most ? a : most;
+        most = z > most ? z : most;
+    }
+    if (most > (uint32_t)kHeavy) heavy = 1;
+    uint32_t before = block_exclusive_scan(tot, wsum, all);
+    if (!heavy && all == cnt) {
+        // part j begins with the first interval that at least j * cnt / exact entries lie before.  A thread whose sixteen intervals
+        // hold no such place has nothing to look for.
+        const float share = (float)cnt / (float)exact;
+        uint32_t j = (uint32_t)((float)before / share);              // first j with j * cnt > before * exact, from one below it
+        j = j > 1 ? j - 1 : 1;
+        while (j < exact && (uint64_t)j * cnt <= (uint64_t)before * exact) ++j;
+        if (j < exact && (uint64_t)j * cnt <= (uint64_t)(before + tot) * exact) {
+            for (uint32_t e = 0; e < 16; ++e) {
+                const uint32_t after = before + ((key[tid * 8 + (e >> 1)] >> ((e & 1u) * 16u)) & 0xffffu);
+                for (; j < exact && (uint64_t)j * cnt <= (uint64_t)after * exact; ++j) {
+                    u.lo[s0 + j] = lo + ((uint64_t)(tid * 16 + e + 1) << cshift);
+                    u.start[s0 + j] = u.cur[s0 + j] = base + after;
+                    u.end[s0 + j - 1] = base + after;
+                }
+                before = after;
+            }
+        }
+        if (tid == 0) {
+            t.used[b] = exact;
+            u.lo[s0] = lo;
+            u.start[s0] = u.cur[s0] = base;
+            u.end[s0 + exact - 1] = base + cnt;
+        }
+        for (uint32_t j = exact + tid; j < room; j += 1024) {
+            u.lo[s0 + j] = t.lo[b + 1];
+            u.start[s0 + j] = u.cur[s0 + j] = u.end[s0 + j] = base + cnt;
+        }
+        return;
+    }
+    __syncthreads();
+    if (tid == 0) t.used[b] = room;
+    const uint32_t S = sub_samples(room);
+    const int shift = bits > 32 ? bits - 32 : 0;
+    auto sampled = [&](uint32_t i) { return (uint32_t)((uint64_t)(K)(kp[sampled_position(i, S, cnt)] - (K)lo) >> shift); };
+    if (S <= 1024) {
+        uint32_t x[1] = {tid < (int)S ? sampled(tid) : 0u};
+        block_sort<1>(x, S, key);
+    } else if (S <= 2048) {
+        uint32_t x[2];
+        for (int e = 0; e < 2; ++e) x[e] = sampled(tid + e * 1024);
+        block_sort<2>(x, S, key);
+    } else {
+        uint32_t x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = (uint32_t)e * 1024u < S ? sampled(tid + e * 1024) : 0u;
+        block_sort<8>(x, S, key);
+    }
+    const uint32_t cap = room > 1 ? (uint32_t)room_for((double)S / (double)room, (double)S, (double)cnt) : (cnt + 15u) & ~15u;
+    for (uint32_t j = tid; j < room; j += 1024) {
+        const uint32_t at = base + j * cap;
+        u.lo[s0 + j] = j ? lo + ((uint64_t)key[(j * S) / room] << shift) : lo;
+        u.start[s0 + j] = u.cur[s0 + j] = at;
+        u.end[s0 + j] = at + cap;
+    }
+}
+
+constexpr int kDump = kWideT * kPR;          // entries of the largest tile
+constexpr int kMaxParts = 1024;
+// Second partition: a tile lies inside one bucket.
+template <typename K, typename P, int R>
+__global__ __launch_bounds__(kPT) void partition_again_kernel(const K *__restrict__ kin, const P *__restrict__ vin, level1 t, level2 u, uint32_t dump,
+                                                              K *__restrict__ kout, P *__restrict__ vout, const int *__restrict__ flags)
+{
+    constexpr int T = kPT * R;
+    __shared__ uint32_t cur[kMaxParts];
+    __shared__ uint32_t wsum[kPT / 64];
+    __shared__ __align__(16) unsigned char stage[stage_bytes<K, P>(kPT * R)];
+    const uint32_t tile = tile_of_block();
+    if (tile >= t.tile0[t.B] || flags[2]) return;
+    const int bkt = u.tile_bucket[tile], tid = threadIdx.x;
+    const uint32_t s0 = t.sub0[bkt], i0 = (tile - t.tile0[bkt]) * (uint32_t)T, held = t.cur[bkt] - t.start[bkt];
+    const int parts = (int)t.used[bkt], cnt = held - i0 < (uint32_t)T ? (int)(held - i0) : T;
+    const uint32_t e0 = t.start[bkt] + i0;
+    const K lo = (K)t.lo[bkt];
+    K *split = (K *)stage;
+    K k[R];
+    P v[R];
+    uint32_t b[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kPT + tid;
+        k[r] = __builtin_nontemporal_load(kin + e0 + (i < cnt ? i : cnt - 1));
+        v[r] = __builtin_nontemporal_load(vin + e0 + (i < cnt ? i : cnt - 1));
+    }
+    for (int i = tid; i < parts; i += kPT) { cur[i] = 0; split[i] = (K)((K)u.lo[s0 + i] - lo); }
+    __syncthreads();
+    int step = 1;
+    while (2 * step < parts) step *= 2;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const K d = (K)(k[r] - lo);
+        int a = 0;
+        for (int w = step; w > 0; w >>= 1)
+            if (a + w < parts && split[a + w] <= d) a += w;
+        b[r] = (uint32_t)a;
+    }
+    __syncthreads();
+    move_tile<K, P, kPT, R, (kMaxParts + kPT - 1) / kPT>(k, b, v, cnt, parts, cur, wsum, stage, u.cur + s0, u.end + s0, dump, kout, vout);
+}
+
+// ---- finish ---------------------------------------------------------------------------------
+// A final bucket, as the finishing kernels take it.
+struct final_bucket {
+    uint64_t lo, next;        // its smallest key, the next bucket's
+    uint32_t start, cnt;      // where its entries are, how many; kOverflow: more than fit
+    uint32_t out;             // where they end up in the sorted order
+    uint32_t scale;           // (distance from lo, shifted) * scale >> 32: its place in the bucket's range in 31 bits
+    int shift;                // > 0: distances to the left, < 0: to the right, so that the range has 32 bits
+};
+constexpr uint32_t kOverflow = 0x80000000u;
+
+struct final_args {
+    const final_bucket *bucket;
+    const uint32_t *count;               // DEVICE: number of final buckets (null: `most`)
+    uint32_t most;
+    int64_t n;
+    uint32_t *left;                      // [most] buckets with a crowded interval: finish_crowded_kernel takes them
+    int *flags;
+    // what leaves: the keys (uint64), or crd / pos of an innermost compressed level under dense ones
+    uint64_t *keys;
+    void *crd, *pos;
+    int32_t *rowblk;                     // row of every kSpmiStreamT-th entry (may be null)
+    int64_t nblocks;
+    spmi_divisor inner;
+    int64_t rows;
+    int pw, cw;
+};
+
+// Thread = final bucket: its description, from the partitions' tables.  One partition: start .. out by final bucket; two: out by
+// bucket of the first one, whose parts [sub0[b], sub0[b + 1]) are block b's.
+__global__ __launch_bounds__(256) void final_buckets_kernel(const uint64_t *__restrict__ lo, const uint32_t *__restrict__ start, const uint32_t *__restrict__ end,
+                                                            const uint32_t *__restrict__ cur, const uint32_t *__restrict__ out,
+                                                            const uint32_t *__restrict__ sub0, uint32_t count, final_bucket *__restrict__ bucket, final_args f)
+{
+    __shared__ uint32_t wsum[4];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !f.keys) {            // the ends of the arrays
+        if (f.pw == 32) ((int32_t *)f.pos)[f.rows] = (int32_t)f.n;
+        else ((int64_t *)f.pos)[f.rows] = f.n;
+        if (f.rowblk) { f.rowblk[0] = 0; f.rowblk[f.nblocks] = (int32_t)f.rows; }
+    }
+    if (f.flags[2]) return;
+    const uint32_t first = sub0 ? sub0[blockIdx.x] : blockIdx.x * 256u;
+    const uint32_t last = sub0 ? sub0[blockIdx.x + 1] : (first + 256u < count ? first + 256u : count);
+    uint32_t at = sub0 ? out[blockIdx.x] : 0u;
+    for (uint32_t b0 = first; b0 < last; b0 += 256) {
+        const uint32_t b = b0 + threadIdx.x;
+        final_bucket w;
+        w.cnt = 0;
+        if (b < last) {
+            w.start = start[b];
+            w.cnt = cur[b] - w.start;
+        }
+        uint32_t all, before = block_exclusive_scan(w.cnt, wsum, all);
+        if (b < last) {
+            w.out = sub0 ? at + before : out[b];
+            w.lo = lo[b];
+            w.next = lo[b + 1];
+            const uint64_t range = w.next - w.lo;
+            const int bits = range > 1 ? 64 - __clzll((long long)(range - 1)) : 0;
+            w.shift = bits ? 32 - bits : 0;
+            const uint64_t steps = bits ? (w.shift >= 0 ? range << w.shift : ((range - 1) >> -w.shift) + 1) : 1;   // in (2^31, 2^32]
+            w.scale = bits ? (uint32_t)((1ull << 63) / steps) : 0u;
+            if (w.cnt > end[b] - w.start || w.cnt > (uint32_t)kCap) { f.flags[3] = 1; w.cnt |= kOverflow; }
+            bucket[b] = w;
+        }
+        at += all;
+    }
+}
+
+// The bucket's keys lie sorted in the LDS as distances from lo: what the format wants of them.
+template <typename K, int T>
+__device__ __forceinline__ void emit_sorted(const final_args &f, const final_bucket &w, const K *dist, uint32_t cnt)
+{
+    if (f.keys) {
+        uint64_t *__restrict__ q = f.keys + w.out;
+        for (uint32_t i = threadIdx.x; i < cnt; i += T) q[i] = w.lo + dist[i];
+        return;
+    }
+    const uint64_t row0 = spmi_div_by(w.lo, f.inner), off = w.lo - row0 * f.inner.d;
+    for (uint32_t i = threadIdx.x; i < cnt; i += T) {
+        const uint64_t x = off + dist[i], row = spmi_div_by(x, f.inner), col = x - row * f.inner.d;
+        const uint32_t at = w.out + i;
+        if (f.cw == 32) ((int32_t *)f.crd)[at] = (int32_t)col;
+        else ((int64_t *)f.crd)[at] = (int64_t)col;
+        if (f.rowblk && (at % (uint32_t)kSpmiStreamT) == 0 && at > 0) f.rowblk[at / (uint32_t)kSpmiStreamT] = (int32_t)(row0 + row);
+    }
+}
+
+// The rows (positions of the level above) that begin in [lo, next) are this bucket's: each looks up its first entry.
+template <typename K, int T>
+__device__ __forceinline__ void emit_rows(const final_args &f, const final_bucket &w, const K *dist, uint32_t cnt)
+{
+    if (f.keys) return;
+    const uint64_t r0 = w.lo == 0 ? 0 : spmi_div_by(w.lo - 1, f.inner) + 1, r1 = w.next == 0 ? 0 : spmi_div_by(w.next - 1, f.inner) + 1;
+    uint32_t top = 1;
+    while (top <= cnt) top *= 2;
+    for (uint64_t r = r0 + threadIdx.x; r < r1; r += T) {
+        const uint64_t first = r * f.inner.d - w.lo;                 // below next - lo: fits K
+        uint32_t a = 0;
+        for (uint32_t s = top / 2; s > 0; s >>= 1)
+            if (a + s <= cnt && (uint64_t)dist[a + s - 1] < first) a += s;
+        if (f.pw == 32) ((int32_t *)f.pos)[r] = (int32_t)(w.out + a);
+        else ((int64_t *)f.pos)[r] = (int64_t)(w.out + a);
+    }
+}
+
+// Distance from a bucket's smallest key -> place in its range, in 31 bits; never decreases with the distance.
+template <typename K>
+__device__ __forceinline__ uint32_t place_in_range(K d, const final_bucket &w)
+{
+    const uint32_t x = sizeof(K) == 4 ? (uint32_t)d << (w.shift & 31) : w.shift >= 0 ? (uint32_t)(d << w.shift) : (uint32_t)(d >> -w.shift);
+    return __umulhi(x, w.scale);
+}
+
+template <typename K, typename P>
+struct finish_lds {
+    static constexpr int kWords = (kFE | 1) * kFT;
+    static constexpr size_t kKeys = kCap * sizeof(K) + (kWords + 1) * 4 + kCells1 * 4, kValues = kCap * sizeof(P);
+    __align__(16) unsigned char stage[kKeys > kValues ? kKeys : kValues];
+    uint32_t wsum[kFT / 64];
+    uint32_t crowded;
+};
+
+// A bucket sorted by value.  Its range is cut into kCells1 equal intervals, each of those into twice as many as it holds
+// entries (rows differ in length, so keys are not spread evenly over a bucket); an entry takes a number in its interval with one
+// returning LDS add, the counts are scanned, the keys are dropped into their intervals, and an entry's place is the
+// interval's start plus the number of smaller keys there.  Counts are 16 bits, two to a word: intervals x and x + words share
+// one, so that one addition per word scans both halves.  (Keys that occur twice may take one place and leave a place as it
+// was: the build ends with an error then.)
+// What bounds it: vector instructions, so a thread has up to sixteen entries and what all entries of a bucket share is worked out
+// before (final_buckets_kernel).
+template <typename K, typename P>
+__global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
+{
+    constexpr int W = kFT / 64;
+    __shared__ finish_lds<K, P> s;
+    const uint32_t b = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (f.flags[2]) {                                                // a bucket overflowed in the first partition: harmless keys, the build will be done again
+        if (f.keys)
+            for (int64_t i = (int64_t)b * kFT + tid; i < f.n; i += (int64_t)f.most * kFT) f.keys[i] = 0;
+        return;
+    }
+    if (b >= (f.count ? *f.count : f.most)) return;
+    const final_bucket w = f.bucket[b];
+    if (tid == 0) { f.left[b] = 0; s.crowded = 0; }
+    const uint32_t cnt = w.cnt;
+    K *dist = (K *)s.stage;
+    uint32_t *bins = (uint32_t *)(dist + kCap), *cells = bins + s.kWords + 1;
+    P *sval = (P *)s.stage;
+    if (cnt & kOverflow) {
+        if (f.keys) for (uint32_t i = tid; i < (cnt & ~kOverflow); i += kFT) f.keys[w.out + i] = 0;
+        else emit_rows<K, kFT>(f, w, dist, 0);
+        return;
+    }
+    if (cnt == 0) {
+        emit_rows<K, kFT>(f, w, dist, 0);
+        return;
+    }
+    const int rounds = (int)((cnt + kFT - 1) / kFT);                 // <= kFE
+    const int per = rounds | 1;                                      // words per thread when they are scanned: odd, no bank conflicts
+    const uint32_t words = (uint32_t)per * kFT;                      // two intervals each
+    K k[kFE];
+    P v[kFE];
+    uint32_t at[kFE], slot[kFE];
+    const K *__restrict__ kp = kin + w.start;
+    const P *__restrict__ vp = vin + w.start;
+#pragma unroll
+    for (int r = 0; r < kFE; ++r) {
+        if (r < rounds) {
+            const uint32_t i = (uint32_t)(r * kFT + tid) < cnt ? (uint32_t)(r * kFT + tid) : cnt - 1;
+            k[r] = __builtin_nontemporal_load(kp + i);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kFE; ++r) {
+        if (r < rounds) {
+            const uint32_t i = (uint32_t)(r * kFT + tid) < cnt ? (uint32_t)(r * kFT + tid) : cnt - 1;
+            v[r] = __builtin_nontemporal_load(vp + i);
+        }
+    }
+    for (int j = 0; j < per; ++j) bins[j * kFT + tid] = 0;
+    for (int j = 0; j < kCells1 / kFT; ++j) cells[j * kFT + tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kFE; ++r) {
+        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) {
+            k[r] -= (K)w.lo;
+            at[r] = place_in_range<K>(k[r], w);
+            atomicAdd(&cells[at[r] >> 22], 1u);
+        }
+    }
+    __syncthreads();
+    static_assert(kCells1 == 512 && kFT == 256, "two cells per thread, nine bits of the place");
+    {
+        const uint32_t c0 = cells[2 * tid], c1 = cells[2 * tid + 1];
+        const uint32_t incl = wave_inclusive_scan(c0 + c1, lane);
+        if (lane == 63) s.wsum[wave] = incl;
+        __syncthreads();
+        uint32_t before = incl - c0 - c1;
+#pragma unroll
+        for (int x = 0; x < W; ++x) before += x < wave ? s.wsum[x] : 0u;
+        cells[2 * tid] = before | (c0 << 16);
+        cells[2 * tid + 1] = (before + c0) | (c1 << 16);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kFE; ++r) {
+        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) {
+            const uint32_t c = cells[at[r] >> 22];
+            // interval: twice what comes before its cell, plus its place in the cell (18 bits) times twice what the cell holds
+            const uint32_t x = 2u * (c & 0xffffu) + (((at[r] >> 4) & 0x3ffffu) * (c >> 16) >> 17);
+            const bool upper = x >= words;
+            const uint32_t word = upper ? x - words : x, half = upper ? 16u : 0u;
+            at[r] = word | (half << 16);
+            slot[r] = (atomicAdd(&bins[word], 1u << half) >> half) & 0xffffu;
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the words, `per` consecutive ones per thread; the upper halves continue after the lower ones' total
+    uint32_t tot = 0;
+    for (int j = 0; j < per; ++j) tot += bins[tid * per + j];
+    const uint32_t incl = wave_inclusive_scan(tot, lane);
+    if (lane == 63) s.wsum[wave] = incl;
+    __syncthreads();
+    uint32_t start = incl - tot, all = 0;
+#pragma unroll
+    for (int x = 0; x < W; ++x) { start += x < wave ? s.wsum[x] : 0u; all += s.wsum[x]; }
+    start += all << 16;
+    for (int j = 0; j < per; ++j) {
+        const uint32_t c = bins[tid * per + j];
+        bins[tid * per + j] = start;
+        start += c;
+    }
+    if (tid == kFT - 1) bins[words] = (all & 0xffffu) | (cnt << 16);
+    __syncthreads();
+    uint32_t longest = 0;
+#pragma unroll
+    for (int r = 0; r < kFE; ++r) {
+        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) {
+            const uint32_t word = at[r] & 0xffffu, half = at[r] >> 16;
+            const uint32_t s0 = (bins[word] >> half) & 0xffffu, len = ((bins[word + 1] >> half) & 0xffffu) - s0;
+            slot[r] += s0;
+            dist[slot[r]] = k[r];
+            at[r] = s0 | (len << 16);
+            longest = len > longest ? len : longest;
+        } else at[r] = 0;
+    }
+    if (longest > (uint32_t)kCrowd) s.crowded = 1;
+    __syncthreads();
+    if (s.crowded) {                                                 // the whole block alike
+        if (tid == 0) f.left[b] = 1;
+        return;
+    }
+    // all rounds side by side, one other key of every interval per step
+    bool dup = false;
+    uint32_t place[kFE];
+#pragma unroll
+    for (int r = 0; r < kFE; ++r) place[r] = at[r] & 0xffffu;
+    for (uint32_t j = 1; j < longest; ++j) {
+#pragma unroll
+        for (int r = 0; r < kFE; ++r) {
+            if (r < rounds) {
+                const uint32_t len = at[r] >> 16;
+                if (j < len) {
+                    const uint32_t x = slot[r] + j, s0 = at[r] & 0xffffu;
+                    const K o = dist[x < s0 + len ? x : x - len];
+                    place[r] += o < k[r] ? 1u : 0u;
+                    dup |= o == k[r];
+                }
+            }
+        }
+    }
+    if (dup) atomicOr(&f.flags[1], 1);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kFE; ++r)
+        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) dist[place[r]] = k[r];
+    __syncthreads();
+    emit_sorted<K, kFT>(f, w, dist, cnt);
+    emit_rows<K, kFT>(f, w, dist, cnt);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kFE; ++r)
+        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) sval[place[r]] = v[r];
+    __syncthreads();
+    for (uint32_t i = tid; i < cnt; i += kFT) vout[w.out + i] = sval[i];
+}
+
+// The buckets the finishing kernel left: entries that crowd in a few intervals (bands, blocks).  Bitonic sort in the LDS, the entry's
+// number travelling with the key.
+template <typename K, typename P>
+__global__ __launch_bounds__(1024) void finish_crowded_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
+{
+    __shared__ K dist[kCap];
+    __shared__ uint16_t idx[kCap];
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (f.flags[2]) return;
+    const uint32_t total = f.count ? *f.count : f.most;
+    for (uint32_t first = blockIdx.x; first < total; first += 64u * gridDim.x) {       // 64 of the block's buckets looked at together
+        const uint64_t mine = (uint64_t)first + (uint64_t)lane * gridDim.x;
+        for (uint64_t todo = __ballot(mine < total && f.left[mine < total ? mine : 0] != 0); todo; todo &= todo - 1) {
+            const uint32_t b = first + (uint32_t)__builtin_ctzll(todo) * gridDim.x;
+            const final_bucket w = f.bucket[b];
+            const uint32_t cnt = w.cnt;
+            uint32_t N = 2;
+            while (N < cnt) N *= 2;
+            for (uint32_t i = tid; i < N; i += 1024) {
+                dist[i] = i < cnt ? (K)(kin[w.start + i] - (K)w.lo) : (K)~(K)0;
+                idx[i] = (uint16_t)i;
+            }
+            __syncthreads();
+            for (uint32_t size = 2; size <= N; size *= 2) {
+                for (uint32_t half = size / 2; half > 0; half /= 2) {
+                    for (uint32_t p = tid; p < N / 2; p += 1024) {
+                        const uint32_t x = 2 * p - (p & (half - 1)), y = x + half;
+                        const K a = dist[x], c = dist[y];
+                        const uint16_t ia = idx[x], ic = idx[y];
+                        const bool greater = a > c || (a == c && ia > ic);             // padding (largest key, largest numbers) stays behind
+                        if (greater == ((x & size) == 0)) { dist[x] = c; dist[y] = a; idx[x] = ic; idx[y] = ia; }
+                    }
+                    __syncthreads();
+                }
+            }
+            bool dup = false;
+            for (uint32_t i = tid; i + 1 < cnt; i += 1024) dup |= dist[i] == dist[i + 1];
+            if (dup) atomicOr(&f.flags[1], 1);
+            emit_sorted<K, 1024>(f, w, dist, cnt);
+            emit_rows<K, 1024>(f, w, dist, cnt);
+            for (uint32_t i = tid; i < cnt; i += 1024) vout[w.out + i] = vin[w.start + idx[i]];
+            __syncthreads();
+        }
+    }
+}
+
+inline size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+template <typename K, typename P>
+sp_status sort_t(const source &src, const P *vals, int64_t n, uint64_t total, int key_bits, const spmi_bucket_plan &plan, const spmi_bucket_out &o,
+                 int *flags, sp_scratch &tmp, hipStream_t st)
+{
+    const uint32_t Q = plan.Q, F = plan.F, S = plan.S;
+    const int B = (int)(Q + F);
+    const bool two = plan.two;
+    const int sshift = key_bits > 32 ? key_bits - 32 : 0;
+    int cell_shift = 0;
+    while (((total - 1) >> cell_shift) >= (uint64_t)kCells) ++cell_shift;
+    // room of the first partition: the shares add up to n, the margins are largest when all buckets are alike
+    uint64_t room1 = (uint64_t)n + 64;
+    if (S) room1 = (uint64_t)((double)n + (double)B * ((double)n / S * (6.0 * sqrt((double)S / B + 4.0) + 10.0) + 32.0)) + 1024;
+    const uint64_t room2 = two ? (uint64_t)(2.2 * (double)n) + (uint64_t)B * 4096 : 0;
+    if (room1 + kDump >= 0xfff00000ull || room2 + kDump >= 0xfff00000ull) return SP_ERR_TOO_LARGE;
+    const uint32_t parts_max = two ? (uint32_t)(n / kTarget) + (uint32_t)B : (uint32_t)B;
+    const uint32_t tiles_max = two ? (uint32_t)(n / (kPT * kPR)) + (uint32_t)B : 1u;
+    K *k1 = (K *)tmp.get((room1 + kDump) * sizeof(K));
+    P *v1 = (P *)tmp.get((room1 + kDump) * sizeof(P));
+    K *k2 = two ? (K *)tmp.get((room2 + kDump) * sizeof(K)) : k1;
+    P *v2 = two ? (P *)tmp.get((room2 + kDump) * sizeof(P)) : v1;
+    // tables
+    size_t bytes = 0;
+    auto place = [&](size_t b) { const size_t at = bytes; bytes += pad256(b); return at; };
+    const size_t a_runs = place((size_t)(S ? S : 4) * 4), a_split = place((size_t)(Q + 1) * 4), a_frank = place((size_t)(F + 1) * 4);
+    const size_t a_lo1 = place((size_t)(B + 1) * 8), a_start1 = place((size_t)B * 4), a_end1 = place((size_t)B * 4), a_cur1 = place((size_t)B * 4);
+    const size_t a_lut = place((size_t)(kCells + 1) * 2), a_out1 = place((size_t)(B + 1) * 4), a_sub0 = place((size_t)(B + 1) * 4);
+    const size_t a_tile0 = place((size_t)(B + 1) * 4), a_room2 = place((size_t)B * 4), a_used = place((size_t)B * 4);
+    const size_t a_lo2 = place((size_t)(parts_max + 1) * 8), a_start2 = place((size_t)parts_max * 4), a_end2 = place((size_t)parts_max * 4);
+    const size_t a_cur2 = place((size_t)parts_max * 4), a_tb = place((size_t)tiles_max * 2);
+    const size_t a_left = place((size_t)parts_max * 4), a_final = place((size_t)parts_max * sizeof(final_bucket));
+    unsigned char *tab = (unsigned char *)tmp.get(bytes);
+    if (!k1 || !v1 || !k2 || !v2 || !tab) return SP_ERR_ALLOC;
+    level1 t;
+    t.lo = (uint64_t *)(tab + a_lo1); t.start = (uint32_t *)(tab + a_start1); t.end = (uint32_t *)(tab + a_end1); t.cur = (uint32_t *)(tab + a_cur1);
+    t.lut = (uint16_t *)(tab + a_lut); t.out = (uint32_t *)(tab + a_out1); t.sub0 = (uint32_t *)(tab + a_sub0); t.tile0 = (uint32_t *)(tab + a_tile0);
+    t.room2 = (uint32_t *)(tab + a_room2); t.used = (uint32_t *)(tab + a_used); t.B = B;
+    level2 u;
+    u.lo = (uint64_t *)(tab + a_lo2); u.start = (uint32_t *)(tab + a_start2); u.end = (uint32_t *)(tab + a_end2); u.cur = (uint32_t *)(tab + a_cur2);
+    u.tile_bucket = (uint16_t *)(tab + a_tb);
+    uint32_t *runs = (uint32_t *)(tab + a_runs), *split = (uint32_t *)(tab + a_split), *frank = (uint32_t *)(tab + a_frank);
+    if (S) {
+        hipLaunchKernelGGL(sample_runs_kernel, dim3(S / kRun), dim3(kRun), 0, st, src, n, S, sshift, runs);
+        if ((size_t)S * 4 > 65536)
+            SP_HIP(hipFuncSetAttribute((const void *)sample_ranks_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSample * 4));
+        hipLaunchKernelGGL(sample_ranks_kernel, dim3((S + F + kRankT - 1) / kRankT), dim3(kRankT), (size_t)S * 4, st, (const uint32_t *)runs, S, sshift, Q, F, split,
+                           frank);
+        SP_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(buckets_kernel, dim3(1), dim3(1024), 0, st, (const uint32_t *)split, (const uint32_t *)frank, S, sshift, Q, F, total, cell_shift, n, t);
+    SP_HIP(hipGetLastError());
+    // first partition
+    const bool small = n < (int64_t)kPT * kPR * 256, wide_tile = !small && B > kPT;
+    const int tile = wide_tile ? kWideT * kPR : small ? kPT * kSmallR : kPT * kPR;
+    const uint32_t tiles = (uint32_t)ceil_div(n, (int64_t)tile);
+    const size_t stage = std::max(stage_bytes<K, P>(tile), (size_t)B * 8 + (kCells + 1) * 2);
+    const size_t lds = (((size_t)B * 4 + 15) & ~(size_t)15) + stage + 16;
+    const uint32_t dump1 = (uint32_t)room1;
+#define SPMI_PART(T_, R_, PER_)                                                                                                    \
+    do {                                                                                                                          \
+        if (lds > 65536) SP_HIP(hipFuncSetAttribute((const void *)partition_kernel<K, P, T_, R_, PER_>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512)); \
+        hipLaunchKernelGGL((partition_kernel<K, P, T_, R_, PER_>), dim3(round8(tiles)), dim3(T_), lds, st, src, vals, n, t, cell_shift, dump1, k1, v1, flags); \
+    } while (0)
+    if (wide_tile) SPMI_PART(kWideT, kPR, kMaxBuckets / kWideT);
+    else if (small && B > kPT) SPMI_PART(kPT, kSmallR, kMaxBuckets / kPT);
+    else if (small) SPMI_PART(kPT, kSmallR, 1);
+    else SPMI_PART(kPT, kPR, 1);
+#undef SPMI_PART
+    hipLaunchKernelGGL(bucket_sizes_kernel, dim3(1), dim3(1024), 0, st, t, two ? 1 : 0, (uint32_t)(kPT * kPR), (uint32_t)room2, flags);
+    SP_HIP(hipGetLastError());
+    if (two) {
+        hipLaunchKernelGGL(parts_kernel<K>, dim3((unsigned)B), dim3(1024), 0, st, t, u, (const K *)k1, total, (const int *)flags);
+        hipLaunchKernelGGL((partition_again_kernel<K, P, kPR>), dim3(round8(tiles_max)), dim3(kPT), 0, st, (const K *)k1, (const P *)v1, t, u, (uint32_t)room2, k2, v2,
+                           (const int *)flags);
+        SP_HIP(hipGetLastError());
+    }
+    final_args f;
+    memset(&f, 0, sizeof(f));
+    final_bucket *bucket = (final_bucket *)(tab + a_final);
+    f.bucket = bucket; f.count = two ? t.sub0 + B : nullptr; f.most = parts_max; f.n = n;
+    f.left = (uint32_t *)(tab + a_left); f.flags = flags;
+    f.keys = o.keys; f.crd = o.crd; f.pos = o.pos; f.rowblk = o.rowblk; f.rows = o.rows; f.pw = o.pw; f.cw = o.cw;
+    f.inner = spmi_make_divisor(o.inner ? o.inner : 1); f.nblocks = ceil_div(n, kSpmiStreamT);
+    hipLaunchKernelGGL(final_buckets_kernel, dim3(two ? (unsigned)B : (unsigned)ceil_div(B, 256)), dim3(256), 0, st, (const uint64_t *)(two ? u.lo : t.lo),
+                       (const uint32_t *)(two ? u.start : t.start), (const uint32_t *)(two ? u.end : t.end), (const uint32_t *)(two ? u.cur : t.cur),
+                       (const uint32_t *)t.out, (const uint32_t *)(two ? t.sub0 : nullptr), (uint32_t)B, bucket, f);
+    hipLaunchKernelGGL((finish_kernel<K, P>), dim3(parts_max), dim3(kFT), 0, st, (const K *)k2, (const P *)v2, (P *)o.values, f);
+    hipLaunchKernelGGL((finish_crowded_kernel<K, P>), dim3(std::min(parts_max, 512u)), dim3(1024), 0, st, (const K *)k2, (const P *)v2, (P *)o.values, f);
+    SP_HIP(hipGetLastError());
+    return SP_OK;
+}
+
+}  // namespace
+
+bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, spmi_bucket_plan *p)
+{
+    memset(p, 0, sizeof(*p));
+    if (n < 1 || total < 1 || key_bits > 48) return false;            // sampled keys keep their upper 32 bits: 16 more may hide a crowd
+    const uint64_t steps = (total - 1) >> 32;                         // multiples of 2^32 inside the key range
+    p->two = n > (int64_t)kTarget * (kMaxSample / kShare);
+    uint64_t Q = p->two ? (uint64_t)std::max<int64_t>(std::min<int64_t>(ceil_div(n, kFirst), 512), ceil_div(n, 4 * kFirst))
+                        : n <= kCap ? 1u : (uint64_t)ceil_div(n, kTarget);
+    const uint64_t most_forced = (uint64_t)std::min<int64_t>(1024, n / kTarget);
+    p->wide = steps > most_forced;
+    p->F = p->wide ? 0u : (uint32_t)steps;
+    if (Q + p->F > (uint64_t)kMaxBuckets) return false;
+    p->Q = (uint32_t)Q;
+    if (Q + p->F > 1) {
+        int64_t S = ceil_div((int64_t)(p->two ? kShareFirst : kShare) * (int64_t)Q, kRun) * kRun;
+        S = std::min<int64_t>(S, kMaxSample);
+        while (S > n) S -= kRun;
+        if (S < kRun) return false;
+        p->S = (uint32_t)S;
+    }
+    return true;
+}
+
+sp_status spmi_bucket_sort(const int64_t *const *level_coords, const uint64_t *keys, const int64_t *level_size, int rank, const void *vals, int payload_bytes,
+                           int64_t n, uint64_t total, int key_bits, const spmi_bucket_plan &plan, const spmi_bucket_out &out, int *flags,
+                           sp_scratch &tmp, hipStream_t st)
+{
+    source s;
+    memset(&s, 0, sizeof(s));
+    s.keys = keys;
+    s.rank = rank;
+    for (int l = 0; l < rank; ++l) { s.coord[l] = keys ? nullptr : level_coords[l]; s.size[l] = level_size[l]; }
+    if (payload_bytes == 4) {
+        if (plan.wide) return sort_t<uint64_t, uint32_t>(s, (const uint32_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
+        return sort_t<uint32_t, uint32_t>(s, (const uint32_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
+    }
+    if (plan.wide) return sort_t<uint64_t, uint64_t>(s, (const uint64_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
+    return sort_t<uint32_t, uint64_t>(s, (const uint64_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
+}

@@ -481,8 +481,8 @@ struct nonempty_probe {
     unsigned long long nz = 0, span = 0;
     bool active = false;
     // the answers come back inside the builder's 64-byte flags block (one copy to the host for everything):
-    // ints 8-9 = the number of non-empty rows, ints 10-11 = the longest run, both as 64-bit values
-    void take(const int *h) { memcpy(&nz, &h[8], 8); memcpy(&span, &h[10], 8); }
+    // ints 8-9 = the number of non-empty rows as a 64-bit value (ints 10-11: the longest run, asked for afterwards)
+    void take(const int *h) { memcpy(&nz, &h[8], 8); }
 };
 
 static bool wants_nonempty(const sp_tensor *t)
@@ -492,17 +492,25 @@ static bool wants_nonempty(const sp_tensor *t)
     return nrows >= 4096 && nrows < ((int64_t)1 << 31) - 1 && t->ncrd[1] != 0;
 }
 
-// flags: the 64 zeroed device bytes of the build (see nonempty_probe for the slots used here); the caller has enqueued
-// pos_stats() with wants_nonempty() true, which counts the non-empty rows into ints 8-9
-static sp_status nonempty_enqueue(const sp_tensor *t, hipStream_t st, int *flags, nonempty_probe &q)
+// the caller has enqueued pos_stats() with wants_nonempty() true, which counts the non-empty rows into ints 8-9 of the flags
+static void nonempty_enqueue(const sp_tensor *t, nonempty_probe &q)
 {
-    if (!wants_nonempty(t)) return SP_OK;
-    if (t->rowblocks.start) {
-        hipLaunchKernelGGL(max_span_kernel, dim3(blocks_for(t->rowblocks.nblocks)), dim3(kThreads), 0, st, (const int32_t *)t->rowblocks.start,
-                           t->rowblocks.nblocks, (unsigned long long *)(flags + 10));
-        SP_HIP(hipGetLastError());
-    }
+    if (!wants_nonempty(t)) return;
     q.nrows = t->npos[1] - 1; q.active = true;
+}
+
+// The longest run of rows in one window, asked for only where it can decide: at least half of the rows hold something, and there are
+// empty ones enough for a long run (a window meets no more than its kSpmiStreamT entries' rows besides them).
+constexpr unsigned long long kLongRun = 65536;
+static sp_status nonempty_span(const sp_tensor *t, int *flags, hipStream_t st, nonempty_probe &q)
+{
+    if (!q.active || !t->rowblocks.start || (int64_t)q.nz * 2 <= q.nrows) return SP_OK;
+    if ((unsigned long long)q.nrows - q.nz + (unsigned long long)kSpmiStreamT + 2 < kLongRun) return SP_OK;
+    hipLaunchKernelGGL(max_span_kernel, dim3(blocks_for(t->rowblocks.nblocks)), dim3(kThreads), 0, st, (const int32_t *)t->rowblocks.start,
+                       t->rowblocks.nblocks, (unsigned long long *)(flags + 10));
+    SP_HIP(hipGetLastError());
+    SP_HIP(hipMemcpyAsync(&q.span, flags + 10, 8, hipMemcpyDeviceToHost, st));
+    SP_HIP(hipStreamSynchronize(st));
     return SP_OK;
 }
 
@@ -516,7 +524,7 @@ static sp_status nonempty_decide(const sp_tensor *t, sp_scratch &tmp, hipStream_
     const int64_t nz = (int64_t)q.nz;
     // not worth it when at least half of the rows hold something, unless one window of the streaming kernels would have to walk
     // over a very long run of empty rows all by itself
-    if (nz * 2 > nrows && q.span < 65536) return SP_OK;
+    if (nz * 2 > nrows && q.span < kLongRun) return SP_OK;
     sp_mem mem{t->alloc, t->free_, t->ctx};
     const int ps = t->enc.pw / 8, cs = t->enc.cw / 8;
     void *rid = mem.get(pad16((size_t)(nz > 0 ? nz : 1) * cs));
@@ -553,11 +561,12 @@ static sp_status build_nonempty_rows(const sp_tensor *t, sp_scratch &tmp, hipStr
     nonempty_probe q;
     if (!wants_nonempty(t)) return SP_OK;
     SP_TRY(pos_stats(t->pos[1], t->enc.pw, t->npos[1] - 1, (unsigned long long *)(flags + 4), (unsigned long long *)(flags + 8), st));
-    SP_TRY(nonempty_enqueue(t, st, flags, q));
+    nonempty_enqueue(t, q);
     int h[16];
     SP_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st));
     SP_HIP(hipStreamSynchronize(st));
     q.take(h);
+    SP_TRY(nonempty_span(t, flags, st, q));
     bool launched = false;
     return nonempty_decide(t, tmp, st, q, &launched);
 }
@@ -1036,8 +1045,9 @@ __global__ __launch_bounds__(kThreads) void emit_inner_kernel(const uint64_t *__
 
 // The tables a finished storage carries for the product kernels: longest innermost segment (kernel choice), the row
 // blocks of the streaming kernels, the list of non-empty rows of a mostly empty CSR.  flags: 64 device bytes, the
-// second half zero.  Synchronises.  input_flags (HOST int[2], may be null) receives flags[0..1], the input checks of
-// the storage builder, read back together with the maximum; when one is set nothing more is built.
+// second half zero.  Synchronises.  input_flags (HOST int[4], may be null) receives flags[0..3], the input checks of
+// the storage builder and the overflow marks of its sort by buckets, read back together with the maximum; when one is set
+// nothing more is built.
 sp_status spmi_finish_tensor(sp_tensor *t, int *flags, sp_scratch &tmp, hipStream_t st, int *input_flags)
 {
     const sp_encoding *enc = &t->enc;
@@ -1050,19 +1060,19 @@ sp_status spmi_finish_tensor(sp_tensor *t, int *flags, sp_scratch &tmp, hipStrea
     // non-empty-rows list (all in bounds whatever the input checks say), then one synchronisation for all read-backs
     SP_TRY(spmi_build_rowblocks(t, st));
     nonempty_probe q;
-    SP_TRY(nonempty_enqueue(t, st, flags, q));
+    nonempty_enqueue(t, q);
     int h[16] = {0};
     if (want_max || input_flags || q.active) SP_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st));
     SP_HIP(hipStreamSynchronize(st));
     q.take(h);
     if (input_flags) {
-        input_flags[0] = h[0];
-        input_flags[1] = h[1];
-        if (h[0] || h[1]) return SP_OK;
+        memcpy(input_flags, h, 4 * sizeof(int));
+        if (h[0] || h[1] || h[2] || h[3]) return SP_OK;
     }
     unsigned long long hmx = 0;
     memcpy(&hmx, &h[4], 8);
     if (want_max) t->max_segment = (int64_t)hmx;
+    SP_TRY(nonempty_span(t, flags, st, q));
     bool launched = false;
     SP_TRY(nonempty_decide(t, tmp, st, q, &launched));
     if (launched) SP_HIP(hipStreamSynchronize(st));
@@ -1084,6 +1094,37 @@ sp_status spmi_ensure_tables(const sp_tensor *t, hipStream_t st)
     SP_TRY(build_nonempty_rows(t, tmp, st));
     SP_HIP(hipStreamSynchronize(st));
     t->tables_pending = 0;
+    return SP_OK;
+}
+
+// 8- and 16-bit widths: the arrays handed out are narrowed copies of the 32-bit working arrays
+static sp_status narrow_copies(sp_tensor *t, const sp_mem &mem, hipStream_t st)
+{
+    const sp_encoding *enc = &t->enc;
+    for (int l = 0; l < enc->rank; ++l) {
+        if (enc->lt[l] != SP_COMPRESSED) continue;
+        if (enc->pw_store < 32) {
+            t->pos_narrow[l] = mem.get(pad16((size_t)t->npos[l] * (enc->pw_store / 8)));
+            if (!t->pos_narrow[l]) return SP_ERR_ALLOC;
+            if (enc->pw_store == 8)
+                hipLaunchKernelGGL((narrow_kernel<int32_t, int8_t>), dim3(blocks_for(t->npos[l])), dim3(kThreads), 0, st,
+                                   (const int32_t *)t->pos[l], t->npos[l], (int8_t *)t->pos_narrow[l]);
+            else
+                hipLaunchKernelGGL((narrow_kernel<int32_t, int16_t>), dim3(blocks_for(t->npos[l])), dim3(kThreads), 0, st,
+                                   (const int32_t *)t->pos[l], t->npos[l], (int16_t *)t->pos_narrow[l]);
+        }
+        if (enc->cw_store < 32) {
+            t->crd_narrow[l] = mem.get(pad16((size_t)(t->ncrd[l] > 0 ? t->ncrd[l] : 1) * (enc->cw_store / 8)));
+            if (!t->crd_narrow[l]) return SP_ERR_ALLOC;
+            if (enc->cw_store == 8)
+                hipLaunchKernelGGL((narrow_kernel<int32_t, int8_t>), dim3(blocks_for(t->ncrd[l])), dim3(kThreads), 0, st,
+                                   (const int32_t *)t->crd[l], t->ncrd[l], (int8_t *)t->crd_narrow[l]);
+            else
+                hipLaunchKernelGGL((narrow_kernel<int32_t, int16_t>), dim3(blocks_for(t->ncrd[l])), dim3(kThreads), 0, st,
+                                   (const int32_t *)t->crd[l], t->ncrd[l], (int16_t *)t->crd_narrow[l]);
+        }
+        SP_HIP(hipGetLastError());
+    }
     return SP_OK;
 }
 
@@ -1114,14 +1155,17 @@ __global__ __launch_bounds__(kThreads) void mark_heads_kernel(const uint64_t *__
     if (e < n) mark[e] = (e == 0 || keys[e] != keys[e - 1]) ? 1u : 0u;
 }
 
+//
+// again not null: keys and payload arrive sorted, by buckets (flags[2..3]); *again says whether a bucket overflowed, and the tensor is
+// of no use then.
 static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void *payload, int key_bits, bool sum_duplicates, int *flags,
-                           sp_scratch &tmp, const sp_mem &mem, hipStream_t st, const sp_msd_plan *plan = nullptr)
+                           sp_scratch &tmp, const sp_mem &mem, hipStream_t st, const sp_msd_plan *plan = nullptr, bool *again = nullptr)
 {
     const sp_encoding *enc = &t->enc;
     const int rank = enc->rank;
     const sp_dtype dt = (sp_dtype)t->dtype;
     const int vsz0 = dt == SP_F64 ? 8 : 4;
-    if (nnz > 0) SP_TRY(spmi_sort_pairs(keys, payload, vsz0, nnz, key_bits, tmp, st, plan, &keys, &payload));
+    if (nnz > 0 && !again) SP_TRY(spmi_sort_pairs(keys, payload, vsz0, nnz, key_bits, tmp, st, plan, &keys, &payload));
     // The input checks (a coordinate out of range, an entry given twice) come back to the host with the last read-back
     // of the build, not here: a host synchronisation in the middle costs a tenth of a small pack.  Every kernel below stays
     // in bounds on such input (bad coordinates were replaced by 0 when the keys were made; equal keys only make equal
@@ -1174,12 +1218,14 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
     bool upper = false;                                   // a compressed level above the innermost
     for (int l = 0; l + 1 < rank; ++l) upper |= enc->lt[l] == SP_COMPRESSED;
     if (upper) {
-        unsigned long long *d_totals = (unsigned long long *)tmp.get(sizeof(totals));
-        if (!d_totals) return SP_ERR_ALLOC;
+        unsigned long long *d_totals = (unsigned long long *)(flags + 16);       // behind the flags: one copy for both
         SP_TRY(spmi_sweep_count(t, keys, nnz, tmp, st, d_totals, &counts));
         if (counts) {
-            SP_HIP(hipMemcpyAsync(totals, d_totals, sizeof(totals), hipMemcpyDeviceToHost, st));
+            int h[16 + 2 * SP_MAX_RANK];
+            SP_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st));
             SP_HIP(hipStreamSynchronize(st));
+            memcpy(totals, h + 16, sizeof(totals));
+            if (again && (h[2] || h[3])) { *again = true; return SP_OK; }
         }
     }
     int64_t P = 1;
@@ -1240,37 +1286,90 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
             if (enc->lt[l] == SP_COMPRESSED && enc->lt[l - 1] == SP_DENSE) SP_TRY(spmi_exclusive_scan(t->pos[l], t->npos[l], enc->pw, tmp, st));
     }
 
-    // 8- and 16-bit widths: the arrays handed out are narrowed copies of the 32-bit working arrays
-    for (int l = 0; l < rank; ++l) {
-        if (enc->lt[l] != SP_COMPRESSED) continue;
-        if (enc->pw_store < 32) {
-            t->pos_narrow[l] = mem.get(pad16((size_t)t->npos[l] * (enc->pw_store / 8)));
-            if (!t->pos_narrow[l]) return SP_ERR_ALLOC;
-            if (enc->pw_store == 8)
-                hipLaunchKernelGGL((narrow_kernel<int32_t, int8_t>), dim3(blocks_for(t->npos[l])), dim3(kThreads), 0, st,
-                                   (const int32_t *)t->pos[l], t->npos[l], (int8_t *)t->pos_narrow[l]);
-            else
-                hipLaunchKernelGGL((narrow_kernel<int32_t, int16_t>), dim3(blocks_for(t->npos[l])), dim3(kThreads), 0, st,
-                                   (const int32_t *)t->pos[l], t->npos[l], (int16_t *)t->pos_narrow[l]);
-        }
-        if (enc->cw_store < 32) {
-            t->crd_narrow[l] = mem.get(pad16((size_t)(t->ncrd[l] > 0 ? t->ncrd[l] : 1) * (enc->cw_store / 8)));
-            if (!t->crd_narrow[l]) return SP_ERR_ALLOC;
-            if (enc->cw_store == 8)
-                hipLaunchKernelGGL((narrow_kernel<int32_t, int8_t>), dim3(blocks_for(t->ncrd[l])), dim3(kThreads), 0, st,
-                                   (const int32_t *)t->crd[l], t->ncrd[l], (int8_t *)t->crd_narrow[l]);
-            else
-                hipLaunchKernelGGL((narrow_kernel<int32_t, int16_t>), dim3(blocks_for(t->ncrd[l])), dim3(kThreads), 0, st,
-                                   (const int32_t *)t->crd[l], t->ncrd[l], (int16_t *)t->crd_narrow[l]);
-        }
-        SP_HIP(hipGetLastError());
-    }
+    SP_TRY(narrow_copies(t, mem, st));
 
-    int hf[2] = {0, 0};
+    int hf[4] = {0, 0, 0, 0};
     SP_TRY(spmi_finish_tensor(t, flags, tmp, st, sum_duplicates ? nullptr : hf));
+    if (again && (hf[2] || hf[3])) { *again = true; return SP_OK; }
     if (hf[0]) return SP_ERR_COORD_RANGE;
     if (hf[1]) return SP_ERR_DUPLICATE;
     return SP_OK;
+}
+
+// The flags of a build: 64 bytes of them, then the sizes of the levels (see pack_core).
+constexpr size_t kFlagBytes = 64 + 8 * SP_MAX_RANK;
+
+// Everything after the input for distinct keys, sorted by buckets.  Entries come as coordinates by level or as keys.  *again: not done
+// (unsuitable input, no room for the buckets, a bucket overflowed): the tensor holds nothing, and the stable sorts have to do it.
+static sp_status pack_buckets(sp_tensor *t, int64_t nnz, const int64_t *const *level_coords, const uint64_t *keys, const void *vals, int key_bits,
+                              const sp_mem &mem, hipStream_t st, bool *again)
+{
+    const sp_encoding *enc = &t->enc;
+    const int rank = enc->rank;
+    const size_t vsz = t->dtype == SP_F64 ? 8 : 4;
+    uint64_t total = 1;
+    for (int l = 0; l < rank; ++l) total *= (uint64_t)(t->size[l] > 0 ? t->size[l] : 1);
+    spmi_bucket_plan plan;
+    *again = true;
+    if (g_pack_sort_mode.load(std::memory_order_relaxed) != 0 || !spmi_bucket_plan_for(nnz, total, key_bits, &plan)) return SP_OK;
+    if (enc->pw_store < 64 && nnz > (((int64_t)1 << (enc->pw_store - 1)) - 1)) return SP_OK;      // pos may not fit: the other path sorts out the errors
+    bool csr_like = enc->lt[rank - 1] == SP_COMPRESSED && rank > 1;
+    for (int l = 0; l + 1 < rank; ++l) csr_like &= enc->lt[l] == SP_DENSE;
+    sp_scratch tmp(mem);
+    auto run = [&]() -> sp_status {
+        int *flags = (int *)tmp.get(kFlagBytes);
+        if (!flags) return SP_ERR_ALLOC;
+        SP_TRY(spmi_fill_zero(flags, kFlagBytes, st));
+        spmi_bucket_out o;
+        memset(&o, 0, sizeof(o));
+        if (!csr_like) {
+            uint64_t *sorted = (uint64_t *)tmp.get((size_t)nnz * 8);
+            void *payload = tmp.get(pad16((size_t)nnz * vsz));
+            if (!sorted || !payload) return SP_ERR_ALLOC;
+            o.keys = sorted;
+            o.values = payload;
+            SP_TRY(spmi_bucket_sort(level_coords, keys, t->size, rank, vals, (int)vsz, nnz, total, key_bits, plan, o, flags, tmp, st));
+            bool overflow = false;
+            SP_TRY(pack_core(t, nnz, sorted, payload, key_bits, false, flags, tmp, mem, st, nullptr, &overflow));
+            *again = overflow;
+            return SP_OK;
+        }
+        const int l = rank - 1;
+        o.inner = (uint64_t)t->size[l];
+        o.rows = (int64_t)(total / o.inner);
+        o.pw = enc->pw; o.cw = enc->cw;
+        t->nnz = t->nvalues = t->ncrd[l] = nnz;
+        t->npos[l] = o.rows + 1;
+        t->pos[l] = o.pos = mem.get(pad16((size_t)t->npos[l] * (enc->pw / 8)));
+        t->crd[l] = o.crd = mem.get(pad16((size_t)nnz * (enc->cw / 8)));
+        t->values = o.values = mem.get(pad16((size_t)nnz * vsz));
+        if (!o.pos || !o.crd || !o.values) return SP_ERR_ALLOC;
+        if (rank == 2 && o.rows < ((int64_t)1 << 31) - 1) {
+            const int64_t nb = ceil_div(nnz, kSpmiStreamT);
+            t->rowblocks.start = mem.get(pad16((size_t)(nb + 1) * 4));
+            t->rowblocks.carry = mem.get(pad16((size_t)nb * 8));
+            t->rowblocks.nblocks = nb;
+            if (!t->rowblocks.start || !t->rowblocks.carry) return SP_ERR_ALLOC;
+            o.rowblk = (int32_t *)t->rowblocks.start;
+        }
+        SP_TRY(spmi_bucket_sort(level_coords, keys, t->size, rank, vals, (int)vsz, nnz, total, key_bits, plan, o, flags, tmp, st));
+        SP_TRY(narrow_copies(t, mem, st));
+        int h[4] = {0, 0, 0, 0};
+        SP_TRY(spmi_finish_tensor(t, flags, tmp, st, h));
+        *again = h[2] || h[3];
+        return *again ? SP_OK : h[0] ? SP_ERR_COORD_RANGE : h[1] ? SP_ERR_DUPLICATE : SP_OK;
+    };
+    const sp_status s = run();
+    if (s != SP_OK && s != SP_ERR_ALLOC && s != SP_ERR_TOO_LARGE) *again = false;
+    if (s == SP_ERR_ALLOC || s == SP_ERR_TOO_LARGE) *again = true;
+    if (s != SP_OK || *again) {
+        (void)hipStreamSynchronize(st);                   // queued kernels may still use what goes now
+        release_tensor_arrays(t);
+        memset(&t->rowblocks, 0, sizeof(t->rowblocks));
+        memset(&t->nz_rowblocks, 0, sizeof(t->nz_rowblocks));
+        t->nz_rows = 0;
+    }
+    return *again ? SP_OK : s;
 }
 
 // A new tensor handle with shape, sizes by level and the key width worked out; SP_ERR_TOO_LARGE / SP_ERR_WIDTH as sp_pack documents.
@@ -1337,16 +1436,22 @@ extern "C" sp_status sp_pack(const sp_encoding *enc, const int64_t *shape, int64
     SP_TRY(spmi_new_tensor(enc, shape, dt, alloc, free_, ctx, zero_dim && nnz > 0, &t, &key_bits));
     sp_mem mem{alloc, free_, ctx};
     sp_status status = SP_OK;
-    {
+    bool again = true;
+    if (nnz > 0) {
+        const int64_t *level_coords[SP_MAX_RANK];
+        for (int l = 0; l < rank; ++l) level_coords[l] = coords[enc->perm[l]];
+        status = pack_buckets(t, nnz, level_coords, nullptr, values, key_bits, mem, st, &again);
+    }
+    if (status == SP_OK && again) {
         sp_scratch tmp(mem);
         const size_t cnt = (size_t)(nnz > 0 ? nnz : 1);
         uint64_t *keys = (uint64_t *)tmp.get(cnt * 8);
-        int *flags = (int *)tmp.get(64);
+        int *flags = (int *)tmp.get(kFlagBytes);
         sp_msd_plan plan;
         memset(&plan, 0, sizeof(plan));
         do {
             if (!keys || !flags) { status = SP_ERR_ALLOC; break; }
-            if ((status = spmi_fill_zero(flags, 64, st)) != SP_OK) break;
+            if ((status = spmi_fill_zero(flags, kFlagBytes, st)) != SP_OK) break;
             if (nnz > 0) {
                 level_args la;
                 memset(&la, 0, sizeof(la));
@@ -1391,8 +1496,8 @@ sp_status spmi_pack_keys(const sp_encoding *enc, const int64_t *shape, sp_dtype 
     int key_bits = 0;
     SP_TRY(spmi_new_tensor(enc, shape, dt, alloc, free_, ctx, false, &t, &key_bits));
     sp_mem mem{alloc, free_, ctx};
-    int *flags = (int *)tmp.get(64);
-    sp_status status = flags ? spmi_fill_zero(flags, 64, st) : SP_ERR_ALLOC;
+    int *flags = (int *)tmp.get(kFlagBytes);
+    sp_status status = flags ? spmi_fill_zero(flags, kFlagBytes, st) : SP_ERR_ALLOC;
     if (status == SP_OK) status = pack_core(t, n, keys, payload, key_bits, true, flags, tmp, mem, st);
     if (status != SP_OK) (void)hipStreamSynchronize(st);
     return spmi_finish_pack(t, status, st, out);
@@ -1414,12 +1519,13 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
     {
         sp_scratch tmp(mem);
         uint64_t *keys = (uint64_t *)tmp.get((size_t)(n > 0 ? n : 1) * 8);
-        int *flags = (int *)tmp.get(64);
+        int *flags = (int *)tmp.get(kFlagBytes);
         sp_msd_plan plan;
         memset(&plan, 0, sizeof(plan));
+        bool by_buckets = false;
         do {
             if (!keys || !flags) { status = SP_ERR_ALLOC; break; }
-            if ((status = spmi_fill_zero(flags, 64, st)) != SP_OK) break;
+            if ((status = spmi_fill_zero(flags, kFlagBytes, st)) != SP_OK) break;
             if (n > 0) {
                 uint64_t weight[SP_MAX_RANK], w = 1;     // by dimension
                 for (int l = rank - 1; l >= 0; --l) { weight[enc->perm[l]] = w; w *= (uint64_t)t->size[l]; }
@@ -1432,7 +1538,10 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
                     a.stride[l] = weight[from->enc.perm[l]];
                     a.lt[l] = from->enc.lt[l];
                 }
-                if ((status = spmi_msd_plan(n, key_bits, tmp, st, &plan)) != SP_OK) break;
+                // the sort by buckets has no use for the counts; should it not do after all, the other sorts make them
+                spmi_bucket_plan buckets;
+                by_buckets = g_pack_sort_mode.load(std::memory_order_relaxed) == 0 && spmi_bucket_plan_for(n, w, key_bits, &buckets);
+                if (!by_buckets && (status = spmi_msd_plan(n, key_bits, tmp, st, &plan)) != SP_OK) break;
                 const dim3 grid((unsigned)ceil_div(n, kSpmiMsdTile));
 #define SPMI_CONVERT(PT, CT) hipLaunchKernelGGL((convert_keys_kernel<PT, CT>), grid, dim3(kThreads), 0, st, a, n, keys, plan)
                 if (from->enc.pw == 32 && from->enc.cw == 32) SPMI_CONVERT(int32_t, int32_t);
@@ -1442,7 +1551,9 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
 #undef SPMI_CONVERT
                 if (hipGetLastError() != hipSuccess) { status = SP_ERR_HIP; break; }
             }
-            status = pack_core(t, n, keys, from->values, key_bits, false, flags, tmp, mem, st, &plan);
+            bool again = true;
+            if (by_buckets && (status = pack_buckets(t, n, nullptr, keys, from->values, key_bits, mem, st, &again)) != SP_OK) break;
+            if (again) status = pack_core(t, n, keys, from->values, key_bits, false, flags, tmp, mem, st, plan.ctr ? &plan : nullptr);
         } while (0);
         if (status != SP_OK) (void)hipStreamSynchronize(st);
     }

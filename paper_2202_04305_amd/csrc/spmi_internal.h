@@ -458,6 +458,20 @@ sp_status spmi_msd_sort_pairs(uint64_t *keys, const void *vals, int payload_byte
 sp_status spmi_sort_pairs(uint64_t *keys, const void *vals, int payload_bytes, int64_t n, int key_bits, sp_scratch &tmp, hipStream_t st,
                           const sp_msd_plan *plan, uint64_t **keys_out, const void **vals_out);
 extern std::atomic<int> g_pack_sort_mode;
+// ---- buckets.hip ----
+// The builder's sort for entries with distinct keys (equal ones are reported, not ordered): spmi_bucket_plan_for() says whether
+// n entries with keys below `total` suit it and how they will be cut; spmi_bucket_sort() enqueues it.  Entries come as
+// coordinates by level (checked against the sizes: flags[0]) or as keys; neither they nor vals are changed.  What leaves is
+// either the sorted keys and values, or (keys null) crd, pos and values of an innermost compressed level of size `inner`
+// under `rows` positions of dense ones and, where rowblk is given, the row of every kSpmiStreamT-th entry.
+// flags (zero before), once the stream is done: [0] a coordinate was out of range, [1] a key occurs twice, [2] or [3] a bucket
+// overflowed: the outputs are of no use then (keys stay below total) and the stable sorts have to do it.
+struct spmi_bucket_plan { uint32_t Q, F, S; bool two, wide; };   // splitters by sample, multiples of 2^32, sampled keys, two partitions, 64-bit keys
+struct spmi_bucket_out { uint64_t *keys; void *values, *crd, *pos; int32_t *rowblk; int64_t rows; uint64_t inner; int pw, cw; };
+bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, spmi_bucket_plan *plan);
+sp_status spmi_bucket_sort(const int64_t *const *level_coords, const uint64_t *keys, const int64_t *level_size, int rank, const void *vals, int payload_bytes,
+                           int64_t n, uint64_t total, int key_bits, const spmi_bucket_plan &plan, const spmi_bucket_out &out, int *flags,
+                           sp_scratch &tmp, hipStream_t st);
 // ---- pack.hip ----
 // The storage of a tensor whose n entries are given as linearised keys (level order, mixed radix over the level sizes)
 // with the value bits as payload, both temporaries of `tmp`; entries with equal keys are added up in the order given.

@@ -1,0 +1,143 @@
+"""The storage builder's sort by buckets against the CPU checker, bit for bit, at the sizes where its choices change: one bucket and
+several, one partition and two, keys of 32 bits, cut at multiples of 2^32, of 64 bits; rows that fill buckets by themselves,
+columns that crowd, a sample that misleads (the build is done again by the stable sorts), entries given twice."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2202_04305_amd as sp
+from gen import prng
+from gpu_util import say, gpu_pack, assert_storage_equal
+
+pytestmark = pytest.mark.gpu
+SEED = 7250311
+CSR, CSC, DCSR, CDR = ((0, 1), (0, 1)), ((0, 1), (1, 0)), ((1, 1), (0, 1)), ((1, 0), (0, 1))
+TWO = 2048 * 682                       # up to here one partition
+
+
+def distinct(shape, nnz, seed):
+    total = int(np.prod([int(s) for s in shape], dtype=object))
+    lin = np.unique(prng.below(seed, 1, int(nnz * 1.2) + 16, total))
+    while lin.size < nnz:
+        lin = np.unique(np.concatenate([lin, prng.below(seed + lin.size, 1, nnz, total)]))
+    return shuffled(lin, nnz, shape, seed)
+
+
+def shuffled(lin, nnz, shape, seed):
+    lin = lin[prng.permutation(seed, 2, lin.size)][:nnz]
+    out = []
+    for s in reversed(shape[1:]):
+        out.append((lin % s).astype(np.int64))
+        lin = lin // s
+    return [lin.astype(np.int64)] + out[::-1]
+
+
+def check(fmt, shape, coords, dtype=np.float64, widths=(32, 32)):
+    n = len(coords[0])
+    say("case", fmt, "shape", shape, "entries", n, dtype.__name__, widths)
+    v = prng.uniform_pm1(SEED + n, 3, n, dtype)
+    ref = oracle.pack(*fmt, shape, coords, v, *widths)
+    assert_storage_equal(gpu_pack(*fmt, shape, coords, v, *widths), ref)
+
+
+@pytest.mark.parametrize("fmt", [CSR, CSC, DCSR, CDR])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+def test_sizes_where_the_number_of_buckets_changes(fmt, dtype):
+    for n in (1, 2, 255, 256, 2047, 2048, 2049, 4095, 4096, 4097, 12289, 100003):
+        shape = (300, 401) if n <= 12289 else (3001, 2003)
+        check(fmt, shape, distinct(shape, n, SEED + n), dtype, (32, 64) if n % 2 else (64, 32))
+
+
+@pytest.mark.parametrize("shape", [(65537, 65521), (1 << 16, 1 << 16), (1 << 20, 1 << 20), ((1 << 22) + 3, (1 << 20) + 7), (1 << 23, 1 << 23), (1 << 24, 1 << 24)])
+def test_keys_around_and_beyond_32_bits(shape):
+    """Multiples of 2^32 inside the key range: none, none, 255, 1024, more than are split at (64-bit keys), and 48 key bits."""
+    for n in (1500, 70001, 700001):
+        coords = distinct(shape, n, SEED + 5 * n)
+        check(CSR if n > 60000 or shape[0] < 1 << 21 else DCSR, shape, coords)
+        if n == 70001:
+            check(DCSR, shape, coords, np.float32)
+
+
+@pytest.mark.parametrize("n", [TWO, TWO + 1, 2 * TWO + 3])
+@pytest.mark.parametrize("shape", [(70001, 65521), (1 << 18, 1 << 21), (1 << 23, 1 << 22)])
+def test_one_partition_and_two(n, shape):
+    check(CSR, shape, distinct(shape, n, SEED + n))
+
+
+def test_ranks():
+    for fmt, shape, n in [(((1,), (0,)), (1 << 22,), 50001), (((0, 1, 1), (0, 2, 1)), (400, 500, 601), 60001), (((0, 0, 1), (2, 0, 1)), (40, 50, 60), 30001),
+                          (((1, 1, 1), (0, 1, 2)), (1200, 900, 2900), TWO + 77), (((1, 0, 1, 1), (0, 1, 3, 2)), (30, 5, 70, 80), 40001),
+                          (((1,) * 5, (4, 3, 2, 1, 0)), (30, 31, 32, 33, 34), 200003)]:
+        check(fmt, shape, distinct(shape, n, SEED + n))
+
+
+@pytest.mark.parametrize("n_rest", [60000, TWO])
+def test_rows_that_fill_buckets_and_columns_that_crowd(n_rest):
+    m, n = 1 << 17, 1 << 20
+    lin = [np.arange(20000, dtype=np.int64) * 37 + 11 * n, np.arange(9000, dtype=np.int64) + 4000 * n + 777,          # a long row, a full stretch of one
+           np.arange(100000, dtype=np.int64) + (m - 1) * n]
+    r = np.arange(1000, dtype=np.int64)
+    lin += [(20000 + r)[:, None].repeat(128, 1).ravel() * n + (r[:, None] * 3 + np.arange(128)).ravel(),               # a band
+            ((50000 + r)[:, None] * n + (r[:, None] // 64 * 64 + np.arange(64))).ravel()]                             # blocks
+    lin.append(prng.below(SEED, 9, n_rest, m * n))
+    lin = np.unique(np.concatenate(lin))
+    coords = shuffled(lin, lin.size, (m, n), SEED)
+    for fmt in (CSR, DCSR):
+        check(fmt, (m, n), coords)
+    check(CSC, (n, m), coords[::-1])
+
+
+def sampled_positions(n):
+    """Where the builder looks: one entry per stretch of n / S, at a scrambled place in it."""
+    if n > TWO:
+        Q, share = max(min(-(-n // 65536), 512), -(-n // (4 * 65536))), 32
+    else:
+        Q, share = -(-n // 2048), 48
+    S = min(-(-share * Q // 1024) * 1024, 32768)
+    i = np.arange(S, dtype=np.uint64)
+    x = i ^ (i >> np.uint64(16))
+    x = (x * np.uint64(0x7feb352d)) & np.uint64(0xffffffff)
+    x ^= x >> np.uint64(15)
+    x = (x * np.uint64(0x846ca68b)) & np.uint64(0xffffffff)
+    x ^= x >> np.uint64(16)
+    return np.minimum(((i.astype(np.float64) + x.astype(np.float64) * 2.0 ** -32) * (float(n) / float(S))).astype(np.int64), n - 1)
+
+
+@pytest.mark.parametrize("fmt", [CSR, DCSR])
+@pytest.mark.parametrize("n", [200000, TWO + 100000])
+def test_a_sample_that_misleads(fmt, n):
+    """The sampled entries are spread over the matrix, all others lie in one corner: a bucket gets more than it has room for."""
+    m = 1 << 16
+    at = np.unique(sampled_positions(n))
+    corner = prng.permutation(SEED, 4, 4 * n)[: n - at.size]
+    side = int(np.ceil(np.sqrt(4 * n)))
+    rows, cols = np.empty(n, np.int64), np.empty(n, np.int64)
+    rest = np.ones(n, bool)
+    rest[at] = False
+    rows[rest], cols[rest] = corner // side, corner % side
+    spread = np.unique(prng.below(SEED, 5, 2 * at.size, m * m))
+    spread = spread[spread // m > side]
+    spread = spread[prng.permutation(SEED, 6, spread.size)][: at.size]
+    assert spread.size == at.size
+    rows[at], cols[at] = spread // m, spread % m
+    check(fmt, (m, m), [rows, cols])
+
+
+@pytest.mark.parametrize("fmt", [CSR, DCSR])
+@pytest.mark.parametrize("n", [3000, 50000, TWO + 1])
+def test_entries_given_twice_and_coordinates_out_of_range(fmt, n):
+    shape = (5000, 4000)
+    coords = distinct(shape, n, SEED + 3)
+    v = np.ones(n)
+    for change, code in [("one twice", 7), ("all the same", 7), ("out of range", 6)]:
+        c = [x.copy() for x in coords]
+        if change == "one twice":
+            c[0][n - 1], c[1][n - 1] = c[0][n // 3], c[1][n // 3]
+        elif change == "all the same":
+            c[0][:], c[1][:] = 17, 23
+        else:
+            c[1][n // 2] = shape[1]
+        say("case", fmt, n, change)
+        with pytest.raises(sp.SpError) as e:
+            gpu_pack(*fmt, shape, c, v, 32, 32)
+        assert e.value.code == code
