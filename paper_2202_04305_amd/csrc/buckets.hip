@@ -35,7 +35,7 @@ constexpr int kSubSample = 8192;              // most keys sampled inside one bu
 constexpr int kShare = 48;                    // sampled keys per final bucket
 constexpr int kShareFirst = 32;               // sampled keys per bucket that is partitioned again
 constexpr int kPR = 12;                       // partition: entries per thread
-constexpr int kPT = 512, kWideT = 1024;       // its threads; a larger tile where there are more than kPT buckets
+constexpr int kPT = 512, kWideT = 1024;       // its threads: the second partition and small inputs, the first one
 constexpr int kSmallR = 2;                    // entries per thread where larger tiles would leave most of the chip idle
 constexpr int kFT = 256, kFE = 16;            // finishing kernel: threads, entries per thread
 constexpr int kCap = kFT * kFE;               // entries a block sorts in the LDS
@@ -43,16 +43,12 @@ constexpr int kTarget = 2048;                 // entries per final bucket where 
 constexpr int kExact = 3456;                  // the same where they are counted first
 constexpr int kPartCells = 16384;             // equal intervals of a bucket whose entries are counted
 constexpr int kHeavy = 512;                   // more entries than this in one of them: a sample cuts the bucket (kExact + kHeavy < kCap)
-constexpr int kFirst = 65536;                 // entries per bucket of the first of two partitions
+constexpr int kFirst = 131072;                 // entries per bucket of the first of two partitions
 constexpr int kCells1 = 2 * kFT;              // equal intervals of a final bucket, each then cut by what it holds
+constexpr int kSpread = 24;                   // more keys than this in one interval: a second attempt at spreading them
 constexpr int kCrowd = 64;                    // more keys than this in one interval: left to finish_crowded_kernel
 
-struct source {
-    const int64_t *coord[SP_MAX_RANK];   // by level, or
-    const uint64_t *keys;                // the keys themselves (coord unused)
-    int64_t size[SP_MAX_RANK];
-    int rank;
-};
+typedef spmi_bucket_source source;
 
 // key of entry e; a coordinate out of range sets bad and makes the key 0
 __device__ __forceinline__ uint64_t key_of(const source &s, int64_t e, bool &bad)
@@ -150,14 +146,14 @@ __global__ __launch_bounds__(kRun) void sample_runs_kernel(source s, int64_t n, 
 // place begins a share of S / Q become splitters.  The multiples of 2^32 get their places the same way.
 constexpr int kRankT = 256;
 __global__ __launch_bounds__(kRankT) void sample_ranks_kernel(const uint32_t *__restrict__ runs, uint32_t S, int shift, uint32_t Q, uint32_t F,
-                                                              uint32_t *__restrict__ splitter, uint32_t *__restrict__ forced_rank)
+                                                              uint32_t *__restrict__ splitter, uint32_t *__restrict__ forced_rank, int fbits)
 {
     extern __shared__ __align__(16) uint32_t key[];
     for (uint32_t i = threadIdx.x; i < S / 4; i += kRankT) ((uint4 *)key)[i] = ((const uint4 *)runs)[i];
     __syncthreads();
     const uint32_t i = blockIdx.x * kRankT + threadIdx.x, nruns = S / kRun;
     if (i >= S + F) return;
-    const uint32_t mine = i < S ? key[i] : (uint32_t)(((uint64_t)(i - S + 1) << 32) >> shift);
+    const uint32_t mine = i < S ? key[i] : (uint32_t)(((uint64_t)(i - S + 1) << fbits) >> shift);
     const uint32_t own = i < S ? i / kRun : nruns;
     uint32_t rank = i < S ? i % kRun : 0;
     for (uint32_t r0 = 0; r0 < nruns; r0 += 4) {
@@ -220,22 +216,23 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *w
 
 // One block: the splitters and the multiples of 2^32 merged into the buckets' lower ends, room for each of them, the cells' table.
 __global__ __launch_bounds__(1024) void buckets_kernel(const uint32_t *__restrict__ splitter, const uint32_t *__restrict__ forced_rank, uint32_t S,
-                                                       int shift, uint32_t Q, uint32_t F, uint64_t total, int cell_shift, int64_t n, level1 t)
+                                                       int shift, uint32_t Q, uint32_t F, int fbits, uint64_t total, int cell_shift, int64_t n, level1 t, int *__restrict__ flags)
 {
     __shared__ uint64_t lo[kMaxBuckets + 1];
     __shared__ uint32_t rank[kMaxBuckets + 1];
     __shared__ uint32_t wsum[16];
     const int tid = threadIdx.x;
     const uint32_t B = Q + F;
+    if (tid < (int)(kSpmiFlagBytes / 4)) flags[tid] = 0;
     if (tid == 0) { lo[0] = 0; rank[0] = 0; lo[B] = total; rank[B] = S; }
     for (uint32_t i = tid; i + 1 < Q; i += 1024) {
         const uint64_t v = (uint64_t)splitter[i] << shift;
-        const uint32_t f = (uint32_t)((v >> 32) < F ? (v >> 32) : F);
+        const uint32_t f = (uint32_t)((v >> fbits) < F ? (v >> fbits) : F);
         lo[1 + i + f] = v;
         rank[1 + i + f] = (uint32_t)(((uint64_t)(i + 1) * S) / Q);
     }
     for (uint32_t j = tid; j < F; j += 1024) {
-        const uint64_t v = (uint64_t)(j + 1) << 32;
+        const uint64_t v = (uint64_t)(j + 1) << fbits;
         uint32_t a = 0, z = Q - 1;                               // splitters below v
         while (a < z) {
             const uint32_t mid = (a + z) / 2;
@@ -291,9 +288,24 @@ __device__ __forceinline__ void move_tile(const K (&k)[R], const uint32_t (&b)[R
     P *sv = (P *)stage;
     const int tid = threadIdx.x;
     uint32_t slot[R];
+    // lanes that agree with the wave's first one take their numbers with one add: entries that come in the order of the keys or nearly
+    // so would queue up at one counter
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (r * PT + tid < cnt) slot[r] = atomicAdd(&cur[b[r]], 1u);
+    for (int r = 0; r < R; ++r) {
+        if (r * PT + tid < cnt) {
+            const uint32_t same = (uint32_t)__builtin_amdgcn_readfirstlane((int)b[r]);
+            const uint64_t m = __ballot(b[r] == same);
+            if (__popcll(m) < 16) slot[r] = atomicAdd(&cur[b[r]], 1u);
+            else {
+                uint32_t at = 0;
+                if (b[r] == same) {
+                    const uint32_t before = (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    if (before == 0) at = atomicAdd(&cur[same], (uint32_t)__popcll(m));
+                    slot[r] = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + before;
+                } else slot[r] = atomicAdd(&cur[b[r]], 1u);
+            }
+        }
+    }
     __syncthreads();
     const int per = (B + PT - 1) / PT;                             // <= PER consecutive buckets per thread
     uint32_t g[PER], tot = 0, all;
@@ -670,8 +682,13 @@ struct final_args {
     int64_t n;
     uint32_t *left;                      // [most] buckets with a crowded interval: finish_crowded_kernel takes them
     int *flags;
-    // what leaves: the keys (uint64), or crd / pos of an innermost compressed level under dense ones
+    // what leaves: the keys (uint64), or what bucket_levels_kernel takes (dist), or crd / pos of an innermost compressed level under dense ones
     uint64_t *keys;
+    uint32_t *dist;                      // every entry's distance from its bucket's lo
+    uint32_t *heads;                     // [slot * most + bucket]: entries that begin a new prefix
+    uint32_t *ends;                      // [2 * most]: first and last distance of a bucket
+    const uint32_t *off;                 // [SP_MAX_RANK * most] levels: lo's coordinate at each compressed level, from the innermost on
+    spmi_levels levels;
     void *crd, *pos;
     int32_t *rowblk;                     // row of every kSpmiStreamT-th entry (may be null)
     int64_t nblocks;
@@ -684,10 +701,11 @@ struct final_args {
 // bucket of the first one, whose parts [sub0[b], sub0[b + 1]) are block b's.
 __global__ __launch_bounds__(256) void final_buckets_kernel(const uint64_t *__restrict__ lo, const uint32_t *__restrict__ start, const uint32_t *__restrict__ end,
                                                             const uint32_t *__restrict__ cur, const uint32_t *__restrict__ out,
-                                                            const uint32_t *__restrict__ sub0, uint32_t count, final_bucket *__restrict__ bucket, final_args f)
+                                                            const uint32_t *__restrict__ sub0, uint32_t count, final_bucket *__restrict__ bucket, uint32_t *__restrict__ off,
+                                                            final_args f)
 {
     __shared__ uint32_t wsum[4];
-    if (blockIdx.x == 0 && threadIdx.x == 0 && !f.keys) {            // the ends of the arrays
+    if (blockIdx.x == 0 && threadIdx.x == 0 && f.pos) {              // the ends of the arrays
         if (f.pw == 32) ((int32_t *)f.pos)[f.rows] = (int32_t)f.n;
         else ((int64_t *)f.pos)[f.rows] = f.n;
         if (f.rowblk) { f.rowblk[0] = 0; f.rowblk[f.nblocks] = (int32_t)f.rows; }
@@ -715,11 +733,20 @@ __global__ __launch_bounds__(256) void final_buckets_kernel(const uint64_t *__re
             const uint64_t steps = bits ? (w.shift >= 0 ? range << w.shift : ((range - 1) >> -w.shift) + 1) : 1;   // in (2^31, 2^32]
             w.scale = bits ? (uint32_t)((1ull << 63) / steps) : 0u;
             if (w.cnt > end[b] - w.start || w.cnt > (uint32_t)kCap) { f.flags[3] = 1; w.cnt |= kOverflow; }
+            uint64_t prefix = w.lo;
+            for (int j = 0; j < f.levels.count; ++j) {
+                const uint64_t up = spmi_div_by(prefix, f.levels.size[j]);
+                off[(size_t)b * SP_MAX_RANK + j] = (uint32_t)(prefix - up * f.levels.size[j].d);
+                prefix = up;
+            }
             bucket[b] = w;
         }
         at += all;
     }
 }
+
+// (off + q) / size for 32-bit numbers: the half keeps every quotient further from a whole number than the arithmetic is off
+__device__ __forceinline__ uint32_t quotient(uint32_t q, double off_and_half, double inv) { return (uint32_t)(((double)q + off_and_half) * inv); }
 
 // The bucket's keys lie sorted in the LDS as distances from lo: what the format wants of them.
 template <typename K, int T>
@@ -730,9 +757,25 @@ __device__ __forceinline__ void emit_sorted(const final_args &f, const final_buc
         for (uint32_t i = threadIdx.x; i < cnt; i += T) q[i] = w.lo + dist[i];
         return;
     }
+    if (f.dist) {
+        uint32_t *__restrict__ q = f.dist + w.out;
+        for (uint32_t i = threadIdx.x; i < cnt; i += T) q[i] = (uint32_t)dist[i];
+        return;
+    }
     const uint64_t row0 = spmi_div_by(w.lo, f.inner), off = w.lo - row0 * f.inner.d;
+    const double half = (double)off + 0.5;
+    const bool narrow = sizeof(K) == 4 && f.inner.d <= 0xffffffffull;      // block-uniform: quotients and coordinates in 32 bits
     for (uint32_t i = threadIdx.x; i < cnt; i += T) {
-        const uint64_t x = off + dist[i], row = spmi_div_by(x, f.inner), col = x - row * f.inner.d;
+        uint64_t row, col;
+        if (narrow) {
+            const uint32_t q = f.inner.shift >= 0 ? (uint32_t)((off + dist[i]) >> f.inner.shift) : quotient((uint32_t)dist[i], half, f.inner.inv);
+            row = q;
+            col = (uint32_t)((uint32_t)off + (uint32_t)dist[i] - q * (uint32_t)f.inner.d);
+        } else {
+            const uint64_t x = off + dist[i];
+            row = spmi_div_by(x, f.inner);
+            col = x - row * f.inner.d;
+        }
         const uint32_t at = w.out + i;
         if (f.cw == 32) ((int32_t *)f.crd)[at] = (int32_t)col;
         else ((int64_t *)f.crd)[at] = (int64_t)col;
@@ -740,18 +783,74 @@ __device__ __forceinline__ void emit_sorted(const final_args &f, const final_buc
     }
 }
 
+// Levels: how many entries of the bucket begin a new prefix at each compressed level above the innermost, but for its first entry
+// (whose predecessor lies in another bucket: bucket_heads_kernel).  Block-wide, with barriers; cnt may be 0.  A wave takes entries
+// that lie side by side, so that the predecessor's quotient is the neighbouring lane's.
+constexpr int kSlots = SP_MAX_RANK - 1;
+struct head_counts { uint32_t n[kSlots]; };
+
+__device__ __forceinline__ uint32_t lane_before(uint32_t v, uint32_t first)
+{
+    // v of the lane below; lane 0 takes `first` (wave shift right by one lane)
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xf, 0xf, false);
+}
+
+template <typename K, int T>
+__device__ __forceinline__ void emit_heads(const final_args &f, const K *dist, uint32_t cnt, uint32_t b, head_counts &h)
+{
+    if (!f.dist) return;
+    const int slots = f.levels.count - 1, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid < kSlots) h.n[tid] = 0;
+    __syncthreads();
+    const int rounds = (int)((cnt + T - 1) / T);
+    const uint32_t i0 = (uint32_t)(wave * rounds) * 64u;
+    if (i0 < cnt) {
+        double half[kSlots];
+        uint32_t edge[kSlots], heads[kSlots], e = i0 ? (uint32_t)dist[i0 - 1] : 0u;
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j) {
+            half[j] = 0;
+            edge[j] = heads[j] = 0;
+            if (j < slots) {
+                half[j] = (double)(uint32_t)__builtin_amdgcn_readfirstlane((int)f.off[(size_t)b * SP_MAX_RANK + j]) + 0.5;
+                e = edge[j] = quotient(e, half[j], f.levels.size[j].inv);
+            }
+        }
+        for (int r = 0; r < rounds; ++r) {
+            const uint32_t i = i0 + (uint32_t)(r * 64 + lane);
+            uint32_t q = (uint32_t)dist[i < cnt ? i : cnt - 1];      // behind the last entry: the same again, no head
+#pragma unroll
+            for (int j = 0; j < kSlots; ++j) {
+                if (j < slots) {
+                    q = quotient(q, half[j], f.levels.size[j].inv);
+                    heads[j] += (uint32_t)__popcll(__ballot(q != lane_before(q, edge[j]) && i > 0));
+                    edge[j] = (uint32_t)__builtin_amdgcn_readlane((int)q, 63);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kSlots; ++j)
+            if (j < slots && lane == 0) atomicAdd(&h.n[j], heads[j]);
+    }
+    __syncthreads();
+    if (tid < slots) f.heads[(size_t)tid * f.most + b] = h.n[tid];
+    if (tid == 0 && cnt) { f.ends[2 * b] = (uint32_t)dist[0]; f.ends[2 * b + 1] = (uint32_t)dist[cnt - 1]; }
+}
+
 // The rows (positions of the level above) that begin in [lo, next) are this bucket's: each looks up its first entry.
 template <typename K, int T>
 __device__ __forceinline__ void emit_rows(const final_args &f, const final_bucket &w, const K *dist, uint32_t cnt)
 {
-    if (f.keys) return;
+    if (!f.pos) return;
     const uint64_t r0 = w.lo == 0 ? 0 : spmi_div_by(w.lo - 1, f.inner) + 1, r1 = w.next == 0 ? 0 : spmi_div_by(w.next - 1, f.inner) + 1;
     uint32_t top = 1;
     while (top <= cnt) top *= 2;
+    const uint64_t last = cnt ? (uint64_t)dist[cnt - 1] : 0;
     for (uint64_t r = r0 + threadIdx.x; r < r1; r += T) {
         const uint64_t first = r * f.inner.d - w.lo;                 // below next - lo: fits K
         uint32_t a = 0;
-        for (uint32_t s = top / 2; s > 0; s >>= 1)
+        if (cnt && first > last) a = cnt;                            // rows after the last entry
+        else for (uint32_t s = top / 2; s > 0; s >>= 1)
             if (a + s <= cnt && (uint64_t)dist[a + s - 1] < first) a += s;
         if (f.pw == 32) ((int32_t *)f.pos)[r] = (int32_t)(w.out + a);
         else ((int64_t *)f.pos)[r] = (int64_t)(w.out + a);
@@ -766,51 +865,39 @@ __device__ __forceinline__ uint32_t place_in_range(K d, const final_bucket &w)
     return __umulhi(x, w.scale);
 }
 
-template <typename K, typename P>
+template <typename K>
+using lds_key = typename std::conditional<sizeof(K) == 8, unsigned long long, unsigned int>::type;
+
+template <typename K, typename P, int ATTEMPT>
 struct finish_lds {
     static constexpr int kWords = (kFE | 1) * kFT;
     static constexpr size_t kKeys = kCap * sizeof(K) + (kWords + 1) * 4 + kCells1 * 4, kValues = kCap * sizeof(P);
     __align__(16) unsigned char stage[kKeys > kValues ? kKeys : kValues];
+    lds_key<K> least[ATTEMPT ? kCells1 : 1], most[ATTEMPT ? kCells1 : 1];     // second attempt: of a cell's keys
     uint32_t wsum[kFT / 64];
     uint32_t crowded;
+    head_counts heads;
 };
 
 // A bucket sorted by value.  Its range is cut into kCells1 equal intervals, each of those into twice as many as it holds
-// entries (rows differ in length, so keys are not spread evenly over a bucket); an entry takes a number in its interval with one
-// returning LDS add, the counts are scanned, the keys are dropped into their intervals, and an entry's place is the
-// interval's start plus the number of smaller keys there.  Counts are 16 bits, two to a word: intervals x and x + words share
-// one, so that one addition per word scans both halves.  (Keys that occur twice may take one place and leave a place as it
-// was: the build ends with an error then.)
+// entries (rows differ in length, so keys are not spread evenly over a bucket), in the second attempt, for bands and blocks, only from
+// its smallest key to its largest; an entry takes a number in its interval with one returning LDS add, the counts are scanned,
+// the keys are dropped into their intervals, and an entry's place is the interval's start plus the number of smaller keys
+// there.  Counts are 16 bits, two to a word: intervals x and x + words share one, so that one addition per word scans both
+// halves.  (Keys that occur twice may take one place and leave a place as it was: the build ends with an error then.)
+// false, for the whole block and with nothing written: an interval is too crowded.
 // What bounds it: vector instructions, so a thread has up to sixteen entries and what all entries of a bucket share is worked out
 // before (final_buckets_kernel).
-template <typename K, typename P>
-__global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
+template <typename K, typename P, int ATTEMPT>
+__device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, const final_args &f, const final_bucket &w,
+                                              finish_lds<K, P, ATTEMPT> &s, uint32_t b)
 {
     constexpr int W = kFT / 64;
-    __shared__ finish_lds<K, P> s;
-    const uint32_t b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (f.flags[2]) {                                                // a bucket overflowed in the first partition: harmless keys, the build will be done again
-        if (f.keys)
-            for (int64_t i = (int64_t)b * kFT + tid; i < f.n; i += (int64_t)f.most * kFT) f.keys[i] = 0;
-        return;
-    }
-    if (b >= (f.count ? *f.count : f.most)) return;
-    const final_bucket w = f.bucket[b];
-    if (tid == 0) { f.left[b] = 0; s.crowded = 0; }
     const uint32_t cnt = w.cnt;
     K *dist = (K *)s.stage;
     uint32_t *bins = (uint32_t *)(dist + kCap), *cells = bins + s.kWords + 1;
     P *sval = (P *)s.stage;
-    if (cnt & kOverflow) {
-        if (f.keys) for (uint32_t i = tid; i < (cnt & ~kOverflow); i += kFT) f.keys[w.out + i] = 0;
-        else emit_rows<K, kFT>(f, w, dist, 0);
-        return;
-    }
-    if (cnt == 0) {
-        emit_rows<K, kFT>(f, w, dist, 0);
-        return;
-    }
     const int rounds = (int)((cnt + kFT - 1) / kFT);                 // <= kFE
     const int per = rounds | 1;                                      // words per thread when they are scanned: odd, no bank conflicts
     const uint32_t words = (uint32_t)per * kFT;                      // two intervals each
@@ -833,8 +920,13 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
             v[r] = __builtin_nontemporal_load(vp + i);
         }
     }
+    if (tid == 0) s.crowded = 0;
     for (int j = 0; j < per; ++j) bins[j * kFT + tid] = 0;
-    for (int j = 0; j < kCells1 / kFT; ++j) cells[j * kFT + tid] = 0;
+#pragma unroll
+    for (int j = 0; j < kCells1 / kFT; ++j) {
+        cells[j * kFT + tid] = 0;
+        if (ATTEMPT) { s.least[j * kFT + tid] = ~(lds_key<K>)0; s.most[j * kFT + tid] = 0; }
+    }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kFE; ++r) {
@@ -842,6 +934,10 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
             k[r] -= (K)w.lo;
             at[r] = place_in_range<K>(k[r], w);
             atomicAdd(&cells[at[r] >> 22], 1u);
+            if (ATTEMPT) {
+                atomicMin(&s.least[at[r] >> 22], (lds_key<K>)k[r]);
+                atomicMax(&s.most[at[r] >> 22], (lds_key<K>)k[r]);
+            }
         }
     }
     __syncthreads();
@@ -862,8 +958,16 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
     for (int r = 0; r < kFE; ++r) {
         if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) {
             const uint32_t c = cells[at[r] >> 22];
-            // interval: twice what comes before its cell, plus its place in the cell (18 bits) times twice what the cell holds
-            const uint32_t x = 2u * (c & 0xffffu) + (((at[r] >> 4) & 0x3ffffu) * (c >> 16) >> 17);
+            uint32_t x;                                              // interval: twice what comes before its cell, and where in the cell
+            if (ATTEMPT == 0) x = ((at[r] >> 4) & 0x3ffffu) * (c >> 16) >> 17;
+            else {
+                const uint32_t twice = 2u * (c >> 16);
+                const K least = (K)s.least[at[r] >> 22];
+                const float span = (float)(K)((K)s.most[at[r] >> 22] - least);
+                x = (uint32_t)((float)(K)(k[r] - least) * ((float)twice / (span + 1.0f)));
+                x = x < twice ? x : twice - 1;
+            }
+            x += 2u * (c & 0xffffu);
             const bool upper = x >= words;
             const uint32_t word = upper ? x - words : x, half = upper ? 16u : 0u;
             at[r] = word | (half << 16);
@@ -900,54 +1004,74 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
             longest = len > longest ? len : longest;
         } else at[r] = 0;
     }
-    if (longest > (uint32_t)kCrowd) s.crowded = 1;
+    if (longest > (uint32_t)(ATTEMPT ? kCrowd : kSpread)) s.crowded = 1;
     __syncthreads();
-    if (s.crowded) {                                                 // the whole block alike
-        if (tid == 0) f.left[b] = 1;
-        return;
-    }
-    // all rounds side by side, one other key of every interval per step
+    if (s.crowded) return false;
+    // all rounds side by side, one other key of every interval per step; smaller ones are counted in the upper half of slot
     bool dup = false;
-    uint32_t place[kFE];
-#pragma unroll
-    for (int r = 0; r < kFE; ++r) place[r] = at[r] & 0xffffu;
     for (uint32_t j = 1; j < longest; ++j) {
 #pragma unroll
         for (int r = 0; r < kFE; ++r) {
-            if (r < rounds) {
-                const uint32_t len = at[r] >> 16;
-                if (j < len) {
-                    const uint32_t x = slot[r] + j, s0 = at[r] & 0xffffu;
-                    const K o = dist[x < s0 + len ? x : x - len];
-                    place[r] += o < k[r] ? 1u : 0u;
-                    dup |= o == k[r];
-                }
+            if (r < rounds && j < (at[r] >> 16)) {
+                const uint32_t x = (slot[r] & 0xffffu) + j, end = (at[r] & 0xffffu) + (at[r] >> 16);
+                const K o = dist[x < end ? x : x - (at[r] >> 16)];
+                slot[r] += o < k[r] ? 0x10000u : 0u;
+                dup |= o == k[r];
             }
         }
     }
     if (dup) atomicOr(&f.flags[1], 1);
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kFE; ++r)
-        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) dist[place[r]] = k[r];
+    for (int r = 0; r < kFE; ++r) {
+        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) {
+            at[r] = (at[r] & 0xffffu) + (slot[r] >> 16);             // the entry's place
+            dist[at[r]] = k[r];
+        }
+    }
     __syncthreads();
     emit_sorted<K, kFT>(f, w, dist, cnt);
     emit_rows<K, kFT>(f, w, dist, cnt);
+    emit_heads<K, kFT>(f, dist, cnt, b, s.heads);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kFE; ++r)
-        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) sval[place[r]] = v[r];
+        if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) sval[at[r]] = v[r];
     __syncthreads();
     for (uint32_t i = tid; i < cnt; i += kFT) vout[w.out + i] = sval[i];
+    return true;
 }
 
-// The buckets the finishing kernel left: entries that crowd in a few intervals (bands, blocks).  Bitonic sort in the LDS, the entry's
-// number travelling with the key.
 template <typename K, typename P>
-__global__ __launch_bounds__(1024) void finish_crowded_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
+__global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
 {
-    __shared__ K dist[kCap];
-    __shared__ uint16_t idx[kCap];
+    __shared__ finish_lds<K, P, 0> s;
+    const uint32_t b = blockIdx.x;
+    if (f.flags[2]) {                                                // a bucket overflowed in the first partition: harmless output, the build will be done again
+        for (int64_t i = (int64_t)b * kFT + threadIdx.x; i < f.n; i += (int64_t)f.most * kFT) {
+            if (f.keys) f.keys[i] = 0;
+        }
+        return;
+    }
+    const bool any = b < (f.count ? *f.count : f.most);
+    final_bucket w;
+    w.cnt = 0;
+    if (any) w = f.bucket[b];
+    bool left = false;
+    if ((w.cnt & kOverflow) || w.cnt == 0) {
+        if ((w.cnt & kOverflow) && f.keys) for (uint32_t i = threadIdx.x; i < (w.cnt & ~kOverflow); i += kFT) f.keys[w.out + i] = 0;
+        if (any) emit_rows<K, kFT>(f, w, (const K *)s.stage, 0);
+        emit_heads<K, kFT>(f, (const K *)s.stage, 0, b, s.heads);
+    } else left = !finish_bucket<K, P, 0>(kin, vin, vout, f, w, s, b);
+    if (any && threadIdx.x == 0) f.left[b] = left ? 1u : 0u;
+}
+
+// The buckets the finishing kernel left, entries that crowd in a few intervals: the second attempt, and where that fails too, a
+// bitonic sort in the LDS, the entry's number travelling with the key.  As many blocks as the chip holds.
+template <typename K, typename P>
+__global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
+{
+    __shared__ union { finish_lds<K, P, 1> s; struct { K dist[kCap]; uint16_t idx[kCap]; head_counts heads; } sort; } lds;
     const int tid = threadIdx.x, lane = tid & 63;
     if (f.flags[2]) return;
     const uint32_t total = f.count ? *f.count : f.most;
@@ -956,17 +1080,22 @@ __global__ __launch_bounds__(1024) void finish_crowded_kernel(const K *__restric
         for (uint64_t todo = __ballot(mine < total && f.left[mine < total ? mine : 0] != 0); todo; todo &= todo - 1) {
             const uint32_t b = first + (uint32_t)__builtin_ctzll(todo) * gridDim.x;
             const final_bucket w = f.bucket[b];
+            __syncthreads();
+            if (finish_bucket<K, P, 1>(kin, vin, vout, f, w, lds.s, b)) continue;
+            __syncthreads();
+            K *dist = lds.sort.dist;
+            uint16_t *idx = lds.sort.idx;
             const uint32_t cnt = w.cnt;
             uint32_t N = 2;
             while (N < cnt) N *= 2;
-            for (uint32_t i = tid; i < N; i += 1024) {
+            for (uint32_t i = tid; i < N; i += kFT) {
                 dist[i] = i < cnt ? (K)(kin[w.start + i] - (K)w.lo) : (K)~(K)0;
                 idx[i] = (uint16_t)i;
             }
             __syncthreads();
             for (uint32_t size = 2; size <= N; size *= 2) {
                 for (uint32_t half = size / 2; half > 0; half /= 2) {
-                    for (uint32_t p = tid; p < N / 2; p += 1024) {
+                    for (uint32_t p = tid; p < N / 2; p += kFT) {
                         const uint32_t x = 2 * p - (p & (half - 1)), y = x + half;
                         const K a = dist[x], c = dist[y];
                         const uint16_t ia = idx[x], ic = idx[y];
@@ -977,72 +1106,244 @@ __global__ __launch_bounds__(1024) void finish_crowded_kernel(const K *__restric
                 }
             }
             bool dup = false;
-            for (uint32_t i = tid; i + 1 < cnt; i += 1024) dup |= dist[i] == dist[i + 1];
+            for (uint32_t i = tid; i + 1 < cnt; i += kFT) dup |= dist[i] == dist[i + 1];
             if (dup) atomicOr(&f.flags[1], 1);
-            emit_sorted<K, 1024>(f, w, dist, cnt);
-            emit_rows<K, 1024>(f, w, dist, cnt);
-            for (uint32_t i = tid; i < cnt; i += 1024) vout[w.out + i] = vin[w.start + idx[i]];
-            __syncthreads();
+            emit_sorted<K, kFT>(f, w, dist, cnt);
+            emit_rows<K, kFT>(f, w, dist, cnt);
+            emit_heads<K, kFT>(f, dist, cnt, b, lds.sort.heads);
+            for (uint32_t i = tid; i < cnt; i += kFT) vout[w.out + i] = vin[w.start + idx[i]];
         }
+    }
+}
+
+// ---- levels ---------------------------------------------------------------------------------
+// A bucket's first entry begins a new prefix at a level where it differs from the last entry of the bucket before it (empty ones
+// skipped): counted, and kept as a bit per level.  Thread = bucket.
+__global__ __launch_bounds__(256) void bucket_heads_kernel(final_args f, uint32_t *__restrict__ first_mask, uint64_t *__restrict__ before_key)
+{
+    const uint32_t b = blockIdx.x * 256u + threadIdx.x;
+    if (f.flags[2] || f.flags[3] || b >= (f.count ? *f.count : f.most)) return;
+    if (f.bucket[b].cnt == 0) return;
+    int64_t p = (int64_t)b - 1;
+    while (p >= 0 && f.bucket[p].cnt == 0) --p;
+    uint64_t mine = f.bucket[b].lo + f.ends[2 * b], other = p < 0 ? 0 : f.bucket[p].lo + f.ends[2 * p + 1];
+    before_key[b] = other;
+    uint32_t mask = 0;
+    for (int j = 0; j < f.levels.count; ++j) {
+        mine = spmi_div_by(mine, f.levels.size[j]);
+        other = spmi_div_by(other, f.levels.size[j]);
+        if (p < 0 || mine != other) {
+            mask |= 2u << j;                                         // bit j + 1: the level above the j-th
+            if (j + 1 < f.levels.count) f.heads[(size_t)j * f.most + b] += 1u;
+        }
+    }
+    first_mask[b] = mask;
+}
+
+__global__ void head_totals_kernel(const uint32_t *__restrict__ scanned, int64_t buckets, int slots, unsigned long long *__restrict__ totals)
+{
+    const int s = threadIdx.x;                                       // slot s: the (s + 1)-th level from the inside
+    if (s < slots) totals[s] = (unsigned long long)(scanned[(int64_t)(s + 1) * buckets] - scanned[(int64_t)s * buckets]);
+}
+
+struct level_arrays {
+    void *crd[SP_MAX_RANK], *pos[SP_MAX_RANK];                       // from the innermost level on
+    const uint32_t *heads;                                           // scanned, slot after slot
+    const uint32_t *first_mask;
+    const uint64_t *before_key;
+    int dense_above;                                                 // the outermost compressed level lies under dense ones
+};
+
+// Sorted entries -> crd and pos of all levels, for compressed levels that lie inside dense ones (or make up the format).  Block = a
+// bucket; 32-bit distances and quotients relative to the bucket's smallest key, one multiplication per level.  From the
+// innermost level outwards: the entry that begins a new prefix of the level above writes that position's pos entry.  pos
+// under a dense level is left as counts (one integer add where a parent begins and one where the next does), to be scanned.
+constexpr int kLT = 512;
+template <typename PT, typename CT>
+__global__ __launch_bounds__(kLT) void bucket_levels_kernel(final_args f, level_arrays a)
+{
+    constexpr int R = kCap / kLT, W = kLT / 64;
+    static_assert(R * W <= 64, "one lane per wave and round");
+    __shared__ uint32_t wcnt[2][R * W];
+    typedef typename std::conditional<sizeof(PT) == 8, unsigned long long, unsigned int>::type UT;
+    const uint32_t b = blockIdx.x;
+    if (b >= (f.count ? *f.count : f.most)) return;
+    const uint32_t cnt = f.bucket[b].cnt, out = f.bucket[b].out;
+    if (cnt == 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, L = f.levels.count;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const uint32_t *__restrict__ dist = f.dist + out;
+    uint32_t q[R], child[R], edge = 0;
+    bool valid[R];
+    uint32_t mark = 0;                                               // a bit per round: the entry begins a position of the current level
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t i = (uint32_t)(r * kLT + tid);
+        valid[r] = i < cnt;
+        q[r] = dist[valid[r] ? i : cnt - 1];
+        child[r] = out + i;
+        mark |= valid[r] ? 1u << r : 0u;
+    }
+    {   // lane r: the distance before the wave's first entry of round r
+        const uint32_t i = (uint32_t)((lane & (R - 1)) * kLT + wave * 64);
+        edge = i == 0 ? 0u : dist[i - 1 < cnt ? i - 1 : cnt - 1];
+    }
+    const bool first_here = tid == 0;                     // round 0 of this thread is the bucket's first entry
+    const uint32_t first = first_here ? a.first_mask[b] : 0u;
+    for (int j = 0; j < L; ++j) {                                    // uniform
+        const uint32_t off = f.off[(size_t)b * SP_MAX_RANK + j], size = (uint32_t)f.levels.size[j].d;
+        const double half = (double)off + 0.5, inv = f.levels.size[j].inv;
+        const uint32_t eup = quotient(edge, half, inv);
+        CT *__restrict__ crd = (CT *)a.crd[j];
+        PT *__restrict__ pos = (PT *)a.pos[j];
+        uint32_t up[R], began = 0, at[R], old[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            up[r] = quotient(q[r], half, inv);
+            if ((mark >> r) & 1u) crd[child[r]] = (CT)(uint32_t)(off + q[r] - up[r] * size);
+            old[r] = lane_before(up[r], (uint32_t)__builtin_amdgcn_readlane((int)eup, r));
+            const bool begins = r == 0 && first_here ? ((first >> (j + 1)) & 1u) != 0 : up[r] != old[r];
+            began |= valid[r] && begins ? 1u << r : 0u;
+        }
+        if (j + 1 < L) {                                             // positions of the compressed level above
+            const uint32_t *before = a.heads + (size_t)j * f.most;
+            const uint32_t base = before[b] - before[0];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const unsigned long long m = __ballot((began >> r) & 1u);
+                at[r] = (uint32_t)__popcll(m & below);
+                if (lane == 0) wcnt[j & 1][r * W + wave] = (uint32_t)__popcll(m);
+            }
+            __syncthreads();
+            const uint32_t n = lane < R * W ? wcnt[j & 1][lane] : 0u, excl = wave_inclusive_scan(n, lane) - n;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool m = (began >> r) & 1u;
+                at[r] += base + (uint32_t)__builtin_amdgcn_readlane((int)excl, r * W + wave) + (m ? 1u : 0u) - 1u;
+                if (m) pos[at[r]] = (PT)child[r];
+                if (valid[r] && out + (uint32_t)(r * kLT + tid) == (uint32_t)(f.n - 1)) pos[at[r] + 1] = (PT)(child[r] + 1);
+                child[r] = at[r];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (!valid[r]) continue;
+                const bool m = (began >> r) & 1u, last = out + (uint32_t)(r * kLT + tid) == (uint32_t)(f.n - 1);
+                if (!a.dense_above) {
+                    if (last) { pos[0] = 0; pos[1] = (PT)(child[r] + 1); }
+                } else if (m || last) {
+                    // the dense position: what lo's prefix is, and the quotient on top of it
+                    uint64_t top = f.bucket[b].lo, prev = a.before_key[b];
+                    for (int k = 0; k < L; ++k) { top = spmi_div_by(top, f.levels.size[k]); prev = spmi_div_by(prev, f.levels.size[k]); }
+                    const uint64_t P = top + up[r], Q = r == 0 && first_here ? prev : top + old[r];
+                    if (m && child[r]) {
+                        atomicAdd((UT *)&pos[P], (UT)0 - (UT)child[r]);
+                        atomicAdd((UT *)&pos[Q], (UT)child[r]);
+                    }
+                    if (last) atomicAdd((UT *)&pos[P], (UT)(child[r] + 1));
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) q[r] = up[r];
+        edge = eup;
+        mark = began;
     }
 }
 
 inline size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-template <typename K, typename P>
-sp_status sort_t(const source &src, const P *vals, int64_t n, uint64_t total, int key_bits, const spmi_bucket_plan &plan, const spmi_bucket_out &o,
-                 int *flags, sp_scratch &tmp, hipStream_t st)
+struct tables {
+    level1 t;
+    level2 u;
+    uint32_t *runs, *split, *frank, *left, *off, *heads, *ends, *first_mask;
+    uint64_t *before_key;
+    final_bucket *bucket;
+    int *flags;
+    uint64_t room1, room2;
+    uint32_t parts_max, tiles_max;
+    size_t bytes;
+};
+
+// The tables of a build, one after the other at `tab` (null: how much they take).
+tables tables_of(const spmi_bucket_plan &plan, int64_t n, unsigned char *tab)
 {
+    tables x;
     const uint32_t Q = plan.Q, F = plan.F, S = plan.S;
-    const int B = (int)(Q + F);
+    const size_t B = Q + F;
+    // room of the first partition: the shares add up to n, the margins are largest when all buckets are alike
+    x.room1 = (uint64_t)n + 64;
+    if (S) x.room1 = (uint64_t)((double)n + (double)B * ((double)n / S * (6.0 * sqrt((double)S / (double)B + 4.0) + 10.0) + 32.0)) + 1024;
+    x.room2 = plan.two ? (uint64_t)(2.2 * (double)n) + (uint64_t)B * 4096 : 0;
+    x.parts_max = plan.two ? (uint32_t)(n / kTarget) + (uint32_t)B : (uint32_t)B;
+    x.tiles_max = plan.two ? (uint32_t)(n / (kPT * kPR)) + (uint32_t)B : 1u;
+    x.bytes = 0;
+    auto place = [&](size_t b) { unsigned char *at = tab + x.bytes; x.bytes += pad256(b); return (void *)at; };
+    x.flags = (int *)place(kSpmiFlagBytes);
+    x.runs = (uint32_t *)place((size_t)(S ? S : 4) * 4); x.split = (uint32_t *)place((size_t)(Q + 1) * 4); x.frank = (uint32_t *)place((size_t)(F + 1) * 4);
+    x.t.lo = (uint64_t *)place((B + 1) * 8); x.t.start = (uint32_t *)place(B * 4); x.t.end = (uint32_t *)place(B * 4); x.t.cur = (uint32_t *)place(B * 4);
+    x.t.lut = (uint16_t *)place((size_t)(kCells + 1) * 2); x.t.out = (uint32_t *)place((B + 1) * 4); x.t.sub0 = (uint32_t *)place((B + 1) * 4);
+    x.t.tile0 = (uint32_t *)place((B + 1) * 4); x.t.room2 = (uint32_t *)place(B * 4); x.t.used = (uint32_t *)place(B * 4); x.t.B = (int)B;
+    const size_t parts = x.parts_max;
+    x.u.lo = (uint64_t *)place((parts + 1) * 8); x.u.start = (uint32_t *)place(parts * 4); x.u.end = (uint32_t *)place(parts * 4); x.u.cur = (uint32_t *)place(parts * 4);
+    x.u.tile_bucket = (uint16_t *)place((size_t)x.tiles_max * 2);
+    x.left = (uint32_t *)place(parts * 4); x.bucket = (final_bucket *)place(parts * sizeof(final_bucket));
+    x.off = (uint32_t *)place(parts * SP_MAX_RANK * 4);
+    x.ends = (uint32_t *)place(parts * 8); x.first_mask = (uint32_t *)place(parts * 4); x.before_key = (uint64_t *)place(parts * 8);
+    x.heads = (uint32_t *)place(((size_t)plan.slots * parts + 1) * 4);
+    return x;
+}
+
+final_args final_args_of(const spmi_bucket_job &job, const tables &x)
+{
+    final_args f;
+    memset(&f, 0, sizeof(f));
+    f.bucket = x.bucket; f.count = job.plan.two ? x.t.sub0 + x.t.B : nullptr; f.most = x.parts_max; f.n = job.n;
+    f.left = x.left; f.flags = x.flags; f.heads = x.heads; f.ends = x.ends; f.off = x.off; f.levels = job.levels;
+    f.inner = spmi_make_divisor(1); f.nblocks = ceil_div(job.n, kSpmiStreamT);
+    return f;
+}
+
+// Room for the entries in their buckets, behind the tables.
+template <typename K, typename P>
+struct moved {
+    K *k1, *k2;
+    P *v1, *v2;
+    size_t bytes;
+    moved(const tables &x, bool two, unsigned char *at)
+    {
+        const size_t n1 = x.room1 + kDump, n2 = two ? x.room2 + kDump : 0;
+        bytes = 0;
+        auto place = [&](size_t b) { unsigned char *p = at + bytes; bytes += pad256(b); return (void *)p; };
+        v1 = (P *)place(n1 * sizeof(P)); k1 = (K *)place(n1 * sizeof(K));
+        v2 = two ? (P *)place(n2 * sizeof(P)) : v1;
+        k2 = two ? (K *)place(n2 * sizeof(K)) : k1;
+    }
+};
+
+template <typename K, typename P>
+sp_status move_entries(const spmi_bucket_job &job, const P *vals, hipStream_t st)
+{
+    const source &src = job.src;
+    const spmi_bucket_plan &plan = job.plan;
+    const int64_t n = job.n;
+    const uint64_t total = job.total;
+    const tables x = tables_of(plan, n, (unsigned char *)job.tab);
+    const moved<K, P> m(x, plan.two, (unsigned char *)job.tab + x.bytes);
+    K *k1 = m.k1, *k2 = m.k2;
+    P *v1 = m.v1, *v2 = m.v2;
+    const level1 &t = x.t;
+    const level2 &u = x.u;
+    const int B = t.B;
     const bool two = plan.two;
-    const int sshift = key_bits > 32 ? key_bits - 32 : 0;
+    const uint64_t room1 = x.room1, room2 = x.room2;
+    const uint32_t tiles_max = x.tiles_max;
+    int *flags = x.flags;
     int cell_shift = 0;
     while (((total - 1) >> cell_shift) >= (uint64_t)kCells) ++cell_shift;
-    // room of the first partition: the shares add up to n, the margins are largest when all buckets are alike
-    uint64_t room1 = (uint64_t)n + 64;
-    if (S) room1 = (uint64_t)((double)n + (double)B * ((double)n / S * (6.0 * sqrt((double)S / B + 4.0) + 10.0) + 32.0)) + 1024;
-    const uint64_t room2 = two ? (uint64_t)(2.2 * (double)n) + (uint64_t)B * 4096 : 0;
-    if (room1 + kDump >= 0xfff00000ull || room2 + kDump >= 0xfff00000ull) return SP_ERR_TOO_LARGE;
-    const uint32_t parts_max = two ? (uint32_t)(n / kTarget) + (uint32_t)B : (uint32_t)B;
-    const uint32_t tiles_max = two ? (uint32_t)(n / (kPT * kPR)) + (uint32_t)B : 1u;
-    K *k1 = (K *)tmp.get((room1 + kDump) * sizeof(K));
-    P *v1 = (P *)tmp.get((room1 + kDump) * sizeof(P));
-    K *k2 = two ? (K *)tmp.get((room2 + kDump) * sizeof(K)) : k1;
-    P *v2 = two ? (P *)tmp.get((room2 + kDump) * sizeof(P)) : v1;
-    // tables
-    size_t bytes = 0;
-    auto place = [&](size_t b) { const size_t at = bytes; bytes += pad256(b); return at; };
-    const size_t a_runs = place((size_t)(S ? S : 4) * 4), a_split = place((size_t)(Q + 1) * 4), a_frank = place((size_t)(F + 1) * 4);
-    const size_t a_lo1 = place((size_t)(B + 1) * 8), a_start1 = place((size_t)B * 4), a_end1 = place((size_t)B * 4), a_cur1 = place((size_t)B * 4);
-    const size_t a_lut = place((size_t)(kCells + 1) * 2), a_out1 = place((size_t)(B + 1) * 4), a_sub0 = place((size_t)(B + 1) * 4);
-    const size_t a_tile0 = place((size_t)(B + 1) * 4), a_room2 = place((size_t)B * 4), a_used = place((size_t)B * 4);
-    const size_t a_lo2 = place((size_t)(parts_max + 1) * 8), a_start2 = place((size_t)parts_max * 4), a_end2 = place((size_t)parts_max * 4);
-    const size_t a_cur2 = place((size_t)parts_max * 4), a_tb = place((size_t)tiles_max * 2);
-    const size_t a_left = place((size_t)parts_max * 4), a_final = place((size_t)parts_max * sizeof(final_bucket));
-    unsigned char *tab = (unsigned char *)tmp.get(bytes);
-    if (!k1 || !v1 || !k2 || !v2 || !tab) return SP_ERR_ALLOC;
-    level1 t;
-    t.lo = (uint64_t *)(tab + a_lo1); t.start = (uint32_t *)(tab + a_start1); t.end = (uint32_t *)(tab + a_end1); t.cur = (uint32_t *)(tab + a_cur1);
-    t.lut = (uint16_t *)(tab + a_lut); t.out = (uint32_t *)(tab + a_out1); t.sub0 = (uint32_t *)(tab + a_sub0); t.tile0 = (uint32_t *)(tab + a_tile0);
-    t.room2 = (uint32_t *)(tab + a_room2); t.used = (uint32_t *)(tab + a_used); t.B = B;
-    level2 u;
-    u.lo = (uint64_t *)(tab + a_lo2); u.start = (uint32_t *)(tab + a_start2); u.end = (uint32_t *)(tab + a_end2); u.cur = (uint32_t *)(tab + a_cur2);
-    u.tile_bucket = (uint16_t *)(tab + a_tb);
-    uint32_t *runs = (uint32_t *)(tab + a_runs), *split = (uint32_t *)(tab + a_split), *frank = (uint32_t *)(tab + a_frank);
-    if (S) {
-        hipLaunchKernelGGL(sample_runs_kernel, dim3(S / kRun), dim3(kRun), 0, st, src, n, S, sshift, runs);
-        if ((size_t)S * 4 > 65536)
-            SP_HIP(hipFuncSetAttribute((const void *)sample_ranks_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSample * 4));
-        hipLaunchKernelGGL(sample_ranks_kernel, dim3((S + F + kRankT - 1) / kRankT), dim3(kRankT), (size_t)S * 4, st, (const uint32_t *)runs, S, sshift, Q, F, split,
-                           frank);
-        SP_HIP(hipGetLastError());
-    }
-    hipLaunchKernelGGL(buckets_kernel, dim3(1), dim3(1024), 0, st, (const uint32_t *)split, (const uint32_t *)frank, S, sshift, Q, F, total, cell_shift, n, t);
-    SP_HIP(hipGetLastError());
     // first partition
-    const bool small = n < (int64_t)kPT * kPR * 256, wide_tile = !small && B > kPT;
-    const int tile = wide_tile ? kWideT * kPR : small ? kPT * kSmallR : kPT * kPR;
+    const bool small = n < (int64_t)kPT * kPR * 256;
+    const int tile = small ? kPT * kSmallR : kWideT * kPR;
     const uint32_t tiles = (uint32_t)ceil_div(n, (int64_t)tile);
     const size_t stage = std::max(stage_bytes<K, P>(tile), (size_t)B * 8 + (kCells + 1) * 2);
     const size_t lds = (((size_t)B * 4 + 15) & ~(size_t)15) + stage + 16;
@@ -1052,10 +1353,9 @@ sp_status sort_t(const source &src, const P *vals, int64_t n, uint64_t total, in
         if (lds > 65536) SP_HIP(hipFuncSetAttribute((const void *)partition_kernel<K, P, T_, R_, PER_>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 512)); \
         hipLaunchKernelGGL((partition_kernel<K, P, T_, R_, PER_>), dim3(round8(tiles)), dim3(T_), lds, st, src, vals, n, t, cell_shift, dump1, k1, v1, flags); \
     } while (0)
-    if (wide_tile) SPMI_PART(kWideT, kPR, kMaxBuckets / kWideT);
-    else if (small && B > kPT) SPMI_PART(kPT, kSmallR, kMaxBuckets / kPT);
-    else if (small) SPMI_PART(kPT, kSmallR, 1);
-    else SPMI_PART(kPT, kPR, 1);
+    if (!small) SPMI_PART(kWideT, kPR, kMaxBuckets / kWideT);
+    else if (B > kPT) SPMI_PART(kPT, kSmallR, kMaxBuckets / kPT);
+    else SPMI_PART(kPT, kSmallR, 1);
 #undef SPMI_PART
     hipLaunchKernelGGL(bucket_sizes_kernel, dim3(1), dim3(1024), 0, st, t, two ? 1 : 0, (uint32_t)(kPT * kPR), (uint32_t)room2, flags);
     SP_HIP(hipGetLastError());
@@ -1065,35 +1365,63 @@ sp_status sort_t(const source &src, const P *vals, int64_t n, uint64_t total, in
                            (const int *)flags);
         SP_HIP(hipGetLastError());
     }
-    final_args f;
-    memset(&f, 0, sizeof(f));
-    final_bucket *bucket = (final_bucket *)(tab + a_final);
-    f.bucket = bucket; f.count = two ? t.sub0 + B : nullptr; f.most = parts_max; f.n = n;
-    f.left = (uint32_t *)(tab + a_left); f.flags = flags;
-    f.keys = o.keys; f.crd = o.crd; f.pos = o.pos; f.rowblk = o.rowblk; f.rows = o.rows; f.pw = o.pw; f.cw = o.cw;
-    f.inner = spmi_make_divisor(o.inner ? o.inner : 1); f.nblocks = ceil_div(n, kSpmiStreamT);
+    return SP_OK;
+}
+
+template <typename K, typename P>
+sp_status finish(const spmi_bucket_job &job, const spmi_bucket_out &o, sp_scratch &tmp, hipStream_t st)
+{
+    const spmi_bucket_plan &plan = job.plan;
+    const tables x = tables_of(plan, job.n, (unsigned char *)job.tab);
+    const moved<K, P> m(x, plan.two, (unsigned char *)job.tab + x.bytes);
+    const K *k2 = m.k2;
+    const P *v2 = m.v2;
+    const level1 &t = x.t;
+    const level2 &u = x.u;
+    const int B = t.B;
+    const bool two = plan.two;
+    const uint32_t parts_max = x.parts_max;
+    final_args f = final_args_of(job, x);
+    f.keys = o.keys; f.dist = o.dist; f.crd = o.crd; f.pos = o.pos; f.rowblk = o.rowblk; f.rows = o.rows; f.pw = o.pw; f.cw = o.cw;
+    f.inner = spmi_make_divisor(o.inner ? o.inner : 1);
     hipLaunchKernelGGL(final_buckets_kernel, dim3(two ? (unsigned)B : (unsigned)ceil_div(B, 256)), dim3(256), 0, st, (const uint64_t *)(two ? u.lo : t.lo),
                        (const uint32_t *)(two ? u.start : t.start), (const uint32_t *)(two ? u.end : t.end), (const uint32_t *)(two ? u.cur : t.cur),
-                       (const uint32_t *)t.out, (const uint32_t *)(two ? t.sub0 : nullptr), (uint32_t)B, bucket, f);
+                       (const uint32_t *)t.out, (const uint32_t *)(two ? t.sub0 : nullptr), (uint32_t)B, x.bucket, x.off, f);
     hipLaunchKernelGGL((finish_kernel<K, P>), dim3(parts_max), dim3(kFT), 0, st, (const K *)k2, (const P *)v2, (P *)o.values, f);
-    hipLaunchKernelGGL((finish_crowded_kernel<K, P>), dim3(std::min(parts_max, 512u)), dim3(1024), 0, st, (const K *)k2, (const P *)v2, (P *)o.values, f);
+    hipLaunchKernelGGL((finish_crowded_kernel<K, P>), dim3(std::min(parts_max, 1024u)), dim3(kFT), 0, st, (const K *)k2, (const P *)v2, (P *)o.values, f);
     SP_HIP(hipGetLastError());
+    if (!o.dist) return SP_OK;
+    hipLaunchKernelGGL(bucket_heads_kernel, dim3((unsigned)ceil_div(parts_max, 256)), dim3(256), 0, st, f, x.first_mask, x.before_key);
+    SP_HIP(hipGetLastError());
+    if (plan.slots > 0) {
+        const int64_t buckets = (int64_t)x.parts_max;
+        SP_TRY(spmi_exclusive_scan(x.heads, plan.slots * buckets + 1, 32, tmp, st));          // the last element's input does not reach any output
+        hipLaunchKernelGGL(head_totals_kernel, dim3(1), dim3(64), 0, st, (const uint32_t *)x.heads, buckets, plan.slots, (unsigned long long *)(x.flags + 16));
+        SP_HIP(hipGetLastError());
+    }
     return SP_OK;
 }
 
 }  // namespace
 
-bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, spmi_bucket_plan *p)
+bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, int64_t rows, spmi_bucket_plan *p)
 {
     memset(p, 0, sizeof(*p));
     if (n < 1 || total < 1 || key_bits > 48) return false;            // sampled keys keep their upper 32 bits: 16 more may hide a crowd
-    const uint64_t steps = (total - 1) >> 32;                         // multiples of 2^32 inside the key range
     p->two = n > (int64_t)kTarget * (kMaxSample / kShare);
-    uint64_t Q = p->two ? (uint64_t)std::max<int64_t>(std::min<int64_t>(ceil_div(n, kFirst), 512), ceil_div(n, 4 * kFirst))
+    uint64_t Q = p->two ? (uint64_t)std::max<int64_t>(std::min<int64_t>(ceil_div(n, kFirst), 512), ceil_div(n, 2 * kFirst))
                         : n <= kCap ? 1u : (uint64_t)ceil_div(n, kTarget);
-    const uint64_t most_forced = (uint64_t)std::min<int64_t>(1024, n / kTarget);
-    p->wide = steps > most_forced;
-    p->F = p->wide ? 0u : (uint32_t)steps;
+    p->wide = ((total - 1) >> 32) > (uint64_t)std::min<int64_t>(1024, n / kTarget);
+    // equal steps of the key range that no bucket crosses: 2^32, so that its keys fit 32 bits, or less where the rows that begin in a
+    // bucket, which its block looks up, could be many (a matrix whose last rows are empty)
+    p->fbits = p->wide ? 63 : 32;
+    const uint64_t stretches = rows > 65536 ? std::min<uint64_t>(std::min<uint64_t>((uint64_t)rows / 16384, 255), Q) : 0;
+    if (stretches) {
+        int bits = 0;
+        while (((total - 1) >> bits) > stretches) ++bits;
+        p->fbits = std::min(p->fbits, bits);
+    }
+    p->F = (uint32_t)((total - 1) >> p->fbits);
     if (Q + p->F > (uint64_t)kMaxBuckets) return false;
     p->Q = (uint32_t)Q;
     if (Q + p->F > 1) {
@@ -1106,19 +1434,60 @@ bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, spmi_bucket_p
     return true;
 }
 
-sp_status spmi_bucket_sort(const int64_t *const *level_coords, const uint64_t *keys, const int64_t *level_size, int rank, const void *vals, int payload_bytes,
-                           int64_t n, uint64_t total, int key_bits, const spmi_bucket_plan &plan, const spmi_bucket_out &out, int *flags,
-                           sp_scratch &tmp, hipStream_t st)
+sp_status spmi_bucket_begin(spmi_bucket_job *job, const void *vals, int payload_bytes, sp_scratch &tmp, hipStream_t st)
 {
-    source s;
-    memset(&s, 0, sizeof(s));
-    s.keys = keys;
-    s.rank = rank;
-    for (int l = 0; l < rank; ++l) { s.coord[l] = keys ? nullptr : level_coords[l]; s.size[l] = level_size[l]; }
-    if (payload_bytes == 4) {
-        if (plan.wide) return sort_t<uint64_t, uint32_t>(s, (const uint32_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
-        return sort_t<uint32_t, uint32_t>(s, (const uint32_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
+    const spmi_bucket_plan &plan = job->plan;
+    job->payload_bytes = payload_bytes;
+    size_t bytes = 0;
+    {
+        const tables s = tables_of(plan, job->n, nullptr);
+        bytes = s.bytes + (payload_bytes == 4 ? (plan.wide ? moved<uint64_t, uint32_t>(s, plan.two, nullptr).bytes : moved<uint32_t, uint32_t>(s, plan.two, nullptr).bytes)
+                                              : (plan.wide ? moved<uint64_t, uint64_t>(s, plan.two, nullptr).bytes : moved<uint32_t, uint64_t>(s, plan.two, nullptr).bytes));
     }
-    if (plan.wide) return sort_t<uint64_t, uint64_t>(s, (const uint64_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
-    return sort_t<uint32_t, uint64_t>(s, (const uint64_t *)vals, n, total, key_bits, plan, out, flags, tmp, st);
+    job->tab = tmp.get(bytes);                                        // one block: an allocation costs the caller about 5 us
+    if (!job->tab) return SP_ERR_ALLOC;
+    const tables x = tables_of(plan, job->n, (unsigned char *)job->tab);
+    if (x.room1 + kDump >= 0xfff00000ull || x.room2 + kDump >= 0xfff00000ull) return SP_ERR_TOO_LARGE;
+    job->flags = x.flags;
+    const uint32_t Q = plan.Q, F = plan.F, S = plan.S;
+    const int sshift = job->key_bits > 32 ? job->key_bits - 32 : 0;
+    int cell_shift = 0;
+    while (((job->total - 1) >> cell_shift) >= (uint64_t)kCells) ++cell_shift;
+    if (S) {
+        hipLaunchKernelGGL(sample_runs_kernel, dim3(S / kRun), dim3(kRun), 0, st, job->src, job->n, S, sshift, x.runs);
+        if ((size_t)S * 4 > 65536)
+            SP_HIP(hipFuncSetAttribute((const void *)sample_ranks_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSample * 4));
+        hipLaunchKernelGGL(sample_ranks_kernel, dim3((S + F + kRankT - 1) / kRankT), dim3(kRankT), (size_t)S * 4, st, (const uint32_t *)x.runs, S, sshift, Q, F,
+                           x.split, x.frank, plan.fbits);
+        SP_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(buckets_kernel, dim3(1), dim3(1024), 0, st, (const uint32_t *)x.split, (const uint32_t *)x.frank, S, sshift, Q, F, plan.fbits, job->total,
+                       cell_shift, job->n, x.t, x.flags);
+    SP_HIP(hipGetLastError());
+    if (payload_bytes == 4) return plan.wide ? move_entries<uint64_t, uint32_t>(*job, (const uint32_t *)vals, st) : move_entries<uint32_t, uint32_t>(*job, (const uint32_t *)vals, st);
+    return plan.wide ? move_entries<uint64_t, uint64_t>(*job, (const uint64_t *)vals, st) : move_entries<uint32_t, uint64_t>(*job, (const uint64_t *)vals, st);
+}
+
+sp_status spmi_bucket_end(const spmi_bucket_job &job, const spmi_bucket_out &out, sp_scratch &tmp, hipStream_t st)
+{
+    if (job.payload_bytes == 4) return job.plan.wide ? finish<uint64_t, uint32_t>(job, out, tmp, st) : finish<uint32_t, uint32_t>(job, out, tmp, st);
+    return job.plan.wide ? finish<uint64_t, uint64_t>(job, out, tmp, st) : finish<uint32_t, uint64_t>(job, out, tmp, st);
+}
+
+sp_status spmi_bucket_levels(const spmi_bucket_job &job, const uint32_t *dist, void *const *crd, void *const *pos, bool dense_above, int pw, int cw, hipStream_t st)
+{
+    const tables x = tables_of(job.plan, job.n, (unsigned char *)job.tab);
+    final_args f = final_args_of(job, x);
+    f.dist = const_cast<uint32_t *>(dist);
+    level_arrays a;
+    memset(&a, 0, sizeof(a));
+    for (int j = 0; j < job.levels.count; ++j) { a.crd[j] = crd[j]; a.pos[j] = pos[j]; }
+    a.heads = x.heads; a.first_mask = x.first_mask; a.before_key = x.before_key; a.dense_above = dense_above ? 1 : 0;
+    const dim3 grid(x.parts_max);
+    if (pw == 32 && cw == 32) hipLaunchKernelGGL((bucket_levels_kernel<int32_t, int32_t>), grid, dim3(kLT), 0, st, f, a);
+    else if (pw == 32) hipLaunchKernelGGL((bucket_levels_kernel<int32_t, int64_t>), grid, dim3(kLT), 0, st, f, a);
+    else if (cw == 32) hipLaunchKernelGGL((bucket_levels_kernel<int64_t, int32_t>), grid, dim3(kLT), 0, st, f, a);
+    else hipLaunchKernelGGL((bucket_levels_kernel<int64_t, int64_t>), grid, dim3(kLT), 0, st, f, a);
+    SP_HIP(hipGetLastError());
+    return SP_OK;
 }

@@ -1296,9 +1296,6 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
     return SP_OK;
 }
 
-// The flags of a build: 64 bytes of them, then the sizes of the levels (see pack_core).
-constexpr size_t kFlagBytes = 64 + 8 * SP_MAX_RANK;
-
 // Everything after the input for distinct keys, sorted by buckets.  Entries come as coordinates by level or as keys.  *again: not done
 // (unsuitable input, no room for the buckets, a bucket overflowed): the tensor holds nothing, and the stable sorts have to do it.
 static sp_status pack_buckets(sp_tensor *t, int64_t nnz, const int64_t *const *level_coords, const uint64_t *keys, const void *vals, int key_bits,
@@ -1309,59 +1306,110 @@ static sp_status pack_buckets(sp_tensor *t, int64_t nnz, const int64_t *const *l
     const size_t vsz = t->dtype == SP_F64 ? 8 : 4;
     uint64_t total = 1;
     for (int l = 0; l < rank; ++l) total *= (uint64_t)(t->size[l] > 0 ? t->size[l] : 1);
-    spmi_bucket_plan plan;
     *again = true;
-    if (g_pack_sort_mode.load(std::memory_order_relaxed) != 0 || !spmi_bucket_plan_for(nnz, total, key_bits, &plan)) return SP_OK;
+    // formats whose compressed levels lie inside dense ones: `outer` dense levels, then compressed ones only
+    int outer = 0;
+    while (outer < rank && enc->lt[outer] == SP_DENSE) ++outer;
+    bool nested = outer < rank, small_sizes = true;
+    for (int l = outer; l < rank; ++l) nested &= enc->lt[l] == SP_COMPRESSED;
+    for (int l = 0; l < rank; ++l) small_sizes &= t->size[l] <= (int64_t)0xffffffffll;
+    // crd and pos straight from the buckets where every level above the innermost is dense; with rows far more than entries, zero
+    // filling and a scan are faster than a search per row
+    const uint64_t inner = (uint64_t)(t->size[rank - 1] > 0 ? t->size[rank - 1] : 1);
+    const bool csr_like = nested && rank > 1 && outer == rank - 1 && total / inner <= 4 * (uint64_t)nnz;
+    spmi_bucket_job job;
+    memset(&job, 0, sizeof(job));
+    if (g_pack_sort_mode.load(std::memory_order_relaxed) != 0 ||
+        !spmi_bucket_plan_for(nnz, total, key_bits, csr_like ? (int64_t)(total / inner) : 0, &job.plan)) return SP_OK;
     if (enc->pw_store < 64 && nnz > (((int64_t)1 << (enc->pw_store - 1)) - 1)) return SP_OK;      // pos may not fit: the other path sorts out the errors
-    bool csr_like = enc->lt[rank - 1] == SP_COMPRESSED && rank > 1;
-    for (int l = 0; l + 1 < rank; ++l) csr_like &= enc->lt[l] == SP_DENSE;
+    job.src.keys = keys;
+    job.src.rank = rank;
+    for (int l = 0; l < rank; ++l) { job.src.coord[l] = keys ? nullptr : level_coords[l]; job.src.size[l] = t->size[l]; }
+    job.n = nnz; job.total = total; job.key_bits = key_bits;
+    const bool levels = !csr_like && nested && small_sizes && !job.plan.wide && !(outer == rank - 1 && rank > 1);
+    if (levels) {
+        job.levels.count = rank - outer;
+        for (int j = 0; j < job.levels.count; ++j) job.levels.size[j] = spmi_make_divisor((uint64_t)t->size[rank - 1 - j]);
+        job.plan.slots = job.levels.count - 1;
+    }
     sp_scratch tmp(mem);
     auto run = [&]() -> sp_status {
-        int *flags = (int *)tmp.get(kFlagBytes);
-        if (!flags) return SP_ERR_ALLOC;
-        SP_TRY(spmi_fill_zero(flags, kFlagBytes, st));
+        SP_TRY(spmi_bucket_begin(&job, vals, (int)vsz, tmp, st));
         spmi_bucket_out o;
         memset(&o, 0, sizeof(o));
-        if (!csr_like) {
+        if (!csr_like && !levels) {
             uint64_t *sorted = (uint64_t *)tmp.get((size_t)nnz * 8);
             void *payload = tmp.get(pad16((size_t)nnz * vsz));
             if (!sorted || !payload) return SP_ERR_ALLOC;
             o.keys = sorted;
             o.values = payload;
-            SP_TRY(spmi_bucket_sort(level_coords, keys, t->size, rank, vals, (int)vsz, nnz, total, key_bits, plan, o, flags, tmp, st));
+            SP_TRY(spmi_bucket_end(job, o, tmp, st));
             bool overflow = false;
-            SP_TRY(pack_core(t, nnz, sorted, payload, key_bits, false, flags, tmp, mem, st, nullptr, &overflow));
+            SP_TRY(pack_core(t, nnz, sorted, payload, key_bits, false, job.flags, tmp, mem, st, nullptr, &overflow));
             *again = overflow;
             return SP_OK;
         }
-        const int l = rank - 1;
-        o.inner = (uint64_t)t->size[l];
-        o.rows = (int64_t)(total / o.inner);
-        o.pw = enc->pw; o.cw = enc->cw;
-        t->nnz = t->nvalues = t->ncrd[l] = nnz;
-        t->npos[l] = o.rows + 1;
-        t->pos[l] = o.pos = mem.get(pad16((size_t)t->npos[l] * (enc->pw / 8)));
-        t->crd[l] = o.crd = mem.get(pad16((size_t)nnz * (enc->cw / 8)));
+        t->nnz = t->nvalues = nnz;
         t->values = o.values = mem.get(pad16((size_t)nnz * vsz));
-        if (!o.pos || !o.crd || !o.values) return SP_ERR_ALLOC;
-        if (rank == 2 && o.rows < ((int64_t)1 << 31) - 1) {
-            const int64_t nb = ceil_div(nnz, kSpmiStreamT);
-            t->rowblocks.start = mem.get(pad16((size_t)(nb + 1) * 4));
-            t->rowblocks.carry = mem.get(pad16((size_t)nb * 8));
-            t->rowblocks.nblocks = nb;
-            if (!t->rowblocks.start || !t->rowblocks.carry) return SP_ERR_ALLOC;
-            o.rowblk = (int32_t *)t->rowblocks.start;
+        if (!o.values) return SP_ERR_ALLOC;
+        if (levels) {
+            o.dist = (uint32_t *)tmp.get((size_t)nnz * 4);
+            if (!o.dist) return SP_ERR_ALLOC;
+            SP_TRY(spmi_bucket_end(job, o, tmp, st));
+            int h[kSpmiFlagBytes / 4];
+            unsigned long long totals[SP_MAX_RANK];
+            SP_HIP(hipMemcpyAsync(h, job.flags, sizeof(h), hipMemcpyDeviceToHost, st));
+            SP_HIP(hipStreamSynchronize(st));
+            memcpy(totals, h + 16, sizeof(totals));
+            if (h[2] || h[3]) return SP_OK;                              // *again stays
+            *again = false;
+            if (h[0] || h[1]) return h[0] ? SP_ERR_COORD_RANGE : SP_ERR_DUPLICATE;
+            void *crd[SP_MAX_RANK], *pos[SP_MAX_RANK];
+            uint64_t P = 1;
+            for (int l = 0; l < outer; ++l) P *= (uint64_t)t->size[l];
+            for (int l = outer; l < rank; ++l) {
+                const int j = rank - 1 - l;                              // from the innermost on
+                const int64_t nchild = j == 0 ? nnz : (int64_t)totals[j - 1];
+                const size_t pbytes = pad16((size_t)(P + 1) * (enc->pw / 8));
+                t->npos[l] = (int64_t)P + 1;
+                t->ncrd[l] = nchild;
+                t->pos[l] = pos[j] = mem.get(pbytes);
+                t->crd[l] = crd[j] = mem.get(pad16((size_t)nchild * (enc->cw / 8)));
+                if (!pos[j] || !crd[j]) return SP_ERR_ALLOC;
+                if (l == outer && outer > 0) SP_TRY(spmi_fill_zero(pos[j], pbytes, st));
+                P = (uint64_t)nchild;
+            }
+            SP_TRY(spmi_bucket_levels(job, o.dist, crd, pos, outer > 0, enc->pw, enc->cw, st));
+            if (outer > 0) SP_TRY(spmi_exclusive_scan(t->pos[outer], t->npos[outer], enc->pw, tmp, st));
+        } else {
+            const int l = rank - 1;
+            o.inner = inner;
+            o.rows = (int64_t)(total / inner);
+            o.pw = enc->pw; o.cw = enc->cw;
+            t->ncrd[l] = nnz;
+            t->npos[l] = o.rows + 1;
+            t->pos[l] = o.pos = mem.get(pad16((size_t)t->npos[l] * (enc->pw / 8)));
+            t->crd[l] = o.crd = mem.get(pad16((size_t)nnz * (enc->cw / 8)));
+            if (!o.pos || !o.crd) return SP_ERR_ALLOC;
+            if (rank == 2 && o.rows < ((int64_t)1 << 31) - 1) {
+                const int64_t nb = ceil_div(nnz, kSpmiStreamT);
+                t->rowblocks.start = mem.get(pad16((size_t)(nb + 1) * 4));
+                t->rowblocks.carry = mem.get(pad16((size_t)nb * 8));
+                t->rowblocks.nblocks = nb;
+                if (!t->rowblocks.start || !t->rowblocks.carry) return SP_ERR_ALLOC;
+                o.rowblk = (int32_t *)t->rowblocks.start;
+            }
+            SP_TRY(spmi_bucket_end(job, o, tmp, st));
         }
-        SP_TRY(spmi_bucket_sort(level_coords, keys, t->size, rank, vals, (int)vsz, nnz, total, key_bits, plan, o, flags, tmp, st));
         SP_TRY(narrow_copies(t, mem, st));
         int h[4] = {0, 0, 0, 0};
-        SP_TRY(spmi_finish_tensor(t, flags, tmp, st, h));
+        SP_TRY(spmi_finish_tensor(t, job.flags, tmp, st, h));
         *again = h[2] || h[3];
         return *again ? SP_OK : h[0] ? SP_ERR_COORD_RANGE : h[1] ? SP_ERR_DUPLICATE : SP_OK;
     };
     const sp_status s = run();
-    if (s != SP_OK && s != SP_ERR_ALLOC && s != SP_ERR_TOO_LARGE) *again = false;
     if (s == SP_ERR_ALLOC || s == SP_ERR_TOO_LARGE) *again = true;
+    else if (s != SP_OK) *again = false;
     if (s != SP_OK || *again) {
         (void)hipStreamSynchronize(st);                   // queued kernels may still use what goes now
         release_tensor_arrays(t);
@@ -1446,12 +1494,12 @@ extern "C" sp_status sp_pack(const sp_encoding *enc, const int64_t *shape, int64
         sp_scratch tmp(mem);
         const size_t cnt = (size_t)(nnz > 0 ? nnz : 1);
         uint64_t *keys = (uint64_t *)tmp.get(cnt * 8);
-        int *flags = (int *)tmp.get(kFlagBytes);
+        int *flags = (int *)tmp.get(kSpmiFlagBytes);
         sp_msd_plan plan;
         memset(&plan, 0, sizeof(plan));
         do {
             if (!keys || !flags) { status = SP_ERR_ALLOC; break; }
-            if ((status = spmi_fill_zero(flags, kFlagBytes, st)) != SP_OK) break;
+            if ((status = spmi_fill_zero(flags, kSpmiFlagBytes, st)) != SP_OK) break;
             if (nnz > 0) {
                 level_args la;
                 memset(&la, 0, sizeof(la));
@@ -1496,8 +1544,8 @@ sp_status spmi_pack_keys(const sp_encoding *enc, const int64_t *shape, sp_dtype 
     int key_bits = 0;
     SP_TRY(spmi_new_tensor(enc, shape, dt, alloc, free_, ctx, false, &t, &key_bits));
     sp_mem mem{alloc, free_, ctx};
-    int *flags = (int *)tmp.get(kFlagBytes);
-    sp_status status = flags ? spmi_fill_zero(flags, kFlagBytes, st) : SP_ERR_ALLOC;
+    int *flags = (int *)tmp.get(kSpmiFlagBytes);
+    sp_status status = flags ? spmi_fill_zero(flags, kSpmiFlagBytes, st) : SP_ERR_ALLOC;
     if (status == SP_OK) status = pack_core(t, n, keys, payload, key_bits, true, flags, tmp, mem, st);
     if (status != SP_OK) (void)hipStreamSynchronize(st);
     return spmi_finish_pack(t, status, st, out);
@@ -1519,13 +1567,13 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
     {
         sp_scratch tmp(mem);
         uint64_t *keys = (uint64_t *)tmp.get((size_t)(n > 0 ? n : 1) * 8);
-        int *flags = (int *)tmp.get(kFlagBytes);
+        int *flags = (int *)tmp.get(kSpmiFlagBytes);
         sp_msd_plan plan;
         memset(&plan, 0, sizeof(plan));
         bool by_buckets = false;
         do {
             if (!keys || !flags) { status = SP_ERR_ALLOC; break; }
-            if ((status = spmi_fill_zero(flags, kFlagBytes, st)) != SP_OK) break;
+            if ((status = spmi_fill_zero(flags, kSpmiFlagBytes, st)) != SP_OK) break;
             if (n > 0) {
                 uint64_t weight[SP_MAX_RANK], w = 1;     // by dimension
                 for (int l = rank - 1; l >= 0; --l) { weight[enc->perm[l]] = w; w *= (uint64_t)t->size[l]; }
@@ -1540,7 +1588,7 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
                 }
                 // the sort by buckets has no use for the counts; should it not do after all, the other sorts make them
                 spmi_bucket_plan buckets;
-                by_buckets = g_pack_sort_mode.load(std::memory_order_relaxed) == 0 && spmi_bucket_plan_for(n, w, key_bits, &buckets);
+                by_buckets = g_pack_sort_mode.load(std::memory_order_relaxed) == 0 && spmi_bucket_plan_for(n, w, key_bits, 0, &buckets);
                 if (!by_buckets && (status = spmi_msd_plan(n, key_bits, tmp, st, &plan)) != SP_OK) break;
                 const dim3 grid((unsigned)ceil_div(n, kSpmiMsdTile));
 #define SPMI_CONVERT(PT, CT) hipLaunchKernelGGL((convert_keys_kernel<PT, CT>), grid, dim3(kThreads), 0, st, a, n, keys, plan)

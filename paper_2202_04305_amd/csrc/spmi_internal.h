@@ -459,19 +459,46 @@ sp_status spmi_sort_pairs(uint64_t *keys, const void *vals, int payload_bytes, i
                           const sp_msd_plan *plan, uint64_t **keys_out, const void **vals_out);
 extern std::atomic<int> g_pack_sort_mode;
 // ---- buckets.hip ----
-// The builder's sort for entries with distinct keys (equal ones are reported, not ordered): spmi_bucket_plan_for() says whether
-// n entries with keys below `total` suit it and how they will be cut; spmi_bucket_sort() enqueues it.  Entries come as
-// coordinates by level (checked against the sizes: flags[0]) or as keys; neither they nor vals are changed.  What leaves is
-// either the sorted keys and values, or (keys null) crd, pos and values of an innermost compressed level of size `inner`
-// under `rows` positions of dense ones and, where rowblk is given, the row of every kSpmiStreamT-th entry.
-// flags (zero before), once the stream is done: [0] a coordinate was out of range, [1] a key occurs twice, [2] or [3] a bucket
-// overflowed: the outputs are of no use then (keys stay below total) and the stable sorts have to do it.
-struct spmi_bucket_plan { uint32_t Q, F, S; bool two, wide; };   // splitters by sample, multiples of 2^32, sampled keys, two partitions, 64-bit keys
-struct spmi_bucket_out { uint64_t *keys; void *values, *crd, *pos; int32_t *rowblk; int64_t rows; uint64_t inner; int pw, cw; };
-bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, spmi_bucket_plan *plan);
-sp_status spmi_bucket_sort(const int64_t *const *level_coords, const uint64_t *keys, const int64_t *level_size, int rank, const void *vals, int payload_bytes,
-                           int64_t n, uint64_t total, int key_bits, const spmi_bucket_plan &plan, const spmi_bucket_out &out, int *flags,
-                           sp_scratch &tmp, hipStream_t st);
+// The builder's sort for entries with distinct keys (equal ones are reported, not ordered).  spmi_bucket_plan_for() says whether
+// n entries with keys below `total` suit it and how they will be cut; rows: as in spmi_bucket_out, 0 where anything else leaves.
+// The caller fills in a job; spmi_bucket_begin() takes scratch and enqueues the sample and the partitions, spmi_bucket_end() the
+// finishing pass (so that the arrays it writes are allocated while the GPU is busy).
+// Entries come as coordinates by level (checked against the sizes: flags[0]) or as keys; neither they nor vals are changed.  What
+// leaves is one of
+//   the sorted keys and values;
+//   crd, pos and values of an innermost compressed level of size `inner` under `rows` positions of dense ones, and, where rowblk is
+//   given, the row of every kSpmiStreamT-th entry;
+//   dist (32-bit keys only) and values: then flags + 16 has the sizes of the levels (64 bits each, from the second on; job.levels,
+//   counted from the innermost outwards), and spmi_bucket_levels() writes crd and pos of them all.  pos of the outermost
+//   one arrives zeroed and is left as counts to be scanned where dense levels lie above it.
+// flags (job.flags, zeroed by spmi_bucket_begin), once the stream is done: [0] a coordinate was out of range, [1] a key occurs
+// twice, [2] or [3] a bucket overflowed: the outputs are of no use then (keys stay below total, dist and heads must not be
+// used) and the stable sorts have to do it.
+constexpr size_t kSpmiFlagBytes = 64 + 8 * SP_MAX_RANK;              // the flags of a build: 64 bytes of them, then the sizes of levels
+struct spmi_bucket_source {
+    const int64_t *coord[SP_MAX_RANK];   // by level, or
+    const uint64_t *keys;                // the keys themselves (coord unused)
+    int64_t size[SP_MAX_RANK];
+    int rank;
+};
+struct spmi_levels { int count; spmi_divisor size[SP_MAX_RANK]; };   // compressed levels from the innermost outwards (0: not wanted)
+// buckets by sample, multiples of 2^fbits, sampled keys; compressed levels above the innermost; two partitions, 64-bit keys
+struct spmi_bucket_plan { uint32_t Q, F, S; int fbits, slots; bool two, wide; };
+struct spmi_bucket_job {
+    spmi_bucket_source src;
+    spmi_bucket_plan plan;
+    spmi_levels levels;
+    int64_t n;
+    uint64_t total;
+    int key_bits, payload_bytes;
+    void *tab;
+    int *flags;                          // DEVICE, kSpmiFlagBytes
+};
+struct spmi_bucket_out { uint64_t *keys; uint32_t *dist; void *values, *crd, *pos; int32_t *rowblk; int64_t rows; uint64_t inner; int pw, cw; };
+bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, int64_t rows, spmi_bucket_plan *plan);
+sp_status spmi_bucket_begin(spmi_bucket_job *job, const void *vals, int payload_bytes, sp_scratch &tmp, hipStream_t st);
+sp_status spmi_bucket_end(const spmi_bucket_job &job, const spmi_bucket_out &out, sp_scratch &tmp, hipStream_t st);
+sp_status spmi_bucket_levels(const spmi_bucket_job &job, const uint32_t *dist, void *const *crd, void *const *pos, bool dense_above, int pw, int cw, hipStream_t st);
 // ---- pack.hip ----
 // The storage of a tensor whose n entries are given as linearised keys (level order, mixed radix over the level sizes)
 // with the value bits as payload, both temporaries of `tmp`; entries with equal keys are added up in the order given.
