@@ -43,8 +43,8 @@ constexpr int kTarget = 2048;                 // entries per final bucket where 
 constexpr int kExact = 3456;                  // the same where they are counted first
 constexpr int kPartCells = 16384;             // equal intervals of a bucket whose entries are counted
 constexpr int kHeavy = 512;                   // more entries than this in one of them: a sample cuts the bucket (kExact + kHeavy < kCap)
-constexpr int kFirst = 131072;                 // entries per bucket of the first of two partitions
-constexpr int kCells1 = 2 * kFT;              // equal intervals of a final bucket, each then cut by what it holds
+constexpr int kFirstLeast = 16384, kFirst = 131072;         // entries per bucket of the first of two partitions: n / 128 between these
+constexpr int kCells1 = 4 * kFT;              // equal intervals of a final bucket, each then cut by what it holds
 constexpr int kSpread = 24;                   // more keys than this in one interval: a second attempt at spreading them
 constexpr int kCrowd = 64;                    // more keys than this in one interval: left to finish_crowded_kernel
 
@@ -896,7 +896,7 @@ __device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t cnt = w.cnt;
     K *dist = (K *)s.stage;
-    uint32_t *bins = (uint32_t *)(dist + kCap), *cells = bins + s.kWords + 1;
+    uint32_t *cells = (uint32_t *)(dist + kCap), *bins = cells + kCells1;
     P *sval = (P *)s.stage;
     const int rounds = (int)((cnt + kFT - 1) / kFT);                 // <= kFE
     const int per = rounds | 1;                                      // words per thread when they are scanned: odd, no bank conflicts
@@ -933,37 +933,37 @@ __device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P
         if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) {
             k[r] -= (K)w.lo;
             at[r] = place_in_range<K>(k[r], w);
-            atomicAdd(&cells[at[r] >> 22], 1u);
+            atomicAdd(&cells[at[r] >> 21], 1u);
             if (ATTEMPT) {
-                atomicMin(&s.least[at[r] >> 22], (lds_key<K>)k[r]);
-                atomicMax(&s.most[at[r] >> 22], (lds_key<K>)k[r]);
+                atomicMin(&s.least[at[r] >> 21], (lds_key<K>)k[r]);
+                atomicMax(&s.most[at[r] >> 21], (lds_key<K>)k[r]);
             }
         }
     }
     __syncthreads();
-    static_assert(kCells1 == 512 && kFT == 256, "two cells per thread, nine bits of the place");
+    static_assert(kCells1 == 1024 && kFT == 256, "four cells per thread, ten bits of the place");
     {
-        const uint32_t c0 = cells[2 * tid], c1 = cells[2 * tid + 1];
-        const uint32_t incl = wave_inclusive_scan(c0 + c1, lane);
+        const uint4 c = ((const uint4 *)cells)[tid];
+        const uint32_t incl = wave_inclusive_scan(c.x + c.y + c.z + c.w, lane);
         if (lane == 63) s.wsum[wave] = incl;
         __syncthreads();
-        uint32_t before = incl - c0 - c1;
+        uint32_t before = incl - c.x - c.y - c.z - c.w;
 #pragma unroll
         for (int x = 0; x < W; ++x) before += x < wave ? s.wsum[x] : 0u;
-        cells[2 * tid] = before | (c0 << 16);
-        cells[2 * tid + 1] = (before + c0) | (c1 << 16);
+        ((uint4 *)cells)[tid] = make_uint4(before | (c.x << 16), (before + c.x) | (c.y << 16), (before + c.x + c.y) | (c.z << 16),
+                                           (before + c.x + c.y + c.z) | (c.w << 16));
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kFE; ++r) {
         if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) {
-            const uint32_t c = cells[at[r] >> 22];
+            const uint32_t c = cells[at[r] >> 21];
             uint32_t x;                                              // interval: twice what comes before its cell, and where in the cell
-            if (ATTEMPT == 0) x = ((at[r] >> 4) & 0x3ffffu) * (c >> 16) >> 17;
+            if (ATTEMPT == 0) x = ((at[r] >> 4) & 0x1ffffu) * (c >> 16) >> 16;
             else {
                 const uint32_t twice = 2u * (c >> 16);
-                const K least = (K)s.least[at[r] >> 22];
-                const float span = (float)(K)((K)s.most[at[r] >> 22] - least);
+                const K least = (K)s.least[at[r] >> 21];
+                const float span = (float)(K)((K)s.most[at[r] >> 21] - least);
                 x = (uint32_t)((float)(K)(k[r] - least) * ((float)twice / (span + 1.0f)));
                 x = x < twice ? x : twice - 1;
             }
@@ -1409,7 +1409,9 @@ bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, int64_t rows,
     memset(p, 0, sizeof(*p));
     if (n < 1 || total < 1 || key_bits > 48) return false;            // sampled keys keep their upper 32 bits: 16 more may hide a crowd
     p->two = n > (int64_t)kTarget * (kMaxSample / kShare);
-    uint64_t Q = p->two ? (uint64_t)std::max<int64_t>(std::min<int64_t>(ceil_div(n, kFirst), 512), ceil_div(n, 2 * kFirst))
+    // blocks enough for the kernel that cuts the buckets (zipf columns, 3.3 M entries, CSR to CSC: 475 us with buckets of 131072)
+    const int64_t first = std::min<int64_t>(std::max<int64_t>(n / 128, kFirstLeast), kFirst);
+    uint64_t Q = p->two ? (uint64_t)std::max<int64_t>(std::min<int64_t>(ceil_div(n, first), 512), ceil_div(n, 2 * kFirst))
                         : n <= kCap ? 1u : (uint64_t)ceil_div(n, kTarget);
     p->wide = ((total - 1) >> 32) > (uint64_t)std::min<int64_t>(1024, n / kTarget);
     // equal steps of the key range that no bucket crosses: 2^32, so that its keys fit 32 bits, or less where the rows that begin in a

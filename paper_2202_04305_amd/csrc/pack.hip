@@ -463,9 +463,13 @@ __global__ __launch_bounds__(kThreads) void compact_rows_kernel(const PT *__rest
     if (pos[r + 1] > pos[r]) { nz_rowid[excl[r]] = (CT)r; nz_pos[excl[r]] = pos[r]; }
 }
 
-// out (zero before) = the largest number of rows that one window of the streaming kernels meets
-__global__ __launch_bounds__(kThreads) void max_span_kernel(const int32_t *__restrict__ rowblk, int64_t nb, unsigned long long *__restrict__ out)
+// out (zero before) = the largest number of rows that one window of the streaming kernels meets, looked for only where it can decide:
+// there are empty rows enough for a long run (a window meets no more than its entries' rows besides them).
+constexpr unsigned long long kLongRun = 65536;
+__global__ __launch_bounds__(kThreads) void max_span_kernel(const int32_t *__restrict__ rowblk, int64_t nb, int64_t nrows,
+                                                            const unsigned long long *__restrict__ nonempty, unsigned long long *__restrict__ out)
 {
+    if ((unsigned long long)nrows - *nonempty + (unsigned long long)kSpmiStreamT + 2 < kLongRun) return;
     const int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     unsigned long long span = b < nb ? (unsigned long long)(rowblk[b + 1] - rowblk[b]) : 0ull;
 #pragma unroll
@@ -481,8 +485,8 @@ struct nonempty_probe {
     unsigned long long nz = 0, span = 0;
     bool active = false;
     // the answers come back inside the builder's 64-byte flags block (one copy to the host for everything):
-    // ints 8-9 = the number of non-empty rows as a 64-bit value (ints 10-11: the longest run, asked for afterwards)
-    void take(const int *h) { memcpy(&nz, &h[8], 8); }
+    // ints 8-9 = the number of non-empty rows, ints 10-11 = the longest run, both as 64-bit values
+    void take(const int *h) { memcpy(&nz, &h[8], 8); memcpy(&span, &h[10], 8); }
 };
 
 static bool wants_nonempty(const sp_tensor *t)
@@ -492,25 +496,17 @@ static bool wants_nonempty(const sp_tensor *t)
     return nrows >= 4096 && nrows < ((int64_t)1 << 31) - 1 && t->ncrd[1] != 0;
 }
 
-// the caller has enqueued pos_stats() with wants_nonempty() true, which counts the non-empty rows into ints 8-9 of the flags
-static void nonempty_enqueue(const sp_tensor *t, nonempty_probe &q)
+// flags: the 64 zeroed device bytes of the build (see nonempty_probe for the slots used here); the caller has enqueued
+// pos_stats() with wants_nonempty() true, which counts the non-empty rows into ints 8-9
+static sp_status nonempty_enqueue(const sp_tensor *t, hipStream_t st, int *flags, nonempty_probe &q)
 {
-    if (!wants_nonempty(t)) return;
+    if (!wants_nonempty(t)) return SP_OK;
     q.nrows = t->npos[1] - 1; q.active = true;
-}
-
-// The longest run of rows in one window, asked for only where it can decide: at least half of the rows hold something, and there are
-// empty ones enough for a long run (a window meets no more than its kSpmiStreamT entries' rows besides them).
-constexpr unsigned long long kLongRun = 65536;
-static sp_status nonempty_span(const sp_tensor *t, int *flags, hipStream_t st, nonempty_probe &q)
-{
-    if (!q.active || !t->rowblocks.start || (int64_t)q.nz * 2 <= q.nrows) return SP_OK;
-    if ((unsigned long long)q.nrows - q.nz + (unsigned long long)kSpmiStreamT + 2 < kLongRun) return SP_OK;
-    hipLaunchKernelGGL(max_span_kernel, dim3(blocks_for(t->rowblocks.nblocks)), dim3(kThreads), 0, st, (const int32_t *)t->rowblocks.start,
-                       t->rowblocks.nblocks, (unsigned long long *)(flags + 10));
-    SP_HIP(hipGetLastError());
-    SP_HIP(hipMemcpyAsync(&q.span, flags + 10, 8, hipMemcpyDeviceToHost, st));
-    SP_HIP(hipStreamSynchronize(st));
+    if (t->rowblocks.start && q.nrows >= (int64_t)kLongRun - kSpmiStreamT - 2) {
+        hipLaunchKernelGGL(max_span_kernel, dim3(blocks_for(t->rowblocks.nblocks)), dim3(kThreads), 0, st, (const int32_t *)t->rowblocks.start,
+                           t->rowblocks.nblocks, q.nrows, (const unsigned long long *)(flags + 8), (unsigned long long *)(flags + 10));
+        SP_HIP(hipGetLastError());
+    }
     return SP_OK;
 }
 
@@ -561,12 +557,11 @@ static sp_status build_nonempty_rows(const sp_tensor *t, sp_scratch &tmp, hipStr
     nonempty_probe q;
     if (!wants_nonempty(t)) return SP_OK;
     SP_TRY(pos_stats(t->pos[1], t->enc.pw, t->npos[1] - 1, (unsigned long long *)(flags + 4), (unsigned long long *)(flags + 8), st));
-    nonempty_enqueue(t, q);
+    SP_TRY(nonempty_enqueue(t, st, flags, q));
     int h[16];
     SP_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st));
     SP_HIP(hipStreamSynchronize(st));
     q.take(h);
-    SP_TRY(nonempty_span(t, flags, st, q));
     bool launched = false;
     return nonempty_decide(t, tmp, st, q, &launched);
 }
@@ -1060,7 +1055,7 @@ sp_status spmi_finish_tensor(sp_tensor *t, int *flags, sp_scratch &tmp, hipStrea
     // non-empty-rows list (all in bounds whatever the input checks say), then one synchronisation for all read-backs
     SP_TRY(spmi_build_rowblocks(t, st));
     nonempty_probe q;
-    nonempty_enqueue(t, q);
+    SP_TRY(nonempty_enqueue(t, st, flags, q));
     int h[16] = {0};
     if (want_max || input_flags || q.active) SP_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st));
     SP_HIP(hipStreamSynchronize(st));
@@ -1072,7 +1067,6 @@ sp_status spmi_finish_tensor(sp_tensor *t, int *flags, sp_scratch &tmp, hipStrea
     unsigned long long hmx = 0;
     memcpy(&hmx, &h[4], 8);
     if (want_max) t->max_segment = (int64_t)hmx;
-    SP_TRY(nonempty_span(t, flags, st, q));
     bool launched = false;
     SP_TRY(nonempty_decide(t, tmp, st, q, &launched));
     if (launched) SP_HIP(hipStreamSynchronize(st));
@@ -1570,7 +1564,7 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
         int *flags = (int *)tmp.get(kSpmiFlagBytes);
         sp_msd_plan plan;
         memset(&plan, 0, sizeof(plan));
-        bool by_buckets = false;
+        bool by_buckets = false, in_order = false;
         do {
             if (!keys || !flags) { status = SP_ERR_ALLOC; break; }
             if ((status = spmi_fill_zero(flags, kSpmiFlagBytes, st)) != SP_OK) break;
@@ -1586,10 +1580,14 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
                     a.stride[l] = weight[from->enc.perm[l]];
                     a.lt[l] = from->enc.lt[l];
                 }
-                // the sort by buckets has no use for the counts; should it not do after all, the other sorts make them
+                // Stored positions come in the order of the source's levels, so with the same dimension at every level the keys are sorted
+                // already (CSR to DCSR, 8.0 M f32 entries: 530 us with the sort, 569 with buckets, 190 without).  Otherwise the sort by
+                // buckets has no use for the counts; should it not do after all, the other sorts make them.
+                in_order = true;
+                for (int l = 0; l < rank; ++l) in_order &= enc->perm[l] == from->enc.perm[l];
                 spmi_bucket_plan buckets;
-                by_buckets = g_pack_sort_mode.load(std::memory_order_relaxed) == 0 && spmi_bucket_plan_for(n, w, key_bits, 0, &buckets);
-                if (!by_buckets && (status = spmi_msd_plan(n, key_bits, tmp, st, &plan)) != SP_OK) break;
+                by_buckets = !in_order && g_pack_sort_mode.load(std::memory_order_relaxed) == 0 && spmi_bucket_plan_for(n, w, key_bits, 0, &buckets);
+                if (!in_order && !by_buckets && (status = spmi_msd_plan(n, key_bits, tmp, st, &plan)) != SP_OK) break;
                 const dim3 grid((unsigned)ceil_div(n, kSpmiMsdTile));
 #define SPMI_CONVERT(PT, CT) hipLaunchKernelGGL((convert_keys_kernel<PT, CT>), grid, dim3(kThreads), 0, st, a, n, keys, plan)
                 if (from->enc.pw == 32 && from->enc.cw == 32) SPMI_CONVERT(int32_t, int32_t);
@@ -1600,6 +1598,11 @@ sp_status spmi_repack(const sp_tensor *from, const sp_encoding *enc, hipStream_t
                 if (hipGetLastError() != hipSuccess) { status = SP_ERR_HIP; break; }
             }
             bool again = true;
+            if (in_order) {                                  // nothing to sort: the level sweep of the target from the keys as they come
+                bool overflow = false;
+                status = pack_core(t, n, keys, from->values, key_bits, false, flags, tmp, mem, st, nullptr, &overflow);
+                break;
+            }
             if (by_buckets && (status = pack_buckets(t, n, nullptr, keys, from->values, key_bits, mem, st, &again)) != SP_OK) break;
             if (again) status = pack_core(t, n, keys, from->values, key_bits, false, flags, tmp, mem, st, plan.ctr ? &plan : nullptr);
         } while (0);

@@ -90,7 +90,8 @@ def test_rows_that_fill_buckets_and_columns_that_crowd(n_rest):
 def sampled_positions(n):
     """Where the builder looks: one entry per stretch of n / S, at a scrambled place in it."""
     if n > TWO:
-        Q, share = max(min(-(-n // 65536), 512), -(-n // (4 * 65536))), 32
+        first = min(max(n // 128, 16384), 131072)
+        Q, share = max(min(-(-n // first), 512), -(-n // (2 * 131072))), 32
     else:
         Q, share = -(-n // 2048), 48
     S = min(-(-share * Q // 1024) * 1024, 32768)
