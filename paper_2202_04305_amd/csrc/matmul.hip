@@ -76,12 +76,15 @@ __global__ __launch_bounds__(kThreads) void spmv_rows_kernel(const PT *__restric
 #ifndef SPMI_WPE
 #define SPMI_WPE 3
 #endif
-template <typename PT, typename CT, typename VT>
-__global__ __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(1, SPMI_WPE))) void spmv_stream_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd,
-                                                               const VT *__restrict__ val, const CT *__restrict__ rowid,
-                                                               const int32_t *__restrict__ rowblk, int64_t nrows, int64_t nnz,
-                                                               const VT *__restrict__ x, int64_t ldb, VT *__restrict__ y, int64_t ldc,
-                                                               VT *__restrict__ carry, int accumulate)
+//
+// ZERO (rows by id, y contiguous, m of them, overwritten): the rows that are not stored become zero here as well.  The block takes the
+// rows from the first stored one that begins in its window (row 0 in the first window) up to the next window's, clears
+// them while its gathers are under way, and the barrier before the sums orders its own stores (hypersparse 8M x 8M, 2.7 M entries:
+// 75.1 us with a launch of its own for 67 MB of zeros, 71.1 so).
+template <typename PT, typename CT, typename VT, bool ZERO>
+__global__ __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(1, SPMI_WPE))) void spmv_stream_kernel(
+    const PT *__restrict__ pos, const CT *__restrict__ crd, const VT *__restrict__ val, const CT *__restrict__ rowid, const int32_t *__restrict__ rowblk,
+    int64_t nrows, int64_t nnz, const VT *__restrict__ x, int64_t ldb, VT *__restrict__ y, int64_t ldc, VT *__restrict__ carry, int accumulate, int64_t m)
 {
     const int64_t win = blockIdx.x;
     __shared__ VT prods[kStreamT];
@@ -117,16 +120,31 @@ __global__ __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(1, SPMI_WPE
         pre_a[i] = pos[r];
         pre_b[i] = pos[r + 1];
     }
+    int64_t za = 0, zb = 0;                            // ZERO: the block's rows of y
+    if (ZERO) {
+        auto first_row = [&](int64_t w, int64_t r) -> int64_t {      // row of y where window w's share begins; r = rowblk[w]
+            if (w == 0) return 0;
+            if (r < nrows && (int64_t)pos[r] < w * kStreamT) ++r;
+            return r < nrows ? (int64_t)rowid[r] : m;
+        };
+        za = first_row(win, lo);
+        zb = win + 1 < (int64_t)gridDim.x ? first_row(win + 1, hi) : m;
+    }
+    auto clear = [&]() {
+        for (int64_t i = za + tid; i < zb; i += kST) y[i] = (VT)0;
+    };
     if (full) {
         VT xv[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) xv[i] = x[(int64_t)k[i] * ldb];
+        if (ZERO) clear();
 #pragma unroll
         for (int t = 0; t < E / 2; ++t) {
             prods[(t * kST + tid) * 2] = v[2 * t] * xv[2 * t];
             prods[(t * kST + tid) * 2 + 1] = v[2 * t + 1] * xv[2 * t + 1];
         }
     } else {
+        if (ZERO) clear();
         for (int i = tid; i < (int)(e - s); i += kST) prods[i] = val[s + i] * x[(int64_t)crd[s + i] * ldb];
     }
     if (tid == 0) lo_began_earlier = (int64_t)pre_a[0] < s;      // thread 0 prefetched pos[lo]
@@ -207,12 +225,14 @@ constexpr int kBinRB = 1 << kSpmiBinRowShift;
 // First pass: block (panel, piece) loads the panel's slice of x into LDS, then streams its share of the panel's entries, 16 bytes
 // of values per lane and load: the product of entry e = val[e] * x[panel * PW + lcol[e]] goes to the row-block-major array, to
 // slot e % 8 of the group that gdst names for e's group of 8.  Padding entries carry value 0 and column PW, where the slice
-// holds a zero, so that they give 0 whatever x holds.
+// holds a zero, so that they give 0 whatever x holds.  Blocks beyond the pieces clear y (m contiguous values, kBinClear of them a
+// block), where rows that are not stored have to become zero.
+constexpr int kBinClear = 16384;
 template <typename VT>
 __global__ __launch_bounds__(kBinThreads) void spmv_bins_multiply_kernel(const VT *__restrict__ val, const uint16_t *__restrict__ lcol,
                                                                          const uint32_t *__restrict__ gdst, const int64_t *__restrict__ pstart,
                                                                          int panels, int pieces, int64_t n, const VT *__restrict__ x, int64_t ldb,
-                                                                         VT *__restrict__ prod)
+                                                                         VT *__restrict__ prod, VT *__restrict__ y, int64_t m)
 {
     constexpr int V = 16 / sizeof(VT);
     typedef VT vec_t __attribute__((ext_vector_type(V)));
@@ -220,7 +240,12 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_multiply_kernel(const V
     __shared__ VT xs[kBinPW + V];
     // blocks go to the eight XCDs in turn: the pieces of one panel are given to blocks b, b + 8, b + 16, ... so that they
     // share an L2 and the panel's slice of x is fetched from memory once, not once per piece
-    const int grp = 8 * pieces;
+    const int grp = 8 * pieces, work = (panels + 7) / 8 * grp;
+    if ((int)blockIdx.x >= work) {                     // whole block
+        const int64_t a = (int64_t)((int)blockIdx.x - work) * kBinClear, b = a + kBinClear < m ? a + kBinClear : m;
+        for (int64_t i = a + threadIdx.x; i < b; i += kBinThreads) y[i] = (VT)0;
+        return;
+    }
     const int p = (int)(blockIdx.x / grp) * 8 + (int)(blockIdx.x % 8), q = (int)(blockIdx.x / 8) % pieces;
     if (p >= panels) return;                           // whole block (the panel count is rounded up to eight)
     const int64_t pa = pstart[p], pb = pstart[p + 1];  // multiples of 8
@@ -270,7 +295,8 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_multiply_kernel(const V
 // (a lane takes a group of 8 with 16-byte loads), and adds them into the block's slice of y in LDS (atomic adds: the order in
 // which a row's products meet is not fixed); the slice is written out at the end.  Every stored row of the row block is
 // written (m of them; rowid[q] is the matrix row of stored row q when not all rows are stored, and the caller has then
-// zeroed the others).
+// zeroed the others).  The slice is f64 for f32 products as well: adds of 32 bits to the LDS are the slower ones (2.7 M entries in 41
+// row blocks, x of 4 MB: 100 us for the product, 29 now), and long sums lose nothing.
 template <typename CT, typename VT>
 __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT *__restrict__ prod, const uint16_t *__restrict__ lrow,
                                                                        const int64_t *__restrict__ rbstart, int rowblocks, int64_t m,
@@ -280,9 +306,9 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
     constexpr int V = 16 / sizeof(VT), NV = 8 / V;
     typedef VT vec_t __attribute__((ext_vector_type(V)));
     typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-    __shared__ VT ys[kBinRB];
+    __shared__ double ys[kBinRB];
     const int rb = (int)blockIdx.x;
-    for (int i = threadIdx.x; i < kBinRB; i += kBinThreads) ys[i] = (VT)0;
+    for (int i = threadIdx.x; i < kBinRB; i += kBinThreads) ys[i] = 0.0;
     __syncthreads();
     const int64_t g0 = rbstart[rb] >> 3, g1 = rbstart[rb + 1] >> 3;
     const vec_t *__restrict__ pp = (const vec_t *)prod;
@@ -295,7 +321,7 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const unsigned w = (t >> 1) == 0 ? r.x : (t >> 1) == 1 ? r.y : (t >> 1) == 2 ? r.z : r.w;
-            atomicAdd(&ys[(t & 1) ? (w >> 16) : (w & 0xffffu)], v[t / V][t % V]);
+            atomicAdd(&ys[(t & 1) ? (w >> 16) : (w & 0xffffu)], (double)v[t / V][t % V]);
         }
     }
     __syncthreads();
@@ -304,7 +330,7 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
         const int64_t q = r0 + i;                      // stored row; rowid maps it to the matrix row where not all rows are stored
         if (q < m) {
             VT *dst = y + (rowid ? (int64_t)rowid[q] : q) * ldc;
-            *dst = accumulate ? *dst + ys[i] : ys[i];
+            *dst = (VT)(accumulate ? (double)*dst + ys[i] : ys[i]);
         }
     }
 }
@@ -996,17 +1022,37 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
         // small and even (no row beyond one wave's stride): one launch of the rows kernel beats stream + fix-up
         const bool small_even = nnz < ((int64_t)1 << 18) && A->max_segment <= 64;
         kernel = (rv.rowblocks->start && nnz >= 8 * kStreamT && !small_even) ? 2 : 1;
-        // a large matrix whose gathers are scattered over a large x: no gather should leave the chip's caches.  The
-        // binned copy keeps them inside the LDS (measured 103 us against 122 us on the 1M x 1M matrix); where it cannot
-        // be built, L2-sized column panels.  Gathers that mostly fall into the line of their predecessor stay as they are.
-        if (kernel == 2 && nnz >= ((int64_t)1 << 21) && A->shape[1] * (int64_t)sizeof(VT) > ((int64_t)3 << 20)) {
+        // A large matrix whose gathers are scattered over a large x: no gather should leave the chip's caches.  The binned copy keeps
+        // them inside the LDS, L2-sized column panels inside the L2.  Gathers that mostly fall into the line of their predecessor
+        // stay as they are.
+        const double xbytes = (double)A->shape[1] * sizeof(VT);
+        if (kernel == 2 && nnz >= ((int64_t)1 << 20) && xbytes > (double)(3 << 20)) {
             double share = 0;
             SP_TRY(spmi_column_scatter(A, st, &share));
-            // ... and buckets of at least 32 entries on average (the second pass reads them a bucket at a time), in enough
-            // row blocks to give every CU one (the hypersparse 8M x 8M workload has 41: 85 us binned, 73 us streamed)
-            const int64_t rowblocks = ceil_div(nrows, (int64_t)kBinRB);
-            const double buckets = (double)ceil_div(A->shape[1], (int64_t)kBinPW) * (double)rowblocks;
-            if (share >= 0.5) kernel = ((double)nnz >= 32.0 * buckets && rowblocks >= 256) ? 4 : (!rv.dcsr && nnz >= ((int64_t)1 << 22)) ? 3 : 2;
+            const int64_t rowblocks = ceil_div(nrows, (int64_t)kBinRB), panels = ceil_div(A->shape[1], (int64_t)kBinPW);
+            const double buckets = (double)panels * (double)rowblocks;
+            const bool large = nnz >= ((int64_t)1 << 21), segments = !rv.dcsr && nnz >= ((int64_t)1 << 22);
+            if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
+                // long rows in f64: the binned copy's second pass adds a row's products one by one, where the others add them up in
+                // trees; it is left to the shapes where it saves most (buckets of 32 entries, a row block for every CU)
+                if (large) kernel = ((double)nnz >= 32.0 * buckets && rowblocks >= 256) ? 4 : segments ? 3 : 2;
+            } else if (share >= 0.5) {
+                // Short rows are added up one by one in every kernel (f32: by the binned one in f64): whichever is the fastest.  Microseconds, fitted to measurements in
+                // f64 over 0.3 to 16 M entries, 9,000 to 3 M rows and x of 4 to 64 MB (most within a sixth):
+                //   streamed: a cache line from beyond the L2 per entry that misses it, and the rows to be cleared
+                //   panels:   5.4 per million entries, 6.9 per million (row, panel) pairs
+                //   binned:   x and 18.5 bytes per entry (buckets padded to eights), then 10 bytes per entry or, with few row
+                //             blocks, one block's share of them
+                // 2.7 M entries in 83,886 rows of 8 M columns: 71 us streamed, 46 binned; 16 M entries in 3 M rows of 4 M columns
+                // 283, 414 (panels) and 99.
+                const double M = 1e-6 * (double)nnz, v = (double)sizeof(VT) / 8.0, clear = rv.dcsr ? 1.6e-7 * (double)A->shape[0] * sizeof(VT) : 0.0;
+                const double padded = M + 1e-6 * std::min(3.5 * buckets, 7.0 * (double)nnz);
+                const double streamed = 5.0 + M * (5.5 + 14.5 * (1.0 - (double)(4 << 20) / std::max(xbytes, (double)(4 << 20)))) + clear;
+                const double paneled = segments ? 3.0 + 5.4 * M + 6.9e-6 * (double)nrows * std::ceil(xbytes / (double)kSpmvSliceBytes) : 1e30;
+                const double binned = 4.0 + 2e-7 * xbytes + padded * (1.0 + 2.8 * v) + 0.6 * clear + std::max(padded * (0.3 + 1.5 * v), 2.0 + 250.0 * padded / (double)rowblocks);
+                if (large && paneled < streamed) kernel = 3;
+                if (binned < 0.9 * std::min(streamed, large ? paneled : streamed)) kernel = 4;
+            }
         }
     }
     if (kernel == 4) {
@@ -1076,13 +1122,15 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
     const sp_rowblocks *rowblocks = rv.rowblocks;
     const int64_t m = A->shape[0];
     const int64_t nnz = A->ncrd[1];
-    if (dcsr && !accumulate) SP_TRY((zero_c<PT, CT, VT>(C, m, N, ldc, st)));   // rows that are not stored become zero
+    if (N == 1 && nrows > 0 && !A->plan_spmv) {  // no sp_prepare before this product: the inspector runs now (may allocate and synchronise)
+        ++A->lazy_prepares;
+        SP_TRY((prepare_spmv_t<PT, CT, VT>(A, st)));
+    }
+    // rows that are not stored become zero; the stream kernel and the first pass of the binned one do that on the way
+    const bool clears = dcsr && !accumulate && N == 1 && nrows > 0 && (A->plan_spmv == 2 || A->plan_spmv == 4) && ldc == 1;
+    if (dcsr && !accumulate && !clears) SP_TRY((zero_c<PT, CT, VT>(C, m, N, ldc, st)));
     if (nrows == 0) return SP_OK;
     if (N == 1) {
-        if (!A->plan_spmv) {                     // no sp_prepare before this product: the inspector runs now (may allocate and synchronise)
-            ++A->lazy_prepares;
-            SP_TRY((prepare_spmv_t<PT, CT, VT>(A, st)));
-        }
         const int kernel = A->plan_spmv;
         if (kernel == 3) {
             // the segmented copy is an ordinary CSR over panels*nrows virtual rows: stream it into the per-panel
@@ -1099,9 +1147,9 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
             }
             const int64_t nb = srb->nblocks;
             sp_prof_scope prof(A, st);
-            hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT>), dim3((unsigned)nb), dim3(kST), 0, st, spos,
+            hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT, false>), dim3((unsigned)nb), dim3(kST), 0, st, spos,
                                (const CT *)S->crd[1], (const VT *)S->values, srowid, (const int32_t *)srb->start,
-                               vrows, S->ncrd[1], B, ldb, (VT *)g->partial, (int64_t)1, (VT *)srb->carry, 0);
+                               vrows, S->ncrd[1], B, ldb, (VT *)g->partial, (int64_t)1, (VT *)srb->carry, 0, (int64_t)0);
             SP_HIP(hipGetLastError());
             if (nb > 1) {
                 hipLaunchKernelGGL((spmv_stream_fixup_kernel<PT, CT, VT>), dim3(grid_for(nb - 1, kThreads)), dim3(kThreads), 0, st,
@@ -1116,9 +1164,9 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
         if (kernel == 4) {
             const sp_bins *g = A->bins;                                       // over the same stored rows as pos / rowid here
             sp_prof_scope prof(A, st);
-            hipLaunchKernelGGL((spmv_bins_multiply_kernel<VT>), dim3((unsigned)(ceil_div(g->panels, 8) * 8 * g->pieces)), dim3(kBinThreads), 0, st,
-                               (const VT *)g->val, (const uint16_t *)g->lcol, (const uint32_t *)g->gdst, (const int64_t *)g->pstart, g->panels,
-                               g->pieces, A->shape[1], B, ldb, (VT *)g->prod);
+            hipLaunchKernelGGL((spmv_bins_multiply_kernel<VT>), dim3((unsigned)(ceil_div(g->panels, 8) * 8 * g->pieces + (clears ? ceil_div(m, kBinClear) : 0))),
+                               dim3(kBinThreads), 0, st, (const VT *)g->val, (const uint16_t *)g->lcol, (const uint32_t *)g->gdst, (const int64_t *)g->pstart,
+                               g->panels, g->pieces, A->shape[1], B, ldb, (VT *)g->prod, C, m);
             SP_HIP(hipGetLastError());
             hipLaunchKernelGGL((spmv_bins_reduce_kernel<CT, VT>), dim3((unsigned)g->rowblocks), dim3(kBinThreads), 0, st, (const VT *)g->prod,
                                (const uint16_t *)g->lrow, (const int64_t *)g->rbstart, g->rowblocks, g->nrows, rowid, C, ldc, accumulate);
@@ -1129,8 +1177,12 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
             const int64_t nb = rowblocks->nblocks;
             {
             sp_prof_scope prof(A, st);
-            hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT>), dim3((unsigned)nb), dim3(kST), 0, st, pos, crd, val, rowid,
-                               (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, (VT *)rowblocks->carry, accumulate);
+            if (clears)
+                hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT, true>), dim3((unsigned)nb), dim3(kST), 0, st, pos, crd, val, rowid,
+                                   (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, (VT *)rowblocks->carry, accumulate, m);
+            else
+                hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT, false>), dim3((unsigned)nb), dim3(kST), 0, st, pos, crd, val, rowid,
+                                   (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, (VT *)rowblocks->carry, accumulate, m);
             }
             SP_HIP(hipGetLastError());
             if (nb > 1) {
