@@ -299,7 +299,7 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_multiply_kernel(const V
 // row blocks, x of 4 MB: 100 us for the product, 29 now), and long sums lose nothing.
 template <typename CT, typename VT>
 __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT *__restrict__ prod, const uint16_t *__restrict__ lrow,
-                                                                       const int64_t *__restrict__ rbstart, int rowblocks, int64_t m,
+                                                                       const int64_t *__restrict__ rbstart, int rshift, int64_t m,
                                                                        const CT *__restrict__ rowid, VT *__restrict__ y, int64_t ldc,
                                                                        int accumulate)
 {
@@ -308,7 +308,8 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
     typedef unsigned uint4v __attribute__((ext_vector_type(4)));
     __shared__ double ys[kBinRB];
     const int rb = (int)blockIdx.x;
-    for (int i = threadIdx.x; i < kBinRB; i += kBinThreads) ys[i] = 0.0;
+    const int rows = 1 << rshift;                      // <= kBinRB
+    for (int i = threadIdx.x; i < rows; i += kBinThreads) ys[i] = 0.0;
     __syncthreads();
     const int64_t g0 = rbstart[rb] >> 3, g1 = rbstart[rb + 1] >> 3;
     const vec_t *__restrict__ pp = (const vec_t *)prod;
@@ -325,8 +326,8 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
         }
     }
     __syncthreads();
-    const int64_t r0 = (int64_t)rb * kBinRB;
-    for (int i = threadIdx.x; i < kBinRB; i += kBinThreads) {
+    const int64_t r0 = (int64_t)rb << rshift;
+    for (int i = threadIdx.x; i < rows; i += kBinThreads) {
         const int64_t q = r0 + i;                      // stored row; rowid maps it to the matrix row where not all rows are stored
         if (q < m) {
             VT *dst = y + (rowid ? (int64_t)rowid[q] : q) * ldc;
@@ -1029,13 +1030,13 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
         if (kernel == 2 && nnz >= ((int64_t)1 << 20) && xbytes > (double)(3 << 20)) {
             double share = 0;
             SP_TRY(spmi_column_scatter(A, st, &share));
-            const int64_t rowblocks = ceil_div(nrows, (int64_t)kBinRB), panels = ceil_div(A->shape[1], (int64_t)kBinPW);
+            const int64_t panels = ceil_div(A->shape[1], (int64_t)kBinPW), rowblocks = ceil_div(nrows, (int64_t)1 << spmi_bin_row_shift(nnz, nrows, panels));
             const double buckets = (double)panels * (double)rowblocks;
             const bool large = nnz >= ((int64_t)1 << 21), segments = !rv.dcsr && nnz >= ((int64_t)1 << 22);
             if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
                 // long rows in f64: the binned copy's second pass adds a row's products one by one, where the others add them up in
                 // trees; it is left to the shapes where it saves most (buckets of 32 entries, a row block for every CU)
-                if (large) kernel = ((double)nnz >= 32.0 * buckets && rowblocks >= 256) ? 4 : segments ? 3 : 2;
+                if (large) kernel = ((double)nnz >= 32.0 * buckets && nrows > 255 * (int64_t)kBinRB) ? 4 : segments ? 3 : 2;
             } else if (share >= 0.5) {
                 // Short rows are added up one by one in every kernel (f32: by the binned one in f64): whichever is the fastest.  Microseconds, fitted to measurements in
                 // f64 over 0.3 to 16 M entries, 9,000 to 3 M rows and x of 4 to 64 MB (most within a sixth):
@@ -1043,7 +1044,7 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
                 //   panels:   5.4 per million entries, 6.9 per million (row, panel) pairs
                 //   binned:   x and 18.5 bytes per entry (buckets padded to eights), then 10 bytes per entry or, with few row
                 //             blocks, one block's share of them
-                // 2.7 M entries in 83,886 rows of 8 M columns: 71 us streamed, 46 binned; 16 M entries in 3 M rows of 4 M columns
+                // 2.7 M entries in 83,886 rows of 8 M columns: 69 us streamed, 46 binned; 16 M entries in 3 M rows of 4 M columns
                 // 283, 414 (panels) and 99.
                 const double M = 1e-6 * (double)nnz, v = (double)sizeof(VT) / 8.0, clear = rv.dcsr ? 1.6e-7 * (double)A->shape[0] * sizeof(VT) : 0.0;
                 const double padded = M + 1e-6 * std::min(3.5 * buckets, 7.0 * (double)nnz);
@@ -1169,7 +1170,7 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
                                g->panels, g->pieces, A->shape[1], B, ldb, (VT *)g->prod, C, m);
             SP_HIP(hipGetLastError());
             hipLaunchKernelGGL((spmv_bins_reduce_kernel<CT, VT>), dim3((unsigned)g->rowblocks), dim3(kBinThreads), 0, st, (const VT *)g->prod,
-                               (const uint16_t *)g->lrow, (const int64_t *)g->rbstart, g->rowblocks, g->nrows, rowid, C, ldc, accumulate);
+                               (const uint16_t *)g->lrow, (const int64_t *)g->rbstart, g->rshift, g->nrows, rowid, C, ldc, accumulate);
             SP_HIP(hipGetLastError());
             return SP_OK;
         }

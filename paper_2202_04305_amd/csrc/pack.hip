@@ -820,8 +820,10 @@ sp_status spmi_build_bins(const sp_tensor *A, hipStream_t st)
     const void *pos = listed ? A->nz_pos : A->pos[1];
     const int64_t m = listed ? A->nz_rows : A->npos[1] - 1;          // stored rows
     const int64_t n = A->shape[1], nnz = A->ncrd[1];
-    const int pshift = kSpmiBinPanelShift, rshift = kSpmiBinRowShift;
-    const int64_t panels = ceil_div(n, (int64_t)1 << pshift), rowblocks = ceil_div(m, (int64_t)1 << rshift);
+    const int pshift = kSpmiBinPanelShift;
+    const int64_t panels = ceil_div(n, (int64_t)1 << pshift);
+    const int rshift = spmi_bin_row_shift(nnz, m, panels);
+    const int64_t rowblocks = ceil_div(m, (int64_t)1 << rshift);
     if (nnz < 1 || m < 1 || panels > 0x7fffffff || rowblocks > 0x7fffffff) return SP_ERR_UNSUPPORTED;
     const unsigned __int128 nb128 = (unsigned __int128)panels * (unsigned __int128)rowblocks;
     if (nb128 > (unsigned __int128)nnz + 4096) return SP_ERR_UNSUPPORTED;
@@ -835,7 +837,7 @@ sp_status spmi_build_bins(const sp_tensor *A, hipStream_t st)
     sp_mem mem{A->alloc, A->free_, A->ctx};
     sp_bins *g = new sp_bins();
     A->bins = g;                                         // owned from here on: free_bins() releases whatever was allocated
-    g->nnz = nnz; g->nrows = m; g->panels = (int)panels; g->rowblocks = (int)rowblocks;
+    g->nnz = nnz; g->nrows = m; g->rshift = rshift; g->panels = (int)panels; g->rowblocks = (int)rowblocks;
     // pieces per panel in the first pass: about 32768 entries each, so that loading the slice of x stays a small part
     const int64_t per_panel = nnz / panels;
     g->pieces = (int)(per_panel / 32768 < 1 ? 1 : per_panel / 32768 > 64 ? 64 : per_panel / 32768);

@@ -53,7 +53,7 @@ struct sp_bins {
     uint16_t *lrow = nullptr;         // DEVICE [np]: stored row - rowblock * 2^rshift; padding 0
     int64_t *rbstart = nullptr;       // DEVICE [rowblocks + 1]: first entry of each row block
     int64_t nnz = 0, np = 0, nrows = 0;   // entries, entries with padding, stored rows
-    int panels = 0, rowblocks = 0, pieces = 0;
+    int panels = 0, rowblocks = 0, pieces = 0, rshift = 0;
 };
 
 
@@ -515,7 +515,16 @@ sp_status spmi_build_segments(const sp_tensor *A, int64_t row_bytes, int64_t sli
 #define SPMI_BIN_RSHIFT 11
 #endif
 constexpr int kSpmiBinPanelShift = SPMI_BIN_PSHIFT;          // columns per panel of the binned copy: 8192 (a 64 KB slice of an f64 x)
-constexpr int kSpmiBinRowShift = SPMI_BIN_RSHIFT;            // rows per row block: 2048 (a 16 KB slice of an f64 y)
+constexpr int kSpmiBinRowShift = SPMI_BIN_RSHIFT;            // most rows per row block: 2048 (a 16 KB slice of y in f64)
+// Rows per row block (a power of two) of the binned copy of nnz entries in m stored rows: 2048, or fewer where these would leave
+// CUs without a row block in the second pass, as long as a bucket keeps 24 entries (padding to eights stays near a seventh).
+// 2.7 M entries in 83,886 rows, x of 4 MB: 37 us a product in 41 row blocks of 2048, 29 in 164 of 512.
+static inline int spmi_bin_row_shift(int64_t nnz, int64_t m, int64_t panels)
+{
+    int shift = kSpmiBinRowShift;
+    while (shift > 8 && ceil_div(m, (int64_t)1 << shift) < 128 && (double)nnz >= 24.0 * (double)panels * (double)ceil_div(m, (int64_t)1 << (shift - 1))) --shift;
+    return shift;
+}
 sp_status spmi_build_bins(const sp_tensor *A, hipStream_t st);
 // How scattered the gathers of a product are: the share of stored entries of the innermost level whose successor is 16 or
 // more coordinates away (or belongs to the next segment).  Measured once per tensor, then cached; synchronises the first time.
