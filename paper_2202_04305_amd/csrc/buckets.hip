@@ -1424,6 +1424,8 @@ bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, int64_t rows,
         p->fbits = std::min(p->fbits, bits);
     }
     p->F = (uint32_t)((total - 1) >> p->fbits);
+    // many equal steps cut the range finely already: fewer splitters besides them (76.9 M entries of rank 3, 745 steps: 2698 -> 2665 us)
+    if (p->two && p->F >= 512) Q = std::max<uint64_t>(std::min<uint64_t>(Q, 256), (uint64_t)ceil_div(n, 2 * kFirst));
     if (Q + p->F > (uint64_t)kMaxBuckets) return false;
     p->Q = (uint32_t)Q;
     if (Q + p->F > 1) {
