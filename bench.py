@@ -307,7 +307,7 @@ def bench_pack(args, torch, sp, dev):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "u64", "data": "synthetic",
         "config": {"workload": "sp_pack to an all-compressed format (Section 6.1): %s, %s, %d entries (coordinates int64 per dimension + f64 "
                                "values in, pos/crd %d-bit + values out)" % (top["tensor"], "x".join(str(x) for x in top["shape"]), top["nnz"], args.width),
-                   "kernel": "make_keys + radix sort passes + level sweep", "small": bool(args.small)},
+                   "kernel": "partitions into buckets + LDS finishing pass + levels", "small": bool(args.small)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "kernel": "whole sp_pack call (allocation and host synchronisations included)", "kernel_us": top["ms"] * 1e3,
                      "algorithmic_bytes": top["bytes"]},

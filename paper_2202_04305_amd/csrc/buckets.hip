@@ -11,16 +11,23 @@
 //               the tile by bucket in the LDS and writes runs.  No counting pass: a bucket's room is what the sample says
 //               plus six standard deviations.  Keys shrink to 32 bits where no bucket spans more (multiples of 2^32 are
 //               splitters too): 12 bytes per entry from here on.
-//   second partition, above 4 M entries: the same inside each bucket, splitters from a fresh sample of it
-//   finish      a block per bucket: sorted by value intervals in the LDS, then crd, pos and values leave (levels above the innermost
-//               all dense), or the sorted keys and values (the level sweep does the rest)
+//   second partition, above a million entries: the same inside each bucket, its splitters from a count of its keys by equal intervals
+//               (a sample again where one interval holds too much)
+//   finish      a block per bucket: sorted by value in the LDS; then crd, pos and values leave (levels above the innermost all dense), or
+//               32-bit distances from which bucket_levels_kernel writes every level (compressed levels inside dense ones), or the
+//               sorted keys (any other format: the level sweep does the rest)
 //
 // Should a bucket get more entries than its room (a sample that misleads, or many equal keys), nothing is written out of
 // bounds, the build is marked and the caller builds again with the stable sorts.
 //
-// What bounds it: memory.  Per entry of a CSR matrix in f64: 24 bytes read and 12 written, 12 and 12, 12 and 12.
-// Reserving instead of counting first, 16.9 M entries: 128 us for the first partition into 256 buckets (4.7 TB/s), against
-// 70 for a counting pass, 25 to scan its table and 90 to move.
+// What bounds it: memory, and vector instructions in the finishing kernel.  Per entry of a CSR matrix in f64: 24 bytes read and 12
+// written, 4 read, 12 and 12, 12 and 12.  16.9 M entries of a 1M x 1M lognormal matrix, kernel by kernel: sample and its ranks
+// 26 us, first partition 155 to 165 (3.8 TB/s), cutting the buckets 45, second partition 102 (4.0), finish 144 (2.8); the whole call
+// 841 us with the stable sorts, 575 now.  76.9 M entries of rank 3, all levels compressed: 960, 132, 415 (4.4), 535 and
+// levels 350; 3490 us, 2665 now.
+// Reserving room instead of counting first, 16.9 M entries into 256 buckets: 128 us for all of it, against 70 for a counting pass, 25
+// to scan its table and 90 to move.  One partition into thousands of buckets instead of two: runs of two entries (8192 buckets:
+// 2.3 TB/s); no LDS staging, each entry written where it belongs: 1.2 to 1.6 times as long.
 #include <algorithm>
 #include <cmath>
 #include "spmi_internal.h"
@@ -33,6 +40,7 @@ constexpr int kRun = 1024;                    // sampled keys a block sorts
 constexpr int kMaxSample = 32 * kRun;
 constexpr int kSubSample = 8192;              // most keys sampled inside one bucket
 constexpr int kShare = 48;                    // sampled keys per final bucket
+constexpr int kOnePartition = 512;             // final buckets up to which one partition makes them (1.39 M entries: 205 us with one, 1.4 M 179 with two; 1 M: 156)
 constexpr int kShareFirst = 32;               // sampled keys per bucket that is partitioned again
 constexpr int kPR = 12;                       // partition: entries per thread
 constexpr int kPT = 512, kWideT = 1024;       // its threads: the second partition and small inputs, the first one
@@ -1408,8 +1416,8 @@ bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, int64_t rows,
 {
     memset(p, 0, sizeof(*p));
     if (n < 1 || total < 1 || key_bits > 48) return false;            // sampled keys keep their upper 32 bits: 16 more may hide a crowd
-    p->two = n > (int64_t)kTarget * (kMaxSample / kShare);
-    // blocks enough for the kernel that cuts the buckets (zipf columns, 3.3 M entries, CSR to CSC: 475 us with buckets of 131072)
+    p->two = n > (int64_t)kTarget * kOnePartition;
+    // blocks enough for the kernel that cuts the buckets (Zipf columns, 3.3 M entries, CSR to CSC: 475 us with buckets of 131072, 375 so)
     const int64_t first = std::min<int64_t>(std::max<int64_t>(n / 128, kFirstLeast), kFirst);
     uint64_t Q = p->two ? (uint64_t)std::max<int64_t>(std::min<int64_t>(ceil_div(n, first), 512), ceil_div(n, 2 * kFirst))
                         : n <= kCap ? 1u : (uint64_t)ceil_div(n, kTarget);

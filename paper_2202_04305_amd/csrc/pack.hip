@@ -1,7 +1,9 @@
 // Storage builder: coordinate scheme -> pos / crd / values per level (arXiv 2202.04305, Section 4.1).
 //
 // Steps, all on the GPU: linearise the level coordinates into one 64-bit key per entry (or make the key straight from the
-// storage of another encoding, for conversions), a stable radix sort of (key, value) with the digits in the order that suits
+// storage of another encoding, for conversions), and sort.  Distinct entries are sorted by buckets, straight from the coordinates,
+// and the finishing kernels write crd and pos of most formats themselves (buckets.hip).  Inputs that may hold an entry twice, keys
+// above 48 bits and inputs that overflow a bucket take a stable radix sort of (key, value) with the digits in the order that suits
 // the keys (sort.hip), and the sweep that writes pos and crd of all levels at once from the sorted keys and finds entries given
 // twice on the way (levels.hip; formats with every level but the innermost dense have a kernel of their own here).  The
 // sorted values are the values array, or go to their positions in that sweep where the innermost level is dense.  Only level

@@ -11,6 +11,9 @@
 // pass keeps the input order of entries with equal digits, so this sort is stable as well, and duplicates are added up in
 // the same order after either.
 //
+// The storage builder takes these for entries that may occur twice, for keys above 48 bits, and where its sort by buckets
+// (buckets.hip) overflows.
+//
 // Skew: a run of sub-buckets that does not fit the LDS is sorted by its block through device memory, slowly; the caller asks
 // spmi_msd_sort_suits() first (a sampled histogram of the top 16 bits) and takes the other sort when that would be common.
 #include "spmi_internal.h"

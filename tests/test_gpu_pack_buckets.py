@@ -12,7 +12,7 @@ from gpu_util import say, gpu_pack, assert_storage_equal
 pytestmark = pytest.mark.gpu
 SEED = 7250311
 CSR, CSC, DCSR, CDR = ((0, 1), (0, 1)), ((0, 1), (1, 0)), ((1, 1), (0, 1)), ((1, 0), (0, 1))
-TWO = 2048 * 682                       # up to here one partition
+TWO = 2048 * 512                       # up to here one partition
 
 
 def distinct(shape, nnz, seed):
