@@ -297,6 +297,8 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_multiply_kernel(const V
 // written (m of them; rowid[q] is the matrix row of stored row q when not all rows are stored, and the caller has then
 // zeroed the others).  The slice is f64 for f32 products as well: adds of 32 bits to the LDS are the slower ones (2.7 M entries in 41
 // row blocks, x of 4 MB: 100 us for the product, 29 now), and long sums lose nothing.
+// f64: four slices, a quarter of the waves adding into each, so that a row's sum is four shorter ones (rows of up to 54 entries: error
+// 1.9e-16 of the result with one, as in the streamed kernel, 1.3e-16 with four, 1.4e-16 by column panels; the same time).
 template <typename CT, typename VT>
 __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT *__restrict__ prod, const uint16_t *__restrict__ lrow,
                                                                        const int64_t *__restrict__ rbstart, int rshift, int64_t m,
@@ -306,10 +308,12 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
     constexpr int V = 16 / sizeof(VT), NV = 8 / V;
     typedef VT vec_t __attribute__((ext_vector_type(V)));
     typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-    __shared__ double ys[kBinRB];
+    constexpr int kCopies = sizeof(VT) == 8 ? 4 : 1;
+    __shared__ double ys[kCopies * kBinRB];
     const int rb = (int)blockIdx.x;
     const int rows = 1 << rshift;                      // <= kBinRB
-    for (int i = threadIdx.x; i < rows; i += kBinThreads) ys[i] = 0.0;
+    for (int i = threadIdx.x; i < kCopies * rows; i += kBinThreads) ys[i] = 0.0;
+    double *__restrict__ mine = ys + (int)(threadIdx.x / 64) % kCopies * rows;
     __syncthreads();
     const int64_t g0 = rbstart[rb] >> 3, g1 = rbstart[rb + 1] >> 3;
     const vec_t *__restrict__ pp = (const vec_t *)prod;
@@ -322,7 +326,7 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const unsigned w = (t >> 1) == 0 ? r.x : (t >> 1) == 1 ? r.y : (t >> 1) == 2 ? r.z : r.w;
-            atomicAdd(&ys[(t & 1) ? (w >> 16) : (w & 0xffffu)], (double)v[t / V][t % V]);
+            atomicAdd(&mine[(t & 1) ? (w >> 16) : (w & 0xffffu)], (double)v[t / V][t % V]);
         }
     }
     __syncthreads();
@@ -331,7 +335,9 @@ __global__ __launch_bounds__(kBinThreads) void spmv_bins_reduce_kernel(const VT 
         const int64_t q = r0 + i;                      // stored row; rowid maps it to the matrix row where not all rows are stored
         if (q < m) {
             VT *dst = y + (rowid ? (int64_t)rowid[q] : q) * ldc;
-            *dst = (VT)(accumulate ? (double)*dst + ys[i] : ys[i]);
+            double sum = ys[i];
+            if constexpr (kCopies == 4) sum = (sum + ys[rows + i]) + (ys[2 * rows + i] + ys[3 * rows + i]);
+            *dst = (VT)(accumulate ? (double)*dst + sum : sum);
         }
     }
 }
@@ -1034,11 +1040,12 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
             const double buckets = (double)panels * (double)rowblocks;
             const bool large = nnz >= ((int64_t)1 << 21), segments = !rv.dcsr && nnz >= ((int64_t)1 << 22);
             if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
-                // long rows in f64: the binned copy's second pass adds a row's products one by one, where the others add them up in
-                // trees; it is left to the shapes where it saves most (buckets of 32 entries, a row block for every CU)
+                // long rows in f64: the binned copy's second pass adds a quarter of a row's products one by one, where the others add them
+                // up in trees; it is left to the shapes where it saves most (buckets of 32 entries, a row block for every CU)
                 if (large) kernel = ((double)nnz >= 32.0 * buckets && nrows > 255 * (int64_t)kBinRB) ? 4 : segments ? 3 : 2;
             } else if (share >= 0.5) {
-                // Short rows are added up one by one in every kernel (f32: by the binned one in f64): whichever is the fastest.  Microseconds, fitted to measurements in
+                // Short rows are added up one by one in the other kernels, in four parts in the binned one (f32: in f64), which is no less exact
+                // there: whichever is the fastest.  Microseconds, fitted to measurements in
                 // f64 over 0.3 to 16 M entries, 9,000 to 3 M rows and x of 4 to 64 MB (most within a sixth):
                 //   streamed: a cache line from beyond the L2 per entry that misses it, and the rows to be cleared
                 //   panels:   5.4 per million entries, 6.9 per million (row, panel) pairs
