@@ -76,15 +76,12 @@ __global__ __launch_bounds__(kThreads) void spmv_rows_kernel(const PT *__restric
 #ifndef SPMI_WPE
 #define SPMI_WPE 3
 #endif
-//
-// ZERO (rows by id, y contiguous, m of them, overwritten): the rows that are not stored become zero here as well.  The block takes the
-// rows from the first stored one that begins in its window (row 0 in the first window) up to the next window's, clears
-// them while its gathers are under way, and the barrier before the sums orders its own stores (hypersparse 8M x 8M, 2.7 M entries:
-// 75.1 us with a launch of its own for 67 MB of zeros, 71.1 so).
-template <typename PT, typename CT, typename VT, bool ZERO>
-__global__ __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(1, SPMI_WPE))) void spmv_stream_kernel(
-    const PT *__restrict__ pos, const CT *__restrict__ crd, const VT *__restrict__ val, const CT *__restrict__ rowid, const int32_t *__restrict__ rowblk,
-    int64_t nrows, int64_t nnz, const VT *__restrict__ x, int64_t ldb, VT *__restrict__ y, int64_t ldc, VT *__restrict__ carry, int accumulate, int64_t m)
+template <typename PT, typename CT, typename VT>
+__global__ __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(1, SPMI_WPE))) void spmv_stream_kernel(const PT *__restrict__ pos, const CT *__restrict__ crd,
+                                                               const VT *__restrict__ val, const CT *__restrict__ rowid,
+                                                               const int32_t *__restrict__ rowblk, int64_t nrows, int64_t nnz,
+                                                               const VT *__restrict__ x, int64_t ldb, VT *__restrict__ y, int64_t ldc,
+                                                               VT *__restrict__ carry, int accumulate)
 {
     const int64_t win = blockIdx.x;
     __shared__ VT prods[kStreamT];
@@ -120,31 +117,16 @@ __global__ __launch_bounds__(kST) __attribute__((amdgpu_waves_per_eu(1, SPMI_WPE
         pre_a[i] = pos[r];
         pre_b[i] = pos[r + 1];
     }
-    int64_t za = 0, zb = 0;                            // ZERO: the block's rows of y
-    if (ZERO) {
-        auto first_row = [&](int64_t w, int64_t r) -> int64_t {      // row of y where window w's share begins; r = rowblk[w]
-            if (w == 0) return 0;
-            if (r < nrows && (int64_t)pos[r] < w * kStreamT) ++r;
-            return r < nrows ? (int64_t)rowid[r] : m;
-        };
-        za = first_row(win, lo);
-        zb = win + 1 < (int64_t)gridDim.x ? first_row(win + 1, hi) : m;
-    }
-    auto clear = [&]() {
-        for (int64_t i = za + tid; i < zb; i += kST) y[i] = (VT)0;
-    };
     if (full) {
         VT xv[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) xv[i] = x[(int64_t)k[i] * ldb];
-        if (ZERO) clear();
 #pragma unroll
         for (int t = 0; t < E / 2; ++t) {
             prods[(t * kST + tid) * 2] = v[2 * t] * xv[2 * t];
             prods[(t * kST + tid) * 2 + 1] = v[2 * t + 1] * xv[2 * t + 1];
         }
     } else {
-        if (ZERO) clear();
         for (int i = tid; i < (int)(e - s); i += kST) prods[i] = val[s + i] * x[(int64_t)crd[s + i] * ldb];
     }
     if (tid == 0) lo_began_earlier = (int64_t)pre_a[0] < s;      // thread 0 prefetched pos[lo]
@@ -1134,8 +1116,8 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
         ++A->lazy_prepares;
         SP_TRY((prepare_spmv_t<PT, CT, VT>(A, st)));
     }
-    // rows that are not stored become zero; the stream kernel and the first pass of the binned one do that on the way
-    const bool clears = dcsr && !accumulate && N == 1 && nrows > 0 && (A->plan_spmv == 2 || A->plan_spmv == 4) && ldc == 1;
+    // rows that are not stored become zero; the first pass of the binned kernel does that on the way
+    const bool clears = dcsr && !accumulate && N == 1 && nrows > 0 && A->plan_spmv == 4 && ldc == 1;
     if (dcsr && !accumulate && !clears) SP_TRY((zero_c<PT, CT, VT>(C, m, N, ldc, st)));
     if (nrows == 0) return SP_OK;
     if (N == 1) {
@@ -1155,9 +1137,9 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
             }
             const int64_t nb = srb->nblocks;
             sp_prof_scope prof(A, st);
-            hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT, false>), dim3((unsigned)nb), dim3(kST), 0, st, spos,
+            hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT>), dim3((unsigned)nb), dim3(kST), 0, st, spos,
                                (const CT *)S->crd[1], (const VT *)S->values, srowid, (const int32_t *)srb->start,
-                               vrows, S->ncrd[1], B, ldb, (VT *)g->partial, (int64_t)1, (VT *)srb->carry, 0, (int64_t)0);
+                               vrows, S->ncrd[1], B, ldb, (VT *)g->partial, (int64_t)1, (VT *)srb->carry, 0);
             SP_HIP(hipGetLastError());
             if (nb > 1) {
                 hipLaunchKernelGGL((spmv_stream_fixup_kernel<PT, CT, VT>), dim3(grid_for(nb - 1, kThreads)), dim3(kThreads), 0, st,
@@ -1185,12 +1167,8 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
             const int64_t nb = rowblocks->nblocks;
             {
             sp_prof_scope prof(A, st);
-            if (clears)
-                hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT, true>), dim3((unsigned)nb), dim3(kST), 0, st, pos, crd, val, rowid,
-                                   (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, (VT *)rowblocks->carry, accumulate, m);
-            else
-                hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT, false>), dim3((unsigned)nb), dim3(kST), 0, st, pos, crd, val, rowid,
-                                   (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, (VT *)rowblocks->carry, accumulate, m);
+            hipLaunchKernelGGL((spmv_stream_kernel<PT, CT, VT>), dim3((unsigned)nb), dim3(kST), 0, st, pos, crd, val, rowid,
+                               (const int32_t *)rowblocks->start, nrows, nnz, B, ldb, C, ldc, (VT *)rowblocks->carry, accumulate);
             }
             SP_HIP(hipGetLastError());
             if (nb > 1) {

@@ -1,5 +1,5 @@
-"""Matrix times vector where only some rows are stored, against the CPU checker: the kernels that clear the other rows on their way
-(streamed, and over the binned copy), at the edges of their windows of 1024 entries, row blocks and panels; rows that are not
+"""Matrix times vector where only some rows are stored, against the CPU checker: the streamed kernel, and the binned one, whose first
+pass clears the other rows, at the edges of their windows of 1024 entries, row blocks and panels; rows that are not
 stored stay untouched under accumulation."""
 import numpy as np
 import pytest
