@@ -375,9 +375,11 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)(n > 0 ? ceil_div(n, kT
 // =========================================================================================
 void *sp_mem::get(size_t bytes) const
 {
-    if (alloc) return alloc(bytes, ctx);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+    if (alloc) p = alloc(bytes, ctx);
+    else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
+    // an allocator that fails leaves HIP's last error behind: the launches that follow, of a path that does with less, would report it
+    if (!p) (void)hipGetLastError();
     return p;
 }
 void sp_mem::put(void *p) const
