@@ -91,6 +91,7 @@ void sp_tensor_free(sp_tensor *t);
  * from the tensor's allocator and kept by the handle until sp_tensor_free; sp_tensor_info reports its size (derivedBytes)
  * and the choice (spmvKernel).  Synchronises `stream`.  Calling it again with the same N is a no-op; a larger N
  * grows the scratch; sp_tensor_tune with a kernel key makes the next sp_prepare (or product) decide again.
+ * Where the allocator refuses the copy that an automatically chosen SpMV kernel reads, a kernel that needs no copy is chosen.
  * After sp_prepare(A, N), sp_matmul(A, .., N' <= N columns ..) neither allocates nor synchronises, so it may be recorded
  * into a HIP graph from its first call on.  Errors: NULL, RANK (not rank 2), SHAPE (N < 0), UNSUPPORTED (a kernel forced
  * with sp_tensor_tune cannot run on this tensor), ALLOC, HIP. */

@@ -998,7 +998,8 @@ sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, co
 
 // The inspector step of the matrix-times-vector product (Section 6.2): decides which SpMV kernel the tensor's products run
 // and builds the regrouped copy that kernel reads.  Measures once how scattered the columns are (one pass over crd, one
-// synchronisation), may allocate through the tensor's allocator.  The decision is kept in A->plan_spmv.
+// synchronisation), may allocate through the tensor's allocator.  The decision is kept in A->plan_spmv.  A kernel chosen here
+// gives way to one that needs less where its copy cannot be had (the streamed kernel needs none); one that was asked for does not.
 template <typename PT, typename CT, typename VT>
 sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
 {
@@ -1017,7 +1018,8 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
         const double xbytes = (double)A->shape[1] * sizeof(VT);
         if (kernel == 2 && nnz >= ((int64_t)1 << 20) && xbytes > (double)(3 << 20)) {
             double share = 0;
-            SP_TRY(spmi_column_scatter(A, st, &share));
+            const sp_status sc = spmi_column_scatter(A, st, &share);
+            if (sc != SP_OK && sc != SP_ERR_ALLOC) return sc;
             const int64_t panels = ceil_div(A->shape[1], (int64_t)kBinPW), rowblocks = ceil_div(nrows, (int64_t)1 << spmi_bin_row_shift(nnz, nrows, panels));
             const double buckets = (double)panels * (double)rowblocks;
             const bool large = nnz >= ((int64_t)1 << 21), segments = !rv.dcsr && nnz >= ((int64_t)1 << 22);
@@ -1047,13 +1049,13 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
     }
     if (kernel == 4) {
         const sp_status sb = spmi_build_bins(A, st);
-        if (sb == SP_ERR_UNSUPPORTED && !fixed) kernel = (!rv.dcsr && nnz >= ((int64_t)1 << 22)) ? 3 : 2;
+        if ((sb == SP_ERR_UNSUPPORTED || sb == SP_ERR_ALLOC) && !fixed) kernel = (!rv.dcsr && nnz >= ((int64_t)1 << 22)) ? 3 : 2;
         else if (sb != SP_OK) return sb;
     }
     if (kernel == 3) {
         if (A->enc.lt[0] == SP_COMPRESSED) return SP_ERR_UNSUPPORTED;
         const sp_status sb = spmi_build_segments(A, sizeof(VT), kSpmvSliceBytes, st);
-        if (sb == SP_ERR_UNSUPPORTED && !fixed) kernel = 2;
+        if ((sb == SP_ERR_UNSUPPORTED || sb == SP_ERR_ALLOC) && !fixed) kernel = 2;
         else if (sb != SP_OK) return sb;
     }
     if (kernel == 2 && !rv.rowblocks->start) return SP_ERR_UNSUPPORTED;

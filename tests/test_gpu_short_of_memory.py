@@ -10,7 +10,7 @@ import oracle
 import paper_2202_04305_amd as sp
 from paper_2202_04305_amd import binding
 from gen import prng
-from gpu_util import say, dev, assert_storage_equal, DEV
+from gpu_util import say, dev, assert_product_close, assert_storage_equal, DEV
 
 pytestmark = pytest.mark.gpu
 SEED = 430917
@@ -72,3 +72,37 @@ def test_no_room_for_the_buckets(fmt, nnz):
     assert_storage_equal(A, ref)
     A.free()
     assert not alloc.live
+
+
+@pytest.mark.parametrize("lt", [(0, 1), (1, 1)])
+@pytest.mark.parametrize("m,n,nnz", [(100000, 3000000, 1500000), (600000, 600000, 5000000)])
+def test_no_room_for_the_copy_of_a_matrix_times_vector(lt, m, n, nnz):
+    """Scattered columns: the automatic choice is a kernel over a regrouped copy.  Without room for it the streamed kernel, which needs
+    none, computes the product; a kernel that was asked for still is an error."""
+    (rows, cols), vals = entries(m, n, nnz, np.float64)
+    x = prng.uniform_pm1(SEED, 4, n, np.float64)
+    ref, mag = oracle.matmul_coo((m, n), rows, cols, vals, x[:, None])
+    enc, cd, vd, xd = sp.sp_encode(lt, (0, 1), 32, 32), [dev(rows), dev(cols)], dev(vals), dev(x)
+    y = torch.empty(m, dtype=torch.float64, device=DEV)
+    A = sp.sp_pack(enc, (m, n), cd, vd)
+    sp.sp_prepare(A, 1)
+    assert sp.sp_tensor_info(A).spmvKernel == 4
+    for prepared in (True, False):
+        alloc = PickyAllocator()
+        A = sp.sp_pack(enc, (m, n), cd, vd, allocator=alloc)
+        held = set(alloc.live)
+        alloc.refuses = lambda nbytes: nbytes > 4096
+        if prepared:
+            sp.sp_prepare(A, 1)
+        sp.sp_matmul(A, xd, y)
+        say("case", lt, (m, n, nnz), "prepared" if prepared else "not prepared", "refused", alloc.refused)
+        assert sp.sp_tensor_info(A).spmvKernel == 2 and set(alloc.live) == held
+        if prepared:
+            assert alloc.refused >= 1
+        assert_product_close(y[:, None], ref, mag, np.float64, "without the copy")
+        sp.sp_tensor_tune(A, sp.SP_TUNE_SPMV_KERNEL, 4)
+        with pytest.raises(sp.SpError) as e:
+            sp.sp_prepare(A, 1)
+        assert e.value.code == 12
+        A.free()
+        assert not alloc.live
