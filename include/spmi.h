@@ -106,7 +106,8 @@ sp_status sp_prepare(sp_tensor *A, int64_t N, void *stream);
  * Enqueues on `stream` and returns without synchronising or allocating, provided sp_prepare(A, N) ran before.
  * Without it the product still works: whatever sp_prepare would have built is built by the first product that needs
  * it (that call then allocates and synchronises `stream`), and sp_tensor_info counts such calls in lazyPrepares, so
- * a caller can assert that its loop ran without any.  The handle's derived state is a cache that a product may fill
+ * a caller can assert that its loop ran without any.  (Exception: for N = 1, regrouped copies that take longer to build than
+ * they save in many products are left to sp_prepare; until it is called, products run a kernel that reads the packed storage.)  The handle's derived state is a cache that a product may fill
  * in although it takes the handle as const: a handle must not be used by two host threads at the same time, and the
  * scratch it holds is shared by all products on it, so products of one tensor that run concurrently on different
  * streams race.  (Exception: products of N >= 2 columns where N * element size, ldb, ldc, B or C are no multiples of 16

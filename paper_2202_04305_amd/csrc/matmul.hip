@@ -1000,10 +1000,16 @@ sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, co
 // and builds the regrouped copy that kernel reads.  Measures once how scattered the columns are (one pass over crd, one
 // synchronisation), may allocate through the tensor's allocator.  The decision is kept in A->plan_spmv.  A kernel chosen here
 // gives way to one that needs less where its copy cannot be had (the streamed kernel needs none); one that was asked for does not.
+// unprepared: a product comes without sp_prepare before it.  Then matrices of fewer than two million entries, and those whose
+// binned copy would be small or sparsely filled, take the streamed kernel as they are: a copy costs more than it saves in ten
+// products (1.5 M entries, 100,000 rows of 3 M columns: 46 us for the first product, 349 with the copy; 8 M in 400,000 rows, DCSR: 218 and
+// 475), and the smaller ones ask nothing of the device, so that their products can be recorded.  A later sp_prepare decides for
+// all products after it.
 template <typename PT, typename CT, typename VT>
-sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
+sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st, bool unprepared)
 {
-    if (A->plan_spmv) return SP_OK;
+    if (A->plan_spmv && (unprepared || !A->plan_spmv_open)) return SP_OK;
+    A->plan_spmv = A->plan_spmv_open = 0;
     const row_view<PT, CT> rv(A);
     const int64_t nnz = A->ncrd[1], nrows = rv.nrows;
     int kernel = A->tune_spmv;
@@ -1016,17 +1022,22 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st)
         // them inside the LDS, L2-sized column panels inside the L2.  Gathers that mostly fall into the line of their predecessor
         // stay as they are.
         const double xbytes = (double)A->shape[1] * sizeof(VT);
-        if (kernel == 2 && nnz >= ((int64_t)1 << 20) && xbytes > (double)(3 << 20)) {
+        const bool large = nnz >= ((int64_t)1 << 21), segments = !rv.dcsr && nnz >= ((int64_t)1 << 22);
+        const bool candidate = kernel == 2 && nnz >= ((int64_t)1 << 20) && xbytes > (double)(3 << 20);
+        if (candidate && unprepared && !large) A->plan_spmv_open = 1;
+        else if (candidate) {
             double share = 0;
             const sp_status sc = spmi_column_scatter(A, st, &share);
             if (sc != SP_OK && sc != SP_ERR_ALLOC) return sc;
             const int64_t panels = ceil_div(A->shape[1], (int64_t)kBinPW), rowblocks = ceil_div(nrows, (int64_t)1 << spmi_bin_row_shift(nnz, nrows, panels));
             const double buckets = (double)panels * (double)rowblocks;
-            const bool large = nnz >= ((int64_t)1 << 21), segments = !rv.dcsr && nnz >= ((int64_t)1 << 22);
-            if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
+            // buckets of 32 entries, a row block for every CU: where the binned copy saves most
+            const bool full_bins = large && (double)nnz >= 32.0 * buckets && nrows > 255 * (int64_t)kBinRB;
+            if (share >= 0.5 && unprepared && !full_bins && !segments) A->plan_spmv_open = 1;
+            else if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
                 // long rows in f64: the binned copy's second pass adds a quarter of a row's products one by one, where the others add them
-                // up in trees; it is left to the shapes where it saves most (buckets of 32 entries, a row block for every CU)
-                if (large) kernel = ((double)nnz >= 32.0 * buckets && nrows > 255 * (int64_t)kBinRB) ? 4 : segments ? 3 : 2;
+                // up in trees; it is left to those shapes
+                kernel = full_bins ? 4 : segments ? 3 : 2;
             } else if (share >= 0.5) {
                 // Short rows are added up one by one in the other kernels, in four parts in the binned one (f32: in f64), which is no less exact
                 // there: whichever is the fastest.  Microseconds, fitted to measurements in
@@ -1097,7 +1108,7 @@ template <typename PT, typename CT, typename VT>
 sp_status prepare_rowmajor_t(const sp_tensor *A, const VT *, int64_t N, int64_t, VT *, int64_t, int, hipStream_t st)
 {
     if (A->npos[1] - 1 <= 0) return SP_OK;
-    if (N == 1) return prepare_spmv_t<PT, CT, VT>(A, st);
+    if (N == 1) return prepare_spmv_t<PT, CT, VT>(A, st, false);
     return prepare_spmm_t<PT, CT, VT>(A, N, st);
 }
 
@@ -1116,7 +1127,7 @@ sp_status rowmajor_t(const sp_tensor *A, const VT *B, int64_t N, int64_t ldb, VT
     const int64_t nnz = A->ncrd[1];
     if (N == 1 && nrows > 0 && !A->plan_spmv) {  // no sp_prepare before this product: the inspector runs now (may allocate and synchronise)
         ++A->lazy_prepares;
-        SP_TRY((prepare_spmv_t<PT, CT, VT>(A, st)));
+        SP_TRY((prepare_spmv_t<PT, CT, VT>(A, st, true)));
     }
     // rows that are not stored become zero; the first pass of the binned kernel does that on the way
     const bool clears = dcsr && !accumulate && N == 1 && nrows > 0 && A->plan_spmv == 4 && ldc == 1;

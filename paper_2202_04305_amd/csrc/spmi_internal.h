@@ -121,6 +121,7 @@ struct sp_tensor {
     mutable size_t outgrown_bytes;
     mutable int tables_pending;              // rowblocks / non-empty rows not built yet (a result of sp_spgemm): built on first use by a product
     mutable int plan_spmv;                   // SpMV kernel a product with one column runs (1..4); 0 = not decided yet (sp_prepare or the first product decides)
+    mutable int plan_spmv_open;              // plan_spmv was taken by a product without sp_prepare, which may still decide otherwise
     mutable int lazy_prepares;               // how many products had to build, allocate or decide something first (none after sp_prepare)
     int tune_spmv, tune_csc, tune_spmm, tune_spgemm;
     int profile;
