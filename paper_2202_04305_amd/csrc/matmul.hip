@@ -996,6 +996,49 @@ sp_status spmm_windows_launch(const sp_tensor *A, const row_view<PT, CT> &rv, co
     return SP_OK;
 }
 
+// What the binned kernel's second pass needs for its heaviest row block, in microseconds (out: bits of a float, zero before): a row
+// block is one workgroup's, and products of one row that meet in a wave add to one address of the LDS one after the other.  Per thousand
+// products 0.25, and 0.17 more for every doubling of the lanes that a bucket's products of a row fill (a lane takes eight): f32,
+// 3 M entries in 200,000 rows of 2 M columns, with one row of 990,000: 1256 us (one of 9000: 26; 20 side by side of 20,000: 317; none: 18).
+template <typename PT>
+__global__ __launch_bounds__(kThreads) void spmv_bins_peak_kernel(const PT *__restrict__ pos, int64_t nrows, int rshift, float lanes_per_product,
+                                                                  unsigned *__restrict__ out)
+{
+    __shared__ float wsum[kThreads / 64];
+    const int64_t r0 = (int64_t)blockIdx.x << rshift, r1 = r0 + ((int64_t)1 << rshift) < nrows ? r0 + ((int64_t)1 << rshift) : nrows;
+    float us = 0;
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += kThreads) {
+        const float len = (float)(pos[r + 1] - pos[r]);
+        us += 1e-3f * len * (0.25f + 0.17f * __log2f(fminf(fmaxf(len * lanes_per_product, 1.0f), 64.0f)));
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) us += __shfl_xor(us, d, 64);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = us;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kThreads / 64; ++w) us += wsum[w];
+        atomicMax(out, __float_as_uint(us));              // positive floats are ordered as their bits are
+    }
+}
+
+template <typename PT>
+sp_status spmv_bins_peak(const sp_tensor *A, const PT *pos, int64_t nrows, int rshift, int64_t panels, hipStream_t st, double *us)
+{
+    sp_mem mem{A->alloc, A->free_, A->ctx};
+    sp_scratch tmp(mem);
+    unsigned *out = (unsigned *)tmp.get(64);
+    if (!out) return SP_ERR_ALLOC;
+    SP_TRY(spmi_fill_zero(out, 64, st));
+    hipLaunchKernelGGL(spmv_bins_peak_kernel<PT>, dim3((unsigned)ceil_div(nrows, (int64_t)1 << rshift)), dim3(kThreads), 0, st, pos, nrows, rshift,
+                       (float)(1.0 / (8.0 * (double)panels)), out);
+    SP_HIP(hipGetLastError());
+    float h = 0;
+    SP_HIP(hipMemcpyAsync(&h, out, 4, hipMemcpyDeviceToHost, st));
+    SP_HIP(hipStreamSynchronize(st));
+    *us = (double)h;
+    return SP_OK;
+}
+
 // The inspector step of the matrix-times-vector product (Section 6.2): decides which SpMV kernel the tensor's products run
 // and builds the regrouped copy that kernel reads.  Measures once how scattered the columns are (one pass over crd, one
 // synchronisation), may allocate through the tensor's allocator.  The decision is kept in A->plan_spmv.  A kernel chosen here
@@ -1029,32 +1072,51 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st, bool unprepared)
             double share = 0;
             const sp_status sc = spmi_column_scatter(A, st, &share);
             if (sc != SP_OK && sc != SP_ERR_ALLOC) return sc;
-            const int64_t panels = ceil_div(A->shape[1], (int64_t)kBinPW), rowblocks = ceil_div(nrows, (int64_t)1 << spmi_bin_row_shift(nnz, nrows, panels));
+            const int64_t panels = ceil_div(A->shape[1], (int64_t)kBinPW);
+            const int rshift = spmi_bin_row_shift(nnz, nrows, panels);
+            const int64_t rowblocks = ceil_div(nrows, (int64_t)1 << rshift);
             const double buckets = (double)panels * (double)rowblocks;
             // buckets of 32 entries, a row block for every CU: where the binned copy saves most
             const bool full_bins = large && (double)nnz >= 32.0 * buckets && nrows > 255 * (int64_t)kBinRB;
+            // Microseconds, fitted to measurements in
+            // f64 over 0.3 to 16 M entries, 9,000 to 3 M rows and x of 4 to 64 MB (most within a sixth):
+            //   streamed: a cache line from beyond the L2 per entry that misses it, and the rows to be cleared
+            //   panels:   5.4 per million entries, 6.9 per million (row, panel) pairs
+            //   binned:   x and 18.5 bytes per entry (buckets padded to eights), then 10 bytes per entry or the heaviest
+            //             row block, which is at least the mean one
+            // Measured (by the formula): f64, 3 M entries in 200,000 rows of 2 M columns 51 us (54) streamed, 22 (25) binned; 16 M in 1 M rows
+            // of 4 M columns 278 (296), 90 (104) and 205 (200) by panels; the same sorted by length, rows of up to 300, f32: 226 (236), 140 (152)
+            // and 112 (200).
+            const double M = 1e-6 * (double)nnz, v = (double)sizeof(VT) / 8.0, clear = rv.dcsr ? 1.6e-7 * (double)A->shape[0] * sizeof(VT) : 0.0;
+            const double padded = M + 1e-6 * std::min(3.5 * buckets, 7.0 * (double)nnz);
+            const double streamed = 5.0 + M * (5.5 + 14.5 * (1.0 - (double)(4 << 20) / std::max(xbytes, (double)(4 << 20)))) + clear;
+            const double paneled = segments ? 3.0 + 5.4 * M + 6.9e-6 * (double)nrows * std::ceil(xbytes / (double)kSpmvSliceBytes) : 1e30;
+            const double others = std::min(streamed, large ? paneled : streamed);
+            auto binned = [&](double peak) {
+                return 4.0 + 2e-7 * xbytes + padded * (1.0 + 2.8 * v) + 0.6 * clear + std::max(padded * (0.3 + 1.5 * v), 2.0 + peak);
+            };
+            const double peak = 250.0 * padded / (double)rowblocks;
+            double limit = 0.9 * others;
             if (share >= 0.5 && unprepared && !full_bins && !segments) A->plan_spmv_open = 1;
             else if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
                 // long rows in f64: the binned copy's second pass adds a quarter of a row's products one by one, where the others add them
                 // up in trees; it is left to those shapes
                 kernel = full_bins ? 4 : segments ? 3 : 2;
+                limit = others;
             } else if (share >= 0.5) {
                 // Short rows are added up one by one in the other kernels, in four parts in the binned one (f32: in f64), which is no less exact
-                // there: whichever is the fastest.  Microseconds, fitted to measurements in
-                // f64 over 0.3 to 16 M entries, 9,000 to 3 M rows and x of 4 to 64 MB (most within a sixth):
-                //   streamed: a cache line from beyond the L2 per entry that misses it, and the rows to be cleared
-                //   panels:   5.4 per million entries, 6.9 per million (row, panel) pairs
-                //   binned:   x and 18.5 bytes per entry (buckets padded to eights), then 10 bytes per entry or, with few row
-                //             blocks, one block's share of them
-                // 2.7 M entries in 83,886 rows of 8 M columns: 69 us streamed, 46 binned; 16 M entries in 3 M rows of 4 M columns
-                // 283, 414 (panels) and 99.
-                const double M = 1e-6 * (double)nnz, v = (double)sizeof(VT) / 8.0, clear = rv.dcsr ? 1.6e-7 * (double)A->shape[0] * sizeof(VT) : 0.0;
-                const double padded = M + 1e-6 * std::min(3.5 * buckets, 7.0 * (double)nnz);
-                const double streamed = 5.0 + M * (5.5 + 14.5 * (1.0 - (double)(4 << 20) / std::max(xbytes, (double)(4 << 20)))) + clear;
-                const double paneled = segments ? 3.0 + 5.4 * M + 6.9e-6 * (double)nrows * std::ceil(xbytes / (double)kSpmvSliceBytes) : 1e30;
-                const double binned = 4.0 + 2e-7 * xbytes + padded * (1.0 + 2.8 * v) + 0.6 * clear + std::max(padded * (0.3 + 1.5 * v), 2.0 + 250.0 * padded / (double)rowblocks);
+                // there: whichever is the fastest.
                 if (large && paneled < streamed) kernel = 3;
-                if (binned < 0.9 * std::min(streamed, large ? paneled : streamed)) kernel = 4;
+                if (binned(peak) < limit) kernel = 4;
+            }
+            // no row block holds more than its rows of the longest length: often that answers it without asking the device
+            const double most = std::min((double)nnz, (double)A->max_segment * (double)((int64_t)1 << rshift));
+            const double lanes = std::min(std::max((double)A->max_segment / (8.0 * (double)panels), 1.0), 64.0);
+            if (kernel == 4 && binned(std::max(peak, 1e-3 * most * (0.25 + 0.17 * std::log2(lanes)))) >= limit) {
+                double heaviest = 0;
+                const sp_status sh = spmv_bins_peak<PT>(A, rv.pos, nrows, rshift, panels, st, &heaviest);
+                if (sh != SP_OK && sh != SP_ERR_ALLOC) return sh;
+                if (binned(std::max(peak, heaviest)) >= limit) kernel = large && paneled < streamed ? 3 : 2;
             }
         }
     }

@@ -61,3 +61,45 @@ def test_product_of_a_middle_sized_matrix_can_be_recorded_without_prepare():
         graph.replay()
         torch.cuda.synchronize()
         assert_product_close(y[:, None], ref, mag, np.float64, "replay %d" % replay)
+
+
+def by_length(m, n, nnz, longest):
+    """About nnz entries in rows sorted by length."""
+    w = np.arange(1, m + 1, dtype=np.float64) ** -0.7
+    lo, hi = 0.0, float(nnz)
+    for _ in range(60):
+        c = 0.5 * (lo + hi)
+        lo, hi = (c, hi) if np.minimum(w * c, longest).round().sum() < nnz else (lo, c)
+    lens = np.minimum(w * hi, longest).round().astype(np.int64)
+    rows = np.repeat(np.arange(m), lens)
+    lin = np.unique(rows * n + prng.below(SEED + longest, 5, rows.size, n))
+    return lin // n, lin % n
+
+
+def one_long(m, n, nnz, longest):
+    (rows, cols), _ = scattered(m, n, nnz - longest)
+    keep = rows != 17
+    return (np.concatenate([rows[keep], np.full(longest, 17)]),
+            np.concatenate([cols[keep], np.sort(prng.permutation(SEED, 6, n)[:longest])]))
+
+
+@pytest.mark.parametrize("dtype,make,args,kernels", [
+    (np.float32, one_long, (200000, 2000000, 3000000, 990000), (2,)),        # binned: 1256 us, streamed: 162
+    (np.float32, by_length, (200000, 2000000, 3000000, 20000), (2,)),        # 131 and 39
+    (np.float32, by_length, (200000, 2000000, 3000000, 64), (4,)),           # 26 and 38
+    (np.float32, one_long, (200000, 2000000, 3000000, 3000), (4,)),          # 19 and 38
+    (np.float64, by_length, (600000, 600000, 4500000, 5000), (2, 3)),        # row blocks of 2048 and 32 entries a bucket, one far above the mean
+])
+def test_the_choice_looks_at_the_heaviest_row_block(dtype, make, args, kernels):
+    m, n = args[:2]
+    rows, cols = make(*args)
+    vals, x = prng.uniform_pm1(SEED, 7, rows.size, dtype), prng.uniform_pm1(SEED, 8, n, dtype)
+    ref, mag = oracle.matmul_coo((m, n), rows, cols, vals, x[:, None])
+    A = sp.sp_pack(sp.sp_encode((0, 1), (0, 1), 32, 32), (m, n), [dev(rows), dev(cols)], dev(vals))
+    sp.sp_prepare(A, 1)
+    info = sp.sp_tensor_info(A)
+    say("case", np.dtype(dtype).name, make.__name__, args, "longest row", info.maxSegment, "kernel", info.spmvKernel)
+    assert info.spmvKernel in kernels
+    y = torch.full((m,), float("nan"), dtype=torch.float32 if dtype == np.float32 else torch.float64, device=DEV)
+    sp.sp_matmul(A, dev(x), y)
+    assert_product_close(y[:, None], ref, mag, dtype, make.__name__)
