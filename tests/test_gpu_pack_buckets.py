@@ -142,3 +142,32 @@ def test_entries_given_twice_and_coordinates_out_of_range(fmt, n):
         with pytest.raises(sp.SpError) as e:
             gpu_pack(*fmt, shape, c, v, 32, 32)
         assert e.value.code == code
+
+
+@pytest.mark.parametrize("fmt", [CSR, CSC, DCSR])
+def test_input_that_is_sorted_already(fmt):
+    """A bucket that gets 256 entries or more of a tile (1024 entries; 12288 from 1,572,864 entries on) gets them in a mixed order: every
+    place exactly once, whatever the number is."""
+    for n in (255, 256, 257, 511, 512, 767, 1023, 1024, 1025, 2048 + 255, 2048 + 256, 100003, TWO + 1, 1572863, 1572864, 1600001):
+        shape = (300, 401) if n < 4096 else (40009, 30011)
+        coords = distinct(shape, n, SEED + 7 * n)
+        key = coords[0] * shape[1] + coords[1] if fmt != CSC else coords[1] * shape[0] + coords[0]
+        order = np.argsort(key)
+        check(fmt, shape, [c[order] for c in coords], np.float64 if n % 2 else np.float32)
+        if n > 100000:
+            check(fmt, shape, [c[order[::-1]] for c in coords])
+
+
+def test_bands_and_blocks_that_are_sorted_already():
+    r = np.arange(1600000 // 64 + 1, dtype=np.int64)
+    m = r.size
+    band = [r.repeat(64), (r[:, None] + np.arange(64)).ravel() % m]
+    order = np.argsort(band[0] * m + band[1])
+    for fmt in (CSR, DCSR, CSC):
+        check(fmt, (m, m), [c[order] for c in band])
+    b = np.arange(1600000 // 4096 + 1, dtype=np.int64)
+    i, j = np.divmod(np.arange(4096), 64)
+    rows, cols = (b[:, None] * 64 + i).ravel(), (b[:, None] * 64 + j).ravel()
+    order = np.argsort(rows * (64 * b.size) + cols)
+    for fmt in (CSR, CSC):
+        check(fmt, (64 * b.size, 64 * b.size), [rows[order], cols[order]], np.float32)
