@@ -867,23 +867,63 @@ __device__ __forceinline__ void emit_heads(const final_args &f, const K *dist, u
     if (tid == 0 && cnt) { f.ends[2 * b] = (uint32_t)dist[0]; f.ends[2 * b + 1] = (uint32_t)dist[cnt - 1]; }
 }
 
-// The rows (positions of the level above) that begin in [lo, next) are this bucket's: each looks up its first entry.
+// The rows (positions of the level above) that begin in [lo, next) are this bucket's: each looks up its first entry.  Many rows (the
+// last ones of an R-MAT graph, mostly empty: 65536 of them in a bucket) take too many reads of the LDS that way: they are counted
+// kRowChunk at a time and the counts summed (R-MAT graph of 2^23 vertices, 4 M f32 entries, CSR: finishing 362 + 330 us by
+// looking up, 179 + 136 so; 2048 rows or 512 make no difference, 8192 3 percent of the call).  counts:
+// LDS, kRowWords words, not in use.
+constexpr int kRowChunk = 16 * kFT, kRowWords = 17 * kFT;            // one word more for every 16: no bank conflicts when a thread sums its 16
+constexpr int kManyRows = 2048;
 template <typename K, int T>
-__device__ __forceinline__ void emit_rows(const final_args &f, const final_bucket &w, const K *dist, uint32_t cnt)
+__device__ __forceinline__ void emit_rows(const final_args &f, const final_bucket &w, const K *dist, uint32_t cnt, uint32_t *counts, uint32_t *wsum)
 {
     if (!f.pos) return;
     const uint64_t r0 = w.lo == 0 ? 0 : spmi_div_by(w.lo - 1, f.inner) + 1, r1 = w.next == 0 ? 0 : spmi_div_by(w.next - 1, f.inner) + 1;
     uint32_t top = 1;
     while (top <= cnt) top *= 2;
     const uint64_t last = cnt ? (uint64_t)dist[cnt - 1] : 0;
-    for (uint64_t r = r0 + threadIdx.x; r < r1; r += T) {
+    auto entries_before = [&](uint64_t r) -> uint32_t {
         const uint64_t first = r * f.inner.d - w.lo;                 // below next - lo: fits K
+        if (cnt && first > last) return cnt;                         // rows after the last entry
         uint32_t a = 0;
-        if (cnt && first > last) a = cnt;                            // rows after the last entry
-        else for (uint32_t s = top / 2; s > 0; s >>= 1)
+        for (uint32_t s = top / 2; s > 0; s >>= 1)
             if (a + s <= cnt && (uint64_t)dist[a + s - 1] < first) a += s;
+        return a;
+    };
+    auto put = [&](uint64_t r, uint32_t a) {
         if (f.pw == 32) ((int32_t *)f.pos)[r] = (int32_t)(w.out + a);
         else ((int64_t *)f.pos)[r] = (int64_t)(w.out + a);
+    };
+    static_assert(T == kFT, "16 rows of a chunk per thread");
+    if (cnt == 0 || r1 - r0 <= (uint64_t)kManyRows || r1 <= r0) {    // block-uniform
+        for (uint64_t r = r0 + threadIdx.x; r < r1; r += T) put(r, entries_before(r));
+        return;
+    }
+    const uint64_t above = spmi_div_by(w.lo, f.inner), off = w.lo - above * f.inner.d;
+    uint32_t done = entries_before(r0);                              // entries of rows before the chunk
+    for (uint64_t c0 = r0; c0 < r1; c0 += kRowChunk) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < kRowWords; j += T) counts[j] = 0;
+        __syncthreads();
+        for (uint32_t i = done + threadIdx.x; i < cnt; i += T) {
+            const uint64_t row = above + spmi_div_by(off + (uint64_t)dist[i], f.inner) - c0;
+            if (row >= (uint64_t)kRowChunk) break;
+            atomicAdd(&counts[row + (row >> 4)], 1u);
+        }
+        __syncthreads();
+        uint32_t *mine = counts + threadIdx.x * 17, sum = 0, all;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sum += mine[j];
+        uint32_t before = done + block_exclusive_scan(sum, wsum, all);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const uint32_t c = mine[j];
+            mine[j] = before;
+            before += c;
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < kRowChunk && c0 + j < r1; j += T) put(c0 + j, counts[j + (j >> 4)]);
+        done += all;
     }
 }
 
@@ -901,6 +941,7 @@ using lds_key = typename std::conditional<sizeof(K) == 8, unsigned long long, un
 template <typename K, typename P, int ATTEMPT>
 struct finish_lds {
     static constexpr int kWords = (kFE | 1) * kFT;
+    static_assert(kWords >= kRowWords, "emit_rows counts in the words of the intervals");
     static constexpr size_t kKeys = kCap * sizeof(K) + (kWords + 1) * 4 + kCells1 * 4, kValues = kCap * sizeof(P);
     __align__(16) unsigned char stage[kKeys > kValues ? kKeys : kValues];
     lds_key<K> least[ATTEMPT ? kCells1 : 1], most[ATTEMPT ? kCells1 : 1];     // second attempt: of a cell's keys
@@ -1061,7 +1102,7 @@ __device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P
     }
     __syncthreads();
     emit_sorted<K, kFT>(f, w, dist, cnt);
-    emit_rows<K, kFT>(f, w, dist, cnt);
+    emit_rows<K, kFT>(f, w, dist, cnt, bins, s.wsum);
     emit_heads<K, kFT>(f, dist, cnt, b, s.heads);
     __syncthreads();
 #pragma unroll
@@ -1090,7 +1131,7 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
     bool left = false;
     if ((w.cnt & kOverflow) || w.cnt == 0) {
         if ((w.cnt & kOverflow) && f.keys) for (uint32_t i = threadIdx.x; i < (w.cnt & ~kOverflow); i += kFT) f.keys[w.out + i] = 0;
-        if (any) emit_rows<K, kFT>(f, w, (const K *)s.stage, 0);
+        if (any) emit_rows<K, kFT>(f, w, (const K *)s.stage, 0, nullptr, s.wsum);
         emit_heads<K, kFT>(f, (const K *)s.stage, 0, b, s.heads);
     } else left = !finish_bucket<K, P, 0>(kin, vin, vout, f, w, s, b);
     if (any && threadIdx.x == 0) f.left[b] = left ? 1u : 0u;
@@ -1101,7 +1142,7 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
 template <typename K, typename P>
 __global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
 {
-    __shared__ union { finish_lds<K, P, 1> s; struct { K dist[kCap]; uint16_t idx[kCap]; head_counts heads; } sort; } lds;
+    __shared__ union { finish_lds<K, P, 1> s; struct { K dist[kCap]; uint16_t idx[kCap]; head_counts heads; uint32_t wsum[kFT / 64], counts[kRowWords]; } sort; } lds;
     const int tid = threadIdx.x, lane = tid & 63;
     if (f.flags[2]) return;
     const uint32_t total = f.count ? *f.count : f.most;
@@ -1139,7 +1180,7 @@ __global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict
             for (uint32_t i = tid; i + 1 < cnt; i += kFT) dup |= dist[i] == dist[i + 1];
             if (dup) atomicOr(&f.flags[1], 1);
             emit_sorted<K, kFT>(f, w, dist, cnt);
-            emit_rows<K, kFT>(f, w, dist, cnt);
+            emit_rows<K, kFT>(f, w, dist, cnt, lds.sort.counts, lds.sort.wsum);
             emit_heads<K, kFT>(f, dist, cnt, b, lds.sort.heads);
             for (uint32_t i = tid; i < cnt; i += kFT) vout[w.out + i] = vin[w.start + idx[i]];
         }

@@ -171,3 +171,23 @@ def test_bands_and_blocks_that_are_sorted_already():
     order = np.argsort(rows * (64 * b.size) + cols)
     for fmt in (CSR, CSC):
         check(fmt, (64 * b.size, 64 * b.size), [rows[order], cols[order]], np.float32)
+
+
+@pytest.mark.parametrize("widths", [(32, 32), (64, 64)])
+@pytest.mark.parametrize("n,columns", [(3000, 50), (40000, 1 << 20), (70000, 1 << 31), (TWO + 5, 1 << 26)])
+def test_many_rows_that_begin_in_one_bucket(n, columns, widths):
+    """Rows of a bucket beyond 2048 are counted 4096 at a time: entries only before, only behind and only at the edges of such stretches, and
+    anywhere in them; the last rows empty."""
+    m = min(4 * n, 1 << 20) - 5
+    for where in ("anywhere", "first rows", "last rows", "edges", "two ends"):
+        rows = prng.below(SEED + n, 11, 2 * n, m)
+        if where == "first rows":
+            rows = rows % max(n // 30, 60)
+        elif where == "last rows":
+            rows = m - 1 - rows % max(n // 30, 60)
+        elif where == "edges":
+            rows = np.minimum(rows // 2048 * 2048 + rows % 3, m - 1)
+        elif where == "two ends":
+            rows = np.where(rows % 2 == 0, rows % 500, m - 1 - rows % 500)
+        lin = np.unique(rows * columns + prng.below(SEED + n, 12, 2 * n, columns))
+        check(CSR, (m, columns), shuffled(lin, n, (m, columns), SEED), np.float32, widths if columns < 1 << 31 else (widths[0], 64))
