@@ -704,13 +704,14 @@ struct final_bucket {
     int shift;                // > 0: distances to the left, < 0: to the right, so that the range has 32 bits
 };
 constexpr uint32_t kOverflow = 0x80000000u;
+constexpr uint32_t kCrowded = 1u, kUncounted = 2u;       // left: a bucket with a crowded interval; the rows of one that has many
 
 struct final_args {
     const final_bucket *bucket;
     const uint32_t *count;               // DEVICE: number of final buckets (null: `most`)
     uint32_t most;
     int64_t n;
-    uint32_t *left;                      // [most] buckets with a crowded interval: finish_crowded_kernel takes them
+    uint32_t *left;                      // [most] what the finishing kernel left to finish_crowded_kernel
     int *flags;
     // what leaves: the keys (uint64), or what bucket_levels_kernel takes (dist), or crd / pos of an innermost compressed level under dense ones
     uint64_t *keys;
@@ -867,63 +868,80 @@ __device__ __forceinline__ void emit_heads(const final_args &f, const K *dist, u
     if (tid == 0 && cnt) { f.ends[2 * b] = (uint32_t)dist[0]; f.ends[2 * b + 1] = (uint32_t)dist[cnt - 1]; }
 }
 
-// The rows (positions of the level above) that begin in [lo, next) are this bucket's: each looks up its first entry.  Many rows (the
-// last ones of an R-MAT graph, mostly empty: 65536 of them in a bucket) take too many reads of the LDS that way: they are counted
-// kRowChunk at a time and the counts summed (R-MAT graph of 2^23 vertices, 4 M f32 entries, CSR: finishing 362 + 330 us by
-// looking up, 179 + 136 so; 2048 rows or 512 make no difference, 8192 3 percent of the call).  counts:
-// LDS, kRowWords words, not in use.
-constexpr int kRowChunk = 16 * kFT, kRowWords = 17 * kFT;            // one word more for every 16: no bank conflicts when a thread sums its 16
+// The rows (positions of the level above) that begin in [lo, next) are this bucket's: each looks up its first entry.  Those of a bucket
+// with more than kManyRows are left to finish_crowded_kernel.
 constexpr int kManyRows = 2048;
+struct row_range { uint64_t first, end; };
+__device__ __forceinline__ row_range rows_of(const final_args &f, const final_bucket &w)
+{
+    return {w.lo == 0 ? 0 : spmi_div_by(w.lo - 1, f.inner) + 1, w.next == 0 ? 0 : spmi_div_by(w.next - 1, f.inner) + 1};
+}
+__device__ __forceinline__ bool many_rows(const final_args &f, const final_bucket &w)
+{
+    const row_range rows = rows_of(f, w);
+    return f.pos && rows.end - rows.first > (uint64_t)kManyRows;
+}
+__device__ __forceinline__ void put_pos(const final_args &f, uint64_t r, uint32_t at)
+{
+    if (f.pw == 32) ((int32_t *)f.pos)[r] = (int32_t)at;
+    else ((int64_t *)f.pos)[r] = (int64_t)at;
+}
+
 template <typename K, int T>
-__device__ __forceinline__ void emit_rows(const final_args &f, const final_bucket &w, const K *dist, uint32_t cnt, uint32_t *counts, uint32_t *wsum)
+__device__ __forceinline__ void emit_rows(const final_args &f, const final_bucket &w, const K *dist, uint32_t cnt)
 {
     if (!f.pos) return;
-    const uint64_t r0 = w.lo == 0 ? 0 : spmi_div_by(w.lo - 1, f.inner) + 1, r1 = w.next == 0 ? 0 : spmi_div_by(w.next - 1, f.inner) + 1;
+    const row_range rows = rows_of(f, w);
+    if (cnt && rows.end - rows.first > (uint64_t)kManyRows) return;  // block-uniform
     uint32_t top = 1;
     while (top <= cnt) top *= 2;
     const uint64_t last = cnt ? (uint64_t)dist[cnt - 1] : 0;
-    auto entries_before = [&](uint64_t r) -> uint32_t {
+    for (uint64_t r = rows.first + threadIdx.x; r < rows.end; r += T) {
         const uint64_t first = r * f.inner.d - w.lo;                 // below next - lo: fits K
-        if (cnt && first > last) return cnt;                         // rows after the last entry
         uint32_t a = 0;
-        for (uint32_t s = top / 2; s > 0; s >>= 1)
+        if (cnt && first > last) a = cnt;                            // rows after the last entry
+        else for (uint32_t s = top / 2; s > 0; s >>= 1)
             if (a + s <= cnt && (uint64_t)dist[a + s - 1] < first) a += s;
-        return a;
-    };
-    auto put = [&](uint64_t r, uint32_t a) {
-        if (f.pw == 32) ((int32_t *)f.pos)[r] = (int32_t)(w.out + a);
-        else ((int64_t *)f.pos)[r] = (int64_t)(w.out + a);
-    };
-    static_assert(T == kFT, "16 rows of a chunk per thread");
-    if (cnt == 0 || r1 - r0 <= (uint64_t)kManyRows || r1 <= r0) {    // block-uniform
-        for (uint64_t r = r0 + threadIdx.x; r < r1; r += T) put(r, entries_before(r));
-        return;
+        put_pos(f, r, w.out + a);
     }
-    const uint64_t above = spmi_div_by(w.lo, f.inner), off = w.lo - above * f.inner.d;
-    uint32_t done = entries_before(r0);                              // entries of rows before the chunk
-    for (uint64_t c0 = r0; c0 < r1; c0 += kRowChunk) {
+}
+
+// Many rows (the last ones of an R-MAT graph, mostly empty: 65536 of them in a bucket) take too many reads of the LDS to be looked up:
+// their entries are counted, from the keys as they came, kRowChunk rows at a time, and the counts summed.  R-MAT graph of 2^23
+// vertices, 4 M f32 entries, CSR: finishing 362 + 330 us by looking up, 117 + 144 so; the same from 512 rows on, 3 % of the call
+// longer from 8192.  (In the finishing kernel itself it costs registers: 4 % of that kernel where no bucket has many rows.)
+// lds: kCap + kRowWords words.
+constexpr int kRowChunk = 16 * kFT, kRowWords = 17 * kFT;            // one word more for every 16: no bank conflicts when a thread sums its 16
+template <typename K>
+__device__ __forceinline__ void count_rows(const final_args &f, const final_bucket &w, const K *__restrict__ kin, uint32_t *lds, uint32_t *wsum)
+{
+    const K *__restrict__ keys = kin + w.start;
+    const uint32_t cnt = w.cnt;
+    const row_range rows = rows_of(f, w);
+    const uint32_t n = (uint32_t)(rows.end - rows.first);            // below 4 * entries (or this format is not written here)
+    const int tid = threadIdx.x;
+    uint32_t *rel = lds, *counts = lds + kCap;                       // an entry's row, counted from the one before the first
+    __syncthreads();
+    for (uint32_t i = tid; i < cnt; i += kFT) rel[i] = (uint32_t)(spmi_div_by(w.lo + (uint64_t)(K)(keys[i] - (K)w.lo), f.inner) + 1 - rows.first);
+    uint32_t before = 0;
+    for (uint32_t c = 0; c < n; c += kRowChunk) {
+        for (int j = tid; j < kRowWords; j += kFT) counts[j] = 0;
         __syncthreads();
-        for (int j = threadIdx.x; j < kRowWords; j += T) counts[j] = 0;
-        __syncthreads();
-        for (uint32_t i = done + threadIdx.x; i < cnt; i += T) {
-            const uint64_t row = above + spmi_div_by(off + (uint64_t)dist[i], f.inner) - c0;
-            if (row >= (uint64_t)kRowChunk) break;
-            atomicAdd(&counts[row + (row >> 4)], 1u);
+        for (uint32_t i = tid; i < cnt; i += kFT) {
+            const uint32_t j = rel[i] - c;                           // below c: beyond the chunk as an unsigned number
+            if (j < (uint32_t)kRowChunk) atomicAdd(&counts[j + (j >> 4)], 1u);
         }
         __syncthreads();
-        uint32_t *mine = counts + threadIdx.x * 17, sum = 0, all;
+        uint32_t *mine = counts + tid * 17, sum = 0, all;
 #pragma unroll
         for (int j = 0; j < 16; ++j) sum += mine[j];
-        uint32_t before = done + block_exclusive_scan(sum, wsum, all);
+        uint32_t up = before + block_exclusive_scan(sum, wsum, all);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const uint32_t c = mine[j];
-            mine[j] = before;
-            before += c;
-        }
+        for (int j = 0; j < 16; ++j) mine[j] = up += mine[j];
         __syncthreads();
-        for (int j = threadIdx.x; j < kRowChunk && c0 + j < r1; j += T) put(c0 + j, counts[j + (j >> 4)]);
-        done += all;
+        for (int j = tid; j < kRowChunk && c + (uint32_t)j < n; j += kFT) put_pos(f, rows.first + c + (uint32_t)j, w.out + counts[j + (j >> 4)]);
+        before += all;
+        __syncthreads();
     }
 }
 
@@ -941,9 +959,9 @@ using lds_key = typename std::conditional<sizeof(K) == 8, unsigned long long, un
 template <typename K, typename P, int ATTEMPT>
 struct finish_lds {
     static constexpr int kWords = (kFE | 1) * kFT;
-    static_assert(kWords >= kRowWords, "emit_rows counts in the words of the intervals");
     static constexpr size_t kKeys = kCap * sizeof(K) + (kWords + 1) * 4 + kCells1 * 4, kValues = kCap * sizeof(P);
     __align__(16) unsigned char stage[kKeys > kValues ? kKeys : kValues];
+    static_assert(sizeof(stage) >= (kCap + kRowWords) * 4, "count_rows");
     lds_key<K> least[ATTEMPT ? kCells1 : 1], most[ATTEMPT ? kCells1 : 1];     // second attempt: of a cell's keys
     uint32_t wsum[kFT / 64];
     uint32_t crowded;
@@ -1102,7 +1120,7 @@ __device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P
     }
     __syncthreads();
     emit_sorted<K, kFT>(f, w, dist, cnt);
-    emit_rows<K, kFT>(f, w, dist, cnt, bins, s.wsum);
+    emit_rows<K, kFT>(f, w, dist, cnt);
     emit_heads<K, kFT>(f, dist, cnt, b, s.heads);
     __syncthreads();
 #pragma unroll
@@ -1131,18 +1149,18 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
     bool left = false;
     if ((w.cnt & kOverflow) || w.cnt == 0) {
         if ((w.cnt & kOverflow) && f.keys) for (uint32_t i = threadIdx.x; i < (w.cnt & ~kOverflow); i += kFT) f.keys[w.out + i] = 0;
-        if (any) emit_rows<K, kFT>(f, w, (const K *)s.stage, 0, nullptr, s.wsum);
+        if (any) emit_rows<K, kFT>(f, w, (const K *)s.stage, 0);
         emit_heads<K, kFT>(f, (const K *)s.stage, 0, b, s.heads);
     } else left = !finish_bucket<K, P, 0>(kin, vin, vout, f, w, s, b);
-    if (any && threadIdx.x == 0) f.left[b] = left ? 1u : 0u;
+    if (any && threadIdx.x == 0) f.left[b] = (left ? kCrowded : 0u) | ((int32_t)w.cnt > 0 && many_rows(f, w) ? kUncounted : 0u);
 }
 
-// The buckets the finishing kernel left, entries that crowd in a few intervals: the second attempt, and where that fails too, a
-// bitonic sort in the LDS, the entry's number travelling with the key.  As many blocks as the chip holds.
+// What the finishing kernel left.  Rows of buckets that have many are counted.  Entries that crowd in a few intervals: the second attempt, and
+// where that fails too, a bitonic sort in the LDS, the entry's number travelling with the key.  As many blocks as the chip holds.
 template <typename K, typename P>
 __global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
 {
-    __shared__ union { finish_lds<K, P, 1> s; struct { K dist[kCap]; uint16_t idx[kCap]; head_counts heads; uint32_t wsum[kFT / 64], counts[kRowWords]; } sort; } lds;
+    __shared__ union { finish_lds<K, P, 1> s; struct { K dist[kCap]; uint16_t idx[kCap]; head_counts heads; } sort; } lds;
     const int tid = threadIdx.x, lane = tid & 63;
     if (f.flags[2]) return;
     const uint32_t total = f.count ? *f.count : f.most;
@@ -1151,8 +1169,10 @@ __global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict
         for (uint64_t todo = __ballot(mine < total && f.left[mine < total ? mine : 0] != 0); todo; todo &= todo - 1) {
             const uint32_t b = first + (uint32_t)__builtin_ctzll(todo) * gridDim.x;
             const final_bucket w = f.bucket[b];
+            const uint32_t left = f.left[b];
             __syncthreads();
-            if (finish_bucket<K, P, 1>(kin, vin, vout, f, w, lds.s, b)) continue;
+            if (left & kUncounted) count_rows<K>(f, w, kin, (uint32_t *)lds.s.stage, lds.s.wsum);
+            if (!(left & kCrowded) || finish_bucket<K, P, 1>(kin, vin, vout, f, w, lds.s, b)) continue;
             __syncthreads();
             K *dist = lds.sort.dist;
             uint16_t *idx = lds.sort.idx;
@@ -1180,7 +1200,7 @@ __global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict
             for (uint32_t i = tid; i + 1 < cnt; i += kFT) dup |= dist[i] == dist[i + 1];
             if (dup) atomicOr(&f.flags[1], 1);
             emit_sorted<K, kFT>(f, w, dist, cnt);
-            emit_rows<K, kFT>(f, w, dist, cnt, lds.sort.counts, lds.sort.wsum);
+            emit_rows<K, kFT>(f, w, dist, cnt);
             emit_heads<K, kFT>(f, dist, cnt, b, lds.sort.heads);
             for (uint32_t i = tid; i < cnt; i += kFT) vout[w.out + i] = vin[w.start + idx[i]];
         }
