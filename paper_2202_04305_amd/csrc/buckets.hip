@@ -54,7 +54,7 @@ constexpr int kHeavy = 512;                   // more entries than this in one o
 constexpr int kFirstLeast = 16384, kFirst = 131072;         // entries per bucket of the first of two partitions: n / 128 between these
 constexpr int kCells1 = 4 * kFT;              // equal intervals of a final bucket, each then cut by what it holds
 constexpr int kSpread = 24;                   // more keys than this in one interval: a second attempt at spreading them
-constexpr int kCrowd = 64;                    // more keys than this in one interval: left to finish_crowded_kernel
+constexpr int kCrowd = 192;                   // more keys than this in one interval: left to a bitonic sort (300,000 entries of long rows far apart: 118 us with 64, 87 so)
 
 typedef spmi_bucket_source source;
 
