@@ -1128,6 +1128,15 @@ static sp_status narrow_copies(sp_tensor *t, const sp_mem &mem, hipStream_t st)
     return SP_OK;
 }
 
+// Builds by buckets that had to be done again, by where a bucket overflowed: in the first partition, later.  In no header: tests read it
+// by its name to know that they reached the second build.
+std::atomic<int> g_pack_overflows[2];
+static bool buckets_overflowed(const int *flags)          // HOST copy, the stream done
+{
+    if (flags[2] || flags[3]) g_pack_overflows[flags[2] ? 0 : 1].fetch_add(1, std::memory_order_relaxed);
+    return flags[2] || flags[3];
+}
+
 // Everything after the keys exist: sort, duplicates (an error, or summed in sorted order when `sum_duplicates`), the
 // level sweep, narrow copies, values, and the tables the product kernels want.  keys / payload: nnz entries in
 // temporaries of `tmp` (the payload is the value's bits); flags: 64 zeroed bytes, flags[0] != 0 afterwards on the
@@ -1225,7 +1234,7 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
             SP_HIP(hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, st));
             SP_HIP(hipStreamSynchronize(st));
             memcpy(totals, h + 16, sizeof(totals));
-            if (again && (h[2] || h[3])) { *again = true; return SP_OK; }
+            if (again && buckets_overflowed(h)) { *again = true; return SP_OK; }
         }
     }
     int64_t P = 1;
@@ -1290,7 +1299,7 @@ static sp_status pack_core(sp_tensor *t, int64_t nnz, uint64_t *keys, const void
 
     int hf[4] = {0, 0, 0, 0};
     SP_TRY(spmi_finish_tensor(t, flags, tmp, st, sum_duplicates ? nullptr : hf));
-    if (again && (hf[2] || hf[3])) { *again = true; return SP_OK; }
+    if (again && buckets_overflowed(hf)) { *again = true; return SP_OK; }
     if (hf[0]) return SP_ERR_COORD_RANGE;
     if (hf[1]) return SP_ERR_DUPLICATE;
     return SP_OK;
@@ -1361,7 +1370,7 @@ static sp_status pack_buckets(sp_tensor *t, int64_t nnz, const int64_t *const *l
             SP_HIP(hipMemcpyAsync(h, job.flags, sizeof(h), hipMemcpyDeviceToHost, st));
             SP_HIP(hipStreamSynchronize(st));
             memcpy(totals, h + 16, sizeof(totals));
-            if (h[2] || h[3]) return SP_OK;                              // *again stays
+            if (buckets_overflowed(h)) return SP_OK;                     // *again stays
             *again = false;
             if (h[0] || h[1]) return h[0] ? SP_ERR_COORD_RANGE : SP_ERR_DUPLICATE;
             void *crd[SP_MAX_RANK], *pos[SP_MAX_RANK];
@@ -1404,7 +1413,7 @@ static sp_status pack_buckets(sp_tensor *t, int64_t nnz, const int64_t *const *l
         SP_TRY(narrow_copies(t, mem, st));
         int h[4] = {0, 0, 0, 0};
         SP_TRY(spmi_finish_tensor(t, job.flags, tmp, st, h));
-        *again = h[2] || h[3];
+        *again = buckets_overflowed(h);
         return *again ? SP_OK : h[0] ? SP_ERR_COORD_RANGE : h[1] ? SP_ERR_DUPLICATE : SP_OK;
     };
     const sp_status s = run();

@@ -1,11 +1,14 @@
 """The storage builder's sort by buckets against the CPU checker, bit for bit, at the sizes where its choices change: one bucket and
 several, one partition and two, keys of 32 bits, cut at multiples of 2^32, of 64 bits; rows that fill buckets by themselves,
-columns that crowd, a sample that misleads (the build is done again by the stable sorts), entries given twice."""
+columns that crowd, buckets that overflow (the build is done again by the stable sorts), entries given twice."""
+import ctypes
+
 import numpy as np
 import pytest
 
 import oracle
 import paper_2202_04305_amd as sp
+from paper_2202_04305_amd import binding
 from gen import prng
 from gpu_util import say, gpu_pack, assert_storage_equal
 
@@ -104,24 +107,123 @@ def sampled_positions(n):
     return np.minimum(((i.astype(np.float64) + x.astype(np.float64) * 2.0 ** -32) * (float(n) / float(S))).astype(np.int64), n - 1)
 
 
-@pytest.mark.parametrize("fmt", [CSR, DCSR])
+class overflows:
+    """The builds inside that were done again, by where a bucket overflowed: [in the first partition, later]."""
+
+    def __enter__(self):
+        self.counters = (ctypes.c_int * 2).in_dll(binding.load_library(), "g_pack_overflows")
+        self.before = list(self.counters)
+        return self
+
+    def __exit__(self, *exc):
+        self.counts = [a - b for a, b in zip(self.counters, self.before)]
+
+
+def unravel(lin, shape):
+    out = []
+    for s in reversed(shape[1:]):
+        out.append(lin % s)
+        lin = lin // s
+    return [lin] + out[::-1]
+
+
+FEW, WIDE = 1 << 23, 1 << 24           # rows: far more than entries; with as many columns 48-bit keys
+OUTPUTS = [(CSR, (1 << 16, 1 << 16)),                                   # crd and pos from the buckets
+           (DCSR, (1 << 16, 1 << 16)),                                  # distances, then all levels
+           (((0, 1, 1), (0, 1, 2)), (40, 1 << 13, 1 << 12)),            # the same under a dense level
+           (CDR, (1 << 17, 40)), (CSR, (FEW, 1 << 9)),                  # sorted keys
+           (DCSR, (WIDE, WIDE))]                                        # sorted keys of 64 bits
+
+
+@pytest.mark.parametrize("fmt,shape", OUTPUTS)
 @pytest.mark.parametrize("n", [200000, TWO + 100000])
-def test_a_sample_that_misleads(fmt, n):
-    """The sampled entries are spread over the matrix, all others lie in one corner: a bucket gets more than it has room for."""
-    m = 1 << 16
+def test_a_sample_that_misleads(fmt, shape, n):
+    """The sampled entries are spread over the upper half of the key range, all others lie at its beginning: the first bucket gets more
+    than it has room for, and the stable sorts build the tensor."""
+    total = int(np.prod([int(s) for s in shape], dtype=object))
     at = np.unique(sampled_positions(n))
-    corner = prng.permutation(SEED, 4, 4 * n)[: n - at.size]
-    side = int(np.ceil(np.sqrt(4 * n)))
-    rows, cols = np.empty(n, np.int64), np.empty(n, np.int64)
+    lin = np.empty(n, np.int64)
     rest = np.ones(n, bool)
     rest[at] = False
-    rows[rest], cols[rest] = corner // side, corner % side
-    spread = np.unique(prng.below(SEED, 5, 2 * at.size, m * m))
-    spread = spread[spread // m > side]
-    spread = spread[prng.permutation(SEED, 6, spread.size)][: at.size]
-    assert spread.size == at.size
-    rows[at], cols[at] = spread // m, spread % m
-    check(fmt, (m, m), [rows, cols])
+    lin[rest] = prng.permutation(SEED, 4, n + n // 4)[: n - at.size]
+    spread = np.unique(prng.below(SEED, 5, 2 * at.size, total // 2)) + total // 2
+    lin[at] = spread[prng.permutation(SEED, 6, spread.size)][: at.size]
+    for dtype in (np.float64, np.float32):
+        with overflows() as o:
+            check(fmt, shape, unravel(lin, shape), dtype)
+        assert o.counts == [1, 0]
+
+
+@pytest.mark.parametrize("fmt", [CSC, ((1, 1), (1, 0))])
+@pytest.mark.parametrize("n", [200000, TWO + 100000])
+def test_a_sample_that_misleads_a_conversion(fmt, n):
+    """One entry per row, so that the source keeps their order; the sampled ones in the last columns, all others in the first sixteen."""
+    N = 1 << 16
+    at = np.unique(sampled_positions(n))
+    cols = prng.below(SEED, 7, n, 16)
+    cols[at] = N // 2 + prng.below(SEED, 8, at.size, N // 2)
+    coords, v = [np.arange(n, dtype=np.int64), cols], prng.uniform_pm1(SEED, 9, n, np.float32)
+    A = gpu_pack(*CSR, (n, N), coords, v)
+    with overflows() as o:
+        B = sp.sp_convert(A, sp.sp_encode(*fmt, 32, 32))
+    say("case", fmt, n, "overflows", o.counts)
+    assert o.counts == [1, 0]
+    assert_storage_equal(B, oracle.pack(*fmt, (n, N), coords, v, 32, 32))
+
+
+@pytest.mark.parametrize("fmt,shape", [(CSR, (1 << 16, 1 << 16)), (DCSR, (1 << 16, 1 << 16)), (CSR, (FEW, 1 << 9))])
+def test_a_bucket_with_more_entries_than_a_block_sorts(fmt, shape):
+    """One partition: a bucket has 4144 entries, its room is 4192, the finishing kernel takes 4096."""
+    n = 200000
+    at = sampled_positions(n)
+    S, Q = at.size, -(-n // 2048)
+    assert np.unique(at).size == S
+    step = (1 << 32) // S
+    i0, i1 = 40 * S // Q, 41 * S // Q                        # the samples of the 40th bucket; between two samples it has `more` others
+    more = np.zeros(S, np.int64)
+    more[i0:i1] = (4144 - (i1 - i0)) // (i1 - i0)
+    more[i0: i0 + (4144 - (i1 - i0)) % (i1 - i0)] += 1
+    elsewhere = np.flatnonzero((np.arange(S) < i0) | (np.arange(S) >= i1))
+    left = n - S - int(more.sum())
+    more[elsewhere] = left // elsewhere.size
+    more[elsewhere[: left % elsewhere.size]] += 1
+    i = np.repeat(np.arange(S), more)
+    others = i * step + 8 + 997 * (np.arange(i.size) - np.repeat(np.cumsum(more) - more, more))
+    lin = np.empty(n, np.int64)
+    rest = np.ones(n, bool)
+    rest[at] = False
+    lin[at] = np.arange(S) * step + 7
+    lin[rest] = others[prng.permutation(SEED, 10, others.size)]
+    assert np.unique(lin).size == n and lin.max() < 1 << 32
+    with overflows() as o:
+        check(fmt, shape, unravel(lin, shape))
+    assert o.counts == [0, 1]
+
+
+def test_a_part_with_more_entries_than_its_room():
+    """Two partitions, 48-bit keys: the last bucket spans a third of the key range or more, so that its sample, cut to 32 bits, cannot tell
+    8000 neighbouring keys apart."""
+    body = np.unique(prng.below(SEED, 11, 1100000, 1 << 44))
+    sparse = (1 << 44) + np.unique(prng.below(SEED, 12, 9000, int(0.7 * 2 ** 48) - (1 << 44)))
+    crowd = 3 * (1 << 46) + np.arange(8000)
+    behind = crowd[-1] + 1 + np.unique(prng.below(SEED, 13, 1000, (1 << 46) - 16000))
+    lin = np.concatenate([body, sparse, crowd, behind])
+    lin = lin[prng.permutation(SEED, 14, lin.size)]
+    with overflows() as o:
+        check(DCSR, (WIDE, WIDE), unravel(lin, (WIDE, WIDE)))
+    assert o.counts == [0, 1]
+
+
+@pytest.mark.parametrize("fmt,shape", OUTPUTS)
+def test_an_entry_given_six_thousand_times(fmt, shape):
+    """They fill a part of the second partition by themselves; the stable sorts report them."""
+    coords = distinct(shape, TWO, SEED + 15)
+    coords = [np.concatenate([c, np.full(6000, c[17])]) for c in coords]
+    order = prng.permutation(SEED, 16, coords[0].size)
+    with overflows() as o, pytest.raises(sp.SpError) as e:
+        gpu_pack(*fmt, shape, [c[order] for c in coords], np.ones(order.size, np.float32))
+    say("case", fmt, shape, "overflows", o.counts)
+    assert e.value.code == 7 and o.counts == [0, 1]
 
 
 @pytest.mark.parametrize("fmt", [CSR, DCSR])
