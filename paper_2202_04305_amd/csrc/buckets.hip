@@ -54,7 +54,7 @@ constexpr int kHeavy = 512;                   // more entries than this in one o
 constexpr int kFirstLeast = 16384, kFirst = 131072;         // entries per bucket of the first of two partitions: n / 128 between these
 constexpr int kCells1 = 4 * kFT;              // equal intervals of a final bucket, each then cut by what it holds
 constexpr int kSpread = 24;                   // more keys than this in one interval: a second attempt at spreading them
-constexpr int kCrowd = 192;                   // more keys than this in one interval: left to a bitonic sort (300,000 entries of long rows far apart: 118 us with 64, 87 so)
+constexpr int kCrowd = 32;                    // more keys than this in one interval then: left to a merge sort (R-MAT, 48-bit keys, 2.5 M entries: 414 us a call, 435 with 96)
 
 typedef spmi_bucket_source source;
 
@@ -704,7 +704,8 @@ struct final_bucket {
     int shift;                // > 0: distances to the left, < 0: to the right, so that the range has 32 bits
 };
 constexpr uint32_t kOverflow = 0x80000000u;
-constexpr uint32_t kCrowded = 1u, kUncounted = 2u;       // left: a bucket with a crowded interval; the rows of one that has many
+// left: a bucket with a crowded interval, whose keys crowd inside it as well; the rows of one that has many
+constexpr uint32_t kCrowded = 1u, kUneven = 2u, kUncounted = 4u;
 
 struct final_args {
     const final_bucket *bucket;
@@ -968,17 +969,44 @@ struct finish_lds {
     head_counts heads;
 };
 
+// Do the keys of an interval that holds len of them crowd inside it as well?  64 are counted by eighths from the least to the
+// greatest: if one eighth has more than a third, cutting the interval again would leave a part with most of its keys.  The same answer in
+// every wave.  (Not asked below kAsked keys, where the second attempt costs least.)
+constexpr uint32_t kAsked = 64;
+template <typename K>
+__device__ __forceinline__ bool crowds_inside(const K *keys, uint32_t len)
+{
+    typedef lds_key<K> key;
+    const key k = (key)keys[(threadIdx.x & 63u) * len >> 6];         // len <= kCap
+    key least = k, most = k;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const key a = __shfl_xor(least, d, 64), c = __shfl_xor(most, d, 64);
+        least = a < least ? a : least;
+        most = c > most ? c : most;
+    }
+    const uint32_t p = (uint32_t)((float)(k - least) * (8.0f / ((float)(most - least) + 1.0f)));
+    int largest = 0;
+#pragma unroll
+    for (uint32_t e = 0; e < 8; ++e) {
+        const int c = __popcll(__ballot((p < 7 ? p : 7) == e));
+        largest = c > largest ? c : largest;
+    }
+    return largest > 64 / 3 + 2;
+}
+
 // A bucket sorted by value.  Its range is cut into kCells1 equal intervals, each of those into twice as many as it holds
 // entries (rows differ in length, so keys are not spread evenly over a bucket), in the second attempt, for bands and blocks, only from
 // its smallest key to its largest; an entry takes a number in its interval with one returning LDS add, the counts are scanned,
 // the keys are dropped into their intervals, and an entry's place is the interval's start plus the number of smaller keys
 // there.  Counts are 16 bits, two to a word: intervals x and x + words share one, so that one addition per word scans both
 // halves.  (Keys that occur twice may take one place and leave a place as it was: the build ends with an error then.)
-// false, for the whole block and with nothing written: an interval is too crowded.
+// 0: done.  kCrowded, for the whole block and with nothing written: an interval is too crowded; with kUneven where the second attempt is
+// not going to help.
 // What bounds it: vector instructions, so a thread has up to sixteen entries and what all entries of a bucket share is worked out
 // before (final_buckets_kernel).
 template <typename K, typename P, int ATTEMPT>
-__device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, const final_args &f, const final_bucket &w,
+__device__ __forceinline__ uint32_t finish_bucket(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, const final_args &f, const final_bucket &w,
                                               finish_lds<K, P, ATTEMPT> &s, uint32_t b)
 {
     constexpr int W = kFT / 64;
@@ -1090,12 +1118,16 @@ __device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P
             slot[r] += s0;
             dist[slot[r]] = k[r];
             at[r] = s0 | (len << 16);
-            longest = len > longest ? len : longest;
+            longest = at[r] > longest ? at[r] : longest;
         } else at[r] = 0;
     }
-    if (longest > (uint32_t)(ATTEMPT ? kCrowd : kSpread)) s.crowded = 1;
+    if ((longest >> 16) > (uint32_t)(ATTEMPT ? kCrowd : kSpread)) s.crowded = longest;      // one of them
     __syncthreads();
-    if (s.crowded) return false;
+    if (s.crowded) {
+        const uint32_t len = s.crowded >> 16;
+        return kCrowded | (ATTEMPT == 0 && len >= kAsked && crowds_inside<K>(dist + (s.crowded & 0xffffu), len) ? kUneven : 0u);
+    }
+    longest >>= 16;
     // all rounds side by side, one other key of every interval per step; smaller ones are counted in the upper half of slot
     bool dup = false;
     for (uint32_t j = 1; j < longest; ++j) {
@@ -1128,7 +1160,7 @@ __device__ __forceinline__ bool finish_bucket(const K *__restrict__ kin, const P
         if (r < rounds && (uint32_t)(r * kFT + tid) < cnt) sval[at[r]] = v[r];
     __syncthreads();
     for (uint32_t i = tid; i < cnt; i += kFT) vout[w.out + i] = sval[i];
-    return true;
+    return 0;
 }
 
 template <typename K, typename P>
@@ -1146,19 +1178,87 @@ __global__ __launch_bounds__(kFT, 4) void finish_kernel(const K *__restrict__ ki
     final_bucket w;
     w.cnt = 0;
     if (any) w = f.bucket[b];
-    bool left = false;
+    uint32_t left = 0;
     if ((w.cnt & kOverflow) || w.cnt == 0) {
         if ((w.cnt & kOverflow) && f.keys) for (uint32_t i = threadIdx.x; i < (w.cnt & ~kOverflow); i += kFT) f.keys[w.out + i] = 0;
         if (any) emit_rows<K, kFT>(f, w, (const K *)s.stage, 0);
         emit_heads<K, kFT>(f, (const K *)s.stage, 0, b, s.heads);
-    } else left = !finish_bucket<K, P, 0>(kin, vin, vout, f, w, s, b);
-    if (any && threadIdx.x == 0) f.left[b] = (left ? kCrowded : 0u) | ((int32_t)w.cnt > 0 && many_rows(f, w) ? kUncounted : 0u);
+    } else left = finish_bucket<K, P, 0>(kin, vin, vout, f, w, s, b);
+    if (any && threadIdx.x == 0) f.left[b] = left | ((int32_t)w.cnt > 0 && many_rows(f, w) ? kUncounted : 0u);
 }
 
-// What the finishing kernel left.  Rows of buckets that have many are counted.  Entries that crowd in a few intervals: the second attempt, and
-// where that fails too, a bitonic sort in the LDS, the entry's number travelling with the key.  As many blocks as the chip holds.
+// The distances of up to kCap keys from lo, sorted in the LDS, and every one's number among them: a thread sorts up to 17 of them in
+// registers (an odd number of them side by side, so that threads meet different banks), then runs are merged two by two, each thread
+// finding by bisection where its part of the merged run begins.  In place of a bitonic sort through the LDS, whose 78 steps for 4096
+// keys move every key each time.  Block-wide, with barriers.
+template <typename K>
+__device__ __forceinline__ void merge_sort(const K *__restrict__ keys, K lo, uint32_t cnt, K *dist, uint16_t *idx)
+{
+    constexpr int E = kFE | 1;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t per = ((cnt + kFT - 1) / kFT) | 1u, x0 = tid * per;        // per <= E
+    for (uint32_t i = tid; i < cnt; i += kFT) dist[i] = (K)(keys[i] - lo);
+    __syncthreads();
+    K k[E];
+    uint32_t id[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const bool any = (uint32_t)e < per && x0 + e < cnt;
+        k[e] = any ? dist[x0 + e] : (K)~(K)0;
+        id[e] = any ? x0 + e : 0xffffu;                      // what fills up stays behind a largest key
+    }
+#pragma unroll
+    for (int step = 0; step < E; ++step) {
+#pragma unroll
+        for (int e = step & 1; e + 1 < E; e += 2) {
+            const K a = k[e], c = k[e + 1];
+            const uint32_t ia = id[e], ic = id[e + 1];
+            const bool swap = c < a || (c == a && ic < ia);
+            k[e] = swap ? c : a; k[e + 1] = swap ? a : c;
+            id[e] = swap ? ic : ia; id[e + 1] = swap ? ia : ic;
+        }
+    }
+    for (uint32_t r = 0;; ++r) {
+        const uint32_t w = per << r;                         // sorted runs of w
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if ((uint32_t)e < per && x0 + e < cnt) { dist[x0 + e] = k[e]; idx[x0 + e] = (uint16_t)id[e]; }
+        __syncthreads();
+        if (w >= cnt) return;
+        if (x0 < cnt) {
+            const uint32_t base = ((tid >> (r + 1)) << (r + 1)) * per, left = cnt - base;
+            const uint32_t na = left < w ? left : w, nb = left - na < w ? left - na : w, at = x0 - base;     // at < na + nb
+            const K *A = dist + base, *B = nb ? A + na : A;
+            uint32_t a = at > nb ? at - nb : 0u, end = at < na ? at : na;
+            while (a < end) {
+                const uint32_t mid = (a + end) / 2;
+                if (A[mid] <= B[at - 1 - mid]) a = mid + 1;
+                else end = mid;
+            }
+            uint32_t b = at - a;
+            K ka = A[a < na ? a : 0], kb = B[b < nb ? b : 0];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                if ((uint32_t)e < per && x0 + e < cnt) {
+                    const bool first = a < na && (b >= nb || ka <= kb);
+                    k[e] = first ? ka : kb;
+                    id[e] = idx[base + (first ? a : na + b)];
+                    if (first) { ++a; ka = A[a < na ? a : 0]; }
+                    else { ++b; kb = B[b < nb ? b : 0]; }
+                }
+            }
+        }
+    }
+}
+
+// What the finishing kernel left.  Rows of buckets that have many are counted.  Entries that crowd in a few intervals: the second attempt,
+// or, where that fails too or is not going to help, a merge sort in the LDS, the entry's number travelling with the key.  As many
+// blocks as the chip holds: the registers are bounded so that the LDS decides how many (one block per CU without: bands of 64, 8 M f32
+// entries, 123 us instead of 110).  7.0 M f32 entries in rows of 350 whose columns are spread evenly over their logarithm, DCSR: this
+// kernel 278 us, 811 with bitonic sorts of what the second attempt leaves, 2331 with a second attempt that stands for 192 keys in an interval.
 template <typename K, typename P>
-__global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
+__global__ __launch_bounds__(kFT, sizeof(K) + sizeof(P) == 8 ? 3 : 2) void finish_crowded_kernel(const K *__restrict__ kin, const P *__restrict__ vin, P *__restrict__ vout, final_args f)
 {
     __shared__ union { finish_lds<K, P, 1> s; struct { K dist[kCap]; uint16_t idx[kCap]; head_counts heads; } sort; } lds;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1172,30 +1272,13 @@ __global__ __launch_bounds__(kFT) void finish_crowded_kernel(const K *__restrict
             const uint32_t left = f.left[b];
             __syncthreads();
             if (left & kUncounted) count_rows<K>(f, w, kin, (uint32_t *)lds.s.stage, lds.s.wsum);
-            if (!(left & kCrowded) || finish_bucket<K, P, 1>(kin, vin, vout, f, w, lds.s, b)) continue;
+            if (!(left & kCrowded)) continue;
+            if (!(left & kUneven) && !finish_bucket<K, P, 1>(kin, vin, vout, f, w, lds.s, b)) continue;
             __syncthreads();
             K *dist = lds.sort.dist;
             uint16_t *idx = lds.sort.idx;
             const uint32_t cnt = w.cnt;
-            uint32_t N = 2;
-            while (N < cnt) N *= 2;
-            for (uint32_t i = tid; i < N; i += kFT) {
-                dist[i] = i < cnt ? (K)(kin[w.start + i] - (K)w.lo) : (K)~(K)0;
-                idx[i] = (uint16_t)i;
-            }
-            __syncthreads();
-            for (uint32_t size = 2; size <= N; size *= 2) {
-                for (uint32_t half = size / 2; half > 0; half /= 2) {
-                    for (uint32_t p = tid; p < N / 2; p += kFT) {
-                        const uint32_t x = 2 * p - (p & (half - 1)), y = x + half;
-                        const K a = dist[x], c = dist[y];
-                        const uint16_t ia = idx[x], ic = idx[y];
-                        const bool greater = a > c || (a == c && ia > ic);             // padding (largest key, largest numbers) stays behind
-                        if (greater == ((x & size) == 0)) { dist[x] = c; dist[y] = a; idx[x] = ic; idx[y] = ia; }
-                    }
-                    __syncthreads();
-                }
-            }
+            merge_sort<K>(kin + w.start, (K)w.lo, cnt, dist, idx);
             bool dup = false;
             for (uint32_t i = tid; i + 1 < cnt; i += kFT) dup |= dist[i] == dist[i + 1];
             if (dup) atomicOr(&f.flags[1], 1);

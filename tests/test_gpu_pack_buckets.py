@@ -90,6 +90,18 @@ def test_rows_that_fill_buckets_and_columns_that_crowd(n_rest):
     check(CSC, (n, m), coords[::-1])
 
 
+@pytest.mark.parametrize("columns", [1 << 20, 1 << 31, 1 << 44])
+def test_keys_that_crowd_at_every_scale(columns):
+    """Columns spread evenly over their logarithm: cutting an interval again leaves one part with most of its keys, and the merge sort has
+    them.  Runs of one key, of an odd and an even number, and of 17; up to 4096 entries in one bucket, more in several."""
+    for n in (150, 255, 256, 257, 300, 511, 513, 1000, 2047, 2304, 3839, 3841, 4095, 4096, 9000, 70000, TWO + 9):
+        c = np.exp2(prng.uniform_pm1(SEED + n, 17, 3 * n, np.float64) * 0.5 * np.log2(columns) + 0.5 * np.log2(columns)).astype(np.int64) % columns
+        m = 1 if n < 300 else min(n // 300 + 1, 1 << (48 - int(columns).bit_length()))
+        lin = np.unique((prng.below(SEED + n, 18, 3 * n, m) ** 2 // m) * columns + c)
+        n = min(n, lin.size)
+        check(DCSR if n % 2 else CSR, (m, columns), shuffled(lin, n, (m, columns), SEED), np.float64 if n % 3 else np.float32, (32, 32) if columns < 1 << 31 else (32, 64))
+
+
 def sampled_positions(n):
     """Where the builder looks: one entry per stretch of n / S, at a scrambled place in it."""
     if n > TWO:
