@@ -69,7 +69,7 @@ def test_convert_rank_three(lt, order):
 @pytest.mark.parametrize("full", ["first", "last"])
 def test_a_full_column_at_the_same_place_of_every_row(per_row, full):
     """Rows of 64 or 128 entries, one column in all of them: whatever places of a row the sort's sample looks at, the columns come out
-    in order (the sample decides between the two sorts; a column of 20,000 entries is no chunk for the finishing kernels)."""
+    in order (a column of 20,000 entries fits no block of the sort by buckets, nor of the most-significant-digit-first one)."""
     m, n = 20000, 1 << 16
     r = np.repeat(np.arange(m, dtype=np.int64), per_row)
     c = np.tile(np.arange(per_row, dtype=np.int64), m) * (n // per_row - 3) + r % 700

@@ -1,5 +1,6 @@
-"""The level sweep of the storage builder around the edges of its tiles of 1024 sorted entries, for every mix of level types of
-rank 1 to 4, against the CPU checker, bit for bit; level sizes that are and are not powers of two; keys above and below 2^52
+"""The levels that the storage builder writes, around the edges of the level sweep's tiles of 1024 sorted entries, for every mix of
+level types of rank 1 to 4 (by the sweep, after a sort that leaves keys, and by the builder's own choice, which writes the levels of
+many formats from its buckets), against the CPU checker, bit for bit; level sizes that are and are not powers of two; keys above and below 2^52
 (where the division of a key by a stride changes its method)."""
 import itertools
 
@@ -7,11 +8,19 @@ import numpy as np
 import pytest
 
 import oracle
+import paper_2202_04305_amd as sp
 from gen import prng
 from gpu_util import say, gpu_pack, assert_storage_equal
 
 pytestmark = pytest.mark.gpu
 SEED = 20220417
+
+
+@pytest.fixture(params=[0, 1], ids=["sort chosen", "level sweep"])
+def sort_mode(request):
+    sp.sp_pack_sort_mode(request.param)
+    yield request.param
+    sp.sp_pack_sort_mode(0)
 
 
 def entries(shape, nnz, stream):
@@ -29,7 +38,7 @@ def entries(shape, nnz, stream):
 
 @pytest.mark.parametrize("nnz", [1, 63, 1023, 1024, 1025, 4097])
 @pytest.mark.parametrize("rank", [1, 2, 3, 4])
-def test_every_mix_of_level_types(nnz, rank):
+def test_every_mix_of_level_types(nnz, rank, sort_mode):
     sides = [(9000,), (64, 150), (16, 25, 22), (8, 11, 10, 9)][rank - 1]
     coords = entries(sides, nnz, 10 * rank)
     for i, lt in enumerate(itertools.product((0, 1), repeat=rank)):

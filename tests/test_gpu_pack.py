@@ -172,9 +172,9 @@ def test_convert_between_encodings():
     assert_storage_equal(Bt, oracle.pack((1, 1), (1, 0), w.shape, [w.rows, w.cols], w.vals, 32, 32))
 
 
-@pytest.fixture(params=[0, 2], ids=["sort chosen", "most significant digit first"])
+@pytest.fixture(params=[0, 1, 2], ids=["sort chosen", "least significant digit first", "most significant digit first"])
 def sort_mode(request):
-    """The storage builder's sort: its own choice (least significant digit first at these sizes), and the other one forced."""
+    """The storage builder's sort: its own choice (by buckets), and each of the stable ones forced."""
     sp.sp_pack_sort_mode(request.param)
     yield request.param
     sp.sp_pack_sort_mode(0)

@@ -1,13 +1,17 @@
-"""The storage builder's two sorts against the CPU checker, bit for bit: the most-significant-digit-first sort forced on
+"""The storage builder's stable sorts against the CPU checker, bit for bit: the most-significant-digit-first sort forced on
 small inputs that reach each of its paths (several LDS chunks, a chunk that does not fit the LDS, keys narrower than its two
-passes), and the builder's own choice on inputs of a million entries and more, even and skewed."""
+passes), and the builder's own choice on inputs of a million entries and more, even and skewed: between the two where the sort by
+buckets is out of the question (keys above 48 bits, sums of equal keys), that one otherwise."""
+from collections import Counter
+
 import numpy as np
 import pytest
 
 import oracle
 import paper_2202_04305_amd as sp
+from paper_2202_04305_amd import binding
 from gen import workloads as W, prng
-from gpu_util import say, gpu_pack, assert_storage_equal
+from gpu_util import say, dev, gpu_pack, assert_storage_equal, DEV
 
 pytestmark = pytest.mark.gpu
 SEED = 20220204
@@ -106,8 +110,8 @@ def test_forced_sums_of_duplicates_keep_their_order(msd_first):
 ])
 @pytest.mark.parametrize("mode", [0, 2])
 def test_a_million_entries_and_more(maker, name, mode):
-    """mode 0: the builder's own choice (even input: most significant digit first; skewed: the other sort); mode 2: most
-    significant digit first also on the skewed input, whose heavy columns then take the slow path."""
+    """mode 0: the builder's own choice (by buckets); mode 2: most significant digit first, also on the skewed input, whose heavy
+    columns then take the slow path."""
     w = maker()
     say("case", name, "mode", mode, w.stats)
     ref = oracle.pack(w.level_types, w.dim_ordering, w.shape, [w.rows, w.cols], w.vals, 32, 32)
@@ -117,3 +121,84 @@ def test_a_million_entries_and_more(maker, name, mode):
     finally:
         sp.sp_pack_sort_mode(0)
     assert_storage_equal(A, ref)
+
+
+class CountingAllocator(binding._TorchAllocator):
+    def __init__(self):
+        super().__init__(DEV)
+        self.sizes = Counter()
+
+    def _alloc(self, nbytes, ctx):
+        self.sizes[nbytes] += 1
+        return super()._alloc(nbytes, ctx)
+
+
+def in_mode(mode, build, alloc):
+    """(result, what it took from the allocator)"""
+    alloc.sizes.clear()
+    sp.sp_pack_sort_mode(mode)
+    try:
+        return build(), Counter(alloc.sizes)
+    finally:
+        sp.sp_pack_sort_mode(0)
+
+
+def the_choice(build, alloc):
+    """The result under the builder's own choice, and the sort it took: the blocks it asks for are one sort's and not the other's,
+    besides the sampled histogram and the counts that the choice looks at (at most two blocks)."""
+    chosen, got = in_mode(0, build, alloc)
+    (_, least), (_, most) = in_mode(1, build, alloc), in_mode(2, build, alloc)
+    is_least = not (least - got) and sum((got - least).values()) <= 2
+    is_most = not (most - got) and sum((got - most).values()) <= 2
+    assert is_least != is_most
+    return chosen, "least" if is_least else "most"
+
+
+WIDE = 1 << 25                         # two of them: 50-bit keys
+
+
+def wide_entries(skewed, nnz=1300000):
+    """Entries of 50-bit keys: even, or two thirds of them in one row (and, for the conversion, in one column)."""
+    rows, cols = prng.below(SEED, 21, nnz, WIDE), prng.below(SEED, 22, nnz, WIDE)
+    if skewed:
+        rows[::3], cols[1::3] = 77, 99
+    lin = np.unique(rows * WIDE + cols)
+    lin = lin[prng.permutation(SEED, 23, lin.size)]
+    return lin // WIDE, lin % WIDE
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("skewed,choice", [(False, "most"), (True, "least")])
+def test_the_choice_between_the_stable_sorts(skewed, choice, dtype):
+    dcsr, dcsc = ((1, 1), (0, 1)), ((1, 1), (1, 0))
+    r, c = wide_entries(skewed)
+    v = prng.uniform_pm1(SEED, 24, r.size, dtype)
+    alloc = CountingAllocator()
+    coords, vals = [dev(r), dev(c)], dev(v)
+    A, took = the_choice(lambda: sp.sp_pack(sp.sp_encode(*dcsr, 32, 32), (WIDE, WIDE), coords, vals, allocator=alloc), alloc)
+    say("case pack", "skewed" if skewed else "even", np.dtype(dtype).name, "entries", r.size, took)
+    assert took == choice
+    assert_storage_equal(A, oracle.pack(*dcsr, (WIDE, WIDE), [r, c], v, 32, 32))
+    B, took = the_choice(lambda: sp.sp_convert(A, sp.sp_encode(*dcsc, 32, 32)), alloc)
+    say("case convert", took)
+    assert took == choice
+    assert_storage_equal(B, oracle.pack(*dcsc, (WIDE, WIDE), [r, c], v, 32, 32))
+
+
+@pytest.mark.parametrize("skewed,choice", [(False, "most"), (True, "least")])
+def test_the_choice_for_sums(skewed, choice):
+    """sp_add of two matrices that store a third of their positions both: 1.3 M entries and more with equal keys among them."""
+    dcsr = ((1, 1), (0, 1))
+    r, c = wide_entries(skewed)
+    third = r.size // 3
+    ca, cb = [x[: 2 * third] for x in (r, c)], [x[third:] for x in (r, c)]
+    va, vb = prng.uniform_pm1(SEED, 25, ca[0].size, np.float32), prng.uniform_pm1(SEED, 26, cb[0].size, np.float32)
+    alloc = CountingAllocator()
+    enc = sp.sp_encode(*dcsr, 32, 32)
+    A = sp.sp_pack(enc, (WIDE, WIDE), [dev(x) for x in ca], dev(va), allocator=alloc)
+    B = sp.sp_pack(enc, (WIDE, WIDE), [dev(x) for x in cb], dev(vb), allocator=alloc)
+    C, took = the_choice(lambda: sp.sp_add(A, B, enc), alloc)
+    say("case add", "skewed" if skewed else "even", took)
+    assert took == choice
+    coords, vals, _ = oracle.add_coo((WIDE, WIDE), ca, va, cb, vb)
+    assert_storage_equal(C, oracle.pack(*dcsr, (WIDE, WIDE), coords, vals, 32, 32))
