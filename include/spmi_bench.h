@@ -33,7 +33,8 @@ sp_status sp_stream_read(const void *src /* DEVICE */, size_t bytes, void *sink 
  * buckets where entries are distinct and keys have at most 48 bits; else most significant digit first with an LDS
  * finishing pass for a million entries or more whose top key bits are spread evenly enough, least significant digit first
  * otherwise), 1 = always least significant digit first, 2 = always most significant
- * digit first (any size below 2^31 entries: how the tests reach its rare paths with small inputs).  All
+ * digit first (any size below 2^31 entries: how the tests reach its rare paths with small inputs).  A conversion
+ * that keeps every level's dimension sorts nothing, whatever the mode.  All
  * give the same storage bit for bit.  Returns SP_ERR_UNSUPPORTED for another value. */
 sp_status sp_pack_sort_mode(int mode);
 

@@ -20,7 +20,7 @@
 // Should a bucket get more entries than its room (a sample that misleads, or many equal keys), nothing is written out of
 // bounds, the build is marked and the caller builds again with the stable sorts.
 //
-// What bounds it: memory, and vector instructions in the finishing kernel.  Per entry of a CSR matrix in f64: 24 bytes read and 12
+// What bounds it: memory; in the finishing kernel vector instructions (issued in 53 % of the busy cycles; bank conflicts of the LDS 17 %).  Per entry of a CSR matrix in f64: 24 bytes read and 12
 // written, 4 read, 12 and 12, 12 and 12.  16.9 M entries of a 1M x 1M lognormal matrix, kernel by kernel: sample and its ranks
 // 26 us, first partition 155 to 165 (3.8 TB/s), cutting the buckets 45, second partition 102 (4.0), finish 144 (2.8); the whole call
 // 841 us with the stable sorts, 575 now.  76.9 M entries of rank 3, all levels compressed: 960, 132, 415 (4.4), 535 and
@@ -73,6 +73,7 @@ __device__ __forceinline__ uint64_t key_of(const source &s, int64_t e, bool &bad
     return b ? 0 : key;
 }
 
+// A published 32-bit mixer: lowbias32, found by Chris Wellons' hash-prospector.
 __device__ __forceinline__ uint32_t scramble(uint32_t x)
 {
     x ^= x >> 16; x *= 0x7feb352du;
@@ -538,7 +539,8 @@ __global__ __launch_bounds__(1024) void bucket_sizes_kernel(level1 t, int two, u
 
 // Block = bucket: splitters of its parts.  Its keys are counted by kPartCells equal intervals of its range; parts end where the count
 // passes their share.  Where an interval holds too much for that, a sorted sample of the bucket gives the splitters instead.
-// Both read little: 4 bytes per entry, 20 us for 16.9 M.
+// 4 bytes read per entry: 44 us for 16.9 M (1.5 TB/s).  A block per bucket is few blocks, in which loads, vector instructions (half of the busy
+// cycles) and LDS atomics take turns.
 template <typename K>
 __global__ __launch_bounds__(1024) void parts_kernel(level1 t, level2 u, const K *__restrict__ keys, uint64_t total, const int *__restrict__ flags)
 {
@@ -1598,7 +1600,8 @@ bool spmi_bucket_plan_for(int64_t n, uint64_t total, int key_bits, int64_t rows,
         p->fbits = std::min(p->fbits, bits);
     }
     p->F = (uint32_t)((total - 1) >> p->fbits);
-    // many equal steps cut the range finely already: fewer splitters besides them (76.9 M entries of rank 3, 745 steps: 2698 -> 2665 us)
+    // many equal steps cut the range finely already: fewer splitters besides them (76.9 M entries of rank 3, 745 steps: 2698 -> 2665 us;
+    // 70 M of 42-bit keys, evenly 2101 -> 2062, in five steps 2183 -> 2117, 90 % in four 2127 -> 2106, R-MAT 2483 -> 2542)
     if (p->two && p->F >= 512) Q = std::max<uint64_t>(std::min<uint64_t>(Q, 256), (uint64_t)ceil_div(n, 2 * kFirst));
     if (Q + p->F > (uint64_t)kMaxBuckets) return false;
     p->Q = (uint32_t)Q;

@@ -1084,7 +1084,7 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st, bool unprepared)
             //   panels:   5.4 per million entries, 6.9 per million (row, panel) pairs
             //   binned:   x and 18.5 bytes per entry (buckets padded to eights), then 10 bytes per entry or the heaviest
             //             row block, which is at least the mean one
-            // Measured (by the formula): f64, 3 M entries in 200,000 rows of 2 M columns 51 us (54) streamed, 22 (25) binned; 16 M in 1 M rows
+            // profiles/spmv_choice_measurements.txt has 30 matrices.  Measured (by the formula): f64, 3 M entries in 200,000 rows of 2 M columns 51 us (54) streamed, 22 (25) binned; 16 M in 1 M rows
             // of 4 M columns 278 (296), 90 (104) and 205 (200) by panels; the same sorted by length, rows of up to 300, f32: 226 (236), 140 (152)
             // and 112 (200).
             const double M = 1e-6 * (double)nnz, v = (double)sizeof(VT) / 8.0, clear = rv.dcsr ? 1.6e-7 * (double)A->shape[0] * sizeof(VT) : 0.0;

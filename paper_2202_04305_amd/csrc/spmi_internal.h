@@ -40,7 +40,7 @@ struct sp_segments {
 // of 2^pshift columns, row block of 2^rshift stored rows), panel-major, rows ascending inside a bucket.  Every entry keeps
 // its value, its column inside the panel and its row inside the row block in 16 bits each.  The product runs in two
 // streaming passes: one multiplies a panel's entries by the panel's slice of x held in LDS and writes the products in
-// place (`prod`), the other adds a row block's products up in an LDS slice of y.  No gather ever leaves the LDS.
+// place (`prod`), the other adds a row block's products up in slices of y in the LDS.  No gather ever leaves the LDS.
 struct sp_bins {
     // Entries regrouped into buckets (column panel, row block), every bucket padded to a multiple of 8 entries (np in all).
     // Panel-major arrays (buckets of a panel side by side, rows ascending inside a bucket):
@@ -516,7 +516,7 @@ sp_status spmi_build_segments(const sp_tensor *A, int64_t row_bytes, int64_t sli
 #define SPMI_BIN_RSHIFT 11
 #endif
 constexpr int kSpmiBinPanelShift = SPMI_BIN_PSHIFT;          // columns per panel of the binned copy: 8192 (a 64 KB slice of an f64 x)
-constexpr int kSpmiBinRowShift = SPMI_BIN_RSHIFT;            // most rows per row block: 2048 (a 16 KB slice of y in f64)
+constexpr int kSpmiBinRowShift = SPMI_BIN_RSHIFT;            // most rows per row block: 2048 (16 KB per slice of y: four slices for f64, one of f64 sums for f32)
 // Rows per row block (a power of two) of the binned copy of nnz entries in m stored rows: 2048, or fewer where these would leave
 // CUs without a row block in the second pass, as long as a bucket keeps 24 entries (padding to eights stays near a seventh).
 // 2.7 M entries in 83,886 rows, x of 4 MB: 37 us a product in 41 row blocks of 2048, 29 in 164 of 512.

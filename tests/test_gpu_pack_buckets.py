@@ -103,7 +103,7 @@ def test_keys_that_crowd_at_every_scale(columns):
 
 
 def sampled_positions(n):
-    """Where the builder looks: one entry per stretch of n / S, at a scrambled place in it."""
+    """Where the builder looks: one entry per stretch of n / S, at a scrambled place in it (the mixer is Chris Wellons' lowbias32)."""
     if n > TWO:
         first = min(max(n // 128, 16384), 131072)
         Q, share = max(min(-(-n // first), 512), -(-n // (2 * 131072))), 32
