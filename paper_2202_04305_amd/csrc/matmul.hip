@@ -1098,11 +1098,16 @@ sp_status prepare_spmv_t(const sp_tensor *A, hipStream_t st, bool unprepared)
             const double peak = 250.0 * padded / (double)rowblocks;
             double limit = 0.9 * others;
             if (share >= 0.5 && unprepared && !full_bins && !segments) A->plan_spmv_open = 1;
-            else if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
+            else if (share >= 0.5 && full_bins) {
+                // as long as no row block is far heavier than the mean one: f64, 16.9 M entries in 1 M rows of 524,288 columns, rows of up to
+                // 4754, the heaviest block 1.3 times the mean: 128 us, streamed 156; sorted by length, 13 times the mean: 87 and 54.  The
+                // streamed kernel misses an x of 3 to 4 MB too (16 M even entries, 400,000 columns: 146 us, binned 123), which the formula leaves out.
+                kernel = 4;
+                limit = std::max(others, 1.5 * binned(peak));
+            } else if (share >= 0.5 && sizeof(VT) == 8 && A->max_segment > kLongRow) {
                 // long rows in f64: the binned copy's second pass adds a quarter of a row's products one by one, where the others add them
-                // up in trees; it is left to those shapes
-                kernel = full_bins ? 4 : segments ? 3 : 2;
-                limit = others;
+                // up in trees; it is left to the shapes above
+                kernel = segments ? 3 : 2;
             } else if (share >= 0.5) {
                 // Short rows are added up one by one in the other kernels, in four parts in the binned one (f32: in f64), which is no less exact
                 // there: whichever is the fastest.

@@ -76,6 +76,10 @@ def by_length(m, n, nnz, longest):
     return lin // n, lin % n
 
 
+def evenly(m, n, nnz):
+    return scattered(m, n, nnz)[0]
+
+
 def one_long(m, n, nnz, longest):
     (rows, cols), _ = scattered(m, n, nnz - longest)
     keep = rows != 17
@@ -89,6 +93,7 @@ def one_long(m, n, nnz, longest):
     (np.float32, by_length, (200000, 2000000, 3000000, 64), (4,)),           # 26 and 38
     (np.float32, one_long, (200000, 2000000, 3000000, 3000), (4,)),          # 19 and 38
     (np.float64, by_length, (600000, 600000, 4500000, 5000), (2, 3)),        # row blocks of 2048 and 32 entries a bucket, one far above the mean
+    (np.float64, evenly, (525000, 420000, 6000000), (4,)),                   # the same with an x of 3.4 MB and no block above the mean
 ])
 def test_the_choice_looks_at_the_heaviest_row_block(dtype, make, args, kernels):
     m, n = args[:2]
